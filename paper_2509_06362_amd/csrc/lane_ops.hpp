@@ -6,6 +6,14 @@
 
 namespace maaso {
 
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+
+// A condition as a mask of the wavefront's lanes (scalar register pair), and back.
+__device__ __forceinline__ unsigned long long lane_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
 // (slack, index) of the better of two candidates: larger slack, lower index among equals.
 __device__ __forceinline__ void take_better(float& s, int32_t& i, float os, int32_t oi) {
   const bool take = (os > s) | ((os == s) & (oi < i));  // no short circuit: three compares, no branches
@@ -71,6 +79,23 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   MAASO_DPP_FOLD_ROWS("v_add_u32_dpp", v, "row_bcast:15", "0xa");
   MAASO_DPP_FOLD_ROWS("v_add_u32_dpp", v, "row_bcast:31", "0xc");
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
+  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+  return v;
+}
+
+// Sum over the wavefront of per-lane tick counts, uniform: in 32 bits when no lane holds 2^26 ticks (64 s
+// of prefill) or more, the usual case; else 26 bits at a time.
+__device__ __forceinline__ unsigned long long wave_sum_ticks(unsigned long long t) {
+  constexpr uint32_t kPart = (1u << 26) - 1u;
+  unsigned long long sum = wave_sum_u32((uint32_t)t & kPart);
+  if (lane_mask((t >> 26) != 0ull) != 0ull) {
+    sum += (unsigned long long)wave_sum_u32((uint32_t)(t >> 26) & kPart) << 26;
+    sum += (unsigned long long)wave_sum_u32((uint32_t)(t >> 52)) << 52;
+  }
+  return sum;
 }
 
 }  // namespace maaso

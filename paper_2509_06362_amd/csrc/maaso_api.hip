@@ -39,6 +39,7 @@ struct maaso_ctx {
   int device;
   uint32_t n_tp, b_cap, cells, n_slo;
   float d_ttft[kMaxSlo], d_tbt[kMaxSlo], i_ttft[kMaxSlo], i_tbt[kMaxSlo];
+  float tbt_max;        // largest entry of the per-token latency table
   float* tab;           // device: three tables back to back, then tp_degree [n_tp] as uint32
   bool has_degree;      // the profile came with GPUs-per-instance figures
   uint32_t* status;     // device status word
@@ -234,8 +235,30 @@ void fill_assign_args(AssignArgs& a, const maaso_ctx* ctx, const maaso_placement
   a.sat_acc = reinterpret_cast<unsigned long long*>(ctx->status + 36);
 }
 
-// One block per (request set, candidate); requests per lane chosen so that a window keeps the lanes
-// busy (by the set with the longest windows: the choice never changes a result).
+// Wavefronts per candidate and requests per lane of the windowed sweep.  One wavefront per candidate wastes
+// least (state, evaluation and the choice of admissible instances are per wavefront) once there are
+// enough candidates to fill the device; four shorten the walk through the windows where there are not.
+// Measured, one wavefront against four: 8192 candidates, windows of 4096: 1.90 / 2.67 ms; 2160 units of
+// 256: 1.33 / 1.60 ms; 2000 of 65,536: 1.49 / 0.52 ms; 700 of 4096: 0.73 / 0.40 ms; 300 of 256:
+// 0.91 / 0.69 ms.  Four requests per lane where a window has them (8192 candidates of 4096: 1.90 against
+// 2.71 ms with one), else one (2000 of 64: 0.51 against 0.62 ms with four).
+template <bool kScore, bool kSQ, int S>
+void launch_sweep_window_s(const SweepWindowArgs& a, uint64_t per_window, size_t lds, hipStream_t s) {
+  const uint64_t units = (uint64_t)a.n_cand * a.n_sets;
+  const bool alone = units >= 4096u || (units >= 1024u && per_window < 4096u);
+  const dim3 b(kAssignThreads);
+  const dim3 g((alone ? (a.n_cand + 3u) / 4u : a.n_cand) * a.n_sets);
+  if (alone) {
+    if (per_window >= 256u) hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 1, 4, kSQ>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 1, 1, kSQ>), g, b, lds, s, a);
+  } else {
+    if (per_window >= 1024u) hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 4, 4, kSQ>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 4, 1, kSQ>), g, b, lds, s, a);
+  }
+}
+
+// The windowed sweep of every (request set, candidate); shapes are chosen by the set with the longest
+// windows (the choice never changes a result).
 template <bool kScore, bool kSQ>
 int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
   uint64_t per_window = 0;
@@ -271,13 +294,9 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
     }
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
-  const dim3 grid((uint32_t)blocks);
-  if (per_window > 2u * kAssignThreads)
-    hipLaunchKernelGGL((sweep_window_kernel<kScore, 4, kSQ>), grid, dim3(kAssignThreads), lds, s, a);
-  else if (per_window > kAssignThreads)
-    hipLaunchKernelGGL((sweep_window_kernel<kScore, 2, kSQ>), grid, dim3(kAssignThreads), lds, s, a);
-  else
-    hipLaunchKernelGGL((sweep_window_kernel<kScore, 1, kSQ>), grid, dim3(kAssignThreads), lds, s, a);
+  if (a.i_pad <= 64u) launch_sweep_window_s<kScore, kSQ, 1>(a, per_window, lds, s);
+  else if (a.i_pad <= 128u) launch_sweep_window_s<kScore, kSQ, 2>(a, per_window, lds, s);
+  else launch_sweep_window_s<kScore, kSQ, 4>(a, per_window, lds, s);
   return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
 }
 
@@ -305,6 +324,16 @@ void fill_sweep_window_args(SweepWindowArgs& a, const maaso_ctx* ctx, const maas
   a.max_batch = pl->max_batch;
   a.occ = pl->occ;
   a.q_ticks = reinterpret_cast<const uint64_t*>(pl->q_ticks);
+  a.bounds = AdmissionBounds{0.0f, 0.0f, 0.0f, 0.0f, false};
+  for (uint32_t k = 0; k < ctx->n_slo; ++k) {
+    a.bounds.d_ttft = std::max(a.bounds.d_ttft, ctx->d_ttft[k]);
+    a.bounds.d_tbt = std::max(a.bounds.d_tbt, ctx->d_tbt[k]);
+  }
+  a.bounds.e_ttft = a.bounds.d_ttft * 0x1p-20f;
+  a.bounds.e_tbt = a.bounds.d_tbt * 0x1p-20f;
+  // the occupancy penalty is at most 1 + pen_kappa; a finite service time leaves no 0 * inf in a wait
+  a.bounds.narrow = a.bounds.d_ttft < kNarrowSeconds &&
+                    (double)prm->s_bar * (double)ctx->tbt_max * (1.0 + (double)prm->pen_kappa) < 1e38;
   a.n_sets = 0;
   std::memset(a.sets, 0, sizeof(a.sets));
   a.status = ctx->status;
@@ -694,6 +723,9 @@ int maaso_profile_tables_load(const maaso_profile_desc* d, int device, maaso_ctx
   ctx->cells = cells;
   ctx->n_slo = d->n_slo;
   ctx->spin_limit = 1u << 22;
+  for (uint32_t t = 0; t < d->n_tp; ++t)
+    for (uint32_t b = 1; b <= d->b_cap; ++b)
+      ctx->tbt_max = std::max(ctx->tbt_max, d->tbt[(size_t)t * (d->b_cap + 1u) + b]);
   for (uint32_t k = 0; k < kMaxSlo; ++k) {
     const bool live = k < d->n_slo;
     ctx->d_ttft[k] = live ? d->d_ttft[k] : 1.0f;

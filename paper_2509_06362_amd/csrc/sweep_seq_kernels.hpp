@@ -24,10 +24,6 @@ namespace maaso {
 
 constexpr int kSeqThreads = 256;  // four wavefronts = four (request set, candidate) units per block
 
-__device__ __forceinline__ float lane_value(float v, int l) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
-}
-
 // Arg-max of (slack, index) over the whole wavefront, lowest index among equals, as uniform values.
 // The largest slack: four DPP steps settle each row of 16 lanes, two row broadcasts carry the rows'
 // maxima into lane 63, one v_readlane fetches it.  The lowest index among the lanes that hold it:

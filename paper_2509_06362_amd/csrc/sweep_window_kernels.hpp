@@ -2,18 +2,21 @@
 // distributor on its own copy of its instance state - the stand-in for the paper's virtual-slot
 // simulator (Sec. V-A "Simulator Implementation") inside the evaluation of a candidate (Alg. 1).
 //
-// Candidates do not interact, so one block owns one candidate and walks the windows by itself: no
-// device-wide barrier.  Thread j keeps instance j's live state (occupancy, queued prefill ticks) in
-// registers; per window the block stages its instances into LDS records, fills the per-(class,
-// instance) between-token margins, scores the window's requests (lanes = requests, four in flight
-// per lane, broadcast LDS reads of the records), adds the admitted load with integer LDS atomics
-// (aggregated per wavefront when all its admitted requests chose the same instance, the common case
-// when a window herds onto the instance with the most slack), and advances the state exactly as the
-// distributor does.
+// Candidates do not interact, so a wavefront (or, where there are few candidates, a block of four) owns one
+// and walks the windows by itself: no device-wide barrier.  Its lanes hold the instances (state, profile
+// evaluation, the drain between windows); per window it works out which instances a request can be
+// admitted to at all (find_admissible: 1 to 4 in nineteen windows of twenty) and scores the requests,
+// lanes = requests, against those alone.
+//
+// What bounds it: vector issue at windows of thousands (8192 candidates x 131,072 requests x 128
+// instances, windows of 4096: 26.8 ms with every instance scored, 1.9 ms now - 263 vector and 96 scalar
+// instructions per wavefront and 256 requests), the chain of one window after the other at short ones
+// (Alg. 2, 720 deployments x three sets, windows of 256: 2.6 -> 1.33 ms, 2.6 us per window of the
+// longest chain).
 #pragma once
 
 #include "assign_kernels.hpp"
-#include "lane_ops.hpp"
+#include "live_slots.hpp"
 
 #pragma clang fp contract(off)
 
@@ -64,6 +67,7 @@ struct SweepWindowArgs {
   ModelParams mp;
   uint32_t n_slo;
   float d_ttft[kMaxSlo], d_tbt[kMaxSlo], i_ttft[kMaxSlo], i_tbt[kMaxSlo];
+  AdmissionBounds bounds;
   uint32_t n_cand, i_pad;
   const uint32_t* n_inst;
   const uint8_t* tp_idx;
@@ -79,221 +83,393 @@ struct SweepWindowArgs {
   float alpha, beta, gamma_t, gamma_l;
 };
 
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-  return v;
+// A request as it comes from memory, and with everything that depends on the request alone worked out
+// (its class row, the end-to-end deadline and its reciprocal).
+constexpr uint32_t kNoRequest = 0x80000000u;  // in place of the class where there is no request
+struct RequestRaw {
+  uint32_t pl, ol, k;
+};
+struct RequestSide {
+  float4 u;  // prompt length, first-token deadline, between-token deadline, output length
+  float4 w;  // reciprocals of the two deadlines, end-to-end deadline, its reciprocal
+};
+
+__device__ __forceinline__ RequestRaw fetch_request(const SweepWindowSet& rs, uint32_t r, uint32_t end) {
+  RequestRaw raw{0u, 0u, kNoRequest};
+  if (r < end) { raw.pl = rs.prompt_len[r]; raw.ol = rs.out_len[r]; raw.k = rs.slo_class[r]; }
+  return raw;
+}
+
+// No request, or a class out of range: deadlines that no latency meets.
+__device__ __forceinline__ RequestSide request_side(const RequestRaw& raw, uint32_t n_slo, const ClassRow* cls,
+                                                    uint32_t* status) {
+  const bool live = raw.k < n_slo;
+  if (!live && raw.k != kNoRequest) raise_status(status, 1u);
+  const ClassRow cr = cls[live ? raw.k : 0u];
+  const float L = (float)raw.pl, S = (float)raw.ol;
+  const float De = fmaf(S, cr.Db, cr.Dt);
+  RequestSide q;
+  q.u = make_float4(L, live ? cr.Dt : -1.0f, live ? cr.Db : -1.0f, S);
+  q.w = make_float4(cr.iDt, cr.iDb, De, 1.0f / De);
+  return q;
+}
+
+// Scores V requests of a lane against M <= kFew instances held in registers and adds what is admitted
+// to the caller's sums: cnt[i] (uniform) requests and acc[i] (per lane) prefill ticks on instance i, except
+// that the entries of instance 0 take everything admitted (the caller subtracts the others).  Who is
+// given what stays in lane masks on the scalar unit.  Needs AdmissionBounds::narrow.
+constexpr int kFew = 4;
+template <int M, int V, bool kSQ>
+__device__ __forceinline__ void score_few(const SlotRecord (&r)[kFew], const float (&rank)[kFew],
+                                          const RequestSide (&q)[V], uint32_t (&cnt)[kFew],
+                                          unsigned long long (&acc)[kFew]) {
+  static_assert(V <= 4, "V prefills of up to 2^29 ticks in 32 bits");
+  uint32_t sum[M] = {};
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    float best, bpre;
+    unsigned long long took[M];  // lanes whose best so far instance i is
+    if (M == 1) {
+      // one instance: only whether it is capable matters.  Its slack is >= 0 iff the first-token and
+      // the between-token latency meet their deadlines (the end-to-end margin is implied by the two).
+      bpre = fmaf(r[0].p, q[v].u.x, r[0].a);
+      took[0] = lane_mask(r[0].wait + bpre <= q[v].u.y) & lane_mask(r[0].tbt <= q[v].u.z);
+    } else {
+      const Deadlines d{q[v].u.y, q[v].u.z, q[v].w.z, q[v].w.x, q[v].w.y, q[v].w.w};
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const Margins m = score_triple(r[i].a, r[i].p, r[i].tbt, r[i].wait, q[v].u.x, q[v].u.w, d);
+        const float val = (kSQ && m.slack >= 0.0f) ? rank[i] : m.slack;
+        if (i == 0) {
+          best = val;
+          bpre = m.pre;
+        } else {
+          const bool better = val > best;
+          took[i] = lane_mask(better);
+          bpre = better ? m.pre : bpre;
+          best = max_no_nan(best, val);
+        }
+      }
+      // admitted requests load their instance; of two takers the later one holds the request
+      unsigned long long left = lane_mask(best >= 0.0f);
+      took[0] = left;
+#pragma unroll
+      for (int i = M - 1; i > 0; --i) {
+        took[i] &= left;
+        left &= ~took[i];
+      }
+    }
+    const uint32_t ticks = (uint32_t)rintf(bpre * 1048576.0f);
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      cnt[i] += (uint32_t)__popcll(took[i]);
+      sum[i] += in_mask(took[i]) ? ticks : 0u;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < M; ++i) acc[i] += sum[i];
 }
 
 // kScore: also observe what the composite serving score needs (Sec. IV-D, Eq. 6-8) - which instances
 // served a request, and the exact integer sum of the admitted requests' queue waits - and finish the
-// candidate's score in the block: Phi = alpha * Phi_S^n + beta * min(Phi_T, gamma_T) / gamma_T +
+// candidate's score: Phi = alpha * Phi_S^n + beta * min(Phi_T, gamma_T) / gamma_T +
 // (1 - beta) * max(gamma_L - Phi_L, 0) / gamma_L with Phi_T = sum of 1 / tbt_j over the serving
 // instances in index order (tbt_j of the first window) and Phi_L = mean wait of the admitted requests.
-// V: requests a lane scores at a time (4 for windows of a thousand requests or more; smaller windows
-// leave most of those idle, so they run with 2 or 1).
-// kSQ: the distributor's shortest-queue rule (see queue_rank_value) instead of the largest slack.
-template <bool kScore, int V, bool kSQ>
-__global__ __launch_bounds__(kAssignThreads) void sweep_window_kernel(const SweepWindowArgs a) {
+// S: instance slots per lane, instance j = s * 64 + lane.
+// NW = 1: a wavefront owns a candidate.  The four of a block score the same requests, so a chunk of 256
+// is fetched and prepared once per block (a request per thread) and read by all from LDS.
+// NW = 4: the wavefronts of a block share a candidate.  Each keeps the whole state and advances it by
+// itself; the requests of a window are dealt among them, V per lane at a time, and the admitted sums
+// meet in LDS behind the window's only barrier.
+// kSQ: the distributor's shortest-queue rule instead of the largest slack.
+template <bool kScore, int S, int NW, int V, bool kSQ>
+__global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_kernel(const SweepWindowArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* tab = reinterpret_cast<float*>(smem);
-  __shared__ float4 recs[256];
   __shared__ ClassRow cls[kMaxSlo];
-  __shared__ float s2tab[kMaxSlo * kS2Stride];
-  __shared__ uint32_t n_blk[256];
-  __shared__ unsigned long long t_blk[256];
-  __shared__ uint32_t wave_sat[kAssignThreads / 64];
-  __shared__ int32_t occ_s[kSQ ? 256 : 1];
-  __shared__ float rankv[kSQ ? 256 : 1];
+  __shared__ float4 chunk_u[NW == 1 ? 2 : 1][NW == 1 ? kAssignThreads : 1];  // RequestSide in two arrays:
+  __shared__ float4 chunk_w[NW == 1 ? 2 : 1][NW == 1 ? kAssignThreads : 1];  // no bank conflicts
+  // admitted sums of a window, NW > 1: three buffers in turn - one is added to, the one before is read,
+  // the one after is cleared
+  __shared__ uint32_t n_sum[NW > 1 ? 3 : 1][NW > 1 ? 64 * S : 1];
+  __shared__ unsigned long long t_sum[NW > 1 ? 3 : 1][NW > 1 ? 64 * S : 1];
 
   const uint32_t tid = threadIdx.x;
-  const uint32_t set = blockIdx.x / a.n_cand;
-  const uint32_t c = blockIdx.x - set * a.n_cand;
-  const SweepWindowSet rs = resolve_set(a.sets[set]);
-  const size_t base = (size_t)c * a.i_pad;
-  const uint32_t n = min(a.n_inst[c], a.i_pad);
-  uint32_t tp = 0, B = 1;
-  int32_t occ = 0;
-  uint64_t q = 0;
-  if (tid < n) {
-    tp = a.tp_idx[base + tid]; B = a.max_batch[base + tid];
-    occ = a.occ[base + tid]; q = a.q_ticks[base + tid];
-  }
+  const uint32_t lane = tid & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   if (tid < a.n_slo) cls[tid] = ClassRow{a.d_ttft[tid], a.d_tbt[tid], a.i_ttft[tid], a.i_tbt[tid]};
   for (uint32_t i = tid; i < 3u * a.cells; i += kAssignThreads) tab[i] = a.tab[i];
+  if (NW > 1)
+    for (uint32_t i = tid; i < 3u * 64u * S; i += kAssignThreads) { (&n_sum[0][0])[i] = 0u; (&t_sum[0][0])[i] = 0ull; }
   __syncthreads();
 
-  const uint64_t R = rs.n_req;
-  const uint64_t n_windows = (R + rs.window - 1) / rs.window;
-  uint32_t sat = 0;
-  uint32_t served = 0;                // requests admitted to instance tid over all windows
-  unsigned long long wait_sum = 0ull; // their queue waits at admission, in ticks
-  unsigned long long wait_ticks = 0ull;
-  float inv_tbt_first = 0.0f;
+  // blocks of one request set first, then the next: a block never mixes sets
+  constexpr uint32_t kPerBlock = (uint32_t)(kAssignThreads / 64) / (uint32_t)NW;  // candidates
+  const uint32_t blocks_per_set = (a.n_cand + kPerBlock - 1u) / kPerBlock;
+  const uint32_t set = blockIdx.x / blocks_per_set;
+  const uint32_t c = (blockIdx.x - set * blocks_per_set) * kPerBlock + (NW == 1 ? wave : 0u);
+  const bool mine_c = c < a.n_cand;  // a block's last wavefronts may have no candidate: they only fetch
+  const SweepWindowSet rs = resolve_set(a.sets[set]);
+  const size_t base = (size_t)c * a.i_pad;
+  const uint32_t n = mine_c ? min(a.n_inst[c], a.i_pad) : 0u;
 
-  for (uint64_t w = 0; w < n_windows; ++w) {
-    const uint64_t s0 = w * rs.window;
-    const uint64_t e0 = (s0 + rs.window < R) ? s0 + rs.window : R;
-    uint32_t delta = 0;
-    if (tid < n && e0 < R) delta = rs.arrival_ticks[e0] - rs.arrival_ticks[s0];
-    float svc = 1.0f;
-    if (tid < n) {
-      Staged st;
-      if (stage_instance(tab, a.cells, a.mp, tp, B, occ, q, st)) {
-        recs[tid] = make_float4(st.a, st.p, st.tbt, st.wait);
-        svc = st.svc;
-        if (kScore) {
-          wait_ticks = (unsigned long long)__float2ll_rn(st.wait * 1048576.0f);
-          if (w == 0) inv_tbt_first = 1.0f / st.tbt;
+  LiveSlot slot[S];
+  unsigned long long bad_slot = 0ull;  // lanes with a slot outside the tables at some window
+  uint32_t served[S];
+  float inv_tbt_first[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const uint32_t j = (uint32_t)s * 64u + lane;
+    served[s] = 0u;
+    inv_tbt_first[s] = 0.0f;
+    slot[s].clear();
+    if (j < n)
+      slot[s].load(a.mp, a.tp_idx[base + j], a.max_batch[base + j], a.occ[base + j], a.q_ticks[base + j]);
+  }
+  uint32_t sat = 0;                    // uniform
+  unsigned long long wait_sum = 0ull;  // queue waits of the admitted requests, in ticks; uniform
+
+  const uint32_t R = rs.n_req;
+  auto window_end = [&](uint32_t s0) __attribute__((always_inline)) { return R - s0 > rs.window ? s0 + rs.window : R; };
+  // Requests are fetched one batch ahead, across window boundaries: no window starts with a trip to
+  // memory (two batches ahead: no faster).  A batch is 256 requests with NW = 1, 256 * V with NW = 4;
+  // (f0, f1) is the next one to fetch and the end of the window it belongs to.  The arrival time that
+  // passes behind a window is fetched one window ahead.
+  constexpr uint32_t kRaw = NW == 1 ? 1u : (uint32_t)V;
+  constexpr uint32_t kBatch = kAssignThreads * kRaw;
+  RequestRaw raw[kRaw];
+#pragma unroll
+  for (uint32_t v = 0; v < kRaw; ++v) raw[v] = RequestRaw{0u, 0u, kNoRequest};
+  uint32_t f0 = 0, f1 = window_end(0u);
+  auto fetch = [&]() __attribute__((always_inline)) {
+    if (f0 >= R) return;
+#pragma unroll
+    for (uint32_t v = 0; v < kRaw; ++v) raw[v] = fetch_request(rs, f0 + v * kAssignThreads + tid, f1);
+    if (f1 - f0 > kBatch) { f0 += kBatch; return; }
+    f0 = f1;
+    if (f0 < R) f1 = window_end(f0);
+  };
+  RequestSide rq[V];
+  uint32_t cbuf = 0, buf = 0;
+  auto next_chunk = [&](uint32_t to) __attribute__((always_inline)) {
+    const RequestSide q = request_side(raw[0], a.n_slo, cls, a.status);
+    chunk_u[to][NW == 1 ? tid : 0u] = q.u;
+    chunk_w[to][NW == 1 ? tid : 0u] = q.w;
+    fetch();
+  };
+  fetch();
+  if (NW == 1) {  // the first chunk; the next is on its way
+    next_chunk(0u);
+    __syncthreads();
+  }
+  uint32_t t_begin = 0, t_end = 0;
+  if (R > rs.window) { t_begin = rs.arrival_ticks[0]; t_end = rs.arrival_ticks[rs.window]; }
+
+  for (uint32_t s0 = 0, e0 = 0; s0 < R; s0 = e0) {
+    e0 = window_end(s0);
+    uint32_t t_next = 0;  // when the window after the next one opens
+    if (e0 < R && window_end(e0) < R) t_next = rs.arrival_ticks[window_end(e0)];
+    SlotRecord rec[S];
+    float svc[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if ((uint32_t)s * 64u >= n && s != 0) continue;  // uniform: no instance in this row of slots
+      unsigned long long bad;
+      slot[s].stage(tab, a.cells, a.mp, rec[s], svc[s], bad);
+      bad_slot |= bad;  // (a lane without an instance is never bad)
+      if (kScore && s0 == 0u) inv_tbt_first[s] = in_mask(bad) ? 0.0f : 1.0f / rec[s].tbt;
+    }
+
+    // which instances a request can be admitted to at all in this window, and the first few of them
+    InstanceSet<S> und;
+    SlotRecord fr[kFew];
+    uint32_t fj[kFew];
+    int32_t focc[kFew];
+    find_admissible<S, kSQ>(rec, slot, n, lane, a.bounds, und);
+    const uint32_t m = und.count();
+    const bool few = m <= (uint32_t)kFew && a.bounds.narrow;
+    if (few) first_of<S, kSQ, kFew>(und, rec, slot, fr, fj, focc);
+    float frank[kFew];
+    uint32_t cnt[kFew];
+    unsigned long long acc[kFew];
+#pragma unroll
+    for (int i = 0; i < kFew; ++i) { cnt[i] = 0u; acc[i] = 0ull; }
+    float rank[S];
+    if (kSQ) {
+      if (few) {
+#pragma unroll
+        for (int i = 0; i < kFew; ++i) {
+          uint32_t ahead = 0;
+#pragma unroll
+          for (int k = 0; k < kFew; ++k)
+            ahead += ((uint32_t)k < m && (focc[k] < focc[i] || (focc[k] == focc[i] && k < i))) ? 1u : 0u;
+          frank[i] = (float)(512u - ahead);
         }
       } else {
-        raise_status(a.status, 2u);
-        recs[tid] = make_float4(1.0f, 1.0f, 1.0f, INFINITY);
-      }
-      n_blk[tid] = 0u;
-      t_blk[tid] = 0ull;
-      if (kSQ) occ_s[tid] = occ;
-      // the instance's between-token margins against every class, while its tbt is at hand
-      const float tbt_j = recs[tid].z;
-      for (uint32_t k = 0; k < a.n_slo; ++k) s2tab[k * kS2Stride + tid] = (cls[k].Db - tbt_j) * cls[k].iDb;
-    }
-    __syncthreads();
-    if (kSQ) {
-      if (tid < n) rankv[tid] = queue_rank_value(occ_s, n, tid);
-      __syncthreads();
-    }
-
-    for (uint64_t b0 = s0; b0 < e0; b0 += (uint64_t)V * kAssignThreads) {
-      float L[V], S[V], Dt[V], iDt[V], De[V], iDe[V], best[V], bpre[V];
-      uint32_t k[V];
-      int32_t idx[V];
-      bool live[V];
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const uint64_t r = b0 + (uint64_t)v * kAssignThreads + tid;
-        live[v] = r < e0;
-        uint32_t pl = 0, ol = 0;
-        k[v] = 0;
-        if (live[v]) { pl = rs.prompt_len[r]; ol = rs.out_len[r]; k[v] = rs.slo_class[r]; }
-        if (k[v] >= a.n_slo) { raise_status(a.status, 1u); live[v] = false; k[v] = 0; }
-        L[v] = (float)pl; S[v] = (float)ol;
-        const ClassRow cr = cls[k[v]];
-        Dt[v] = cr.Dt; iDt[v] = cr.iDt;
-        De[v] = fmaf(S[v], cr.Db, cr.Dt);
-        iDe[v] = 1.0f / De[v];
-        best[v] = -INFINITY; idx[v] = -1; bpre[v] = 0.0f;
-      }
-      // one (request v, instance j) triple; r = {a, p, tbt, wait}, s2 = the between-token margin
-      auto score_one = [&](const float4 r, float s2, uint32_t j, int v) {
-        const float pre = fmaf(r.y, L[v], r.x);
-        const float ttft = r.w + pre;
-        const float e2e = fmaf(S[v], r.z, ttft);
-        const float s1 = (Dt[v] - ttft) * iDt[v];
-        const float s3 = (De[v] - e2e) * iDe[v];
-        const float slack = fminf(fminf(s1, s2), s3);
-        const float val = (kSQ && slack >= 0.0f) ? rankv[j] : slack;
-        // one compare, one select, one max: the winner's prefill time is recomputed after the loop
-        idx[v] = (val > best[v]) ? (int32_t)j : idx[v];
-        best[v] = max_no_nan(best[v], val);
-      };
-      // U records are fetched per trip before any is used.  With one request per lane a wavefront has
-      // little else to overlap an LDS read with (short windows leave a SIMD a few wavefronts);
-      // with four, a longer trip also spreads the address bookkeeping of the per-class margin reads
-      // over more triples.  Measured: V = 1: U = 4 beats 1 and 8; V = 4: U = 4 beats 1 and 2
-      // (128 registers, still four wavefronts per SIMD).
-      constexpr uint32_t U = (V == 2) ? 2u : 4u;
-      uint32_t j = 0;
-      for (; j + U <= n; j += U) {
-        float4 r[U];
-        float s2[U][V];
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-          r[u] = recs[j + u];
-#pragma unroll
-          for (int v = 0; v < V; ++v) s2[u][v] = s2tab[k[v] * kS2Stride + j + u];
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u)
-#pragma unroll
-          for (int v = 0; v < V; ++v) score_one(r[u], s2[u][v], j + u, v);
-      }
-      for (; j < n; ++j) {
-        const float4 r = recs[j];
-#pragma unroll
-        for (int v = 0; v < V; ++v) score_one(r, s2tab[k[v] * kS2Stride + j], j, v);
-      }
-#pragma unroll
-      for (int v = 0; v < V; ++v)
-        if (idx[v] >= 0) { const float4 r = recs[idx[v]]; bpre[v] = fmaf(r.y, L[v], r.x); }
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const bool adm = live[v] && best[v] >= 0.0f;  // admitted requests load their instance
-        const uint64_t am = __ballot(adm);
-        if (am == 0ull) continue;
-        sat += adm ? 1u : 0u;
-        const unsigned long long ticks = adm ? (unsigned long long)__float2ll_rn(bpre[v] * 1048576.0f) : 0ull;
-        const int32_t first = __builtin_amdgcn_readlane(idx[v], __builtin_ctzll(am));
-        if (__ballot(adm && idx[v] == first) == am) {  // the whole wavefront chose one instance
-          // prefill times below 64 s each (2^26 ticks) add up in 32 bits: the usual case
-          const unsigned long long tsum = __ballot((ticks >> 26) != 0ull) == 0ull
-                                              ? (unsigned long long)wave_sum_u32((uint32_t)ticks)
-                                              : wave_sum_u64(ticks);
-          if ((tid & 63u) == 0u) {
-            atomicAdd(&n_blk[first], (uint32_t)__popcll(am));
-            atomicAdd(&t_blk[first], tsum);
-          }
-        } else if (adm) {
-          atomicAdd(&n_blk[idx[v]], 1u);
-          atomicAdd(&t_blk[idx[v]], ticks);
-        }
+        queue_ranks<S>(slot, und, lane, rank);
       }
     }
-    lds_atomics_barrier();
-
-    if (tid < n) {
+    // adds to the state: instance j (uniform) admitted `num` requests of `ticks` prefill in all
+    auto admit = [&](uint32_t j, uint32_t num, unsigned long long ticks, float wait) __attribute__((always_inline)) {
+      sat += num;
       if (kScore) {
-        served += n_blk[tid];
-        wait_sum += (unsigned long long)n_blk[tid] * wait_ticks;
+        const float ticks_w = wait * 1048576.0f;
+        wait_sum += (unsigned long long)num * (a.bounds.narrow ? (unsigned long long)(uint32_t)rintf(ticks_w)
+                                                                : (unsigned long long)__float2ll_rn(ticks_w));
       }
-      occ += (int32_t)n_blk[tid];
-      q += t_blk[tid];
-      if (e0 < R) {  // time passes until the next window opens
-        q -= (q < (uint64_t)delta) ? q : (uint64_t)delta;
-        const int32_t run = min(occ, (int32_t)B);
-        const float x = ((float)run * ((float)delta * 0x1p-20f)) / svc;
-        const int32_t done = min(occ, (int32_t)floorf(fminf(x, 2147483520.0f)));
-        occ -= done;
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (j >> 6 == (uint32_t)s && (j & 63u) == lane) {
+          slot[s].occ += (int32_t)num;
+          slot[s].q += ticks;
+          served[s] += num;
+        }
+    };
+    // V requests per lane against the window's few instances
+    auto score = [&](const RequestSide (&q)[V]) __attribute__((always_inline)) {
+      if (m == 1u) score_few<1, V, kSQ>(fr, frank, q, cnt, acc);
+      else if (m == 2u) score_few<2, V, kSQ>(fr, frank, q, cnt, acc);
+      else if (m == 3u) score_few<3, V, kSQ>(fr, frank, q, cnt, acc);
+      else if (m == 4u) score_few<4, V, kSQ>(fr, frank, q, cnt, acc);
+    };
+    // ... or against any number of them
+    auto score_any = [&](const RequestSide (&q)[V]) __attribute__((always_inline)) {
+      float best[V], bpre[V];
+      uint32_t idx[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) { best[v] = -INFINITY; bpre[v] = 0.0f; idx[v] = 0xffffffffu; }
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        for (unsigned long long todo = und.m[s]; todo != 0ull; todo &= todo - 1ull) {
+          const int l = (int)__builtin_ctzll(todo);
+          const SlotRecord r = rec[s].of_lane(l);
+          const float rk = kSQ ? lane_value(rank[s], l) : 0.0f;
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            const Deadlines d{q[v].u.y, q[v].u.z, q[v].w.z, q[v].w.x, q[v].w.y, q[v].w.w};
+            const Margins mg = score_triple(r.a, r.p, r.tbt, r.wait, q[v].u.x, q[v].u.w, d);
+            const float val = (kSQ && mg.slack >= 0.0f) ? rk : mg.slack;
+            const bool better = val > best[v];
+            idx[v] = better ? (uint32_t)(s * 64 + l) : idx[v];
+            bpre[v] = better ? mg.pre : bpre[v];
+            best[v] = max_no_nan(best[v], val);
+          }
+        }
       }
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const bool adm = best[v] >= 0.0f;  // admitted requests load their instance
+        const unsigned long long ticks = adm ? (unsigned long long)__float2ll_rn(bpre[v] * 1048576.0f) : 0ull;
+        for (unsigned long long am = lane_mask(adm); am != 0ull;) {  // one trip per instance chosen
+          const uint32_t j = (uint32_t)__builtin_amdgcn_readlane((int)idx[v], (int)__builtin_ctzll(am));
+          const bool here = adm && idx[v] == j;
+          const unsigned long long held = lane_mask(here);
+          const unsigned long long tsum = wave_sum_ticks(here ? ticks : 0ull);
+          if (NW > 1) {
+            if (lane == 0u) {
+              atomicAdd(&n_sum[buf][j], (uint32_t)__popcll(held));
+              atomicAdd(&t_sum[buf][j], tsum);
+            }
+          } else {
+            float w = 0.0f;
+            if (kScore) {
+#pragma unroll
+              for (int s = 0; s < S; ++s)
+                if (j >> 6 == (uint32_t)s) w = lane_value(rec[s].wait, (int)(j & 63u));
+            }
+            admit(j, (uint32_t)__popcll(held), tsum, w);
+          }
+          am &= ~held;
+        }
+      }
+    };
+    auto close_few = [&]() __attribute__((always_inline)) {
+      if (!few) return;
+#pragma unroll
+      for (int i = 1; i < kFew; ++i) { cnt[0] -= cnt[i]; acc[0] -= acc[i]; }
+#pragma unroll
+      for (int i = 0; i < kFew; ++i)
+        if (cnt[i] != 0u) {
+          const unsigned long long tsum = wave_sum_ticks(acc[i]);
+          if (NW > 1) {
+            if (lane == 0u) { atomicAdd(&n_sum[buf][fj[i]], cnt[i]); atomicAdd(&t_sum[buf][fj[i]], tsum); }
+          } else {
+            admit(fj[i], cnt[i], tsum, fr[i].wait);
+          }
+        }
+    };
+
+    if (NW == 1) {
+      for (uint32_t b0 = s0; b0 < e0; b0 += kBatch) {
+        next_chunk(cbuf ^ 1u);  // the chunk after this one (past the end: nothing that counts)
+        const uint32_t len = min(e0 - b0, kBatch);
+        if (m != 0u) {
+          for (uint32_t i0 = 0; i0 < len; i0 += 64u * V) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+              const uint32_t i = i0 + (uint32_t)v * 64u + lane;
+              rq[v] = RequestSide{chunk_u[cbuf][i], chunk_w[cbuf][i]};
+            }
+            if (few) score(rq);
+            else score_any(rq);
+          }
+        }
+        cbuf ^= 1u;
+        __syncthreads();
+      }
+      close_few();
+    } else {
+      for (uint32_t b0 = s0; b0 < e0; b0 = e0 - b0 > kBatch ? b0 + kBatch : e0) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) rq[v] = request_side(raw[NW == 1 ? 0 : v], a.n_slo, cls, a.status);
+        fetch();
+        if (few) score(rq);
+        else score_any(rq);
+      }
+      close_few();
+      // the buffer of the window after next was read behind the previous barrier; it is clean before
+      // anyone passes this one
+      const uint32_t later = buf == 0u ? 2u : buf - 1u;
+      if (tid < 64u * S) { n_sum[later][tid] = 0u; t_sum[later][tid] = 0ull; }
+      lds_atomics_barrier();
+      if (few) {
+#pragma unroll
+        for (int i = 0; i < kFew; ++i)
+          if ((uint32_t)i < m) admit(fj[i], n_sum[buf][fj[i]], t_sum[buf][fj[i]], fr[i].wait);
+      } else {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          for (unsigned long long todo = und.m[s]; todo != 0ull; todo &= todo - 1ull) {
+            const int l = (int)__builtin_ctzll(todo);
+            admit((uint32_t)(s * 64 + l), n_sum[buf][s * 64 + l], t_sum[buf][s * 64 + l],
+                  lane_value(rec[s].wait, l));
+          }
+      }
+      buf = buf == 2u ? 0u : buf + 1u;
     }
-    // No barrier before the next stage: it rewrites recs and the margin table, which every thread
-    // finished reading before the barrier above, and n_blk / t_blk entries that only their own thread
-    // reads; the next window's atomics on them come after the stage's barrier.
+    if (e0 < R) {  // time passes until the next window opens
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (s == 0 || (uint32_t)s * 64u < n) slot[s].advance(t_end - t_begin, svc[s]);
+    }
+    t_begin = t_end;
+    t_end = t_next;
   }
 
-  __syncthreads();  // the last update has read n_blk / t_blk, which are reused below
-  for (int d = 32; d >= 1; d >>= 1) sat += __shfl_xor(sat, d);
-  if ((tid & 63u) == 0u) wave_sat[tid >> 6] = sat;
+  if (bad_slot != 0ull) raise_status(a.status, 2u);
+  float pt = 0.0f;
   if (kScore) {
-    // reuse the LDS arrays of the window loop (all threads are past its last barrier):
-    // s2tab[j] = 1 / tbt_j of a serving instance, or -1; t_blk[wave] = wait ticks of the wavefront
-    s2tab[tid] = (tid < n && served != 0u) ? inv_tbt_first : -1.0f;
-    wait_sum = wave_sum_u64(wait_sum);
-    if ((tid & 63u) == 0u) t_blk[tid >> 6] = wait_sum;
+    // Phi_T: 1 / tbt of the serving instances, added in index order
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      for (unsigned long long todo = lane_mask(served[s] != 0u); todo != 0ull; todo &= todo - 1ull)
+        pt = pt + lane_value(inv_tbt_first[s], (int)__builtin_ctzll(todo));
   }
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t t = 0;
-    for (int wv = 0; wv < kAssignThreads / 64; ++wv) t += wave_sat[wv];
-    rs.sat_count[c] = t;
+  if (lane == 0u && mine_c && (NW == 1 || wave == 0u)) {
+    rs.sat_count[c] = sat;
     if (kScore) {
-      unsigned long long ticks = 0ull;
-      for (int wv = 0; wv < kAssignThreads / 64; ++wv) ticks += t_blk[wv];
-      const float ps = (rs.n_req == 0u) ? 0.0f : (float)t / (float)rs.n_req;
-      float pt = 0.0f;
-      for (uint32_t j = 0; j < n; ++j) {
-        const float inv = s2tab[j];
-        if (inv >= 0.0f) pt = pt + inv;
-      }
-      const float pl = (t == 0u) ? 0.0f : ((float)ticks * 0x1p-20f) / (float)t;
+      const float ps = (rs.n_req == 0u) ? 0.0f : (float)sat / (float)rs.n_req;
+      const float pl = (sat == 0u) ? 0.0f : ((float)wait_sum * 0x1p-20f) / (float)sat;
       const float ptn = fminf(pt, a.gamma_t) / a.gamma_t;
       const float pln = fmaxf(a.gamma_l - pl, 0.0f) / a.gamma_l;
       const float sc = fmaf(a.alpha, ps, fmaf(a.beta, ptn, (1.0f - a.beta) * pln));

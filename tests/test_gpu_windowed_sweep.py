@@ -1,0 +1,62 @@
+"""The windowed sweep and score against the CPU oracle at the edges of its shapes: a candidate per
+wavefront and per block, 64 / 128 / 256 instance slots, windows around the 64-, 256- and
+1024-request batches, placements whose instances are all alike, all different, or out of the tables,
+and deadlines beyond what the 32-bit tick sums take."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from paper_2509_06362_amd import binding, workloads as W  # noqa: E402
+
+WEIGHTS = (4.0, 0.3, 2048.0, 1.0)
+
+
+@pytest.mark.parametrize("n_cand,i_pad,window,n_req,variant", [
+    (1030, 3, 255, 600, "mixed"), (1030, 65, 256, 520, "mixed"), (1025, 129, 257, 300, "mixed"),
+    (1027, 64, 64, 130, "alike"), (1, 64, 63, 400, "mixed"), (3, 65, 1023, 2500, "different"),
+    (2, 256, 1024, 3000, "different"), (5, 128, 1025, 2100, "alike"), (4, 200, 300, 1000, "long"),
+    (1024, 20, 256, 513, "long"), (6, 33, 40, 500, "bad"), (1031, 9, 100, 350, "bad"),
+    (4100, 2, 5000, 300, "mixed"),
+])
+def test_windowed_sweep_edges(n_cand, i_pad, window, n_req, variant):
+    w = W.random_small(n_cand * 7 + i_pad, n_cand, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
+    if variant == "alike":
+        one = lambda x: np.ascontiguousarray(np.broadcast_to(x[:, :1], x.shape))
+        w = W.replace(w, tp_idx=one(w.tp_idx), max_batch=one(w.max_batch), occ=np.zeros_like(w.occ),
+                      q_ticks=np.zeros_like(w.q_ticks), n_inst=np.full_like(w.n_inst, i_pad))
+    elif variant == "different":  # longer queues on the stronger instances: few are dominated
+        q = (w.tp_idx.astype(np.uint64) * np.uint64(1 << 19) + w.max_batch.astype(np.uint64) * np.uint64(4099))
+        w = W.replace(w, q_ticks=q, occ=np.zeros_like(w.occ), n_inst=np.full_like(w.n_inst, i_pad))
+    elif variant == "long":
+        w = W.replace(w, d_ttft=w.d_ttft * np.float32(1000.0),
+                      q_ticks=w.q_ticks * np.uint64(300), prompt_len=w.prompt_len * np.uint32(700))
+    ref_w = w
+    if variant == "bad":
+        # slots outside the tables are absent: as good as instances nobody can ever be admitted to
+        tp, B, q = w.tp_idx.copy(), w.max_batch.copy(), w.q_ticks.copy()
+        q[:, [0, i_pad // 2]] = np.uint64(1 << 50)
+        ref_w = W.replace(w, q_ticks=q)
+        tp[:, 0] = 9
+        B[:, i_pad // 2] = 65
+        w = W.replace(w, tp_idx=tp, max_batch=B)
+    for policy in (0, 1):
+        wp = W.replace(w, policy=policy)
+        print(f"windowed sweep C={n_cand} I={i_pad} window={window} R={n_req} {variant} policy={policy}", flush=True)
+        dw = binding.DeviceWorkload(wp)
+        try:
+            cnt, _, best = dw.sweep(window=window)
+            sc = dw.score(*WEIGHTS, window=window)
+            torch.cuda.synchronize()
+            ref = oracle.placement_score(W.replace(ref_w, policy=policy), *WEIGHTS, window=window)
+            assert np.array_equal(cnt.cpu().numpy().view(np.uint32), ref["sat_count"])
+            assert int(best.item()) == int(np.argmax(ref["sat_count"]))
+            for k in ("sat_count", "phi_s", "phi_t", "phi_l", "score"):
+                got = sc[k].cpu().numpy()
+                assert np.array_equal(got.view(np.uint32) if k == "sat_count" else got, ref[k]), k
+            assert binding.maaso_ctx_device_status(dw.ctx) == (2 if variant == "bad" else 0)
+        finally:
+            dw.close()
