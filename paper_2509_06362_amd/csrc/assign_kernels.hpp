@@ -43,6 +43,7 @@ struct AssignArgs {
   float* e2e;
   unsigned long long* n_satisfied;
   uint32_t* status;
+  bool narrow;  // AdmissionBounds::narrow_queue
   unsigned long long* sat_acc;  // [1] admitted count and delivered-blocks counter of the static kernel; zero between calls
 };
 

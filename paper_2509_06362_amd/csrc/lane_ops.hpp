@@ -14,6 +14,21 @@ __device__ __forceinline__ float lane_value(float v, int l) {
 __device__ __forceinline__ unsigned long long lane_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
+// At the head of a branch that is hardly ever taken: keeps the compiler from working out both sides of
+// it and selecting.
+__device__ __forceinline__ void rare_path() { asm volatile(""); }
+
+// A non-negative time in ticks of 2^-20 s, rounded to nearest; `narrow`: known to be below 2^32 ticks.
+__device__ __forceinline__ unsigned long long to_ticks(float seconds, bool narrow) {
+  const float x = seconds * 1048576.0f;
+  unsigned long long t = (unsigned long long)(uint32_t)rintf(x);
+  if (!narrow) {
+    rare_path();
+    t = (unsigned long long)__float2ll_rn(x);
+  }
+  return t;
+}
+
 // (slack, index) of the better of two candidates: larger slack, lower index among equals.
 __device__ __forceinline__ void take_better(float& s, int32_t& i, float os, int32_t oi) {
   const bool take = (os > s) | ((os == s) & (oi < i));  // no short circuit: three compares, no branches

@@ -42,30 +42,51 @@ struct LiveSlot {
     q = ticks;
   }
 
-  // stage_instance on the live state.  A slot outside the tables gets a record that is never chosen (an
-  // infinite wait) and drains with a service time of one second; `bad` has its lane's bit.
-  __device__ __forceinline__ void stage(const float* tab, uint32_t cells, const ModelParams& mp, SlotRecord& r,
-                                        float& svc, unsigned long long& bad) const {
+  // stage_instance on the live state, up to the queued prefill: {a, p, tbt}, the expected service time and
+  // the wait for a slot past the batch cap.  `tab`: the three tables, `stride` entries each.  A slot
+  // outside the tables gets a record that is never chosen (an infinite wait) and drains with a service
+  // time of one second; `bad` has its lane's bit.
+  __device__ __forceinline__ void evaluate(const float* tab, uint32_t stride, const ModelParams& mp, SlotRecord& r,
+                                           float& svc, float& past, unsigned long long& bad) const {
     bad = lane_mask(!configured | (occ < 0));
     const uint32_t arriving = (uint32_t)occ + 1u;
     uint32_t w = mp.tbt_mode == 1u ? B : min(arriving, B);
     if (bad != 0ull) w = in_mask(bad) ? 1u : w;
     const uint32_t row = row0 + w;
     r.a = tab[row];
-    r.p = tab[cells + row];
-    r.tbt = tab[2u * cells + row];
+    r.p = tab[stride + row];
+    r.tbt = tab[2u * stride + row];
     if (mp.pen_kappa != 0.0f) {  // a factor of exactly one without a penalty
       const int32_t over = max(4 * (int32_t)w - 3 * (int32_t)B, 0);  // > 0 iff the batch is > 75 % full
       r.tbt = r.tbt * fmaf(mp.pen_kappa, (float)over * invB, 1.0f);
     }
     svc = mp.s_bar * r.tbt;
     const uint32_t ov = arriving > B ? arriving - B : 0u;  // requests beyond the batch cap
-    const float past = ((float)ov * invB) * svc;
-    // queued ticks below 2^32 (over an hour) convert in one instruction; scaling by 2^-20 is exact, so
-    // the fused form rounds once like the sum it stands for
-    const float qf = lane_mask((q >> 32) != 0ull) == 0ull ? (float)(uint32_t)q : (float)q;
-    r.wait = fmaf(qf, 0x1p-20f, past);
-    if (bad != 0ull && in_mask(bad)) { r = SlotRecord{1.0f, 1.0f, 1.0f, INFINITY}; svc = 1.0f; }
+    past = ((float)ov * invB) * svc;
+    if (bad != 0ull && in_mask(bad)) {
+      r.a = r.p = r.tbt = svc = 1.0f;
+      past = INFINITY;
+    }
+  }
+
+  // The whole wait: queued ticks in seconds on top of `past`.  Ticks below 2^32 (over an hour; `wide`, the
+  // same for all lanes, says that some lane has more) convert in one instruction; scaling by 2^-20 is
+  // exact, so the fused form rounds once like the sum it stands for.
+  __device__ __forceinline__ float wait_with(float past, bool wide) const {
+    float qf = (float)(uint32_t)q;
+    if (wide) {
+      rare_path();
+      qf = (float)q;
+    }
+    return fmaf(qf, 0x1p-20f, past);
+  }
+  __device__ __forceinline__ bool any_wide() const { return lane_mask((q >> 32) != 0ull) != 0ull; }
+
+  __device__ __forceinline__ void stage(const float* tab, uint32_t cells, const ModelParams& mp, SlotRecord& r,
+                                        float& svc, unsigned long long& bad) const {
+    float past;
+    evaluate(tab, cells, mp, r, svc, past, bad);
+    r.wait = wait_with(past, any_wide());
   }
 
   // `delta` ticks pass: queued prefill drains, min(occ, B) running requests complete at 1 / svc each.
@@ -129,6 +150,8 @@ struct AdmissionBounds {
   // the largest first-token deadline is below kNarrowSeconds and no wait can come out as no number: the
   // ticks of an admitted request's wait or prefill, and the sum of four prefills, fit 32 bits
   bool narrow;
+  // the same, and the queue of an instance that admits all of a window stays below 2^32 ticks
+  bool narrow_queue;
 };
 
 template <int S, bool kSQ>

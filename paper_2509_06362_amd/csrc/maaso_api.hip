@@ -187,6 +187,16 @@ ModelParams model_params(const maaso_ctx* ctx, const maaso_params* prm) {
   return mp;
 }
 
+// AdmissionBounds::narrow (per_window = 0) and narrow_queue.  The occupancy penalty is at most 1 + pen_kappa;
+// a finite service time leaves no 0 * inf in a wait.  An instance admits while its wait is within the
+// largest first-token deadline D, and so is each prefill: its queue ends a window below D * (1 + window).
+bool narrow_ticks(const maaso_ctx* ctx, const maaso_params* prm, uint64_t per_window) {
+  double d = 0.0;
+  for (uint32_t k = 0; k < ctx->n_slo; ++k) d = std::max(d, (double)ctx->d_ttft[k]);
+  return d < (double)kNarrowSeconds && d * (1.0 + (double)per_window) < 4095.0 &&
+         (double)prm->s_bar * (double)ctx->tbt_max * (1.0 + (double)prm->pen_kappa) < 1e38;
+}
+
 template <int Q>
 int launch_sweep(const SweepArgs& a, uint32_t blocks, hipStream_t s) {
   hipLaunchKernelGGL(sweep_kernel<Q>, dim3(blocks), dim3(kSweepThreads), 0, s, a);
@@ -232,6 +242,7 @@ void fill_assign_args(AssignArgs& a, const maaso_ctx* ctx, const maaso_placement
   a.e2e = out->e2e;
   a.n_satisfied = reinterpret_cast<unsigned long long*>(out->n_satisfied);
   a.status = ctx->status;
+  a.narrow = narrow_ticks(ctx, prm, prm->window);
   a.sat_acc = reinterpret_cast<unsigned long long*>(ctx->status + 36);
 }
 
@@ -276,20 +287,21 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
   bool one_by_one = !kSQ;
   for (uint32_t k = 0; k < a.n_sets; ++k) one_by_one = one_by_one && a.sets[k].window <= short_window;
   if (one_by_one) {
-    const dim3 g((uint32_t)((blocks + kSeqThreads / 64 - 1) / (kSeqThreads / 64)));
+    const dim3 g((a.n_cand + kSeqThreads / 64 - 1) / (kSeqThreads / 64) * a.n_sets);
+    const size_t lds_seq = lds + 3u * sizeof(float);  // one more row: slots without an instance
     bool one = true;  // every set request by request
     for (uint32_t k = 0; k < a.n_sets; ++k) one = one && a.sets[k].window == 1u;
     if (!kSQ) {
       const dim3 b(kSeqThreads);
       if (a.i_pad <= 64u) {
-        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1, true>), g, b, lds, s, a);
-        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1>), g, b, lds, s, a);
+        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1, true>), g, b, lds_seq, s, a);
+        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1>), g, b, lds_seq, s, a);
       } else if (a.i_pad <= 128u) {
-        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 2, true>), g, b, lds, s, a);
-        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 2>), g, b, lds, s, a);
+        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 2, true>), g, b, lds_seq, s, a);
+        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 2>), g, b, lds_seq, s, a);
       } else {
-        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 4, true>), g, b, lds, s, a);
-        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 4>), g, b, lds, s, a);
+        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 4, true>), g, b, lds_seq, s, a);
+        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 4>), g, b, lds_seq, s, a);
       }
     }
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
@@ -324,16 +336,15 @@ void fill_sweep_window_args(SweepWindowArgs& a, const maaso_ctx* ctx, const maas
   a.max_batch = pl->max_batch;
   a.occ = pl->occ;
   a.q_ticks = reinterpret_cast<const uint64_t*>(pl->q_ticks);
-  a.bounds = AdmissionBounds{0.0f, 0.0f, 0.0f, 0.0f, false};
+  a.bounds = AdmissionBounds{0.0f, 0.0f, 0.0f, 0.0f, false, false};
   for (uint32_t k = 0; k < ctx->n_slo; ++k) {
     a.bounds.d_ttft = std::max(a.bounds.d_ttft, ctx->d_ttft[k]);
     a.bounds.d_tbt = std::max(a.bounds.d_tbt, ctx->d_tbt[k]);
   }
   a.bounds.e_ttft = a.bounds.d_ttft * 0x1p-20f;
   a.bounds.e_tbt = a.bounds.d_tbt * 0x1p-20f;
-  // the occupancy penalty is at most 1 + pen_kappa; a finite service time leaves no 0 * inf in a wait
-  a.bounds.narrow = a.bounds.d_ttft < kNarrowSeconds &&
-                    (double)prm->s_bar * (double)ctx->tbt_max * (1.0 + (double)prm->pen_kappa) < 1e38;
+  a.bounds.narrow = narrow_ticks(ctx, prm, 0u);
+  a.bounds.narrow_queue = narrow_ticks(ctx, prm, prm->window ? prm->window : MAASO_MAX_REQUESTS);
   a.n_sets = 0;
   std::memset(a.sets, 0, sizeof(a.sets));
   a.status = ctx->status;
@@ -1284,7 +1295,7 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   // to a value asks for the persistent kernel below whatever the window.
   const uint32_t short_window = pl->i_pad <= 128u ? 4u : 2u;
   if (prm->policy == 0u && prm->window <= short_window && ctx->window_blocks == 0u) {
-    const size_t lds = (size_t)3 * ctx->cells * sizeof(float);
+    const size_t lds = (size_t)3 * (ctx->cells + 1u) * sizeof(float);
     TimedRegion timed(ctx, s);
     if (pl->i_pad <= 64u) {
       if (lat) hipLaunchKernelGGL((assign_seq_kernel<true, 1>), dim3(1), dim3(64), lds, s, a, prm->window);

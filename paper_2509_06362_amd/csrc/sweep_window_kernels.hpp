@@ -312,11 +312,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
     // adds to the state: instance j (uniform) admitted `num` requests of `ticks` prefill in all
     auto admit = [&](uint32_t j, uint32_t num, unsigned long long ticks, float wait) __attribute__((always_inline)) {
       sat += num;
-      if (kScore) {
-        const float ticks_w = wait * 1048576.0f;
-        wait_sum += (unsigned long long)num * (a.bounds.narrow ? (unsigned long long)(uint32_t)rintf(ticks_w)
-                                                                : (unsigned long long)__float2ll_rn(ticks_w));
-      }
+      if (kScore) wait_sum += (unsigned long long)num * to_ticks(wait, a.bounds.narrow);
 #pragma unroll
       for (int s = 0; s < S; ++s)
         if (j >> 6 == (uint32_t)s && (j & 63u) == lane) {
@@ -359,7 +355,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const bool adm = best[v] >= 0.0f;  // admitted requests load their instance
-        const unsigned long long ticks = adm ? (unsigned long long)__float2ll_rn(bpre[v] * 1048576.0f) : 0ull;
+        const unsigned long long ticks = adm ? to_ticks(bpre[v], a.bounds.narrow) : 0ull;
         for (unsigned long long am = lane_mask(adm); am != 0ull;) {  // one trip per instance chosen
           const uint32_t j = (uint32_t)__builtin_amdgcn_readlane((int)idx[v], (int)__builtin_ctzll(am));
           const bool here = adm && idx[v] == j;
