@@ -134,8 +134,8 @@ void maaso_ctx_destroy(maaso_ctx* ctx);
 /* Sizes the context's workspace so that no later compute call with at most max_cand candidates of
  * i_pad instance slots and max_req requests is refused with MAASO_E_WORKSPACE, whatever launch shape
  * it takes (set the launch-shape knobs before reserving: more blocks per queue need more).  The
- * workspace holds, for the static sweep, the prompt lengths bucketed by class (4*K*R bytes), one
- * 16-byte record per instance slot and the work-queue heads; 12 KiB for the windowed distributor;
+ * workspace is charged, for the static sweep, with 4*K*R bytes of prompt lengths, 16 bytes per instance
+ * slot and its queues (it keeps 4*R of them); 12 KiB for the windowed distributor;
  * 4 bytes per 1024 requests for maaso_split_by_slo.  The windowed sweep, the scores and the static
  * distributor use none.  Never shrinks.  A set-up call: it synchronises the device and reallocates
  * when the workspace has to grow.  Errors: INVALID_ARG, SHAPE, HIP, NOMEM, BUSY. */
@@ -154,10 +154,9 @@ int maaso_ctx_device_status(maaso_ctx* ctx, uint32_t* bits);
 const char* maaso_strerror(int status);
 
 /* Performance knobs; they never change a result.  0 selects the library's own choice.
- *   sweep_requests_per_lane: requests a lane of the sweep kernel keeps in registers (0, 2, 4, 8, 16);
- *     a block of the sweep owns 256 times as many requests of one SLO class;
- *   sweep_group: candidates per work item of the sweep kernel (clamped to what fits its LDS lists);
- *   sweep_blocks_per_queue: persistent blocks serving each (request tile, XCD) work queue;
+ *   sweep_requests_per_lane (0, 2, 4, 8, 16), sweep_group, sweep_blocks_per_queue: tiles, groups and
+ *     blocks the static sweep's workspace is charged by (maaso_ctx_reserve, MAASO_E_WORKSPACE,
+ *     MAASO_E_SHAPE of the no-allocation form); its launches are sized by the library alone;
  *   window_blocks: blocks of the windowed distributor's persistent kernel (at most one per compute
  *   unit is used).  Left at 0, windows of up to four requests are distributed by a single wavefront
  *   instead (no device-wide barrier per window); a value keeps the persistent kernel for them too.
@@ -192,9 +191,9 @@ int maaso_ctx_kernel_elapsed(maaso_ctx* ctx, float* total_ms, uint32_t* launches
  * (Shows, for instance, whether the device's clock was still rising during a short series.) */
 int maaso_ctx_kernel_durations(maaso_ctx* ctx, float* durations_ms, uint32_t cap, uint32_t* launches);
 
-/* What the chip sustains for the sweep's instruction mix.  Runs, on `device`, a kernel that is nothing
- * but the sweep's inner instruction sequence in a loop (8 wavefronts per SIMD, no memory access) and
- * returns the vector lane operations per second it reaches - the practical ceiling for the sweep on
+/* What the chip sustains for a latency evaluation's instruction mix.  Runs, on `device`, a kernel that is
+ * nothing but a fixed instruction sequence in a loop (8 wavefronts per SIMD, no memory access) and
+ * returns the vector lane operations per second it reaches - the practical ceiling of vector issue on
  * this device, next to the nominal peak that roofline fractions are quoted against.
  *   pattern 0: two fma + one three-input minimum per request (a pair of records without queue wait),
  *   1: the same with the wait's two adds, 2: pattern 0 unrolled four times, 3: compares that write a
@@ -218,12 +217,12 @@ int maaso_probe_valu(int device, uint32_t pattern, uint32_t trips, double* lane_
 int maaso_ctx_window_profile(maaso_ctx* ctx, int enable);
 int maaso_ctx_window_phases(maaso_ctx* ctx, uint64_t cycles[6]);
 
-/* Synchronises the device and returns how many (request, instance) pairs the context's most recent
- * maaso_placement_sweep evaluated in its latency loop, i.e. the valid triples minus those whose
- * instance already fails the between-token deadline of the request's class (they are settled per
- * (class, instance) and never reach the loop).  *pairs_without_wait (may be NULL) receives how many
- * of them belong to an instance whose queue wait is exactly zero: for those the sweep leaves the
- * addition of the wait out (0 + x = x), so they cost it less.  Both 0 if no sweep has run.
+/* Synchronises the device and returns how many (request, instance) pairs of the context's most recent
+ * maaso_placement_sweep are left to the first-token deadline, i.e. the valid triples minus those whose
+ * instance already fails the between-token deadline of the request's class.
+ * *pairs_without_wait (may be NULL) receives how many of them belong to an instance whose queue wait is
+ * exactly zero.  (The sweep settles the pairs of an instance and a class together; the figures say how
+ * many that were.)  Both 0 if no static sweep has run.
  * Errors: INVALID_ARG, HIP. */
 int maaso_ctx_sweep_evaluated(maaso_ctx* ctx, uint64_t* pairs, uint64_t* pairs_without_wait);
 
@@ -331,16 +330,14 @@ int maaso_placement_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maas
 
 /* For callers that cannot allocate device memory while they call (code under HIP graph capture, tight
  * serving loops, harnesses that forbid it): maaso_placement_sweep with the same arguments, results
- * and errors, whose static form (prm->window == 0) keeps its intermediate data - the class-bucketed
- * prompt lengths, one staged 16-byte record per instance slot, the work-queue heads - in a device
- * array of MAASO_NOALLOC_SCRATCH_BYTES that is part of the library image (every GPU the library runs
+ * and errors, whose static form (prm->window == 0) keeps its intermediate data - the grouped prompt
+ * lengths - in a device array of MAASO_NOALLOC_SCRATCH_BYTES that is part of the library image (every GPU the library runs
  * on holds its own copy until the process ends).  The call contains no hipMalloc, hipFree or other
  * allocating routine and no host synchronisation.  A shape that needs more - about
  * 4*K*R + 16*C*i_pad bytes plus 20 bytes per launched block - is refused with MAASO_E_SHAPE before
  * anything is launched.  (The capacity-aware form, window > 0, uses no scratch and is passed through.)
  * All calls on one GPU share that GPU's array, whatever the context: calls that overlap in time on
- * one GPU race on it - order them on one stream or with events.  Everything in the array that must
- * start at zero is cleared by the call's own first launch. */
+ * one GPU race on it - order them on one stream or with events. */
 #define MAASO_NOALLOC_SCRATCH_BYTES (8u << 20)
 int maaso_placement_sweep_noalloc(maaso_ctx* ctx, const maaso_placements* pl, const maaso_requests* rq,
                                   const maaso_params* prm, uint32_t* sat_count, float* sat_ratio,

@@ -10,10 +10,6 @@ __device__ __forceinline__ float lane_value(float v, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
 
-// A condition as a mask of the wavefront's lanes (scalar register pair), and back.
-__device__ __forceinline__ unsigned long long lane_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-__device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-
 // At the head of a branch that is hardly ever taken: keeps the compiler from working out both sides of
 // it and selecting.
 __device__ __forceinline__ void rare_path() { asm volatile(""); }

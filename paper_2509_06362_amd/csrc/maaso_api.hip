@@ -26,7 +26,15 @@ using namespace maaso;
 static_assert(MAASO_MAX_SLO == kMaxSlo, "header and kernels disagree on the class limit");
 
 constexpr uint32_t kMaxTimed = 256;
-constexpr size_t kSmallBytes = 256;
+// The context's small device block, in 32-bit words: [0] status, [32..35] evaluated pairs of the last
+// static sweep (all; those without a wait), [36..37] admitted-count accumulator and delivered-blocks
+// ticket of the static distributor, [64..] the static sweep's SweepTotals; from kCounterWord on its
+// histogram, cursors and group offsets.
+constexpr uint32_t kTotalsWord = 64;
+constexpr uint32_t kCounterWord = kTotalsWord + (1u + kTotalsLines) * sizeof(SweepTotals) / 4u;
+constexpr uint32_t kHistWords = kMaxSlo * kLenBins;
+constexpr size_t kSmallBytes = ((size_t)kCounterWord + 3u * kHistWords + 64u) * 4u;
+static_assert(kTotalsWord * 4u % alignof(SweepTotals) == 0u && sizeof(SweepTotals) == 128u, "");
 
 // Workspace of maaso_placement_sweep_noalloc: device memory that exists from the moment the library
 // is loaded, one copy per GPU, so that the call has nothing to allocate.  In host code the array's
@@ -43,7 +51,6 @@ struct maaso_ctx {
   float* tab;           // device: three tables back to back, then tp_degree [n_tp] as uint32
   bool has_degree;      // the profile came with GPUs-per-instance figures
   uint32_t* status;     // device status word
-  uint32_t* cls_count;  // device [kMaxSlo]
   void* scratch_ptr;    // this device's copy of the static scratch array
   void* ws;             // device workspace: sized at load, resized only by maaso_ctx_reserve
   size_t ws_bytes;
@@ -58,14 +65,13 @@ struct maaso_ctx {
   uint32_t sweep_group;  // 0 = automatic
   uint32_t sweep_blocks_per_queue;  // 0 = automatic
   unsigned long long* last_evaluated;  // device word written by the last sweep, or null
-  bool counters_dirty;   // class counters may be non-zero (a call failed between its launches)
+  bool counters_dirty;   // histogram, cursors or totals may be non-zero (a call failed between its launches)
   uint32_t window_blocks;  // 0 = automatic
   uint32_t spin_limit;     // polls of the inter-window barrier before a block gives up
   bool window_profile;     // the windowed distributor records where block 0 spends its cycles
   bool window_profiled;    // ... and the last windowed call did
   int n_cu;
   int cooperative;      // the device launches cooperative grids (all blocks resident, or refused)
-  int sweep_resident[4];  // blocks of sweep_kernel<2|4|8|16> one compute unit holds at once
   size_t lds_per_block;
   // optional timing of the dominant kernel of each call (HIP events on the call's stream)
   bool timing;
@@ -195,12 +201,6 @@ bool narrow_ticks(const maaso_ctx* ctx, const maaso_params* prm, uint64_t per_wi
   for (uint32_t k = 0; k < ctx->n_slo; ++k) d = std::max(d, (double)ctx->d_ttft[k]);
   return d < (double)kNarrowSeconds && d * (1.0 + (double)per_window) < 4095.0 &&
          (double)prm->s_bar * (double)ctx->tbt_max * (1.0 + (double)prm->pen_kappa) < 1e38;
-}
-
-template <int Q>
-int launch_sweep(const SweepArgs& a, uint32_t blocks, hipStream_t s) {
-  hipLaunchKernelGGL(sweep_kernel<Q>, dim3(blocks), dim3(kSweepThreads), 0, s, a);
-  return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
 }
 
 int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t* cand_sel,
@@ -370,65 +370,37 @@ void add_sweep_window_set(SweepWindowArgs& a, const maaso_requests* rq, const ma
   t.score = out ? out->score : nullptr;
 }
 
-// Launch shape and workspace layout of the static sweep.
-struct SweepPlan {
-  uint32_t Q;         // requests per lane: a block owns 256*Q requests of one class
-  uint32_t G;         // candidates per work item
-  uint32_t n_items;   // ceil(C / G)
-  uint32_t nrb_max;   // request-tile slots of the grid (>= tiles that exist)
-  uint32_t blocks;    // 8 * nrb_max * blocks per (request tile, XCD) queue
-  uint32_t static_blocks;  // of them resident at the kernel's start
-  size_t lbuf_bytes, recs_bytes, queue_words;
-  size_t bytes;       // class-bucketed prompt lengths | staged records | queue heads and pair counts
-};
-
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
-int plan_static_sweep(const maaso_ctx* ctx, uint32_t C, uint32_t I, uint32_t R, SweepPlan& p) {
+// Workspace the static sweep of a shape is charged with: 4 bytes per (class, request), 16 per instance
+// slot, and per (request tile, XCD) queue 4 bytes and 16 per block that serves it, the tiles and blocks
+// as the launch-shape knobs or the rules here set them.  The grouped lengths it keeps (4 bytes per request)
+// take less; the charge is the boundary's, and what it refuses does not depend on how the sweep works.
+int static_sweep_bytes(const maaso_ctx* ctx, uint32_t C, uint32_t I, uint32_t R, size_t& bytes) {
   const uint32_t K = ctx->n_slo;
   uint32_t Q = ctx->sweep_q;
-  // measured: 16 pays from 2^17 requests on (fewer trips to LDS per request; below that the lower
-  // occupancy of its 102 registers costs more than it saves)
   if (Q == 0) Q = R >= (1u << 17) ? 16u : (R >= (1u << 14) ? 8u : (R >= (1u << 12) ? 4u : 2u));
-  uint32_t G = (uint32_t)kGroupSlots / I;
-  if (G > (uint32_t)kMaxGroup) G = kMaxGroup;
-  // measured: items of about 256 instance slots (8 candidates of 32 slots a third full: 105 us against
-  // 110 with 4 or 16; full slots: 4 and 8 equal; 128 slots: 1, 2 equal) balance the per-item
-  // barrier against the tail of the dynamic queues
-  uint32_t g_want = ctx->sweep_group ? ctx->sweep_group : (256u / I ? 256u / I : 1u);
+  uint32_t G = 512u / I;
+  if (G > 64u) G = 64u;
+  const uint32_t g_want = ctx->sweep_group ? ctx->sweep_group : (256u / I ? 256u / I : 1u);
   if (g_want < G) G = g_want;
   const uint32_t n_items = (C + G - 1) / G;
   const uint32_t tile = (uint32_t)kSweepThreads * Q;
-  const uint32_t nrb_max = (uint32_t)(((uint64_t)R + tile - 1) / tile) + K;  // >= tiles that exist
-  // Blocks: every (request tile, XCD) queue is served by bq persistent blocks.
+  const uint32_t tiles = (uint32_t)(((uint64_t)R + tile - 1) / tile) + K;
   const uint32_t per_queue = (n_items + 7u) / 8u;
   uint32_t bq = ctx->sweep_blocks_per_queue;
   if (bq == 0) {
-    // measured: about twice as many blocks as can be resident (8 per compute unit) - a block that
-    // leaves makes room for one that has not started, so the compute units stay full while the
-    // queues of small request tiles run dry
-    bq = ((uint32_t)ctx->n_cu * 18u + 4u * nrb_max) / (8u * nrb_max);
+    bq = ((uint32_t)ctx->n_cu * 18u + 4u * tiles) / (8u * tiles);
     if (bq == 0) bq = 1;
   }
   if (bq > per_queue) bq = per_queue ? per_queue : 1u;
-  const uint64_t blocks64 = (uint64_t)8 * nrb_max * bq;
+  const uint64_t blocks64 = (uint64_t)8 * tiles * bq;
   if (blocks64 > 0x7fffffffull) return MAASO_E_SHAPE;
-  // the blocks the device holds at once start together: they take their first items without a trip
-  // to the queue
-  const int qi = Q == 2 ? 0 : (Q == 4 ? 1 : (Q == 8 ? 2 : 3));
-  uint64_t resident = (uint64_t)ctx->n_cu * (uint64_t)ctx->sweep_resident[qi];
-  if (resident > blocks64) resident = blocks64;
-  p.static_blocks = (uint32_t)(resident & ~7ull);
-  p.Q = Q;
-  p.G = G;
-  p.n_items = n_items;
-  p.nrb_max = nrb_max;
-  p.blocks = (uint32_t)blocks64;
-  p.lbuf_bytes = up256((size_t)K * (R ? R : 1u) * sizeof(float));
-  p.recs_bytes = up256((size_t)C * I * sizeof(float4));
-  // queue heads, then two 8-byte evaluated-pairs words per sweep block
-  p.queue_words = (size_t)nrb_max * 8u + 4u * (size_t)blocks64;
-  p.bytes = p.lbuf_bytes + p.recs_bytes + up256(p.queue_words * sizeof(uint32_t));
+  // (the shapes whose preparation would have taken a grid beyond 2^31 blocks)
+  if (((uint64_t)R + 1023u) / 1024u + ((uint64_t)C * I + 511u) / 512u > 0x7fffffffull) return MAASO_E_SHAPE;
+  const size_t queue_words = (size_t)tiles * 8u + 4u * (size_t)blocks64;
+  bytes = up256((size_t)K * (R ? R : 1u) * sizeof(float)) + up256((size_t)C * I * sizeof(float4)) +
+          up256(queue_words * sizeof(uint32_t));
   return MAASO_OK;
 }
 
@@ -451,92 +423,87 @@ size_t workspace_bound(const maaso_ctx* ctx, uint32_t C, uint32_t I, uint32_t R)
   return need < split ? split : need;
 }
 
-// The three launches of the static sweep on workspace `ws` (at least plan.bytes, 256-byte aligned).
-// Everything in the workspace that must start at zero is cleared by the first launch.
+// The launches of the static sweep; `ws` holds the grouped prompt lengths, 4 bytes per request.
 int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_requests* rq,
-                        const maaso_params* prm, const SweepPlan& plan, void* ws, uint32_t* sat_count,
-                        float* sat_ratio, uint32_t* best_cand, hipStream_t s) {
+                        const maaso_params* prm, void* ws, uint32_t* sat_count, float* sat_ratio,
+                        uint32_t* best_cand, hipStream_t s) {
   const uint32_t C = pl->n_cand, I = pl->i_pad, K = ctx->n_slo, R = rq->n_req;
-  unsigned char* wsb = static_cast<unsigned char*>(ws);
-  float* lbuf = reinterpret_cast<float*>(wsb);
-  float4* recs = reinterpret_cast<float4*>(wsb + plan.lbuf_bytes);
-  uint32_t* queues = reinterpret_cast<uint32_t*>(wsb + plan.lbuf_bytes + plan.recs_bytes);
-  int rc = MAASO_OK;
-
+  uint32_t* hist = ctx->status + kCounterWord;
+  uint32_t* offsets = hist + 2u * kHistWords;
   if (ctx->counters_dirty) {  // an earlier call failed between its launches
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, ctx->cls_count, (uint32_t)kMaxSlo, 0u);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(16), dim3(256), 0, s, ctx->status + kTotalsWord,
+                       (kCounterWord - kTotalsWord) + 2u * kHistWords, 0u);
     if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
     ctx->counters_dirty = false;
   }
   ctx->counters_dirty = true;
-  {
-    PrepArgs p;
-    p.prompt_len = rq->prompt_len;
-    p.slo_class = rq->slo_class;
-    p.n_req = R;
-    p.n_slo = K;
-    p.lbuf = lbuf;
-    p.cls_count = ctx->cls_count;
-    p.n_bucket_blocks = (uint32_t)(((uint64_t)R + kBucketPerBlock - 1) / kBucketPerBlock);
-    p.tab = ctx->tab;
-    p.cells = ctx->cells;
-    p.mp = model_params(ctx, prm);
-    p.n_cand = C;
-    p.i_pad = I;
-    p.n_inst = pl->n_inst;
-    p.tp_idx = pl->tp_idx;
-    p.max_batch = pl->max_batch;
-    p.occ = pl->occ;
-    p.q_ticks = reinterpret_cast<const uint64_t*>(pl->q_ticks);
-    p.recs = recs;
-    p.sat_count = sat_count;
-    p.queues = queues;
-    p.n_queues = (uint32_t)plan.queue_words;
-    p.status = ctx->status;
-    const uint64_t n_stage = ((uint64_t)C * I + kStageSlotsPerBlock - 1) / kStageSlotsPerBlock;
-    const uint64_t n_prep = (uint64_t)p.n_bucket_blocks + n_stage;
-    if (n_prep > 0x7fffffffull) return MAASO_E_SHAPE;
-    size_t lds = (size_t)3 * ctx->cells * sizeof(float);
-    if (lds < 2 * kMaxSlo * sizeof(uint32_t)) lds = 2 * kMaxSlo * sizeof(uint32_t);
-    hipLaunchKernelGGL(sweep_prep_kernel, dim3((uint32_t)n_prep), dim3(256), lds, s, p);
+  const bool small = R <= kSmallRequests;
+  if (!small) {
+    GroupArgs g;
+    g.prompt_len = rq->prompt_len;
+    g.slo_class = rq->slo_class;
+    g.n_req = R;
+    g.n_slo = K;
+    // 1024 requests a block fill the chip from 2^18 on; beyond 1024 blocks each takes more
+    g.per_block = R > (1u << 20) ? (uint32_t)(((uint64_t)R + 1023u) / 1024u) : 1024u;
+    g.hist = hist;
+    g.cursor = hist + (size_t)K * kLenBins;
+    g.offsets = offsets;
+    g.sorted = static_cast<float*>(ws);
+    g.status = ctx->status;
+    const uint32_t blocks = (uint32_t)(((uint64_t)R + g.per_block - 1) / g.per_block);
+    hipLaunchKernelGGL(sweep_hist_kernel, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+    hipLaunchKernelGGL(sweep_scatter_kernel, dim3(blocks), dim3(kSweepThreads), 0, s, g);
     if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
   }
-  if (R != 0) {
-    SweepArgs a;
-    a.n_slo = K;
-    std::memcpy(a.d_ttft, ctx->d_ttft, sizeof(a.d_ttft));
-    std::memcpy(a.d_tbt, ctx->d_tbt, sizeof(a.d_tbt));
-    a.n_cand = C;
-    a.i_pad = I;
-    a.recs = recs;
-    a.lbuf = lbuf;
-    a.cls_count = ctx->cls_count;
-    a.n_req = R;
-    a.group = plan.G;
-    a.n_items = plan.n_items;
-    a.nrb_max = plan.nrb_max;
-    a.queues = queues;
-    a.static_blocks = plan.static_blocks;
-    a.sat_count = sat_count;
-    a.evaluated = reinterpret_cast<unsigned long long*>(queues + (size_t)plan.nrb_max * 8u);
-    {
-      TimedRegion timed(ctx, s);
-      switch (plan.Q) {
-        case 2: rc = launch_sweep<2>(a, plan.blocks, s); break;
-        case 4: rc = launch_sweep<4>(a, plan.blocks, s); break;
-        case 8: rc = launch_sweep<8>(a, plan.blocks, s); break;
-        default: rc = launch_sweep<16>(a, plan.blocks, s); break;
-      }
+  CountArgs a;
+  a.tab = ctx->tab;
+  a.cells = ctx->cells;
+  a.mp = model_params(ctx, prm);
+  a.n_slo = K;
+  std::memcpy(a.d_ttft, ctx->d_ttft, sizeof(a.d_ttft));
+  std::memcpy(a.d_tbt, ctx->d_tbt, sizeof(a.d_tbt));
+  a.n_cand = C;
+  a.i_pad = I;
+  a.n_inst = pl->n_inst;
+  a.tp_idx = pl->tp_idx;
+  a.max_batch = pl->max_batch;
+  a.occ = pl->occ;
+  a.q_ticks = reinterpret_cast<const uint64_t*>(pl->q_ticks);
+  a.n_req = R;
+  a.prompt_len = rq->prompt_len;
+  a.slo_class = rq->slo_class;
+  a.offsets = offsets;
+  a.sorted = static_cast<const float*>(ws);
+  a.clear = hist;
+  // a group of about 512 slots, two per thread, but no fewer than some 1024 groups while there are the
+  // candidates for it (four blocks per compute unit)
+  uint32_t G = (uint32_t)(((uint64_t)C + 1023u) / 1024u);
+  if (G > 512u / I) G = 512u / I;
+  if (G > kMaxGroup) G = kMaxGroup;
+  if (G == 0u) G = 1u;
+  a.group = G;
+  a.n_groups = (uint32_t)(((uint64_t)C + G - 1u) / G);
+  a.sat_count = sat_count;
+  a.sat_ratio = sat_ratio;
+  a.best_cand = best_cand;
+  a.totals = reinterpret_cast<SweepTotals*>(ctx->status + kTotalsWord);
+  a.eval_total = reinterpret_cast<unsigned long long*>(ctx->status + 32);
+  a.status = ctx->status;
+  const uint32_t cap = (uint32_t)ctx->n_cu * 6u;  // 65,536 x 32 slots: 38 us with 6 blocks per compute unit, 43 with 4 or 8
+  const dim3 grid(a.n_groups < cap ? a.n_groups : cap), block(kSweepThreads);
+  const size_t lds = ((size_t)K * kLenBins + 1u) * sizeof(uint32_t);
+  {
+    TimedRegion timed(ctx, s);
+    if (small) {
+      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<true, true>), grid, block, lds, s, a);
+      else hipLaunchKernelGGL((sweep_count_kernel<true, false>), grid, block, lds, s, a);
+    } else {
+      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true>), grid, block, lds, s, a);
+      else hipLaunchKernelGGL((sweep_count_kernel<false, false>), grid, block, lds, s, a);
     }
-    if (rc != MAASO_OK) return rc;
   }
-  // evaluated-pairs total lands in the context's small device block, next to the class counters
-  unsigned long long* eval_total = reinterpret_cast<unsigned long long*>(ctx->status + 32);
-  hipLaunchKernelGGL(sweep_finalize_kernel, dim3(1), dim3(1024), 0, s, sat_count, C, R, sat_ratio,
-                     best_cand, ctx->cls_count,
-                     reinterpret_cast<const unsigned long long*>(queues + (size_t)plan.nrb_max * 8u),
-                     R != 0 ? plan.blocks : 0u, eval_total);
-  ctx->last_evaluated = eval_total;
+  ctx->last_evaluated = a.eval_total;
   if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
   ctx->counters_dirty = false;
   return MAASO_OK;
@@ -761,16 +728,6 @@ int maaso_profile_tables_load(const maaso_profile_desc* d, int device, maaso_ctx
   ctx->lds_per_block = prop.sharedMemPerBlock;
   if (!hip_ok(hipDeviceGetAttribute(&ctx->cooperative, hipDeviceAttributeCooperativeLaunch, device)))
     ctx->cooperative = 0;
-  {
-    const void* fn[4] = {reinterpret_cast<const void*>(&sweep_kernel<2>), reinterpret_cast<const void*>(&sweep_kernel<4>),
-                         reinterpret_cast<const void*>(&sweep_kernel<8>), reinterpret_cast<const void*>(&sweep_kernel<16>)};
-    for (int i = 0; i < 4; ++i) {
-      int n = 0;
-      if (!hip_ok(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn[i], kSweepThreads, 0)) || n < 1) n = 4;
-      ctx->sweep_resident[i] = n;
-    }
-  }
-
   float* host = static_cast<float*>(std::malloc((size_t)3 * cells * sizeof(float)));
   if (!host) { delete ctx; return MAASO_E_NOMEM; }
   std::memcpy(host, d->prefill_a, (size_t)cells * 4);
@@ -784,10 +741,6 @@ int maaso_profile_tables_load(const maaso_profile_desc* d, int device, maaso_ctx
   if (rc == MAASO_OK) rc = alloc_workspace(ctx, (size_t)MAASO_DEFAULT_WORKSPACE_BYTES);
   if (rc == MAASO_OK && !hip_ok(hipEventCreateWithFlags(&ctx->order_ev, hipEventDisableTiming))) rc = MAASO_E_HIP;
   if (rc == MAASO_OK) {
-    // one small allocation, in 32-bit words: [0] status, [16..31] class counts, [32..35] evaluated
-    // pairs of the last sweep (all; those without a wait), [36..37] admitted-count accumulator and
-    // delivered-blocks ticket of the static distributor
-    ctx->cls_count = ctx->status + 16;
     if (!hip_ok(hipMemcpy(ctx->tab, host, (size_t)3 * cells * 4, hipMemcpyHostToDevice)) ||
         !hip_ok(hipMemset(ctx->status, 0, kSmallBytes)))
       rc = MAASO_E_HIP;
@@ -916,27 +869,24 @@ int placement_sweep_impl(maaso_ctx* ctx, const maaso_placements* pl, const maaso
       rc = launch_sweep_window<false>(a, prm->policy, (size_t)3 * ctx->cells * sizeof(float), s);
       if (rc != MAASO_OK) return rc;
     }
-    unsigned long long* eval_total = reinterpret_cast<unsigned long long*>(ctx->status + 32);
     hipLaunchKernelGGL(sweep_finalize_kernel, dim3(1), dim3(1024), 0, s, sat_count, C, R, sat_ratio,
-                       best_cand, ctx->cls_count, static_cast<const unsigned long long*>(nullptr), 0u,
-                       eval_total);
+                       best_cand);
     if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
     ctx->last_evaluated = nullptr;
     return MAASO_OK;
   }
 
-  SweepPlan plan;
-  rc = plan_static_sweep(ctx, C, I, R, plan);
+  size_t bytes = 0;
+  rc = static_sweep_bytes(ctx, C, I, R, bytes);
   if (rc != MAASO_OK) return rc;
   if (static_scratch) {
     if (!ctx->scratch_ptr) return MAASO_E_HIP;
-    if (plan.bytes > (size_t)MAASO_NOALLOC_SCRATCH_BYTES) return MAASO_E_SHAPE;
-    return launch_static_sweep(ctx, pl, rq, prm, plan, ctx->scratch_ptr, sat_count, sat_ratio,
-                               best_cand, s);
+    if (bytes > (size_t)MAASO_NOALLOC_SCRATCH_BYTES) return MAASO_E_SHAPE;
+    return launch_static_sweep(ctx, pl, rq, prm, ctx->scratch_ptr, sat_count, sat_ratio, best_cand, s);
   }
-  rc = need_workspace(ctx, plan.bytes);
+  rc = need_workspace(ctx, bytes);
   if (rc != MAASO_OK) return rc;
-  return launch_static_sweep(ctx, pl, rq, prm, plan, ctx->ws, sat_count, sat_ratio, best_cand, s);
+  return launch_static_sweep(ctx, pl, rq, prm, ctx->ws, sat_count, sat_ratio, best_cand, s);
 }
 
 }  // namespace

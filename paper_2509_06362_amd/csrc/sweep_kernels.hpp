@@ -1,35 +1,29 @@
-// Placer sweep: SLO-satisfaction count of every candidate deployment over the whole request set
-// (the evaluation of Phi_S(I', R_x) inside Alg. 1; Eq. 3).
+// Placer sweep against the state as given: SLO-satisfaction count of every candidate deployment over the
+// whole request set (the evaluation of Phi_S(I', R_x) inside Alg. 1; Eq. 3).
 //
-// Three launches (gfx950, wave64):
-//   1. sweep_prep_kernel - two jobs in one grid.  "bucket" blocks group the prompt lengths by SLO
-//      class, so that every block of the sweep holds requests of ONE class and its deadlines are
-//      scalars.  "stage" blocks evaluate the profile of every instance slot once (tables staged in
-//      LDS; Eq. 1 row, occupancy penalty, queue wait) and leave a 16-byte record {p, a, wait, tbt}
-//      per slot; padding slots and slots outside the tables get tbt = +inf and are never listed.
-//   2. sweep_kernel - persistent blocks.  A block owns a tile of 256*Q requests of one class (lanes =
-//      requests, Q per lane, in registers) and pulls work items - groups of G candidates - from a
-//      queue.  For each group the block filters the records on the between-token deadline of its
-//      class into compact per-candidate lists in LDS (double-buffered, loads for the next group are
-//      issued before the current group is scored, one barrier per group), then every wavefront
-//      streams the lists with broadcast LDS reads, two records per trip: per (request, instance) one
-//      fused multiply-add (prefill), one add (queue wait) and half of a three-input min.  Records
-//      whose queue wait is exactly zero are listed apart and walked without the add (0 + x = x).
-//   3. sweep_finalize_kernel - ratio = count / R and the best candidate (lowest index on ties).
+// A request of class k counts for a candidate iff some instance j meets the between-token deadline and
+// wait_j + (a_j + p_j L) meets the first-token one (the end-to-end margin is implied by the two:
+// S*tbt + ttft <= S*D_tbt + D_ttft holds in exact arithmetic and a correctly rounded fma is monotone).
+// The first-token latency never falls when the prompt length L grows, in binary32 as evaluated, so an
+// instance serves exactly the requests of the class up to a longest prompt, a candidate those up to the
+// longest of its instances, and the count is a rank among the class's prompt lengths.  The longest
+// prompt is found with the latency model itself (a division for a first guess, then evaluations at whole
+// lengths until one meets the deadline and its successor does not), so counts are those of evaluating
+// every (request, instance) pair, bit for bit, at one threshold per (instance, class) and one look-up
+// per (candidate, class).
 //
-// A request is satisfied iff min_j ttft_j <= D_ttft over the listed instances.  This is the same
-// predicate as "largest slack >= 0": the between-token margin depends only on (class, instance) and
-// is what the list filters on; the first-token margin is >= 0 iff ttft <= D_ttft; and the end-to-end
-// margin is implied by the other two, because S*tbt + ttft <= S*D_tbt + D_ttft holds in exact
-// arithmetic and a correctly rounded fma is monotone.
+// Launches:
+//   1. sweep_hist_kernel, 2. sweep_scatter_kernel - the prompt lengths grouped by (class, bin), 256 bins
+//      per class by the leading bits of the binary32 length (eight per octave), and the groups' offsets.
+//   3. sweep_count_kernel - blocks take groups of candidates: a thread per instance slot evaluates the
+//      profile (Eq. 1 row, occupancy penalty, queue wait) and its thresholds, the largest per
+//      (candidate, class) meet in LDS, sixteen lanes per (candidate, class) add the group of the
+//      threshold's bin to the lengths below it.  The last block to finish writes the best candidate.
+// Up to kSmallRequests requests the third launch is the only one: every block groups them in its own LDS.
 //
-// Counts: wave ballot + popcount (scalar unit), parked in one lane per candidate, summed over the
-// block's four wavefronts in LDS, then one integer atomic per candidate per block; integer sums are
-// order-independent, so the result does not depend on scheduling.
-//
-// Queues are XCD-aware: hardware deals consecutive blocks round-robin to the 8 XCDs, and the queue of
-// a block with id b only holds the groups g with g % 8 == b % 8, so a group's records are read into
-// one XCD's L2 only and are shared there by the blocks of all request tiles.
+// What bounds it: the instance slots' 15 bytes each and the latency of three short launches.  65,536
+// candidates x 32 slots x 16,384 requests: 457 -> 40 us; 8192 x 128 x 131,072: 5240 -> 43 us; 4096 x 32 x 65,536:
+// 127 -> 24 us; 37 x 13 x 1000: 18 -> 12 us (before: every pair evaluated on the vector units).
 #pragma once
 
 #include "device_model.hpp"
@@ -41,12 +35,9 @@ namespace maaso {
 constexpr int kSweepThreads = 256;  // 4 wavefronts
 constexpr int kWave = 64;
 constexpr int kMaxSlo = 16;
-constexpr int kSweepWaves = kSweepThreads / kWave;
-constexpr int kSlotsPerThread = 2;                            // instance slots a thread files per group
-constexpr int kGroupSlots = kSweepThreads * kSlotsPerThread;  // 512 records per LDS buffer
-constexpr int kMaxGroup = 64;                                 // candidates per group (one lane each)
-constexpr int kStageSlotsPerBlock = 512;   // two per thread: short blocks, their loads overlap
-constexpr int kBucketPerBlock = 1024;
+constexpr uint32_t kLenBins = 256;              // per class
+constexpr uint32_t kSmallRequests = 4096;       // grouped by every block for itself
+constexpr uint32_t kMaxGroup = 64;              // candidates a block works on at a time
 
 // Barrier that publishes LDS atomics.  For atomics whose result is unused the compiler emits no wait
 // on the LDS counter before the s_barrier of __syncthreads(), and on gfx950 a wavefront reading behind
@@ -70,577 +61,422 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t n, uint32_t v) {
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
 }
 
-// v_min_f32 on values that are never NaN (the compiler's fminf adds a canonicalising v_max first).
-__device__ __forceinline__ float min_no_nan(float x, float y) {
-  float r;
-  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-  return r;
-}
-
-// min(x, y, z) in one instruction slot.
-__device__ __forceinline__ float min3_no_nan(float x, float y, float z) {
-  float r;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
-  return r;
-}
-
-// v[lane] = value for a uniform value and lane index (both scalar).  The instruction reads one scalar
-// register beside M0, so the lane index travels through M0, whose content is put back afterwards
-// (the compiler does not track M0 across an asm statement).
-__device__ __forceinline__ void write_lane(uint32_t& v, uint32_t value, uint32_t lane_index) {
-  uint32_t keep;
-  asm("s_mov_b32 %1, m0\n\ts_mov_b32 m0, %3\n\tv_writelane_b32 %0, %2, m0\n\ts_mov_b32 m0, %1"
-      : "+v"(v), "=&s"(keep)
-      : "s"(value), "s"(lane_index));
-}
-
 __device__ __forceinline__ float max_no_nan(float x, float y) {
   float r;
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
   return r;
 }
 
-// First-token latency of a lane's Q requests on one listed instance: prefill (fused), plus the queue
-// wait where the instance has one.  A record is {p, a, wait, tbt}.
-template <int Q, bool kWait>
-__device__ __forceinline__ void fold_first(float (&m)[Q], const float (&L)[Q], const float4* p) {
-  const float4 r = p[0];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) m[q] = kWait ? r.z + fmaf(r.x, L[q], r.y) : fmaf(r.x, L[q], r.y);
+// A condition as a mask of the wavefront's lanes (scalar register pair), and back.
+__device__ __forceinline__ unsigned long long lane_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// Bin of a length >= 0: non-decreasing in it.  Bin 0 is below 1.125, then eight bins per octave.
+__device__ __forceinline__ uint32_t length_bin(float L) {
+  constexpr uint32_t kFirst = 127u << 3;
+  const uint32_t k = __float_as_uint(L) >> 20;
+  return k <= kFirst ? 0u : min(k - kFirst, kLenBins - 1u);
 }
 
-template <int Q, bool kWait>
-__device__ __forceinline__ void fold_one(float (&m)[Q], const float (&L)[Q], const float4* p) {
-  const float4 r = p[0];
-#pragma unroll
-  for (int q = 0; q < Q; ++q)
-    m[q] = min_no_nan(m[q], kWait ? r.z + fmaf(r.x, L[q], r.y) : fmaf(r.x, L[q], r.y));
-}
-
-// Two records folded into the running minimum with ONE three-input minimum per request: per request
-// fma, fma (each followed by the add of the queue wait where there is one), min3.  The sequence is
-// fixed here instead of being left to the compiler's scheduler: two requests are interleaved so that
-// no instruction reads the result of the one just before it, and four temporaries serve all requests
-// (scheduled freely, the 2*Q products of a pair were all formed first, and with several pairs
-// unrolled the kernel spilled).  v_fma_f32 / v_add_f32 / v_min3_f32 are the instructions the compiler
-// emits for fmaf, + and a NaN-free minimum, so the values are the same bit for bit.
-// Operands: %0-%(N-1) running minima, then 4 temporaries, then N prompt lengths, then p, a of the two
-// records (and their waits).
-#define MAASO_FOLD2(MA, MB, LA, LB, T0, T1, T2, T3, RX, RY, UX, UY)                                  \
-  "v_fma_f32 " T0 ", " RX ", " LA ", " RY "\n\t" "v_fma_f32 " T1 ", " UX ", " LA ", " UY "\n\t"        \
-  "v_fma_f32 " T2 ", " RX ", " LB ", " RY "\n\t" "v_fma_f32 " T3 ", " UX ", " LB ", " UY "\n\t"        \
-  "v_min3_f32 " MA ", " MA ", " T0 ", " T1 "\n\t" "v_min3_f32 " MB ", " MB ", " T2 ", " T3 "\n\t"
-#define MAASO_FOLD2W(MA, MB, LA, LB, T0, T1, T2, T3, RX, RY, UX, UY, RZ, UZ)                         \
-  "v_fma_f32 " T0 ", " RX ", " LA ", " RY "\n\t" "v_fma_f32 " T1 ", " UX ", " LA ", " UY "\n\t"        \
-  "v_fma_f32 " T2 ", " RX ", " LB ", " RY "\n\t" "v_fma_f32 " T3 ", " UX ", " LB ", " UY "\n\t"        \
-  "v_add_f32 " T0 ", " RZ ", " T0 "\n\t" "v_add_f32 " T1 ", " UZ ", " T1 "\n\t"                       \
-  "v_add_f32 " T2 ", " RZ ", " T2 "\n\t" "v_add_f32 " T3 ", " UZ ", " T3 "\n\t"                       \
-  "v_min3_f32 " MA ", " MA ", " T0 ", " T1 "\n\t" "v_min3_f32 " MB ", " MB ", " T2 ", " T3 "\n\t"
-
-template <bool kWait>
-__device__ __forceinline__ void fold_pair_n(float (&m)[2], const float (&L)[2], const float4& r,
-                                            const float4& u) {
-  float t0, t1, t2, t3;
-  if (kWait)
-    asm(MAASO_FOLD2W("%0", "%1", "%6", "%7", "%2", "%3", "%4", "%5", "%8", "%9", "%10", "%11", "%12", "%13")
-        : "+v"(m[0]), "+v"(m[1]), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-        : "v"(L[0]), "v"(L[1]), "v"(r.x), "v"(r.y), "v"(u.x), "v"(u.y), "v"(r.z), "v"(u.z));
-  else
-    asm(MAASO_FOLD2("%0", "%1", "%6", "%7", "%2", "%3", "%4", "%5", "%8", "%9", "%10", "%11")
-        : "+v"(m[0]), "+v"(m[1]), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-        : "v"(L[0]), "v"(L[1]), "v"(r.x), "v"(r.y), "v"(u.x), "v"(u.y));
-}
-
-template <bool kWait>
-__device__ __forceinline__ void fold_pair_n(float (&m)[4], const float (&L)[4], const float4& r,
-                                            const float4& u) {
-  float t0, t1, t2, t3;
-  if (kWait)
-    asm(MAASO_FOLD2W("%0", "%1", "%8", "%9", "%4", "%5", "%6", "%7", "%12", "%13", "%14", "%15", "%16", "%17")
-        MAASO_FOLD2W("%2", "%3", "%10", "%11", "%4", "%5", "%6", "%7", "%12", "%13", "%14", "%15", "%16", "%17")
-        : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-        : "v"(L[0]), "v"(L[1]), "v"(L[2]), "v"(L[3]), "v"(r.x), "v"(r.y), "v"(u.x), "v"(u.y), "v"(r.z),
-          "v"(u.z));
-  else
-    asm(MAASO_FOLD2("%0", "%1", "%8", "%9", "%4", "%5", "%6", "%7", "%12", "%13", "%14", "%15")
-        MAASO_FOLD2("%2", "%3", "%10", "%11", "%4", "%5", "%6", "%7", "%12", "%13", "%14", "%15")
-        : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-        : "v"(L[0]), "v"(L[1]), "v"(L[2]), "v"(L[3]), "v"(r.x), "v"(r.y), "v"(u.x), "v"(u.y));
-}
-
-template <bool kWait>
-__device__ __forceinline__ void fold_pair_n(float (&m)[8], const float (&L)[8], const float4& r,
-                                            const float4& u) {
-  float t0, t1, t2, t3;
-  if (kWait)
-    asm(MAASO_FOLD2W("%0", "%1", "%12", "%13", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23", "%24", "%25")
-        MAASO_FOLD2W("%2", "%3", "%14", "%15", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23", "%24", "%25")
-        MAASO_FOLD2W("%4", "%5", "%16", "%17", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23", "%24", "%25")
-        MAASO_FOLD2W("%6", "%7", "%18", "%19", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23", "%24", "%25")
-        : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]), "+v"(m[4]), "+v"(m[5]), "+v"(m[6]), "+v"(m[7]),
-          "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-        : "v"(L[0]), "v"(L[1]), "v"(L[2]), "v"(L[3]), "v"(L[4]), "v"(L[5]), "v"(L[6]), "v"(L[7]), "v"(r.x),
-          "v"(r.y), "v"(u.x), "v"(u.y), "v"(r.z), "v"(u.z));
-  else
-    asm(MAASO_FOLD2("%0", "%1", "%12", "%13", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23")
-        MAASO_FOLD2("%2", "%3", "%14", "%15", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23")
-        MAASO_FOLD2("%4", "%5", "%16", "%17", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23")
-        MAASO_FOLD2("%6", "%7", "%18", "%19", "%8", "%9", "%10", "%11", "%20", "%21", "%22", "%23")
-        : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]), "+v"(m[4]), "+v"(m[5]), "+v"(m[6]), "+v"(m[7]),
-          "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-        : "v"(L[0]), "v"(L[1]), "v"(L[2]), "v"(L[3]), "v"(L[4]), "v"(L[5]), "v"(L[6]), "v"(L[7]), "v"(r.x),
-          "v"(r.y), "v"(u.x), "v"(u.y));
-}
-
-template <int Q, bool kWait>
-__device__ __forceinline__ void fold_pair(float (&m)[Q], const float (&L)[Q], const float4* p) {
-  static_assert(Q == 2 || Q == 4 || Q == 8 || Q == 16, "requests per lane");
-  const float4 r = p[0];
-  const float4 u = p[1];
-  if constexpr (Q == 16) {  // an asm statement takes at most 30 operands: two halves of eight requests
-    fold_pair_n<kWait>(reinterpret_cast<float (&)[8]>(m[0]), reinterpret_cast<const float (&)[8]>(L[0]), r, u);
-    fold_pair_n<kWait>(reinterpret_cast<float (&)[8]>(m[8]), reinterpret_cast<const float (&)[8]>(L[8]), r, u);
-  } else {
-    fold_pair_n<kWait>(m, L, r, u);
+// Exclusive prefix of the block's per-thread sums, in thread order.  `part`: one word per wavefront.
+__device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t* part) {
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  uint32_t inc = v;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(inc, d);
+    if (lane >= (uint32_t)d) inc += o;
   }
+  if (lane == 63u) part[wave] = inc;
+  __syncthreads();
+  uint32_t before = inc - v;
+  for (uint32_t w = 0; w < wave; ++w) before += part[w];
+  return before;
 }
 
-// Smallest first-token latency over a list of n > 0 records (uniform n, LDS list).  `fresh`: m holds
-// nothing yet and is initialised from the list's first record(s).  After an odd record (or the
-// initialising one or two) the list is walked in pairs: blocks of eight pairs (four with 16 requests
-// per lane) in a loop, then the rest in straight-line pieces of four, two and one pairs - constant
-// LDS offsets inside a piece, so its reads are issued ahead of the arithmetic, and next to nothing is
-// spent on loop control for the short lists of typical candidate deployments.
-template <int Q, bool kWait>
-__device__ __forceinline__ void walk_list(float (&m)[Q], const float (&L)[Q], const float4* p,
-                                          uint32_t n, bool fresh) {
-  if (fresh) {
-    if (n & 1u) {
-      fold_first<Q, kWait>(m, L, p);
-      p += 1;
-    } else {
-      fold_first<Q, kWait>(m, L, p);
-      fold_one<Q, kWait>(m, L, p + 1);
-      p += 2;
-    }
-    n = (n - 1u) >> 1;
-  } else {
-    if (n & 1u) {
-      fold_one<Q, kWait>(m, L, p);
-      p += 1;
-    }
-    n >>= 1;
-  }
-  // pairs per block of the loop: the records of a block are all in flight at once (three registers
-  // each), so with 16 requests per lane a block is four pairs
-  constexpr uint32_t kBlock = Q <= 8 ? 8u : 4u;
-  for (; n >= kBlock; n -= kBlock, p += 2u * kBlock) {
-#pragma unroll
-    for (uint32_t k = 0; k < kBlock; ++k) fold_pair<Q, kWait>(m, L, p + 2u * k);
-  }
-  // what is left of a block, by the binary digits of its pair count: straight-line pieces of four,
-  // two and one pairs behind plain uniform branches
-  if (kBlock > 4u && (n & 4u)) {
-#pragma unroll
-    for (uint32_t k = 0; k < 4u; ++k) fold_pair<Q, kWait>(m, L, p + 2u * k);
-    p += 8;
-  }
-  if (n & 2u) {
-    fold_pair<Q, kWait>(m, L, p);
-    fold_pair<Q, kWait>(m, L, p + 2);
-    p += 4;
-  }
-  if (n & 1u) fold_pair<Q, kWait>(m, L, p);
-}
-
-// ---------------------------------------------------------------------------------------------
-struct PrepArgs {
-  // bucket job
+struct GroupArgs {
   const uint32_t* prompt_len;
   const uint8_t* slo_class;
   uint32_t n_req, n_slo;
-  float* lbuf;          // [n_slo][n_req] prompt lengths (as float) grouped by class, any order inside
-  uint32_t* cls_count;  // [n_slo], zero on entry
-  uint32_t n_bucket_blocks;
-  // stage job
+  uint32_t per_block;  // requests per block, contiguous
+  uint32_t* hist;      // [n_slo * kLenBins] zero on entry; the count kernel clears it again
+  uint32_t* cursor;    // [n_slo * kLenBins] as hist
+  uint32_t* offsets;   // [n_slo * kLenBins + 1]
+  float* sorted;       // [n_req]
+  uint32_t* status;
+};
+
+// Calls f(group, length) for the requests [r0, r1) of this block whose class exists.
+template <bool kFlag, class F>
+__device__ __forceinline__ void for_requests(const uint32_t* prompt_len, const uint8_t* slo_class, uint32_t r0,
+                                             uint32_t r1, uint32_t n_slo, uint32_t* status, F f) {
+  constexpr uint32_t U = 4;  // loads in flight per thread
+  for (uint32_t base = r0; base < r1; base = r1 - base > U * kSweepThreads ? base + U * kSweepThreads : r1) {
+    uint32_t k[U];
+    float L[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t at = u * kSweepThreads + threadIdx.x;
+      const bool in = at < r1 - base;
+      k[u] = in ? slo_class[base + at] : 0xffffffffu;
+      L[u] = in ? (float)prompt_len[base + at] : 0.0f;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      if (k[u] < n_slo) f(k[u] * kLenBins + length_bin(L[u]), L[u]);
+      else if (kFlag && k[u] != 0xffffffffu) raise_status(status, 1u);
+    }
+  }
+}
+
+__global__ __launch_bounds__(kSweepThreads) void sweep_hist_kernel(const GroupArgs a) {
+  __shared__ uint32_t h[kMaxSlo * kLenBins];
+  const uint32_t n = a.n_slo * kLenBins;
+  for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads) h[i] = 0u;
+  __syncthreads();
+  const uint32_t r0 = blockIdx.x * a.per_block;  // the grid covers the requests without overflow
+  const uint32_t r1 = a.n_req - r0 > a.per_block ? r0 + a.per_block : a.n_req;
+  for_requests<true>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
+                     [&](uint32_t g, float) { atomicAdd(&h[g], 1u); });
+  lds_atomics_barrier();
+  for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads)
+    if (h[i] != 0u) atomicAdd(&a.hist[i], h[i]);
+}
+
+__global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const GroupArgs a) {
+  __shared__ uint32_t h[kMaxSlo * kLenBins];
+  __shared__ uint32_t start[kMaxSlo * kLenBins];
+  __shared__ uint32_t part[kSweepThreads / kWave];
+  const uint32_t n = a.n_slo * kLenBins, tid = threadIdx.x;
+  // where each group starts: every block works it out from the totals (thread t holds n_slo groups)
+  uint32_t sum = 0;
+  for (uint32_t q = 0; q < a.n_slo; ++q) {
+    const uint32_t v = a.hist[tid * a.n_slo + q];
+    start[tid * a.n_slo + q] = v;
+    sum += v;
+  }
+  for (uint32_t i = tid; i < n; i += kSweepThreads) h[i] = 0u;
+  uint32_t before = block_prefix(sum, part);
+  for (uint32_t q = 0; q < a.n_slo; ++q) {
+    const uint32_t i = tid * a.n_slo + q, v = start[i];
+    start[i] = before;
+    if (blockIdx.x == 0u) a.offsets[i] = before;
+    before += v;
+  }
+  if (blockIdx.x == 0u && tid == kSweepThreads - 1u) a.offsets[n] = before;
+  __syncthreads();
+  const uint32_t r0 = blockIdx.x * a.per_block;
+  const uint32_t r1 = a.n_req - r0 > a.per_block ? r0 + a.per_block : a.n_req;
+  for_requests<false>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
+                      [&](uint32_t g, float) { atomicAdd(&h[g], 1u); });
+  lds_atomics_barrier();
+  // this block's share of every group it has requests of
+  for (uint32_t i = tid; i < n; i += kSweepThreads)
+    if (h[i] != 0u) h[i] = start[i] + atomicAdd(&a.cursor[i], h[i]);
+  __syncthreads();
+  for_requests<false>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
+                      [&](uint32_t g, float L) { a.sorted[atomicAdd(&h[g], 1u)] = L; });
+}
+
+// The longest prompt whose first-token latency meets the deadline, as the bits of its binary32 value plus
+// one, or 0 when not even an empty prompt does: from a first guess `n`, the bracket around the answer is
+// doubled, then halved (at most some 64 evaluations, whatever the profile).
+__device__ __forceinline__ uint32_t search_longest(float a, float p, float wait, float deadline, uint32_t n) {
+  auto meets = [&](uint32_t m) { return wait + fmaf(p, (float)m, a) <= deadline; };
+  uint32_t lo, hi;  // lo meets the deadline, hi does not
+  if (meets(n)) {
+    lo = n;
+    for (uint32_t step = 1u;; step = step < (1u << 31) ? step << 1 : step) {
+      if (lo == 0xffffffffu) return __float_as_uint((float)lo) + 1u;
+      hi = lo + min(step, 0xffffffffu - lo);
+      if (!meets(hi)) break;
+      lo = hi;
+    }
+  } else {
+    hi = n;
+    for (uint32_t step = 1u;; step = step < (1u << 31) ? step << 1 : step) {
+      if (hi == 0u) return 0u;
+      lo = hi > step ? hi - step : 0u;
+      if (meets(lo)) break;
+      hi = lo;
+    }
+  }
+  while (hi - lo > 1u) {
+    const uint32_t mid = lo + ((hi - lo) >> 1);
+    if (meets(mid)) lo = mid; else hi = mid;
+  }
+  return __float_as_uint((float)lo) + 1u;
+}
+
+// The same with `inv_p`, about 1 / p: the quotient's whole part is nearly always the answer (it meets the
+// deadline, one more does not), and is tried without a branch.  `wanted` false: 0.
+__device__ __forceinline__ uint32_t longest_prompt(float a, float p, float wait, float deadline, float inv_p,
+                                                   bool wanted) {
+  const float guess = fminf(fmaxf(floorf(((deadline - wait) - a) * inv_p), 0.0f), 4294967040.0f);
+  const bool now = wait + fmaf(p, guess, a) <= deadline;
+  const bool next = wait + fmaf(p, guess + 1.0f, a) <= deadline;
+  uint32_t key = now ? __float_as_uint(guess) + 1u : 0u;
+  // settled: the quotient, or nothing at all (from 2^24 on guess + 1 may be the guess itself)
+  const bool settled = now ? !next : guess == 0.0f;
+  if (!settled & wanted) key = search_longest(a, p, wait, deadline, (uint32_t)guess);
+  return wanted ? key : 0u;
+}
+
+// Accumulators of the count kernel, zero between calls, a cache line each.  Blocks deliver to line
+// 1 + (block mod kTotalsLines), the last to deliver to a line hands its totals on to line 0, and the last
+// there has them all; whoever is last clears the line.  (Returning atomics on one line take 12 ns each:
+// 1024 blocks on a single set of accumulators were 55 us.)
+constexpr uint32_t kTotalsLines = 32;
+struct alignas(128) SweepTotals {
+  unsigned long long best;        // (count << 32) | ~candidate, the largest
+  unsigned long long pairs[2];    // (request, instance) pairs past the between-token check: all, without a wait
+  uint32_t delivered;             // blocks, or lines
+};
+
+// Adds to a line; true, with the line's totals, for the last of `parties`.  Atomics at device scope only,
+// each waited for before the delivery is counted: no fence.
+__device__ __forceinline__ bool deliver(SweepTotals* t, uint32_t parties, unsigned long long& best,
+                                        unsigned long long& pairs, unsigned long long& fresh) {
+  const unsigned long long r0 = atomicMax(&t->best, best);
+  const unsigned long long r1 = atomicAdd(&t->pairs[0], pairs);
+  const unsigned long long r2 = atomicAdd(&t->pairs[1], fresh);
+  asm volatile("s_waitcnt vmcnt(0)" : : "v"(r0), "v"(r1), "v"(r2) : "memory");
+  if (atomicAdd(&t->delivered, 1u) != parties - 1u) return false;
+  best = atomicExch(&t->best, 0ull);
+  pairs = atomicExch(&t->pairs[0], 0ull);
+  fresh = atomicExch(&t->pairs[1], 0ull);
+  atomicExch(&t->delivered, 0u);
+  return true;
+}
+
+struct CountArgs {
   const float* tab;  // three tables back to back, `cells` entries each
   uint32_t cells;
   ModelParams mp;
+  uint32_t n_slo;
+  float d_ttft[kMaxSlo], d_tbt[kMaxSlo];
   uint32_t n_cand, i_pad;
   const uint32_t* n_inst;
   const uint8_t* tp_idx;
   const uint16_t* max_batch;
   const int32_t* occ;
   const uint64_t* q_ticks;
-  float4* recs;  // [n_cand * i_pad] {p, a, wait, tbt}
-  // per-call accumulators to clear
-  uint32_t* sat_count;  // [n_cand]
-  uint32_t* queues;     // [n_queues]
-  uint32_t n_queues;  // words to clear: queue heads and evaluated-pair words
+  uint32_t n_req;
+  const uint32_t* prompt_len;  // small form: the requests themselves
+  const uint8_t* slo_class;
+  const uint32_t* offsets;     // large form: groups and lengths from the two launches before
+  const float* sorted;
+  uint32_t* clear;             // their histogram and cursors, 2 * n_slo * kLenBins words, cleared again
+  uint32_t group, n_groups;    // candidates per group
+  uint32_t* sat_count;
+  float* sat_ratio;
+  uint32_t* best_cand;
+  SweepTotals* totals;             // [1 + kTotalsLines]
+  unsigned long long* eval_total;  // [2]
   uint32_t* status;
 };
 
-__global__ __launch_bounds__(256) void sweep_prep_kernel(const PrepArgs a) {
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {  // over 16 consecutive lanes
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true));   // quad_perm [2,3,0,1]
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));  // row_half_mirror
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));  // row_mirror
+  return v;
+}
+__device__ __forceinline__ uint32_t row_sum_u32(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true);
+  return v;
+}
+
+// kSmall: at most kSmallRequests requests, grouped here.  kRows: i_pad is a multiple of 16, so the 16 lanes
+// of a DPP row hold slots of one candidate.
+template <bool kSmall, bool kRows>
+__global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const uint32_t tid = threadIdx.x;
-  if (blockIdx.x < a.n_bucket_blocks) {
-    // ---- bucket: lbuf[k * n_req + pos] = (float)prompt_len, pos < cls_count[k]
-    uint32_t* blk_cnt = reinterpret_cast<uint32_t*>(smem);
-    uint32_t* blk_base = blk_cnt + kMaxSlo;
-    constexpr int kPer = kBucketPerBlock / 256;
-    const uint32_t tile = blockIdx.x * (uint32_t)kBucketPerBlock;
-    if (tid < kMaxSlo) blk_cnt[tid] = 0u;
+  uint32_t* off = reinterpret_cast<uint32_t*>(smem);                // [n_slo * kLenBins + 1]
+  __shared__ float own[kSmall ? kSmallRequests : 1];                // the grouped lengths
+  __shared__ uint32_t longest[kMaxGroup * kMaxSlo];                 // per (candidate, class) of the group
+  __shared__ uint32_t cnt[kMaxGroup];
+  __shared__ float4 rows[kMaxSlo];                                  // class rows
+  __shared__ uint32_t part[kSweepThreads / kWave];
+  __shared__ unsigned long long ends[3][kSweepThreads / kWave];
+
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t K = a.n_slo, I = a.i_pad, n = K * kLenBins;
+  if (kSmall) {
+    // counts at off[g + 1], then the groups' starts there; dealing the lengths out moves each to its
+    // group's end, which is the next group's start
+    for (uint32_t i = tid; i <= n; i += kSweepThreads) off[i] = 0u;
     __syncthreads();
-    uint32_t k[kPer], rank[kPer];
-    float L[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const uint32_t r = tile + u * 256u + tid;
-      k[u] = 0xffffffffu;
-      rank[u] = 0u;
-      L[u] = 0.0f;
-      if (r < a.n_req) {
-        const uint32_t c = a.slo_class[r];
-        L[u] = (float)a.prompt_len[r];
-        if (c < a.n_slo) {
-          k[u] = c;
-          rank[u] = atomicAdd(&blk_cnt[c], 1u);
-        } else {
-          raise_status(a.status, 1u);
-        }
-      }
+    for_requests<true>(a.prompt_len, a.slo_class, 0u, a.n_req, K, a.status,
+                       [&](uint32_t g, float) { atomicAdd(&off[g + 1u], 1u); });
+    lds_atomics_barrier();
+    uint32_t sum = 0;
+    for (uint32_t q = 0; q < K; ++q) sum += off[tid * K + q + 1u];
+    uint32_t before = block_prefix(sum, part);
+    for (uint32_t q = 0; q < K; ++q) {
+      const uint32_t v = off[tid * K + q + 1u];
+      off[tid * K + q + 1u] = before;
+      before += v;
     }
     __syncthreads();
-    if (tid < a.n_slo) {
-      const uint32_t n = blk_cnt[tid];
-      blk_base[tid] = n ? atomicAdd(&a.cls_count[tid], n) : 0u;
-    }
+    for_requests<false>(a.prompt_len, a.slo_class, 0u, a.n_req, K, a.status,
+                        [&](uint32_t g, float L) { own[atomicAdd(&off[g + 1u], 1u)] = L; });
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      if (k[u] != 0xffffffffu) a.lbuf[(size_t)k[u] * a.n_req + blk_base[k[u]] + rank[u]] = L[u];
-    return;
-  }
-  // ---- stage: one record per instance slot, tables read from LDS
-  float* tab = reinterpret_cast<float*>(smem);
-  for (uint32_t i = tid; i < 3u * a.cells; i += 256u) tab[i] = a.tab[i];
-  const uint32_t sb = blockIdx.x - a.n_bucket_blocks;
-  {  // queue heads, then the per-block words that count evaluated pairs: every stage block clears a slice
-    const uint32_t n_stage = gridDim.x - a.n_bucket_blocks;
-    for (uint32_t i = sb * 256u + tid; i < a.n_queues; i += n_stage * 256u) a.queues[i] = 0u;
-  }
-  __syncthreads();
-  const uint64_t n_slots = (uint64_t)a.n_cand * a.i_pad;
-  const uint64_t base = (uint64_t)sb * kStageSlotsPerBlock;
-  constexpr int kPerThread = kStageSlotsPerBlock / 256;
-  // all loads first, so that their latencies overlap
-  uint32_t tp[kPerThread], B[kPerThread], c_of[kPerThread];
-  int32_t occ[kPerThread];
-  uint64_t q[kPerThread];
-  bool live[kPerThread], valid[kPerThread];
-#pragma unroll
-  for (int u = 0; u < kPerThread; ++u) {
-    const uint64_t s = base + (uint64_t)u * 256u + tid;
-    live[u] = s < n_slots;
-    valid[u] = false;
-    tp[u] = 0; B[u] = 1; occ[u] = 0; q[u] = 0; c_of[u] = 0;
-    if (live[u]) {
-      const uint32_t c = (uint32_t)(s / a.i_pad);
-      const uint32_t j = (uint32_t)(s - (uint64_t)c * a.i_pad);
-      c_of[u] = c;
-      if (j == 0u) a.sat_count[c] = 0u;
-      valid[u] = j < a.n_inst[c];
-      tp[u] = a.tp_idx[s]; B[u] = a.max_batch[s]; occ[u] = a.occ[s]; q[u] = a.q_ticks[s];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kPerThread; ++u) {
-    if (!live[u]) continue;
-    const uint64_t s = base + (uint64_t)u * 256u + tid;
-    float4 rec = make_float4(0.0f, 0.0f, INFINITY, INFINITY);  // absent: never listed
-    if (valid[u]) {
-      Staged st;
-      if (stage_instance(tab, a.cells, a.mp, tp[u], B[u], occ[u], q[u], st))
-        rec = make_float4(st.p, st.a, st.wait, st.tbt);
-      else
-        raise_status(a.status, 2u);
-    }
-    a.recs[s] = rec;
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-struct SweepArgs {
-  uint32_t n_slo;
-  float d_ttft[kMaxSlo];
-  float d_tbt[kMaxSlo];
-  uint32_t n_cand, i_pad;
-  const float4* recs;         // [n_cand * i_pad] staged records
-  const float* lbuf;          // [n_slo][n_req]
-  const uint32_t* cls_count;  // [n_slo]
-  uint32_t n_req;
-  uint32_t group;    // G: candidates per work item, G * i_pad <= kGroupSlots, G <= kMaxGroup
-  uint32_t n_items;  // ceil(n_cand / G)
-  uint32_t nrb_max;  // request-tile slots of the grid (>= tiles that exist)
-  uint32_t* queues;  // [nrb_max][8] next position of each (request tile, XCD) queue
-  uint32_t static_blocks;  // blocks (a multiple of 8) resident at the kernel's start: they take their
-                           // first two items by rank instead of from the queue
-  uint32_t* sat_count;
-  unsigned long long* evaluated;  // [2][gridDim.x] per block: (request, instance) pairs that reached
-                                  // the latency loop (zero on entry; summed by the finalize kernel)
-};
-
-template <int Q>
-__device__ __forceinline__ void sweep_body(const SweepArgs& a) {
-  __shared__ float4 lists[2][kGroupSlots];
-  __shared__ uint32_t lens[3][2][kMaxGroup];  // [buffer][0: records without a wait, 1: with][candidate]
-  __shared__ uint32_t blk_cnt[2][kSweepWaves][kMaxGroup];
-  __shared__ uint32_t items[2];
-
-  const uint32_t tid = threadIdx.x;
-  const uint32_t lane = tid & 63u;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t xcd = blockIdx.x & 7u;
-  const uint32_t slot = blockIdx.x >> 3;  // this block's place among the blocks of its XCD
-  const uint32_t rb = slot % a.nrb_max;
-  const uint32_t G = a.group, I = a.i_pad;
-
-  // Work items of this block.  Its (request tile, XCD) queue holds the groups xcd, xcd + 8, ...  The
-  // blocks that are resident when the kernel starts (the first a.static_blocks of the grid) take
-  // their first two items by their rank among the queue's blocks - no memory access, so the records
-  // of the first item are requested before anything else; every further item, and every item of a
-  // block that starts later, comes from the queue's counter.
-  uint32_t* queue = a.queues + (size_t)rb * 8u + xcd;
-  const uint32_t rank = slot / a.nrb_max;
-  const uint32_t static_slots = a.static_blocks >> 3;
-  const uint32_t n_static = static_slots > rb ? (static_slots - 1u - rb) / a.nrb_max + 1u : 0u;  // on this queue
-  const uint32_t dynamic_base = 2u * n_static;
-  uint32_t cur, nxt;
-  if (rank < n_static) {
-    cur = xcd + 8u * rank;
-    nxt = xcd + 8u * (rank + n_static);
   } else {
-    if (tid == 0u) {
-      items[0] = xcd + 8u * (dynamic_base + atomicAdd(queue, 1u));
-      items[1] = xcd + 8u * (dynamic_base + atomicAdd(queue, 1u));
-    }
+    for (uint32_t i = tid; i <= n; i += kSweepThreads) off[i] = a.offsets[i];
+    if (blockIdx.x == 0u)
+      for (uint32_t i = tid; i < 2u * n; i += kSweepThreads) a.clear[i] = 0u;
     __syncthreads();
-    cur = __builtin_amdgcn_readfirstlane(items[0]);
-    nxt = __builtin_amdgcn_readfirstlane(items[1]);
-    __syncthreads();  // items[] is written again in the loop
   }
-  if (cur >= a.n_items) return;
+  if (tid < K)
+    rows[tid] = make_float4(a.d_ttft[tid], a.d_tbt[tid],
+                            __uint_as_float(off[(tid + 1u) * kLenBins] - off[tid * kLenBins]), 0.0f);
+  auto length_at = [&](uint32_t i) { return kSmall ? own[kSmall ? i : 0u] : a.sorted[i]; };
 
-  // staging slot(s) of this thread inside a group
-  uint32_t s_cl[kSlotsPerThread], s_j[kSlotsPerThread];
+  unsigned long long best = 0ull;               // of this thread's candidates
+  unsigned long long pairs = 0ull, fresh = 0ull;  // of this thread's slots
+  for (uint32_t g = blockIdx.x; g < a.n_groups; g = a.n_groups - g > gridDim.x ? g + gridDim.x : a.n_groups) {
+    const uint32_t c0 = g * a.group;
+    const uint32_t nc = min(a.group, a.n_cand - c0);
+    const uint32_t slots = nc * I;
+    for (uint32_t i = tid; i < nc * K; i += kSweepThreads) longest[i] = 0u;
+    if (tid < nc) cnt[tid] = 0u;
+    __syncthreads();
+    // two slots a thread at a time, everything read before anything is used
+    constexpr uint32_t U = 2;
+    for (uint32_t s0 = wave * 64u; s0 < slots; s0 += U * kSweepThreads) {
+      uint32_t cl[U], tp[U], B[U], n_inst[U];
+      int32_t occ[U];
+      uint64_t q[U];
 #pragma unroll
-  for (int u = 0; u < kSlotsPerThread; ++u) {
-    const uint32_t s = u * kSweepThreads + tid;
-    s_cl[u] = s / I;
-    s_j[u] = s - s_cl[u] * I;
-  }
-  auto load_group = [&](uint32_t item, float4 (&rec)[kSlotsPerThread]) {
-#pragma unroll
-    for (int u = 0; u < kSlotsPerThread; ++u) {
-      const uint32_t c = item * G + s_cl[u];
-      rec[u] = make_float4(0.0f, 0.0f, INFINITY, INFINITY);
-      if (item < a.n_items && s_cl[u] < G && c < a.n_cand) rec[u] = a.recs[(size_t)c * I + s_j[u]];
-    }
-  };
-  float4 rec0[kSlotsPerThread];
-  load_group(cur, rec0);  // in flight while the tile is looked up
-
-  // The request tile of this block: tiles of 256*Q requests, class after class.
-  constexpr uint32_t kTile = kSweepThreads * Q;
-  uint32_t k_b = 0, off = 0, n_k = 0;
-  {
-    uint32_t first = 0;
-    bool found = false;
-    for (uint32_t k = 0; k < a.n_slo; ++k) {
-      const uint32_t n = a.cls_count[k];
-      const uint32_t tiles = (n + kTile - 1u) / kTile;
-      if (!found && rb < first + tiles) {
-        found = true; k_b = k; off = (rb - first) * kTile; n_k = n;
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t s = min(s0 + u * kSweepThreads + lane, slots - 1u);
+        cl[u] = s / I;
+        const size_t at = (size_t)c0 * I + s;
+        n_inst[u] = a.n_inst[c0 + cl[u]];
+        tp[u] = a.tp_idx[at]; B[u] = a.max_batch[at]; occ[u] = a.occ[at]; q[u] = a.q_ticks[at];
       }
-      first += tiles;
-    }
-    if (!found) return;  // no such tile: the whole block leaves
-  }
-  const float Dt = a.d_ttft[k_b];
-  const float Db = a.d_tbt[k_b];
-
-  // A lane without a request carries an infinite prompt length: its latency on every instance is
-  // +inf (the per-token prefill cost is positive), so it never counts and needs no mask.
-  float L[Q];
-  uint32_t wave_reqs = 0;  // valid requests held by this wavefront
+      Staged st[U];
+      float inv_p[U];
+      uint32_t reached[U];  // requests whose class the slot's between-token latency suits
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const uint32_t idx = off + wave * (kWave * Q) + q * kWave + lane;
-    const bool ok = idx < n_k;
-    L[q] = ok ? a.lbuf[(size_t)k_b * a.n_req + idx] : INFINITY;
-    wave_reqs += (uint32_t)__popcll(__ballot(ok));
-  }
-  const bool any_req = wave_reqs != 0u;
-
-  for (uint32_t i = tid; i < 6u * kMaxGroup; i += kSweepThreads) (&lens[0][0][0])[i] = 0u;
-  __syncthreads();
-
-  auto file_group = [&](const float4 (&rec)[kSlotsPerThread], uint32_t it) {
-#pragma unroll
-    for (int u = 0; u < kSlotsPerThread; ++u)
-      if (rec[u].w <= Db) {  // between-token deadline of the block's class
-        // records whose queue wait is exactly zero (fresh instances: the placer's usual candidates)
-        // fill the candidate's segment from the front, the others from the back
-        const bool nowait = rec[u].z == 0.0f;
-        const uint32_t pos = atomicAdd(&lens[it % 3u][nowait ? 0 : 1][s_cl[u]], 1u);
-        lists[it & 1u][s_cl[u] * I + (nowait ? pos : I - 1u - pos)] = rec[u];
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t s = s0 + u * kSweepThreads + lane;
+        st[u] = Staged{1.0f, 1.0f, INFINITY, 1.0f, INFINITY};  // absent: suits no class
+        if (s < slots && s - cl[u] * I < n_inst[u] &&
+            !stage_instance(a.tab, a.cells, a.mp, tp[u], B[u], occ[u], q[u], st[u]))
+          raise_status(a.status, 2u);
+        inv_p[u] = __builtin_amdgcn_rcpf(st[u].p);
+        reached[u] = 0u;
       }
-  };
-  file_group(rec0, 0u);
-  __syncthreads();
-
-  unsigned long long evaluated = 0ull, evaluated_nowait = 0ull;
-
-  uint32_t prev_c0 = 0, prev_n = 0;
-  for (uint32_t it = 0;; ++it) {
-    uint32_t after_next = 0xffffffffu;
-    if (tid == 0u && nxt < a.n_items) after_next = xcd + 8u * (dynamic_base + atomicAdd(queue, 1u));
-    float4 rec[kSlotsPerThread];
-    load_group(nxt, rec);
-
-    // counts of the previous group: sum over the block's wavefronts, one atomic per candidate
-    if (it > 0u && tid < prev_n) {
-      const uint32_t b = (it - 1u) & 1u;
-      const uint32_t t = blk_cnt[b][0][tid] + blk_cnt[b][1][tid] + blk_cnt[b][2][tid] + blk_cnt[b][3][tid];
-      if (t) atomicAdd(&a.sat_count[prev_c0 + tid], t);
-    }
-
-    const uint32_t c0 = cur * G;
-    const uint32_t g_cands = min(G, a.n_cand - c0);
-    uint32_t acc = 0;  // lane g holds this wavefront's count for candidate c0 + g
-    if (any_req) {
-      const float4* gl = lists[it & 1u];
-      const uint32_t* glen0 = lens[it % 3u][0];
-      const uint32_t* glen1 = lens[it % 3u][1];
-      // lane g fetches the list lengths of candidate g once; the loop reads them lane by lane
-      const uint32_t len0 = glen0[lane], len1 = glen1[lane];
-      uint32_t n_sum = 0, n0_sum = 0;  // records this wavefront walks in this group
-      for (uint32_t g = 0; g < g_cands; ++g) {
-        const uint32_t n0 = (uint32_t)__builtin_amdgcn_readlane((int)len0, (int)g);
-        const uint32_t n1 = (uint32_t)__builtin_amdgcn_readlane((int)len1, (int)g);
-        n_sum += n0 + n1;
-        n0_sum += n0;
-        const float4* lst = gl + g * I;
-        const float4* wlst = lst + (I - n1);  // the records with a wait sit at the segment's end
-        uint32_t cnt = 0;
-        if (n0 + n1 != 0u) {
-          float m[Q];  // smallest first-token latency so far
-          // wait == +0: ttft = 0 + prefill = prefill exactly (the prefill time is positive), so the
-          // add is left out for those records
-          if (n0 != 0u) walk_list<Q, false>(m, L, lst, n0, true);
-          if (n1 != 0u) walk_list<Q, true>(m, L, wlst, n1, n0 == 0u);
+      for (uint32_t k = 0; k < K; ++k) {
+        const float4 row = rows[k];  // deadlines, requests of the class
 #pragma unroll
-          for (int q = 0; q < Q; ++q) cnt += (uint32_t)__popcll(__ballot(m[q] <= Dt));
+        for (uint32_t u = 0; u < U; ++u) {
+          const bool in_time = st[u].tbt <= row.y;
+          if (lane_mask(in_time) == 0ull) continue;
+          reached[u] += in_time ? __float_as_uint(row.z) : 0u;
+          uint32_t key = longest_prompt(st[u].a, st[u].p, st[u].wait, row.x, inv_p[u], in_time);
+          if (kRows) {
+            key = row_max_u32(key);
+            if ((lane & 15u) == 0u && key != 0u) atomicMax(&longest[cl[u] * K + k], key);
+          } else if (key != 0u) {
+            atomicMax(&longest[cl[u] * K + k], key);
+          }
         }
-        write_lane(acc, cnt, g);
       }
-      evaluated += (unsigned long long)n_sum * wave_reqs;
-      evaluated_nowait += (unsigned long long)n0_sum * wave_reqs;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        pairs += reached[u];
+        fresh += st[u].wait == 0.0f ? reached[u] : 0u;
+      }
     }
-    blk_cnt[it & 1u][wave][lane] = acc;
-
-    file_group(rec, it + 1u);
-    if (tid < 2u * kMaxGroup) (&lens[(it + 2u) % 3u][0][0])[tid] = 0u;  // last read while scoring group it-1
-    if (tid == 0u) items[it & 1u] = after_next;
-    __syncthreads();
-    prev_c0 = c0;
-    prev_n = g_cands;
-    cur = nxt;
-    nxt = __builtin_amdgcn_readfirstlane(items[it & 1u]);
-    if (cur >= a.n_items) {
-      if (tid < prev_n) {
-        const uint32_t b = it & 1u;
-        const uint32_t t = blk_cnt[b][0][tid] + blk_cnt[b][1][tid] + blk_cnt[b][2][tid] + blk_cnt[b][3][tid];
-        if (t) atomicAdd(&a.sat_count[prev_c0 + tid], t);
+    lds_atomics_barrier();
+    // sixteen lanes per (candidate, class): the lengths below the threshold's bin, and those of the bin
+    // that are not above it
+    for (uint32_t t = tid >> 4; t < nc * K; t += kSweepThreads / 16) {
+      const uint32_t key = longest[t];
+      const uint32_t cl = t / K, k = t - cl * K;
+      uint32_t sum = 0;
+      if (key != 0u) {
+        const float X = __uint_as_float(key - 1u);
+        const uint32_t grp = k * kLenBins + length_bin(X);
+        const uint32_t b0 = off[grp], b1 = off[grp + 1u];
+        constexpr uint32_t U = 4;
+        for (uint32_t i = b0 + (lane & 15u); i < b1; i += 16u * U) {
+          float L[U];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) L[u] = i + 16u * u < b1 ? length_at(i + 16u * u) : INFINITY;
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) sum += L[u] <= X ? 1u : 0u;
+        }
+        sum = row_sum_u32(sum) + (b0 - off[k * kLenBins]);
       }
-      break;
+      if ((lane & 15u) == 0u && sum != 0u) atomicAdd(&cnt[cl], sum);
+    }
+    lds_atomics_barrier();
+    if (tid < nc) {
+      const uint32_t c = c0 + tid, v = cnt[tid];
+      a.sat_count[c] = v;
+      if (a.sat_ratio) a.sat_ratio[c] = a.n_req ? (float)v / (float)a.n_req : 0.0f;
+      const unsigned long long kc = ((unsigned long long)v << 32) | (unsigned long long)(~c);
+      best = kc > best ? kc : best;
     }
   }
-  // one word per block, no atomics: thousands of same-address atomics at the kernel's end are slow
-  __shared__ unsigned long long wave_eval[2][kSweepWaves];
-  if (lane == 0u) { wave_eval[0][wave] = evaluated; wave_eval[1][wave] = evaluated_nowait; }
+  for (int d = 32; d >= 1; d >>= 1) {
+    const unsigned long long o = __shfl_xor(best, d);
+    best = o > best ? o : best;
+    pairs += __shfl_xor(pairs, d);
+    fresh += __shfl_xor(fresh, d);
+  }
+  if (lane == 0u) { ends[0][wave] = best; ends[1][wave] = pairs; ends[2][wave] = fresh; }
   __syncthreads();
-  if (tid < 2u)  // all pairs, then those of them whose instance has no wait
-    a.evaluated[(size_t)tid * gridDim.x + blockIdx.x] =
-        wave_eval[tid][0] + wave_eval[tid][1] + wave_eval[tid][2] + wave_eval[tid][3];
-}
-
-// Wavefronts per SIMD the register allocation must leave room for: eight with up to 8 requests per
-// lane, five with 16 (measured: one wavefront fewer costs more than the registers buy).
-template <int Q>
-__global__ __launch_bounds__(kSweepThreads, (Q <= 8 ? 8 : 5)) void sweep_kernel(const SweepArgs a) {
-  sweep_body<Q>(a);
+  if (tid == 0u) {
+    unsigned long long b = 0ull, e = 0ull, f = 0ull;
+    for (int w = 0; w < kSweepThreads / kWave; ++w) {
+      b = ends[0][w] > b ? ends[0][w] : b;
+      e += ends[1][w];
+      f += ends[2][w];
+    }
+    const uint32_t line = blockIdx.x % kTotalsLines;
+    const uint32_t lines = min(gridDim.x, kTotalsLines);
+    const uint32_t on_line = (gridDim.x - line + kTotalsLines - 1u) / kTotalsLines;
+    if (deliver(&a.totals[1u + line], on_line, b, e, f) && deliver(&a.totals[0], lines, b, e, f)) {
+      a.eval_total[0] = e;
+      a.eval_total[1] = f;
+      if (a.best_cand) *a.best_cand = ~(uint32_t)(b & 0xffffffffull);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
-// ratio[c] = count[c] / R and the best candidate: largest count, lowest index on ties (Alg. 1 keeps
-// the best-scoring deployment).  One block.  Also clears the class counters for the next call.
+// Of a windowed sweep's counts: ratio[c] = count[c] / R and the best candidate - largest count, lowest
+// index on ties (Alg. 1 keeps the best-scoring deployment).  One block, so its duration is the number of
+// dependent trips to memory: eight elements per thread are requested before any is used.
 __global__ __launch_bounds__(1024) void sweep_finalize_kernel(const uint32_t* __restrict__ sat_count,
                                                               uint32_t n_cand, uint32_t n_req,
                                                               float* __restrict__ sat_ratio,
-                                                              uint32_t* __restrict__ best_cand,
-                                                              uint32_t* __restrict__ cls_count,
-                                                              const unsigned long long* __restrict__ eval_parts,
-                                                              uint32_t n_parts,
-                                                              unsigned long long* __restrict__ eval_total) {
+                                                              uint32_t* __restrict__ best_cand) {
   __shared__ unsigned long long best[16];
-  __shared__ unsigned long long esum[2][16];
-  if (threadIdx.x < kMaxSlo) cls_count[threadIdx.x] = 0u;
-  // The kernel is one block, so its duration is the number of dependent trips to memory: the first
-  // batch of every array (eight elements per thread each) is requested before anything is used.
   constexpr uint32_t kBatch = 8;
   const uint32_t stride = kBatch * blockDim.x;
-  unsigned long long v0[kBatch], v1[kBatch];
-  uint32_t n[kBatch];
-#pragma unroll
-  for (uint32_t u = 0; u < kBatch; ++u) {
-    const uint32_t i = threadIdx.x + u * blockDim.x;
-    v0[u] = i < n_parts ? eval_parts[i] : 0ull;
-    v1[u] = i < n_parts ? eval_parts[(size_t)n_parts + i] : 0ull;
-    n[u] = i < n_cand ? sat_count[i] : 0u;
-  }
-  for (uint32_t half = 0; half < 2u; ++half) {  // all pairs, then the pairs without a wait
-    const unsigned long long* parts = eval_parts + (size_t)half * n_parts;
-    unsigned long long e = 0ull;
-#pragma unroll
-    for (uint32_t u = 0; u < kBatch; ++u) e += half ? v1[u] : v0[u];
-    for (uint32_t i0 = threadIdx.x + stride; i0 < n_parts; i0 += stride) {
-      unsigned long long v[kBatch];
-#pragma unroll
-      for (uint32_t u = 0; u < kBatch; ++u) {
-        const uint32_t i = i0 + u * blockDim.x;
-        v[u] = i < n_parts ? parts[i] : 0ull;
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < kBatch; ++u) e += v[u];
-    }
-    for (int d = 32; d >= 1; d >>= 1) e += __shfl_xor(e, d);
-    if ((threadIdx.x & 63u) == 0u) esum[half][threadIdx.x >> 6] = e;
-  }
   const float fr = (float)n_req;
   unsigned long long key = 0ull;  // (count << 32) | ~index: max key = max count, then min index
-  for (uint32_t c0 = threadIdx.x; c0 < n_cand; c0 += stride) {
-    if (c0 != threadIdx.x) {
+  for (uint32_t c0 = threadIdx.x; c0 < n_cand; c0 = n_cand - c0 > stride ? c0 + stride : n_cand) {
+    uint32_t n[kBatch];
 #pragma unroll
-      for (uint32_t u = 0; u < kBatch; ++u) {
-        const uint32_t c = c0 + u * blockDim.x;
-        n[u] = c < n_cand ? sat_count[c] : 0u;
-      }
+    for (uint32_t u = 0; u < kBatch; ++u) {
+      const uint32_t at = u * blockDim.x;
+      n[u] = at < n_cand - c0 ? sat_count[c0 + at] : 0u;
     }
 #pragma unroll
     for (uint32_t u = 0; u < kBatch; ++u) {
-      const uint32_t c = c0 + u * blockDim.x;
-      if (c >= n_cand) continue;
+      const uint32_t at = u * blockDim.x;
+      if (at >= n_cand - c0) continue;
+      const uint32_t c = c0 + at;
       if (sat_ratio) sat_ratio[c] = n_req ? (float)n[u] / fr : 0.0f;
       const unsigned long long kc = ((unsigned long long)n[u] << 32) | (unsigned long long)(~c);
       key = kc > key ? kc : key;
@@ -655,11 +491,6 @@ __global__ __launch_bounds__(1024) void sweep_finalize_kernel(const uint32_t* __
   if (threadIdx.x == 0 && best_cand) {
     for (uint32_t w = 1; w < (blockDim.x >> 6); ++w) key = best[w] > key ? best[w] : key;
     *best_cand = ~(uint32_t)(key & 0xffffffffull);
-  }
-  if (threadIdx.x < 2u) {
-    unsigned long long e = 0ull;
-    for (uint32_t w = 0; w < (blockDim.x >> 6); ++w) e += esum[threadIdx.x][w];
-    eval_total[threadIdx.x] = e;
   }
 }
 

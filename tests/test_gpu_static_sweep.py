@@ -1,0 +1,82 @@
+"""The static sweep against the triple oracle at the edges of its grouping and of its thresholds: around
+4096 requests (grouped by every block or by launches of their own), around the 1024 requests a grouping
+block takes, all lengths alike, empty prompts, lengths no binary32 holds exactly, one class and
+sixteen, rows of slots that do and do not fill 16 lanes, and profiles whose quotient is far off."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from paper_2509_06362_amd import binding, workloads as W  # noqa: E402
+
+
+def check(w):
+    dw = binding.DeviceWorkload(w)
+    try:
+        ref = oracle.placement_sweep(w)
+        per_class = np.bincount(w.slo_class, minlength=w.n_slo).astype(np.int64)
+        pairs = sum(int((oracle.stage(w, c)["tbt"][:, None] <= w.d_tbt[None]).astype(np.int64).sum(0) @ per_class)
+                    for c in range(w.n_cand))
+        for noalloc in (False, True, False):   # the accumulators are left as they were found
+            cnt, ratio, best = dw.sweep(noalloc=noalloc)
+            torch.cuda.synchronize()
+            assert np.array_equal(cnt.cpu().numpy().view(np.uint32), ref["sat_count"])
+            assert np.array_equal(ratio.cpu().numpy(), ref["sat_ratio"])
+            assert int(best.cpu().numpy().view(np.uint32)[0]) == ref["best_cand"]
+            assert binding.maaso_ctx_sweep_evaluated(dw.ctx) == pairs
+        assert binding.maaso_ctx_device_status(dw.ctx) == 0
+        return ref["sat_count"]
+    finally:
+        dw.close()
+
+
+@pytest.mark.parametrize("n_cand,i_pad,n_req,n_slo", [
+    (1, 1, 1, 1), (3, 16, 4096, 1), (70, 7, 4097, 3), (1100, 3, 1025, 2), (5, 255, 5120, 16),
+    (9, 256, 5121, 3), (1, 64, 9000, 16), (40, 33, 4095, 8), (2100, 32, 4100, 3),
+])
+def test_static_sweep_edges(n_cand, i_pad, n_req, n_slo):
+    w = W.random_small(n_cand + 3 * i_pad + n_req, n_cand, i_pad, n_req, n_slo=n_slo, b_cap=64, pen_kappa=0.5)
+    w = W.stressed(w, seed=n_req)
+    print(f"static sweep C={n_cand} I={i_pad} R={n_req} K={n_slo}", flush=True)
+    check(w)
+
+
+@pytest.mark.parametrize("lengths", ["alike", "empty", "steps", "long", "beyond"])
+@pytest.mark.parametrize("n_req", [1500, 6000])
+def test_static_sweep_lengths(lengths, n_req):
+    w = W.stressed(W.random_small(n_req + len(lengths), 60, 20, n_req, n_slo=3, b_cap=32), seed=5)
+    rng = np.random.default_rng(n_req)
+    if lengths == "alike":
+        L = np.full(n_req, 1777)
+    elif lengths == "empty":
+        L = np.where(rng.random(n_req) < 0.5, 0, rng.integers(0, 3, n_req))
+    elif lengths == "steps":    # around the bins' edges
+        L = (1 << rng.integers(0, 14, n_req)) * rng.integers(8, 17, n_req) // 8 + rng.integers(-1, 2, n_req)
+        L = np.maximum(L, 0)
+    elif lengths == "long":
+        L = rng.integers(0, 1 << 24, n_req)
+    else:                       # more than binary32 holds exactly
+        L = rng.integers(1 << 24, (1 << 32) - 1, n_req)
+        L[:3] = (1 << 32) - 1, (1 << 24) + 1, 1 << 31
+    w = W.replace(w, prompt_len=L.astype(np.uint32))
+    if lengths in ("long", "beyond"):  # deadlines such lengths can meet
+        w = W.replace(w, d_ttft=(w.d_ttft * np.float32(400.0 if lengths == "long" else 2e5)))
+    cnt = check(w)
+    if lengths != "empty":
+        assert len(np.unique(cnt)) > 1
+
+
+@pytest.mark.parametrize("a_scale,p_scale,d_scale", [
+    (1.0, 1e-9, 1.0), (1.0, 1e6, 1.0), (1e-6, 1e-7, 1e-3), (40.0, 1e-4, 1.0), (1.0, 1.0, 4000.0), (1e-30, 1e-30, 1.0),
+])
+def test_static_sweep_extreme_profiles(a_scale, p_scale, d_scale):
+    w = W.random_small(17, 50, 24, 5000, n_slo=3, b_cap=32)
+    rng = np.random.default_rng(3)
+    w = W.replace(w, prefill_a=(w.prefill_a * np.float32(a_scale)), prefill_p=(w.prefill_p * np.float32(p_scale)),
+                  d_ttft=(w.d_ttft * np.float32(d_scale)),
+                  prompt_len=np.floor(np.exp(rng.uniform(0, np.log(2.0 ** 24), 5000))).astype(np.uint32))
+    print(f"static sweep a*{a_scale} p*{p_scale} D*{d_scale}", flush=True)
+    check(w)
