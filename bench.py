@@ -3,7 +3,7 @@
 
 A step is one pass of the whole path over one batch of synthetic input that is already resident in
 HBM: maaso_placement_sweep over every candidate deployment (profile evaluation, queue wait, SLO
-fetch, per-triple latency, SLO check, per-request feasibility, per-candidate reduction, best
+fetch, the prompt lengths each instance serves in time, per-candidate count over the requests, best
 candidate) followed by maaso_score_assign of the same requests on the winning deployment (best
 instance per request, admitted count).  For the two distributor workloads a step is
 maaso_score_assign alone (windowed for the online distributor).
@@ -35,25 +35,11 @@ if str(ROOT) not in sys.path:
     sys.path.insert(0, str(ROOT))
 
 # MI355X fp32 vector peak: 157.3 TFLOP/s published = 256 compute units x 4 SIMDs x 32 lanes per clock
-# x 2.4 GHz x 2 flop per fused multiply-add, i.e. 78.6e12 VALU lane operations per second.  A
-# min, add or compare occupies a lane slot exactly as an fma does, so the kernels are priced in lane
-# operations; the flop figure (an fma counts two, everything else one) is given beside it.
+# x 2.4 GHz x 2 flop per fused multiply-add, i.e. 78.6e12 VALU lane operations per second (a min, add
+# or compare occupies a lane slot exactly as an fma does).
 VALU_PEAK_TLANEOPS = 256 * 4 * 32 * 2.4e9 / 1e12
-FP32_VECTOR_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBS = 8000.0
 
-# Sweep, per (request, instance) pair that reaches the latency loop: prefill fma, queue-wait add, and
-# half of a three-input minimum (one v_min3_f32 folds two pairs into the running minimum): 2.5
-# instruction slots per pair is the least this instruction set needs.  Where an instance's queue wait
-# is exactly zero (fresh instances, the placer's usual candidates) the add changes nothing and the
-# kernel leaves it out: 1.5 slots.  The roofline fraction uses these figures with the kernel's own
-# counts of both kinds of pair.  Counted as operations of the model (fma, add, min) a pair is 3; that
-# figure is reported beside it and exceeds the slot fraction.
-SWEEP_SLOTS_PER_PAIR = 2.5
-SWEEP_SLOTS_PER_PAIR_NO_WAIT = 1.5
-SWEEP_OPERATIONS_PER_PAIR = 3
-SWEEP_FLOP_PER_PAIR = 4          # fma = 2
-SWEEP_FLOP_PER_PAIR_NO_WAIT = 3
 # Distributor, per triple: 2 fma, 1 add, 2 sub, 2 mul, 2 min, 1 compare, 2 selects (the between-token
 # margin comes from a per-(class, instance) table).
 ASSIGN_LANEOPS_PER_TRIPLE = 12
@@ -390,37 +376,24 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
     k_avg_s = sum(durs) / max(k_n, 1) * 1e-3
     traffic, traffic_info = measured_traffic(w.name)
     if kind == "sweep" and sweep_window:
-        ops = ASSIGN_LANEOPS_PER_TRIPLE * triples_sweep
         roofline = {
             "kernel": "sweep_seq_kernel" if sweep_window == 1 else "sweep_window_kernel", "bound": "alu",
-            "achieved": ops / k_avg_s / 1e12, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlaneop/s",
-            "frac": ops / k_avg_s / 1e12 / VALU_PEAK_TLANEOPS, "traffic": traffic,
-            "kernel_ms": k_avg_s * 1e3, "launches_timed": k_n,
-            "laneops_per_triple": ASSIGN_LANEOPS_PER_TRIPLE,
+            "achieved": None, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlaneop/s", "frac": None,
+            "traffic": traffic, "kernel_ms": k_avg_s * 1e3, "launches_timed": k_n,
             "kernel_triples_per_s": triples_sweep / k_avg_s,
+            "note": "a request is scored against the instances it can be given at all, which the kernel "
+                    "finds per window, or with all of them in the lanes of a wavefront: triples settled "
+                    "are no measure of the operations issued",
         }
     elif kind == "sweep":
-        # pairs that reached the latency loop, and those of them on an instance without a wait
+        # pairs past the between-token check, and those of them on an instance without a wait
         pairs, pairs_nowait = binding.maaso_ctx_sweep_evaluated(dw.ctx, split=True)
-        ops = (SWEEP_SLOTS_PER_PAIR * (pairs - pairs_nowait)
-               + SWEEP_SLOTS_PER_PAIR_NO_WAIT * pairs_nowait)
-        flop = (SWEEP_FLOP_PER_PAIR * (pairs - pairs_nowait)
-                + SWEEP_FLOP_PER_PAIR_NO_WAIT * pairs_nowait)
         roofline = {
-            "kernel": "sweep_kernel", "bound": "alu",
-            "achieved": ops / k_avg_s / 1e12, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlaneop/s",
-            "frac": ops / k_avg_s / 1e12 / VALU_PEAK_TLANEOPS, "traffic": traffic,
-            "kernel_ms": k_avg_s * 1e3, "launches_timed": k_n,
-            "slots_per_pair": SWEEP_SLOTS_PER_PAIR,
-            "slots_per_pair_without_wait": SWEEP_SLOTS_PER_PAIR_NO_WAIT,
-            "operations_per_pair": SWEEP_OPERATIONS_PER_PAIR,
-            "frac_counting_operations": SWEEP_OPERATIONS_PER_PAIR * pairs / k_avg_s / 1e12
-            / VALU_PEAK_TLANEOPS,
-            "pairs_evaluated": pairs, "pairs_without_wait": pairs_nowait,
+            "kernel": "sweep_count_kernel", "bound": "hbm", "unit": "GB/s", "peak": HBM_PEAK_GBS,
+            "traffic": traffic, "kernel_ms": k_avg_s * 1e3, "launches_timed": k_n,
+            "pairs_past_between_token_check": pairs, "pairs_without_wait": pairs_nowait,
             "valid_triples": triples_sweep,
             "settled_per_class_instance": triples_sweep - pairs,
-            "tflops": flop / k_avg_s / 1e12,
-            "frac_of_fp32_vector_peak": flop / k_avg_s / 1e12 / FP32_VECTOR_PEAK_TFLOPS,
             "kernel_triples_per_s": triples_sweep / k_avg_s,
         }
         # the metric also asks for the fraction of the HBM roofline: each request record (9 B), each
@@ -430,9 +403,11 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
             "algorithmic_bytes": alg_bytes, "achieved_GBps": alg_bytes / k_avg_s / 1e9,
             "frac_of_peak": alg_bytes / k_avg_s / 1e9 / HBM_PEAK_GBS,
             "measured_frac_of_peak": None if traffic is None else traffic / k_avg_s / 1e9 / HBM_PEAK_GBS,
-            "note": "the sweep moves about 1e-3 B per triple: it is bound by the VALU, not by HBM; the "
-                    "60 %-of-HBM target is literal only on the streaming distributor shape",
+            "note": "three short launches whose latency, not HBM, is most of the time; the 60 %-of-HBM "
+                    "target is literal only on the streaming distributor shape",
         }
+        roofline["achieved"] = roofline["hbm"]["achieved_GBps"]
+        roofline["frac"] = roofline["hbm"]["frac_of_peak"]
     else:
         nbytes = ASSIGN_BYTES_PER_REQUEST * w.n_req
         ops = ASSIGN_LANEOPS_PER_TRIPLE * triples_assign
@@ -535,8 +510,8 @@ PROBE_PATTERNS = (
 
 
 def valu_probe():
-    """What the chip sustains for the sweep's instruction mix (maaso_probe_valu): vector lane operations
-    per second of loops that are nothing but the sweep's inner instruction sequence."""
+    """What the chip sustains for a latency evaluation's instruction mix (maaso_probe_valu): vector lane
+    operations per second of loops that are nothing but fixed instruction sequences."""
     from paper_2509_06362_amd import binding
     out = {"peak_Tlaneops": VALU_PEAK_TLANEOPS, "patterns": []}
     for pat, text in PROBE_PATTERNS:
@@ -590,7 +565,6 @@ def bench_alg2(args) -> int:
     k_ms, k_n = binding.maaso_ctx_kernel_elapsed(dw.ctx)
     binding.maaso_ctx_kernel_timing(dw.ctx, False)
     k_total_s = k_ms * 1e-3 / max(n_timed, 1)       # the scoring launch of one step (three request sets)
-    ops = ASSIGN_LANEOPS_PER_TRIPLE * triples_step
     part = res["partition"].cpu().numpy()
     result = {
         "metric": "scored (candidate,request,instance) triples/sec",
@@ -605,11 +579,11 @@ def bench_alg2(args) -> int:
                            "Alg. 1's selection per set, partition scan; |R_t| stays on the device",
                    "partition": {"g_t": int(part[0]), "g_l": int(part[1]),
                                  "heterogeneous": int(part[2]), "phi_opt": float(res["phi_opt"].item())}},
-        "roofline": {"kernel": "sweep_window_kernel", "bound": "alu",
-                     "achieved": ops / k_total_s / 1e12, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlaneop/s",
-                     "frac": ops / k_total_s / 1e12 / VALU_PEAK_TLANEOPS, "traffic": None,
+        "roofline": {"kernel": "sweep_window_kernel", "bound": "latency", "achieved": None, "peak": None,
+                     "unit": None, "frac": None, "traffic": None,
                      "kernel_ms": k_ms / max(k_n, 1), "launches_timed": k_n,
-                     "laneops_per_triple": ASSIGN_LANEOPS_PER_TRIPLE},
+                     "kernel_triples_per_s": triples_step / k_total_s,
+                     "note": "a chain of 512 dependent windows per deployment"},
         "device_status": binding.maaso_ctx_device_status(dw.ctx),
     }
     if not args.no_cpu_baseline:
@@ -655,11 +629,13 @@ def top_level(entry, args, steps, warmup):
         "ms_per_step": entry["ms_per_step"], "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "value_counts": "valid (candidate, request, instance) triples SETTLED per second with inputs "
-                        "resident in HBM: the sweep settles a triple whose instance fails the class's "
-                        "between-token deadline per (class, instance) and evaluates first-token "
-                        "latency and deadline for every other one (roofline.pairs_evaluated); it does "
-                        "not compute three slacks per triple - the distributor does, on the winning "
-                        "deployment",
+                        "resident in HBM, NOT latencies evaluated per second: the sweep finds per (class, "
+                        "instance) the longest prompt whose first-token latency meets the deadline, "
+                        "with the latency model itself, and counts by the ranks of a class's prompt "
+                        "lengths; the distributor scores a request against the instances it can be "
+                        "given at all.  The counts, choices and slacks are those of evaluating every "
+                        "triple, bit for bit (oracle_check); a figure from before either was built "
+                        "counts another amount of work per triple",
         "config": entry["config"], "roofline": entry["roofline"],
         "device_status": entry["device_status"],
     }
@@ -743,8 +719,8 @@ def main() -> int:
     stream = next(e for e, _ in others if e["config"]["workload"] == "streaming_i4")
     result["hbm_roofline"] = {
         "note": "the 60 %-of-peak-HBM target is meaningful where HBM binds: the streaming distributor "
-                "shape (4 instances, 2^26 requests, 17 B per request); the sweeps move ~1e-3 B per "
-                "triple and are priced against the VALU peak",
+                "shape (4 instances, 2^26 requests, 17 B per request); the sweeps' inputs are a few tens "
+                "of MB and most of their time is the latency of three launches",
         "streaming_frac_of_hbm_peak": stream["roofline"]["frac"],
         "headline_frac_of_hbm_peak": head["roofline"]["hbm"]["frac_of_peak"],
     }
