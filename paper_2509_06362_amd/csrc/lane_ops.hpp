@@ -2,7 +2,7 @@
 // request that is spread over several lanes, and to add up what a wavefront admits.
 #pragma once
 
-#include "assign_kernels.hpp"
+#include "sweep_kernels.hpp"
 
 namespace maaso {
 

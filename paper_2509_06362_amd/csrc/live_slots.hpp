@@ -155,9 +155,8 @@ struct AdmissionBounds {
 };
 
 template <int S, bool kSQ>
-__device__ __forceinline__ void find_admissible(const SlotRecord (&rec)[S], const LiveSlot (&slot)[S],
-                                                uint32_t n, uint32_t lane, const AdmissionBounds& lim,
-                                                InstanceSet<S>& und) {
+__device__ __forceinline__ void find_admissible(const SlotRecord (&rec)[S], const int32_t (&occ)[S], uint32_t n, uint32_t lane,
+                                                const AdmissionBounds& lim, InstanceSet<S>& und) {
 #pragma unroll
   for (int s = 0; s < S; ++s)
     und.m[s] = lane_mask(((uint32_t)s * 64u + lane < n) & (rec[s].tbt <= lim.d_tbt) &
@@ -169,7 +168,7 @@ __device__ __forceinline__ void find_admissible(const SlotRecord (&rec)[S], cons
       const int b = (int)__builtin_ctzll(todo);
       const SlotRecord k = rec[s].of_lane(b);
       const float t_above = k.tbt + lim.e_tbt, w_above = k.wait + lim.e_ttft;
-      const int32_t ko = kSQ ? (int32_t)__builtin_amdgcn_readlane(slot[s].occ, b) : 0;
+      const int32_t ko = kSQ ? (int32_t)__builtin_amdgcn_readlane(occ[s], b) : 0;
 #pragma unroll
       for (int t = 0; t < S; ++t) {
         const bool ap = (k.a <= rec[t].a) & (k.p <= rec[t].p);
@@ -178,7 +177,7 @@ __device__ __forceinline__ void find_admissible(const SlotRecord (&rec)[S], cons
         const unsigned long long behind = t > s ? ~0ull : (t == s ? ~1ull << b : 0ull);
         unsigned long long gone;
         if (kSQ) {
-          gone = lane_mask(le & (ko < slot[t].occ)) | (lane_mask(le & (ko == slot[t].occ)) & behind);
+          gone = lane_mask(le & (ko < occ[t])) | (lane_mask(le & (ko == occ[t])) & behind);
         } else {
           gone = (lane_mask(le) & behind) |
                  lane_mask(ap & (t_above <= rec[t].tbt) & (w_above <= rec[t].wait));
@@ -190,11 +189,37 @@ __device__ __forceinline__ void find_admissible(const SlotRecord (&rec)[S], cons
   }
 }
 
+// The instances a request can be given whether it is admitted or not: only the second rule above, which
+// holds for slacks of any sign.  (A blocked request is reported with the largest slack under both
+// selection rules.)
+template <int S>
+__device__ __forceinline__ void find_undominated(const SlotRecord (&rec)[S], uint32_t n, uint32_t lane,
+                                                 InstanceSet<S>& und) {
+#pragma unroll
+  for (int s = 0; s < S; ++s) und.m[s] = lane_mask((uint32_t)s * 64u + lane < n);
+  uint32_t steps = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    for (unsigned long long todo = und.m[s]; todo != 0ull && steps < kMaxDominators; ++steps) {
+      const int b = (int)__builtin_ctzll(todo);
+      const SlotRecord k = rec[s].of_lane(b);
+#pragma unroll
+      for (int t = s; t < S; ++t) {
+        unsigned long long gone = lane_mask((k.a <= rec[t].a) & (k.p <= rec[t].p) & (k.tbt <= rec[t].tbt) &
+                                            (k.wait <= rec[t].wait));
+        if (t == s) gone &= ~1ull << b;  // those behind it, not itself
+        und.m[t] &= ~gone;
+      }
+      todo = und.m[s] & (~1ull << b);
+    }
+  }
+}
+
 // The first F of a set, in index order: record, index, requests on it (kSQ); entries past its end are
 // left as they are.
 template <int S, bool kSQ, int F>
 __device__ __forceinline__ void first_of(const InstanceSet<S>& set, const SlotRecord (&rec)[S],
-                                         const LiveSlot (&slot)[S], SlotRecord (&fr)[F], uint32_t (&fj)[F],
+                                         const int32_t (&occ)[S], SlotRecord (&fr)[F], uint32_t (&fj)[F],
                                          int32_t (&focc)[F]) {
   InstanceSet<S> left = set;
 #pragma unroll
@@ -207,7 +232,7 @@ __device__ __forceinline__ void first_of(const InstanceSet<S>& set, const SlotRe
         left.m[s] &= left.m[s] - 1ull;
         fr[i] = rec[s].of_lane(b);
         fj[i] = (uint32_t)(s * 64 + b);
-        if (kSQ) focc[i] = (int32_t)__builtin_amdgcn_readlane(slot[s].occ, b);
+        if (kSQ) focc[i] = (int32_t)__builtin_amdgcn_readlane(occ[s], b);
         found = true;
       }
   }
@@ -217,7 +242,7 @@ __device__ __forceinline__ void first_of(const InstanceSet<S>& set, const SlotRe
 // it, index) - see queue_rank_value - here among the instances of a set, which is all the order is used
 // for.
 template <int S>
-__device__ __forceinline__ void queue_ranks(const LiveSlot (&slot)[S], const InstanceSet<S>& und, uint32_t lane,
+__device__ __forceinline__ void queue_ranks(const int32_t (&occ)[S], const InstanceSet<S>& und, uint32_t lane,
                                             float (&rank)[S]) {
   uint32_t ahead[S];
 #pragma unroll
@@ -226,11 +251,11 @@ __device__ __forceinline__ void queue_ranks(const LiveSlot (&slot)[S], const Ins
   for (int s = 0; s < S; ++s)
     for (unsigned long long todo = und.m[s]; todo != 0ull; todo &= todo - 1ull) {
       const int b = (int)__builtin_ctzll(todo);
-      const int32_t ko = (int32_t)__builtin_amdgcn_readlane(slot[s].occ, b);
+      const int32_t ko = (int32_t)__builtin_amdgcn_readlane(occ[s], b);
 #pragma unroll
       for (int t = 0; t < S; ++t) {
         const bool before = s < t || (s == t && (uint32_t)b < lane);
-        ahead[t] += (ko < slot[t].occ || (ko == slot[t].occ && before)) ? 1u : 0u;
+        ahead[t] += (ko < occ[t] || (ko == occ[t] && before)) ? 1u : 0u;
       }
     }
 #pragma unroll

@@ -27,10 +27,10 @@ static_assert(MAASO_MAX_SLO == kMaxSlo, "header and kernels disagree on the clas
 
 constexpr uint32_t kMaxTimed = 256;
 // The context's small device block, in 32-bit words: [0] status, [32..35] evaluated pairs of the last
-// static sweep (all; those without a wait), [36..37] admitted-count accumulator and delivered-blocks
-// ticket of the static distributor, [64..] the static sweep's SweepTotals; from kCounterWord on its
-// histogram, cursors and group offsets.
-constexpr uint32_t kTotalsWord = 64;
+// static sweep (all; those without a wait), [64..] the static distributor's admitted-count accumulators,
+// then the static sweep's SweepTotals; from kCounterWord on its histogram, cursors and group offsets.
+constexpr uint32_t kSatWord = 64;
+constexpr uint32_t kTotalsWord = kSatWord + (1u + kSatLines) * kSatStride * 2u;
 constexpr uint32_t kCounterWord = kTotalsWord + (1u + kTotalsLines) * sizeof(SweepTotals) / 4u;
 constexpr uint32_t kHistWords = kMaxSlo * kLenBins;
 constexpr size_t kSmallBytes = ((size_t)kCounterWord + 3u * kHistWords + 64u) * 4u;
@@ -203,6 +203,19 @@ bool narrow_ticks(const maaso_ctx* ctx, const maaso_params* prm, uint64_t per_wi
          (double)prm->s_bar * (double)ctx->tbt_max * (1.0 + (double)prm->pen_kappa) < 1e38;
 }
 
+AdmissionBounds admission_bounds(const maaso_ctx* ctx, const maaso_params* prm) {
+  AdmissionBounds b{0.0f, 0.0f, 0.0f, 0.0f, false, false};
+  for (uint32_t k = 0; k < ctx->n_slo; ++k) {
+    b.d_ttft = std::max(b.d_ttft, ctx->d_ttft[k]);
+    b.d_tbt = std::max(b.d_tbt, ctx->d_tbt[k]);
+  }
+  b.e_ttft = b.d_ttft * 0x1p-20f;
+  b.e_tbt = b.d_tbt * 0x1p-20f;
+  b.narrow = narrow_ticks(ctx, prm, 0u);
+  b.narrow_queue = narrow_ticks(ctx, prm, prm->window ? prm->window : MAASO_MAX_REQUESTS);
+  return b;
+}
+
 int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t* cand_sel,
                       const maaso_requests* rq, const maaso_params* prm, const maaso_assign_out* out,
                       void* hip_stream);
@@ -242,8 +255,8 @@ void fill_assign_args(AssignArgs& a, const maaso_ctx* ctx, const maaso_placement
   a.e2e = out->e2e;
   a.n_satisfied = reinterpret_cast<unsigned long long*>(out->n_satisfied);
   a.status = ctx->status;
-  a.narrow = narrow_ticks(ctx, prm, prm->window);
-  a.sat_acc = reinterpret_cast<unsigned long long*>(ctx->status + 36);
+  a.bounds = admission_bounds(ctx, prm);
+  a.sat_acc = reinterpret_cast<unsigned long long*>(ctx->status + kSatWord);
 }
 
 // Wavefronts per candidate and requests per lane of the windowed sweep.  One wavefront per candidate wastes
@@ -336,15 +349,7 @@ void fill_sweep_window_args(SweepWindowArgs& a, const maaso_ctx* ctx, const maas
   a.max_batch = pl->max_batch;
   a.occ = pl->occ;
   a.q_ticks = reinterpret_cast<const uint64_t*>(pl->q_ticks);
-  a.bounds = AdmissionBounds{0.0f, 0.0f, 0.0f, 0.0f, false, false};
-  for (uint32_t k = 0; k < ctx->n_slo; ++k) {
-    a.bounds.d_ttft = std::max(a.bounds.d_ttft, ctx->d_ttft[k]);
-    a.bounds.d_tbt = std::max(a.bounds.d_tbt, ctx->d_tbt[k]);
-  }
-  a.bounds.e_ttft = a.bounds.d_ttft * 0x1p-20f;
-  a.bounds.e_tbt = a.bounds.d_tbt * 0x1p-20f;
-  a.bounds.narrow = narrow_ticks(ctx, prm, 0u);
-  a.bounds.narrow_queue = narrow_ticks(ctx, prm, prm->window ? prm->window : MAASO_MAX_REQUESTS);
+  a.bounds = admission_bounds(ctx, prm);
   a.n_sets = 0;
   std::memset(a.sets, 0, sizeof(a.sets));
   a.status = ctx->status;

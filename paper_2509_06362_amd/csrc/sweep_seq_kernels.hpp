@@ -382,7 +382,7 @@ __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint
             for (int s = 0; s < S; ++s)
               if (j >> 6 == (uint32_t)s) {
                 rare_path();
-                sq.admit(s, j & 63u, lane, a.narrow);
+                sq.admit(s, j & 63u, lane, a.bounds.narrow_queue);
               }
           }
         }

@@ -285,10 +285,13 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
     SlotRecord fr[kFew];
     uint32_t fj[kFew];
     int32_t focc[kFew];
-    find_admissible<S, kSQ>(rec, slot, n, lane, a.bounds, und);
+    int32_t occ[S];  // as the window opens
+#pragma unroll
+    for (int s = 0; s < S; ++s) occ[s] = slot[s].occ;
+    find_admissible<S, kSQ>(rec, occ, n, lane, a.bounds, und);
     const uint32_t m = und.count();
     const bool few = m <= (uint32_t)kFew && a.bounds.narrow;
-    if (few) first_of<S, kSQ, kFew>(und, rec, slot, fr, fj, focc);
+    if (few) first_of<S, kSQ, kFew>(und, rec, occ, fr, fj, focc);
     float frank[kFew];
     uint32_t cnt[kFew];
     unsigned long long acc[kFew];
@@ -306,7 +309,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
           frank[i] = (float)(512u - ahead);
         }
       } else {
-        queue_ranks<S>(slot, und, lane, rank);
+        queue_ranks<S>(occ, und, lane, rank);
       }
     }
     // adds to the state: instance j (uniform) admitted `num` requests of `ticks` prefill in all
