@@ -176,20 +176,38 @@ def _host(a: np.ndarray, dtype) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=dtype)
 
 
+_torch = None
+
+
+def _t():
+    """torch, imported on first use (the module itself loads without it)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _dptr(t, dtype=None) -> Optional[int]:
-    """Device pointer of a torch tensor (None -> NULL)."""
+    """Device pointer of a torch tensor (None -> NULL).  Called a dozen times per entry point, so the
+    checks are spelled out instead of formatted ahead."""
     if t is None:
         return None
-    assert t.is_cuda and t.is_contiguous(), "device buffers must be contiguous GPU tensors"
-    if dtype is not None:
-        assert t.dtype == dtype, f"expected {dtype}, got {t.dtype}"
+    if not t.is_cuda or not t.is_contiguous():
+        raise AssertionError("device buffers must be contiguous GPU tensors")
+    if dtype is not None and t.dtype != dtype:
+        raise AssertionError(f"expected {dtype}, got {t.dtype}")
     return t.data_ptr()
 
 
 def _stream_handle(stream) -> Optional[int]:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    torch = _t()
+    if stream is not None:
+        return stream.cuda_stream or None
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream or None
+    # the handle torch.cuda.current_stream() carries, without building the stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
 
 
 class Context:
@@ -324,13 +342,13 @@ def maaso_ctx_sweep_evaluated(ctx: Context, split: bool = False):
 
 
 def _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks) -> Requests:
-    import torch
+    torch = _t()
     return Requests(int(n_req), _dptr(prompt_len, torch.int32), _dptr(out_len, torch.int32),
                     _dptr(slo_class, torch.uint8), _dptr(arrival_ticks, torch.int32))
 
 
 def _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks) -> Placements:
-    import torch
+    torch = _t()
     return Placements(int(n_cand), int(i_pad), _dptr(n_inst, torch.int32), _dptr(tp_idx, torch.uint8),
                       _dptr(max_batch, torch.int16), _dptr(occ, torch.int32),
                       _dptr(q_ticks, torch.int64))
@@ -343,7 +361,7 @@ def maaso_score_assign(ctx: Context, *, n_cand, i_pad, n_inst, tp_idx, max_batch
                        stream=None) -> None:
     """All array arguments are GPU torch tensors holding the C types' bit patterns
     (uint32 as int32, uint16 as int16, uint64 as int64)."""
-    import torch
+    torch = _t()
     pl = _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks)
     rq = _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks)
     prm = Params(float(s_bar), float(pen_kappa), int(tbt_mode), int(window), int(policy))
@@ -361,7 +379,7 @@ def maaso_score_assign_selected(ctx: Context, *, cand, n_cand, i_pad, n_inst, tp
                                 chosen=None, slack=None, ttft=None, tbt=None, e2e=None,
                                 n_satisfied=None, stream=None) -> None:
     """maaso_score_assign on the row whose index is the device word `cand` (an int32 tensor)."""
-    import torch
+    torch = _t()
     pl = _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks)
     rq = _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks)
     prm = Params(float(s_bar), float(pen_kappa), int(tbt_mode), int(window), int(policy))
@@ -377,7 +395,7 @@ def maaso_placement_sweep(ctx: Context, *, n_cand, i_pad, n_inst, tp_idx, max_ba
                           n_req, prompt_len, out_len, slo_class, arrival_ticks=None, s_bar,
                           pen_kappa=0.0, tbt_mode=0, window=0, policy=0, sat_count, sat_ratio=None,
                           best_cand=None, stream=None) -> None:
-    import torch
+    torch = _t()
     pl = _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks)
     rq = _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks)
     prm = Params(float(s_bar), float(pen_kappa), int(tbt_mode), int(window), int(policy))
@@ -391,7 +409,7 @@ def maaso_placement_sweep_noalloc(ctx: Context, *, n_cand, i_pad, n_inst, tp_idx
                                   n_req, prompt_len, out_len, slo_class, arrival_ticks=None, s_bar,
                                   pen_kappa=0.0, tbt_mode=0, window=0, policy=0, sat_count,
                                   sat_ratio=None, best_cand=None, stream=None) -> None:
-    import torch
+    torch = _t()
     pl = _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks)
     rq = _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks)
     prm = Params(float(s_bar), float(pen_kappa), int(tbt_mode), int(window), int(policy))
@@ -406,7 +424,7 @@ def maaso_placement_score(ctx: Context, *, n_cand, i_pad, n_inst, tp_idx, max_ba
                           pen_kappa=0.0, tbt_mode=0, window=0, policy=0, alpha, beta, gamma_t, gamma_l,
                           sat_count, score, phi_s=None, phi_t=None, phi_l=None, best_cand=None,
                           stream=None) -> None:
-    import torch
+    torch = _t()
     pl = _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks)
     rq = _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks)
     prm = Params(float(s_bar), float(pen_kappa), int(tbt_mode), int(window), int(policy))
@@ -425,7 +443,7 @@ def maaso_placement_score_sets(ctx: Context, *, n_cand, i_pad, n_inst, tp_idx, m
     """`sets`: one dict per request set with the request keywords (n_req, prompt_len, out_len,
     slo_class, arrival_ticks) and the output keywords (sat_count, score, phi_s, phi_t, phi_l,
     best_cand) of maaso_placement_score."""
-    import torch
+    torch = _t()
     pl = _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks)
     prm = Params(float(s_bar), float(pen_kappa), int(tbt_mode), int(window), int(policy))
     wts = ScoreWeights(float(alpha), float(beta), float(gamma_t), float(gamma_l))
@@ -465,7 +483,7 @@ def maaso_profile_fit(offsets, level, thr, b_cap: int, eps_lo: float = 2.0 ** -1
 def maaso_split_by_slo(ctx: Context, *, n_req, prompt_len, out_len, slo_class, arrival_ticks=None,
                        tight_classes, prompt_len_out, out_len_out, slo_class_out,
                        arrival_ticks_out=None, n_tight, stream=None) -> None:
-    import torch
+    torch = _t()
     rq = _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks)
     _check(load_library().maaso_split_by_slo(
         ctx.handle, C.byref(rq), int(tight_classes), _dptr(prompt_len_out, torch.int32),
@@ -476,7 +494,7 @@ def maaso_split_by_slo(ctx: Context, *, n_req, prompt_len, out_len, slo_class, a
 
 def maaso_ins_deploy_select(ctx: Context, *, n_cand, i_pad, n_inst, tp_idx, score, chain_offsets=None,
                             n_gpus, phi_star, cand_star, stream=None) -> None:
-    import torch
+    torch = _t()
     pl = Placements(int(n_cand), int(i_pad), _dptr(n_inst, torch.int32), _dptr(tp_idx, torch.uint8),
                     None, None, None)
     n_chains = 0 if chain_offsets is None else int(chain_offsets.numel()) - 1
@@ -489,7 +507,7 @@ def maaso_ins_deploy_select(ctx: Context, *, n_cand, i_pad, n_inst, tp_idx, scor
 def maaso_resource_partition(ctx: Context, *, n_gpus, phi_t_star, phi_l_star, phi_h_star=None,
                              cand_t_star=None, cand_l_star=None, cand_h_star=None, n_req_l, n_req,
                              partition, phi_opt, stream=None) -> None:
-    import torch
+    torch = _t()
     _check(load_library().maaso_resource_partition(
         ctx.handle, int(n_gpus), _dptr(phi_t_star, torch.float32), _dptr(phi_l_star, torch.float32),
         _dptr(phi_h_star, torch.float32), _dptr(cand_t_star, torch.int32),
@@ -500,7 +518,7 @@ def maaso_resource_partition(ctx: Context, *, n_gpus, phi_t_star, phi_l_star, ph
 
 def maaso_batch_size_prune(ctx: Context, *, n_cand, group_offsets, sat_count, latency, keep, n_kept,
                            stream=None) -> None:
-    import torch
+    torch = _t()
     n_groups = int(group_offsets.numel()) - 1
     _check(load_library().maaso_batch_size_prune(
         ctx.handle, int(n_cand), _dptr(group_offsets, torch.int32), n_groups,
@@ -514,7 +532,7 @@ def maaso_resource_partition_requests(ctx: Context, *, n_cand, i_pad, n_inst, tp
                                       pen_kappa=0.0, tbt_mode=0, window=0, policy=0, alpha, beta,
                                       gamma_t, gamma_l, work, stream=None) -> None:
     """`work`: dict of tensors keyed by the fields of maaso_partition_work (absent or None = NULL)."""
-    import torch
+    torch = _t()
     pl = _placements(n_cand, i_pad, n_inst, tp_idx, max_batch, occ, q_ticks)
     rq = _requests(n_req, prompt_len, out_len, slo_class, arrival_ticks)
     prm = Params(float(s_bar), float(pen_kappa), int(tbt_mode), int(window), int(policy))
