@@ -135,7 +135,8 @@ struct CandidateList {
 // index order and a strict '>' give the lowest index among equal slacks.
 //
 // NREG = 0: a request is compared with the instances it can be admitted to at all (`adm`) and, if none
-// of them can serve it, with those that can be reported for a blocked one (`rep`), both lists in LDS.
+// of them can serve it, with those that can be reported for a blocked one (`rep`; empty where `adm` has
+// all of them), both lists in LDS.
 // NREG > 0: the placement has at most NREG instances and the caller holds their records in
 // registers (`rreg`), so the loop touches no LDS - the form used when there are so few instances that
 // the request stream from HBM is the bound.
@@ -269,7 +270,7 @@ __device__ __forceinline__ uint32_t assign_requests(const AssignArgs& a, uint64_
       idx[v] = idx[v] >= 0 ? (int32_t)adm.idx[idx[v]] : -1;
       blocked |= !(best[v] >= 0.0f);
     }
-    if (lane_mask(blocked) != 0ull) {  // some lane has a request that nothing can serve
+    if (rep.n && lane_mask(blocked) != 0ull) {  // some lane has a request that nothing can serve
       float top[V];
       int32_t at[V];
 #pragma unroll
@@ -336,6 +337,11 @@ __device__ __forceinline__ uint32_t assign_requests(const AssignArgs& a, uint64_
   }
   return sat;
 }
+
+// Listing takes a wavefront about as long as comparing a thread's requests with this many instances: up to
+// there all of them are compared with all requests (31 jittered slots, 316,707 requests, one group of four a
+// thread: 17.6 us with lists, 14.0 without; 49 slots, 6145 requests: 14.2 and 16.4).
+constexpr uint32_t kListPays = 32;
 
 // Lists the instances of a staged placement that matter (one wavefront).
 template <bool kSQ>
@@ -412,6 +418,13 @@ __global__ __launch_bounds__(kAssignThreads) void assign_static_kernel(const Ass
   if (NREG) {
     if (kSQ)
       for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) rankv[j] = queue_rank_value(occ_s, n, j);
+  } else if (n_vec <= stride * (kListPays / max(n, 1u))) {  // groups per thread x instances
+    for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
+      adm_recs[j] = recs[j];
+      adm_idx[j] = j;
+      if (kSQ) adm_rank[j] = queue_rank_value(occ_s, n, j);
+    }
+    if (threadIdx.x == 0u) { sizes[0] = n; sizes[1] = 0u; }
   } else if (threadIdx.x < 64u) {
     list_candidates<kSQ>(a, recs, occ_s, n, threadIdx.x, adm_recs, adm_idx, adm_rank, rep_recs, rep_idx, sizes);
   }

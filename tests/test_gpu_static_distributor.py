@@ -1,6 +1,6 @@
 """The static distributor against the CPU oracle where a request is compared with lists of instances:
 lists that end inside and at a trip of four records, placements whose instances are all alike or all
-listed, requests nothing can serve (their list is another one), both selection rules, block counts on
+listed, requests nothing can serve (their list is another one, or the same where nearly all are listed), both selection rules, block counts on
 both sides of one accumulator line each, aligned arrays and not."""
 import numpy as np
 import pytest
@@ -16,7 +16,7 @@ from paper_2509_06362_amd import binding, workloads as W  # noqa: E402
 @pytest.mark.parametrize("i_pad,n_req,variant", [
     (9, 1000, "mixed"), (64, 32768, "mixed"), (64, 32769, "mixed"), (256, 33000, "different"),
     (65, 40001, "alike"), (128, 2051, "different"), (200, 36000, "blocked"), (33, 5, "blocked"),
-    (16, 70000, "bad"),
+    (16, 70000, "bad"), (256, 3000, "different blocked"), (70, 3001, "different blocked"),
 ])
 def test_static_distributor_lists(i_pad, n_req, variant):
     w = W.random_small(i_pad + n_req, 1, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
@@ -24,13 +24,13 @@ def test_static_distributor_lists(i_pad, n_req, variant):
     if variant == "alike":
         w = W.replace(w, tp_idx=np.full_like(w.tp_idx, 2), max_batch=np.full_like(w.max_batch, 8),
                       occ=np.zeros_like(w.occ), q_ticks=np.zeros_like(w.q_ticks))
-    elif variant == "different":   # nobody dominates: the stronger the instance, the longer its queue
+    elif variant.startswith("different"):   # nobody dominates: the stronger the instance, the longer its queue
         order = np.argsort(w.tp_idx[0], kind="stable")
         q = np.empty(i_pad, np.uint64)
         q[order] = np.arange(i_pad, dtype=np.uint64) * np.uint64(1500)
         w = W.replace(w, q_ticks=q[None], occ=np.zeros_like(w.occ),
                       max_batch=(1 + np.argsort(np.argsort(-q.astype(np.int64))) % 64).astype(np.uint16)[None])
-    elif variant == "blocked":     # most requests cannot be served by anyone
+    if variant.endswith("blocked"):     # most requests cannot be served by anyone
         w = W.replace(w, d_ttft=w.d_ttft * np.float32(0.02), d_tbt=w.d_tbt * np.float32(0.3))
     elif variant == "bad":
         w = W.replace(w, tp_idx=np.where(np.arange(i_pad) % 3 == 0, 9, w.tp_idx).astype(np.uint8))
