@@ -20,6 +20,7 @@
 //      (candidate, class) meet in LDS, sixteen lanes per (candidate, class) add the group of the
 //      threshold's bin to the lengths below it.  The last block to finish writes the best candidate.
 // Up to kSmallRequests requests the third launch is the only one: every block groups them in its own LDS.
+// With few candidates sweep_few_kernel is: every block compares its share of the requests with all thresholds.
 //
 // What bounds it: the instance slots' 15 bytes each and the latency of three short launches.  65,536
 // candidates x 32 slots x 16,384 requests: 457 -> 40 us; 8192 x 128 x 131,072: 5240 -> 43 us; 4096 x 32 x 65,536:
@@ -93,6 +94,20 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t* part) {
   return before;
 }
 
+// dst[0 .. n) = src[0 .. n), by the block; eight words a thread in flight (one after the other, the 4096
+// group totals of sixteen classes were sixteen trips to memory: 10 us of a 15 us launch).
+__device__ __forceinline__ void copy_words(uint32_t* dst, const uint32_t* src, uint32_t n) {
+  constexpr uint32_t U = 8;
+  for (uint32_t i = threadIdx.x; i < n; i += U * kSweepThreads) {
+    uint32_t v[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) v[u] = src[min(i + u * kSweepThreads, n - 1u)];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      if (i + u * kSweepThreads < n) dst[i + u * kSweepThreads] = v[u];
+  }
+}
+
 struct GroupArgs {
   const uint32_t* prompt_len;
   const uint8_t* slo_class;
@@ -144,34 +159,62 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_hist_kernel(const GroupAr
 
 __global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const GroupArgs a) {
   __shared__ uint32_t h[kMaxSlo * kLenBins];
-  __shared__ uint32_t start[kMaxSlo * kLenBins];
+  __shared__ uint32_t start[kMaxSlo * kLenBins / 16 * 17];
   __shared__ uint32_t part[kSweepThreads / kWave];
   const uint32_t n = a.n_slo * kLenBins, tid = threadIdx.x;
-  // where each group starts: every block works it out from the totals (thread t holds n_slo groups)
-  uint32_t sum = 0;
-  for (uint32_t q = 0; q < a.n_slo; ++q) {
-    const uint32_t v = a.hist[tid * a.n_slo + q];
-    start[tid * a.n_slo + q] = v;
-    sum += v;
+  // where each group starts: every block works it out from the totals, thread t for n_slo groups in a row (a
+  // word of padding every sixteen keeps the threads' rows off each other's banks)
+  auto padded = [](uint32_t i) { return i + (i >> 4); };
+  constexpr uint32_t U = 8;  // trips to memory side by side
+  for (uint32_t i0 = tid; i0 < n; i0 += U * kSweepThreads) {
+    uint32_t v[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) v[u] = a.hist[min(i0 + u * kSweepThreads, n - 1u)];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t i = i0 + u * kSweepThreads;
+      if (i < n) { start[padded(i)] = v[u]; h[i] = 0u; }
+    }
   }
-  for (uint32_t i = tid; i < n; i += kSweepThreads) h[i] = 0u;
+  __syncthreads();
+  uint32_t held[kMaxSlo], sum = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < kMaxSlo; ++q) {
+    held[q] = start[padded(tid * a.n_slo + min(q, a.n_slo - 1u))];
+    sum += q < a.n_slo ? held[q] : 0u;
+  }
   uint32_t before = block_prefix(sum, part);
-  for (uint32_t q = 0; q < a.n_slo; ++q) {
-    const uint32_t i = tid * a.n_slo + q, v = start[i];
-    start[i] = before;
-    if (blockIdx.x == 0u) a.offsets[i] = before;
-    before += v;
-  }
+#pragma unroll
+  for (uint32_t q = 0; q < kMaxSlo; ++q)
+    if (q < a.n_slo) {
+      start[padded(tid * a.n_slo + q)] = before;
+      before += held[q];
+    }
   if (blockIdx.x == 0u && tid == kSweepThreads - 1u) a.offsets[n] = before;
   __syncthreads();
+  if (blockIdx.x == 0u)
+    for (uint32_t i = tid; i < n; i += kSweepThreads) a.offsets[i] = start[padded(i)];
   const uint32_t r0 = blockIdx.x * a.per_block;
   const uint32_t r1 = a.n_req - r0 > a.per_block ? r0 + a.per_block : a.n_req;
   for_requests<false>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
                       [&](uint32_t g, float) { atomicAdd(&h[g], 1u); });
   lds_atomics_barrier();
-  // this block's share of every group it has requests of
-  for (uint32_t i = tid; i < n; i += kSweepThreads)
-    if (h[i] != 0u) h[i] = start[i] + atomicAdd(&a.cursor[i], h[i]);
+  // this block's share of every group it has requests of, eight returning atomics a thread in flight
+  for (uint32_t i0 = tid; i0 < n; i0 += U * kSweepThreads) {
+    uint32_t own[U], at[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t i = i0 + u * kSweepThreads;
+      own[u] = i < n ? h[i] : 0u;
+      at[u] = 0u;
+      if (own[u] != 0u) at[u] = atomicAdd(&a.cursor[i], own[u]);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t i = i0 + u * kSweepThreads;
+      if (own[u] != 0u) h[i] = start[padded(i)] + at[u];
+    }
+  }
   __syncthreads();
   for_requests<false>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
                       [&](uint32_t g, float L) { a.sorted[atomicAdd(&h[g], 1u)] = L; });
@@ -246,6 +289,16 @@ __device__ __forceinline__ bool deliver(SweepTotals* t, uint32_t parties, unsign
   fresh = atomicExch(&t->pairs[1], 0ull);
   atomicExch(&t->delivered, 0u);
   return true;
+}
+
+// A block's delivery; true, with the grid's totals, for the last block.  Few blocks meet on line 0 at once.
+__device__ __forceinline__ bool deliver_block(SweepTotals* totals, unsigned long long& best,
+                                              unsigned long long& pairs, unsigned long long& fresh) {
+  if (gridDim.x <= 16u) return deliver(&totals[0], gridDim.x, best, pairs, fresh);
+  const uint32_t line = blockIdx.x % kTotalsLines;
+  const uint32_t lines = min(gridDim.x, kTotalsLines);
+  const uint32_t on_line = (gridDim.x - line + kTotalsLines - 1u) / kTotalsLines;
+  return deliver(&totals[1u + line], on_line, best, pairs, fresh) && deliver(&totals[0], lines, best, pairs, fresh);
 }
 
 struct CountArgs {
@@ -326,7 +379,7 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
                         [&](uint32_t g, float L) { own[atomicAdd(&off[g + 1u], 1u)] = L; });
     __syncthreads();
   } else {
-    for (uint32_t i = tid; i <= n; i += kSweepThreads) off[i] = a.offsets[i];
+    copy_words(off, a.offsets, n + 1u);
     if (blockIdx.x == 0u)
       for (uint32_t i = tid; i < 2u * n; i += kSweepThreads) a.clear[i] = 0u;
     __syncthreads();
@@ -395,25 +448,32 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
       }
     }
     lds_atomics_barrier();
-    // sixteen lanes per (candidate, class): the lengths below the threshold's bin, and those of the bin
-    // that are not above it
-    for (uint32_t t = tid >> 4; t < nc * K; t += kSweepThreads / 16) {
+    // the lengths below the threshold's bin, and those of the bin that are not above it: sixteen lanes per
+    // (candidate, class), as many more as the block has over (89 candidates x 3 slots, one class, 217k
+    // requests, 3000 to a bin: 27 -> 9 us)
+    const uint32_t tasks = nc * K;
+    const uint32_t width = tasks > 8u ? 4u : tasks > 4u ? 5u : tasks > 2u ? 6u : tasks > 1u ? 7u : 8u;
+    static_assert(kSweepThreads == 256, "one (candidate, class) takes at most the block");
+    for (uint32_t t = tid >> width; t < tasks; t += kSweepThreads >> width) {
       const uint32_t key = longest[t];
       const uint32_t cl = t / K, k = t - cl * K;
+      const uint32_t part_of = tid & ((1u << width) - 1u);
       uint32_t sum = 0;
       if (key != 0u) {
         const float X = __uint_as_float(key - 1u);
         const uint32_t grp = k * kLenBins + length_bin(X);
         const uint32_t b0 = off[grp], b1 = off[grp + 1u];
-        constexpr uint32_t U = 4;
-        for (uint32_t i = b0 + (lane & 15u); i < b1; i += 16u * U) {
+        constexpr uint32_t U = 8;
+        for (uint32_t i = b0 + part_of; i < b1; i = b1 - i > (U << width) ? i + (U << width) : b1) {
           float L[U];
 #pragma unroll
-          for (uint32_t u = 0; u < U; ++u) L[u] = i + 16u * u < b1 ? length_at(i + 16u * u) : INFINITY;
+          for (uint32_t u = 0; u < U; ++u) {
+            L[u] = (u << width) < b1 - i ? length_at(i + (u << width)) : INFINITY;
+          }
 #pragma unroll
           for (uint32_t u = 0; u < U; ++u) sum += L[u] <= X ? 1u : 0u;
         }
-        sum = row_sum_u32(sum) + (b0 - off[k * kLenBins]);
+        sum = row_sum_u32(sum) + (part_of == 0u ? b0 - off[k * kLenBins] : 0u);
       }
       if ((lane & 15u) == 0u && sum != 0u) atomicAdd(&cnt[cl], sum);
     }
@@ -441,14 +501,143 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
       e += ends[1][w];
       f += ends[2][w];
     }
-    const uint32_t line = blockIdx.x % kTotalsLines;
-    const uint32_t lines = min(gridDim.x, kTotalsLines);
-    const uint32_t on_line = (gridDim.x - line + kTotalsLines - 1u) / kTotalsLines;
-    if (deliver(&a.totals[1u + line], on_line, b, e, f) && deliver(&a.totals[0], lines, b, e, f)) {
+    if (deliver_block(a.totals, b, e, f)) {
       a.eval_total[0] = e;
       a.eval_total[1] = f;
       if (a.best_cand) *a.best_cand = ~(uint32_t)(b & 0xffffffffull);
     }
+  }
+}
+
+// The same counts in one launch where there are few candidates: every block works out the thresholds of all of
+// them (at most kFewSlots slots) and compares its share of the requests with each, a count per candidate from
+// the lanes' masks.  Grouping the lengths costs two launches and pays only where a length is looked up often.
+constexpr uint32_t kFewSlots = 512, kFewCandidates = 128;
+__global__ __launch_bounds__(kSweepThreads) void sweep_few_kernel(const CountArgs a) {
+  __shared__ uint32_t longest[kMaxSlo * (kFewCandidates + 1u)];  // [class][candidate], rows of odd length
+  __shared__ uint32_t cnt[kFewCandidates];
+  __shared__ uint32_t suits[2][kMaxSlo], of_class[kMaxSlo];  // slots a class can use (all; without a wait); requests
+  __shared__ unsigned long long ends[kSweepThreads / kWave];
+  __shared__ uint32_t last;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t K = a.n_slo, I = a.i_pad, C = a.n_cand, slots = C * I, pitch = C | 1u;
+  constexpr uint32_t U = 4;
+  const uint32_t per_trip = gridDim.x * U * kSweepThreads;  // the host keeps it far below 2^32
+  // this block's first requests are on their way while the thresholds are worked out
+  uint32_t r0 = blockIdx.x * U * kSweepThreads;
+  uint32_t k[U], key[U];
+  auto fetch = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t at = u * kSweepThreads + tid;
+      const bool in = r0 < a.n_req && at < a.n_req - r0;
+      k[u] = in ? a.slo_class[r0 + at] : 0xffffffffu;
+      key[u] = in ? a.prompt_len[r0 + at] : 0u;
+    }
+  };
+  fetch();
+  for (uint32_t i = tid; i < K * pitch; i += kSweepThreads) longest[i] = 0u;
+  if (tid < C) cnt[tid] = 0u;
+  if (tid < K) { suits[0][tid] = 0u; suits[1][tid] = 0u; of_class[tid] = 0u; }
+  __syncthreads();
+  for (uint32_t s0 = wave * 64u; s0 < slots; s0 += kSweepThreads) {
+    const uint32_t s = min(s0 + lane, slots - 1u), c = s / I;
+    Staged st{1.0f, 1.0f, INFINITY, 1.0f, INFINITY};  // absent: suits no class
+    if (s0 + lane < slots && s - c * I < a.n_inst[c] &&
+        !stage_instance(a.tab, a.cells, a.mp, a.tp_idx[s], a.max_batch[s], a.occ[s], a.q_ticks[s], st))
+      raise_status(a.status, 2u);
+    const float inv_p = __builtin_amdgcn_rcpf(st.p);
+    for (uint32_t q = 0; q < K; ++q) {
+      const bool in_time = st.tbt <= a.d_tbt[q];
+      const unsigned long long m = lane_mask(in_time);
+      if (m == 0ull) continue;
+      const unsigned long long f = lane_mask(in_time && st.wait == 0.0f);
+      if (lane == 0u) {
+        atomicAdd(&suits[0][q], (uint32_t)__popcll(m));
+        atomicAdd(&suits[1][q], (uint32_t)__popcll(f));
+      }
+      const uint32_t x = longest_prompt(st.a, st.p, st.wait, a.d_ttft[q], inv_p, in_time);
+      if (x != 0u) atomicMax(&longest[q * pitch + c], x);
+    }
+  }
+  lds_atomics_barrier();
+  uint32_t mine[2] = {0u, 0u};
+  while (r0 < a.n_req) {  // the same for all threads of the block
+    uint32_t have[U], row[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const bool ok = k[u] < K;
+      if (!ok && k[u] != 0xffffffffu) raise_status(a.status, 1u);
+      // thresholds are the bits of a length plus one: a request counts when its own bits are below
+      have[u] = ok ? __float_as_uint((float)key[u]) : 0xffffffffu;
+      row[u] = (ok ? k[u] : 0u) * pitch;
+    }
+    for (uint32_t q = 0; q < K; ++q) {
+      uint32_t sum = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) sum += (uint32_t)__popcll(lane_mask(k[u] == q));
+      if (lane == 0u) atomicAdd(&of_class[q], sum);
+    }
+    r0 = a.n_req - r0 > per_trip ? r0 + per_trip : a.n_req;
+    fetch();
+    // candidate c's count in lane c mod 64; four candidates' thresholds read ahead of their use
+    constexpr uint32_t V = 4;
+    for (uint32_t c0 = 0; c0 < C; c0 += V) {
+      uint32_t x[V][U];
+#pragma unroll
+      for (uint32_t v = 0; v < V; ++v)
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) x[v][u] = longest[row[u] + min(c0 + v, C - 1u)];
+#pragma unroll
+      for (uint32_t v = 0; v < V; ++v) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) sum += (uint32_t)__popcll(lane_mask(have[u] < x[v][u]));
+        const uint32_t c = c0 + v;
+        if (c < 64u) mine[0] += lane == c ? sum : 0u;
+        else mine[1] += lane == c - 64u ? sum : 0u;  // (c >= C: nobody's)
+      }
+    }
+  }
+#pragma unroll
+  for (uint32_t w = 0; w < 2u; ++w) {
+    const uint32_t c = w * 64u + lane;
+    if (c < C && mine[w] != 0u) atomicAdd(&cnt[c], mine[w]);
+  }
+  lds_atomics_barrier();
+  if (tid < C) {
+    const uint32_t before = atomicAdd(&a.clear[tid], cnt[tid]);  // zero between calls
+    asm volatile("s_waitcnt vmcnt(0)" : : "v"(before) : "memory");
+  }
+  __syncthreads();
+  if (tid == 0u) {
+    unsigned long long b = 0ull, e = 0ull, f = 0ull;
+    for (uint32_t q = 0; q < K; ++q) {
+      e += (unsigned long long)suits[0][q] * of_class[q];
+      f += (unsigned long long)suits[1][q] * of_class[q];
+    }
+    const bool all = deliver_block(a.totals, b, e, f);
+    last = all ? 1u : 0u;
+    if (all) { a.eval_total[0] = e; a.eval_total[1] = f; }
+  }
+  __syncthreads();
+  if (last == 0u) return;
+  unsigned long long best = 0ull;
+  if (tid < C) {
+    const uint32_t v = atomicExch(&a.clear[tid], 0u);
+    a.sat_count[tid] = v;
+    if (a.sat_ratio) a.sat_ratio[tid] = a.n_req ? (float)v / (float)a.n_req : 0.0f;
+    best = ((unsigned long long)v << 32) | (unsigned long long)(~tid);
+  }
+  for (int d = 32; d >= 1; d >>= 1) {
+    const unsigned long long o = __shfl_xor(best, d);
+    best = o > best ? o : best;
+  }
+  if (lane == 0u) ends[wave] = best;
+  __syncthreads();
+  if (tid == 0u && a.best_cand) {
+    for (int w = 1; w < kSweepThreads / kWave; ++w) best = ends[w] > best ? ends[w] : best;
+    *a.best_cand = ~(uint32_t)(best & 0xffffffffull);
   }
 }
 

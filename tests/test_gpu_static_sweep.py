@@ -1,5 +1,5 @@
 """The static sweep against the triple oracle at the edges of its grouping and of its thresholds: around
-4096 requests (grouped by every block or by launches of their own), around the 1024 requests a grouping
+4096 requests (grouped by every block or by launches of their own, or compared with every threshold), around the 1024 requests a grouping
 block takes, all lengths alike, empty prompts, lengths no binary32 holds exactly, one class and
 sixteen, rows of slots that do and do not fill 16 lanes, and profiles whose quotient is far off."""
 import numpy as np
@@ -36,6 +36,8 @@ def check(w):
 @pytest.mark.parametrize("n_cand,i_pad,n_req,n_slo", [
     (1, 1, 1, 1), (3, 16, 4096, 1), (70, 7, 4097, 3), (1100, 3, 1025, 2), (5, 255, 5120, 16),
     (9, 256, 5121, 3), (1, 64, 9000, 16), (40, 33, 4095, 8), (2100, 32, 4100, 3),
+    # compared with every threshold (up to 128 candidates of 512 slots together), or grouped
+    (128, 4, 5000, 16), (129, 3, 5000, 16), (2, 256, 4097, 5), (3, 171, 4097, 5), (37, 13, 20481, 1),
 ])
 def test_static_sweep_edges(n_cand, i_pad, n_req, n_slo):
     w = W.random_small(n_cand + 3 * i_pad + n_req, n_cand, i_pad, n_req, n_slo=n_slo, b_cap=64, pen_kappa=0.5)
@@ -45,9 +47,9 @@ def test_static_sweep_edges(n_cand, i_pad, n_req, n_slo):
 
 
 @pytest.mark.parametrize("lengths", ["alike", "empty", "steps", "long", "beyond"])
-@pytest.mark.parametrize("n_req", [1500, 6000])
-def test_static_sweep_lengths(lengths, n_req):
-    w = W.stressed(W.random_small(n_req + len(lengths), 60, 20, n_req, n_slo=3, b_cap=32), seed=5)
+@pytest.mark.parametrize("n_req,i_pad", [(1500, 20), (6000, 20), (6000, 8)])
+def test_static_sweep_lengths(lengths, n_req, i_pad):
+    w = W.stressed(W.random_small(n_req + len(lengths), 60, i_pad, n_req, n_slo=3, b_cap=32), seed=5)
     rng = np.random.default_rng(n_req)
     if lengths == "alike":
         L = np.full(n_req, 1777)
@@ -72,8 +74,9 @@ def test_static_sweep_lengths(lengths, n_req):
 @pytest.mark.parametrize("a_scale,p_scale,d_scale", [
     (1.0, 1e-9, 1.0), (1.0, 1e6, 1.0), (1e-6, 1e-7, 1e-3), (40.0, 1e-4, 1.0), (1.0, 1.0, 4000.0), (1e-30, 1e-30, 1.0),
 ])
-def test_static_sweep_extreme_profiles(a_scale, p_scale, d_scale):
-    w = W.random_small(17, 50, 24, 5000, n_slo=3, b_cap=32)
+@pytest.mark.parametrize("n_cand", [50, 20])
+def test_static_sweep_extreme_profiles(a_scale, p_scale, d_scale, n_cand):
+    w = W.random_small(17, n_cand, 24, 5000, n_slo=3, b_cap=32)
     rng = np.random.default_rng(3)
     w = W.replace(w, prefill_a=(w.prefill_a * np.float32(a_scale)), prefill_p=(w.prefill_p * np.float32(p_scale)),
                   d_ttft=(w.d_ttft * np.float32(d_scale)),
