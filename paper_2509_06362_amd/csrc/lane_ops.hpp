@@ -25,13 +25,6 @@ __device__ __forceinline__ unsigned long long to_ticks(float seconds, bool narro
   return t;
 }
 
-// (slack, index) of the better of two candidates: larger slack, lower index among equals.
-__device__ __forceinline__ void take_better(float& s, int32_t& i, float os, int32_t oi) {
-  const bool take = (os > s) | ((os == s) & (oi < i));  // no short circuit: three compares, no branches
-  s = take ? os : s;
-  i = take ? oi : i;
-}
-
 // x = OP(x, x of the lane that the DPP control CTRL names), one instruction.  A DPP operand written by
 // the vector instruction just before needs two wait states, which the assembler does not add inside
 // an asm statement: hence the s_nop.
@@ -90,11 +83,6 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   MAASO_DPP_FOLD_ROWS("v_add_u32_dpp", v, "row_bcast:15", "0xa");
   MAASO_DPP_FOLD_ROWS("v_add_u32_dpp", v, "row_bcast:31", "0xc");
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-  return v;
 }
 
 // Sum over the wavefront of per-lane tick counts, uniform: in 32 bits when no lane holds 2^26 ticks (64 s

@@ -1,7 +1,6 @@
 // Host side of the C ABI declared in include/maaso.h: argument validation, the context, launch
-// shapes.  Every step of the scoring path runs in the kernels of sweep_kernels.hpp and
-// assign_kernels.hpp; nothing here computes on the CPU beyond table validation and the reciprocals
-// of the class deadlines.
+// shapes.  Every step of the scoring path runs in the kernels of the headers below; nothing here
+// computes on the CPU beyond table validation and the reciprocals of the class deadlines.
 #include "../../include/maaso.h"
 
 #include <hip/hip_runtime.h>
@@ -261,19 +260,23 @@ void fill_assign_args(AssignArgs& a, const maaso_ctx* ctx, const maaso_placement
 
 // Wavefronts per candidate and requests per lane of the windowed sweep.  One wavefront per candidate wastes
 // least (state, evaluation and the choice of admissible instances are per wavefront) once there are
-// enough candidates to fill the device; four shorten the walk through the windows where there are not.
+// enough candidates to fill the device, and where a window is no more than its lanes; four shorten the walk
+// through the windows where they are not.
 // Measured, one wavefront against four: 8192 candidates, windows of 4096: 1.90 / 2.67 ms; 2160 units of
-// 256: 1.33 / 1.60 ms; 2000 of 65,536: 1.49 / 0.52 ms; 700 of 4096: 0.73 / 0.40 ms; 300 of 256:
-// 0.91 / 0.69 ms.  Four requests per lane where a window has them (8192 candidates of 4096: 1.90 against
-// 2.71 ms with one), else one (2000 of 64: 0.51 against 0.62 ms with four).
+// 256: 1.33 / 1.58 ms; 2000 of 65,536: 1.49 / 0.52 ms; 700 of 4096: 0.73 / 0.40 ms; 300 of 255:
+// 0.11 / 0.10 ms (8192 requests, 32 slots), of 128: 0.13 / 0.14 ms, of 64: 0.20 / 0.24 ms.
+// Requests per lane: as many as a window has for one pass (2000 candidates, 128 slots, 1 / 2 / 4: windows of 64
+// 0.73 / 0.78 / 0.88 ms, of 128 0.53 / 0.47 / 0.53 ms, of 192 0.44 / 0.42 / 0.37 ms, of 256
+// 0.42 / 0.35 / 0.30 ms); with four wavefronts one up to windows of 1024.
 template <bool kScore, bool kSQ, int S>
 void launch_sweep_window_s(const SweepWindowArgs& a, uint64_t per_window, size_t lds, hipStream_t s) {
   const uint64_t units = (uint64_t)a.n_cand * a.n_sets;
-  const bool alone = units >= 4096u || (units >= 1024u && per_window < 4096u);
+  const bool alone = units >= 4096u || (units >= 1024u && per_window < 4096u) || per_window <= 64u;
   const dim3 b(kAssignThreads);
   const dim3 g((alone ? (a.n_cand + 3u) / 4u : a.n_cand) * a.n_sets);
   if (alone) {
-    if (per_window >= 256u) hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 1, 4, kSQ>), g, b, lds, s, a);
+    if (per_window > 128u) hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 1, 4, kSQ>), g, b, lds, s, a);
+    else if (per_window > 64u) hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 1, 2, kSQ>), g, b, lds, s, a);
     else hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 1, 1, kSQ>), g, b, lds, s, a);
   } else {
     if (per_window >= 1024u) hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 4, 4, kSQ>), g, b, lds, s, a);
@@ -292,11 +295,13 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
   }
   const uint64_t blocks = (uint64_t)a.n_cand * a.n_sets;
   if (blocks == 0 || blocks > 0x7fffffffull) return MAASO_E_SHAPE;
-  // Short windows go to the kernel that gives a wavefront to each (set, candidate) and its lanes to
-  // the instances.  Measured crossover with the lanes-are-requests kernel (2048-8192 candidates): up to
-  // 32 slots a window of 4 (6.2 against 7.6 ms; 8: 5.7 against 3.8), 128 slots 16 (6.6 against 9.4; 32:
-  // 6.4 against 4.8), 256 slots 32 (7.7 against 8.9; 64: 7.6 against 4.5).
-  const uint32_t short_window = a.i_pad / 8u > 4u ? a.i_pad / 8u : 4u;
+  // Short windows go to the kernel whose lanes are the instances while a request is scored (no search for
+  // the instances a request can be given, but all of them at every request).  Measured, lanes-are-requests
+  // against it (2048 candidates, 2048 requests): 16 slots, windows of 8: 0.72 / 0.49 ms, of 16: 0.32 / 0.48;
+  // 32 slots, 8: 0.97 / 0.51, 16: 0.46 / 0.49; 64 slots, 16: 0.67 / 0.52, 32: 0.31 / 0.52; 128 slots, 16:
+  // 1.00 / 0.74, 32: 0.42 / 0.73; 256 slots, 16: 1.26 / 0.95, 32: 0.58 / 0.92.  512 and 8192 candidates
+  // cross over at the same windows.
+  const uint32_t short_window = a.i_pad > 32u ? 16u : 8u;
   bool one_by_one = !kSQ;
   for (uint32_t k = 0; k < a.n_sets; ++k) one_by_one = one_by_one && a.sets[k].window <= short_window;
   if (one_by_one) {
@@ -1252,10 +1257,10 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   }
 
   // Short windows (down to one request per window, the online distributor taken literally): one
-  // wavefront with the instances in its lanes and no device-wide barrier.  Measured per request, one
-  // wavefront against the persistent kernel: window 1: 0.88 against 2.72 us (64 slots), 1.72 against
-  // 2.86 (256); window 4: 0.59 against 0.68 (64), 0.94 against 0.75 (256).  The window_blocks knob set
-  // to a value asks for the persistent kernel below whatever the window.
+  // wavefront with the instances in its lanes and no device-wide barrier.  Measured per request, the
+  // persistent kernel against one wavefront: window 1: 1.98 / 0.41 us (64 slots), 2.20 / 0.80 (256); window 4:
+  // 0.51 / 0.30, 0.57 / 0.54; window 8: 0.27 / 0.28, 0.30 / 0.49.  The window_blocks knob set to a value
+  // asks for the persistent kernel below whatever the window.
   const uint32_t short_window = pl->i_pad <= 128u ? 4u : 2u;
   if (prm->policy == 0u && prm->window <= short_window && ctx->window_blocks == 0u) {
     const size_t lds = (size_t)3 * (ctx->cells + 1u) * sizeof(float);

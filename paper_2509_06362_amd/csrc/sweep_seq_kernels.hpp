@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : 4) void sweep_seq_kernel(
   uint32_t behind = 0;
   auto fetch = [&]() __attribute__((always_inline)) {
     if (f0 >= R) return;
-    raw = fetch_request(rs, f0 + lane, R);
+    raw = fetch_request(rs, f0, lane, R);
     if (f0 + lane + 1u < R) behind = rs.arrival_ticks[f0 + lane + 1u];
     f0 = R - f0 > 4u * kSeqChunk ? f0 + 4u * kSeqChunk : R;
   };

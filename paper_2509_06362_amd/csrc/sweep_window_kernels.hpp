@@ -94,9 +94,11 @@ struct RequestSide {
   float4 w;  // reciprocals of the two deadlines, end-to-end deadline, its reciprocal
 };
 
-__device__ __forceinline__ RequestRaw fetch_request(const SweepWindowSet& rs, uint32_t r, uint32_t end) {
+// Request r0 + i, if that is before `end`.
+__device__ __forceinline__ RequestRaw fetch_request(const SweepWindowSet& rs, uint32_t r0, uint32_t i, uint32_t end) {
   RequestRaw raw{0u, 0u, kNoRequest};
-  if (r < end) { raw.pl = rs.prompt_len[r]; raw.ol = rs.out_len[r]; raw.k = rs.slo_class[r]; }
+  const uint32_t r = r0 + i;
+  if (r0 < end && i < end - r0) { raw.pl = rs.prompt_len[r]; raw.ol = rs.out_len[r]; raw.k = rs.slo_class[r]; }
   return raw;
 }
 
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
   auto fetch = [&]() __attribute__((always_inline)) {
     if (f0 >= R) return;
 #pragma unroll
-    for (uint32_t v = 0; v < kRaw; ++v) raw[v] = fetch_request(rs, f0 + v * kAssignThreads + tid, f1);
+    for (uint32_t v = 0; v < kRaw; ++v) raw[v] = fetch_request(rs, f0, v * kAssignThreads + tid, f1);
     if (f1 - f0 > kBatch) { f0 += kBatch; return; }
     f0 = f1;
     if (f0 < R) f1 = window_end(f0);
@@ -399,7 +401,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
     };
 
     if (NW == 1) {
-      for (uint32_t b0 = s0; b0 < e0; b0 += kBatch) {
+      for (uint32_t b0 = s0; b0 < e0; b0 = e0 - b0 > kBatch ? b0 + kBatch : e0) {
         next_chunk(cbuf ^ 1u);  // the chunk after this one (past the end: nothing that counts)
         const uint32_t len = min(e0 - b0, kBatch);
         if (m != 0u) {

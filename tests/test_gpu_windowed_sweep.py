@@ -1,7 +1,7 @@
 """The windowed sweep and score against the CPU oracle at the edges of its shapes: a candidate per
 wavefront and per block, 64 / 128 / 256 instance slots, windows around the 64-, 256- and
 1024-request batches, placements whose instances are all alike, all different, or out of the tables,
-and deadlines beyond what the 32-bit tick sums take."""
+deadlines beyond what the 32-bit tick sums take, and both sides of the longest short window."""
 import numpy as np
 import pytest
 
@@ -21,6 +21,9 @@ WEIGHTS = (4.0, 0.3, 2048.0, 1.0)
     (2, 256, 1024, 3000, "different"), (5, 128, 1025, 2100, "alike"), (4, 200, 300, 1000, "long"),
     (1024, 20, 256, 513, "long"), (6, 33, 40, 500, "bad"), (1031, 9, 100, 350, "bad"),
     (4100, 2, 5000, 300, "mixed"),
+    # the longest windows in which a candidate's lanes are its instances, and one request more
+    (33, 32, 8, 210, "mixed"), (33, 32, 9, 210, "different"), (30, 33, 16, 210, "different"),
+    (30, 33, 17, 210, "mixed"), (9, 256, 16, 150, "long"), (9, 256, 17, 150, "mixed"),
 ])
 def test_windowed_sweep_edges(n_cand, i_pad, window, n_req, variant):
     w = W.random_small(n_cand * 7 + i_pad, n_cand, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
