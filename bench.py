@@ -68,15 +68,16 @@ PAPER_CONTEXT = (
 # figure only holds for the kernel it was taken with: it is reported while the digest of that kernel's
 # source files matches and as null - with both digests, so that the staleness is visible - afterwards.
 KERNEL_SOURCES = {
-    "sweep_kernel": ("device_model.hpp", "sweep_kernels.hpp"),
-    "assign_static_kernel": ("device_model.hpp", "sweep_kernels.hpp", "assign_kernels.hpp"),
-    "assign_window_kernel": ("device_model.hpp", "sweep_kernels.hpp", "assign_kernels.hpp",
-                             "window_kernels.hpp"),
+    "sweep_count_kernel": ("device_model.hpp", "sweep_kernels.hpp"),
+    "assign_static_kernel": ("device_model.hpp", "sweep_kernels.hpp", "lane_ops.hpp", "live_slots.hpp",
+                             "assign_kernels.hpp"),
+    "assign_window_kernel": ("device_model.hpp", "sweep_kernels.hpp", "lane_ops.hpp", "live_slots.hpp",
+                             "assign_kernels.hpp", "window_kernels.hpp"),
 }
 TRAFFIC = {
     # workload name: (kernel, bytes per launch, digest of the kernel's sources at measurement, summary)
-    "cfg4_skewed_stress": ("sweep_kernel", 3.0879e7, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg4.md"),
-    "cfg1_placer_sweep": ("sweep_kernel", 5.641e6, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg1.md"),
+    "cfg4_skewed_stress": ("sweep_count_kernel", 3.0879e7, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg4.md"),
+    "cfg1_placer_sweep": ("sweep_count_kernel", 5.641e6, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg1.md"),
     "streaming_i4": ("assign_static_kernel", 1.1410e9, "db880294941b8bee",
                      "profiles/assign_static_kernel_stream.md"),
 }
