@@ -24,6 +24,7 @@
 
 #include "sweep_window_kernels.hpp"
 #include "window_kernels.hpp"
+#include "window_rules.hpp"
 
 #pragma clang fp contract(off)
 
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : 4) void sweep_seq_kernel(
   auto fetch = [&]() __attribute__((always_inline)) {
     if (f0 >= R) return;
     raw = fetch_request(rs, f0, lane, R);
-    if (f0 + lane + 1u < R) behind = rs.arrival_ticks[f0 + lane + 1u];
+    if (reads_arrival_behind(f0 + lane, R, W)) behind = rs.arrival_ticks[f0 + lane + 1u];
     f0 = R - f0 > 4u * kSeqChunk ? f0 + 4u * kSeqChunk : R;
   };
   auto prepare = [&](uint32_t to) __attribute__((always_inline)) {

@@ -1,0 +1,37 @@
+"""The index rules of the windowed sweeps (window_rules.hpp), compiled for the CPU and run through every
+small case: which arrivals a set's windows read."""
+import shutil
+import subprocess
+from pathlib import Path
+
+import pytest
+
+CSRC = Path(__file__).resolve().parent.parent / "paper_2509_06362_amd" / "csrc"
+
+
+def run_rules(tmp_path, body):
+    """Compiles `body` behind the header and returns the integers it prints."""
+    if shutil.which("g++") is None:
+        pytest.skip("no C++ compiler")
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include <cstdio>\n#include "window_rules.hpp"\nusing namespace maaso;\n'
+                   "int main() {\n" + body + "\n  return 0;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", f"-I{CSRC}", str(src), "-o", str(exe)],
+                   check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
+    return [[int(x) for x in line.split()] for line in out.splitlines()]
+
+
+def test_arrivals_are_read_between_windows_only(tmp_path):
+    """A set that is one window (a static score) may come without arrivals: none is read.  With more
+    windows every request that a window can end at has the arrival behind it, and none past the set."""
+    rows = run_rules(tmp_path, """
+  for (uint32_t n = 0; n <= 70; ++n)
+    for (uint32_t w = 1; w <= 72; ++w)
+      for (uint32_t r = 0; r < 130; ++r)
+        if (reads_arrival_behind(r, n, w)) printf("%u %u %u\\n", n, w, r);
+  const uint32_t most = 1u << 31;
+  if (reads_arrival_behind(most - 1u, most, 1u) || !reads_arrival_behind(most - 2u, most, 1u)) printf("0 0 0\\n");""")
+    read = {tuple(row) for row in rows}
+    expected = {(n, w, r) for n in range(71) for w in range(1, 73) if w < n for r in range(n - 1)}
+    assert read == expected
