@@ -17,6 +17,7 @@
 
 #include "assign_kernels.hpp"
 #include "live_slots.hpp"
+#include "window_rules.hpp"
 
 #pragma clang fp contract(off)
 
@@ -193,8 +194,9 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
   __shared__ float4 chunk_w[NW == 1 ? 2 : 1][NW == 1 ? kAssignThreads : 1];  // no bank conflicts
   // admitted sums of a window, NW > 1: three buffers in turn - one is added to, the one before is read,
   // the one after is cleared
-  __shared__ uint32_t n_sum[NW > 1 ? 3 : 1][NW > 1 ? 64 * S : 1];
-  __shared__ unsigned long long t_sum[NW > 1 ? 3 : 1][NW > 1 ? 64 * S : 1];
+  constexpr uint32_t kSums = NW > 1 ? kSumBuffers : 1u;
+  __shared__ uint32_t n_sum[kSums][NW > 1 ? 64 * S : 1];
+  __shared__ unsigned long long t_sum[kSums][NW > 1 ? 64 * S : 1];
 
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u;
@@ -202,7 +204,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
   if (tid < a.n_slo) cls[tid] = ClassRow{a.d_ttft[tid], a.d_tbt[tid], a.i_ttft[tid], a.i_tbt[tid]};
   for (uint32_t i = tid; i < 3u * a.cells; i += kAssignThreads) tab[i] = a.tab[i];
   if (NW > 1)
-    for (uint32_t i = tid; i < 3u * 64u * S; i += kAssignThreads) { (&n_sum[0][0])[i] = 0u; (&t_sum[0][0])[i] = 0ull; }
+    for (uint32_t i = tid; i < kSums * 64u * S; i += kAssignThreads) { (&n_sum[0][0])[i] = 0u; (&t_sum[0][0])[i] = 0ull; }
   __syncthreads();
 
   // blocks of one request set first, then the next: a block never mixes sets
@@ -428,10 +430,8 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
         else score_any(rq);
       }
       close_few();
-      // the buffer of the window after next was read behind the previous barrier; it is clean before
-      // anyone passes this one
-      const uint32_t later = buf == 0u ? 2u : buf - 1u;
-      if (tid < 64u * S) { n_sum[later][tid] = 0u; t_sum[later][tid] = 0ull; }
+      const uint32_t free = cleared_sum_buffer(buf);  // clean before anyone passes this barrier
+      if (tid < 64u * S) { n_sum[free][tid] = 0u; t_sum[free][tid] = 0ull; }
       lds_atomics_barrier();
       if (few) {
 #pragma unroll
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
                   lane_value(rec[s].wait, l));
           }
       }
-      buf = buf == 2u ? 0u : buf + 1u;
+      buf = next_sum_buffer(buf);
     }
     if (e0 < R) {  // time passes until the next window opens
 #pragma unroll

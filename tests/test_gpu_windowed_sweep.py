@@ -63,3 +63,52 @@ def test_windowed_sweep_edges(n_cand, i_pad, window, n_req, variant):
             assert binding.maaso_ctx_device_status(dw.ctx) == (2 if variant == "bad" else 0)
         finally:
             dw.close()
+
+
+@pytest.mark.parametrize("i_pad,window,n_windows,variant", [
+    (5, 65, 60, "alike"), (64, 200, 48, "mixed"), (128, 96, 48, "different"), (256, 130, 40, "different"),
+    (33, 1024, 30, "alike"), (100, 1025, 24, "different"), (256, 1500, 24, "mixed"),
+])
+def test_wavefronts_that_share_a_candidate_stay_alike(i_pad, window, n_windows, variant):
+    """Few candidates and windows of more than 64 requests: four wavefronts per candidate, one request a lane
+    below 1024 and four from there on.  Dozens of windows in bursts: over all slots windows with one to several
+    instances to choose among, over two slots windows in which nobody can be admitted next to others."""
+    n_req = window * n_windows - window // 3
+    w = W.random_small(i_pad + n_windows, 3, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
+    n_inst = np.array([i_pad, 2, i_pad // 2 + 1], np.uint32)
+    burst = np.arange(n_req) // (6 * window)
+    # within a burst 64 ticks from one request to the next; then half a minute in which the queues empty
+    ticks = np.arange(n_req, dtype=np.uint64) * 64 + burst.astype(np.uint64) * (30 << 20)
+    w = W.replace(w, n_inst=n_inst, arrival_ticks=ticks.astype(np.uint32), occ=np.zeros_like(w.occ))
+    if variant == "alike":
+        w = W.replace(w, tp_idx=np.full_like(w.tp_idx, 1), max_batch=np.full_like(w.max_batch, 16),
+                      q_ticks=np.zeros_like(w.q_ticks))
+    elif variant == "different":  # longer queues on the stronger instances: few are dominated
+        q = w.tp_idx.astype(np.uint64) * np.uint64(1 << 19) + w.max_batch.astype(np.uint64) * np.uint64(4099)
+        w = W.replace(w, q_ticks=q)
+    if variant != "alike":
+        w = W.replace(w, d_ttft=w.d_ttft * np.float32(0.1))
+    chosen = [0, 0]  # windows by the instances that are chosen: two or more of all slots, none of two slots
+    for c in (0, 1):
+        run = oracle.score_assign(w, cand=c, window=window)
+        for lo in range(0, n_req, window):
+            of = run["chosen"][lo:lo + window][run["slack"][lo:lo + window] >= 0]
+            chosen[c] += len(np.unique(of)) >= 2 if c == 0 else len(of) == 0
+    assert (variant == "alike" or chosen[0] >= 3) and 2 <= chosen[1] <= n_windows - 2, chosen
+    for policy in (0, 1):
+        wp = W.replace(w, policy=policy)
+        print(f"shared candidate I={i_pad} window={window} windows={n_windows} {variant} policy={policy}", flush=True)
+        dw = binding.DeviceWorkload(wp)
+        try:
+            cnt, _, best = dw.sweep(window=window)
+            sc = dw.score(*WEIGHTS, window=window)
+            torch.cuda.synchronize()
+            ref = oracle.placement_score(wp, *WEIGHTS, window=window)
+            assert np.array_equal(cnt.cpu().numpy().view(np.uint32), ref["sat_count"])
+            assert int(best.item()) == int(np.argmax(ref["sat_count"]))
+            for k in ("sat_count", "phi_s", "phi_t", "phi_l", "score"):
+                got = sc[k].cpu().numpy()
+                assert np.array_equal(got.view(np.uint32) if k == "sat_count" else got, ref[k]), k
+            assert binding.maaso_ctx_device_status(dw.ctx) == 0
+        finally:
+            dw.close()

@@ -1,5 +1,5 @@
 """The index rules of the windowed sweeps (window_rules.hpp), compiled for the CPU and run through every
-small case: which arrivals a set's windows read."""
+small case: which arrivals a set's windows read, and which buffer of admitted sums is free to be cleared."""
 import shutil
 import subprocess
 from pathlib import Path
@@ -35,3 +35,23 @@ def test_arrivals_are_read_between_windows_only(tmp_path):
     read = {tuple(row) for row in rows}
     expected = {(n, w, r) for n in range(71) for w in range(1, 73) if w < n for r in range(n - 1)}
     assert read == expected
+
+
+def test_sum_buffers_are_cleared_while_nobody_uses_them(tmp_path):
+    """Wavefronts that share a candidate meet at one barrier per window and are otherwise in any order, so
+    in the interval that ends at window w's barrier anyone may be reading the sums of window w - 1, adding
+    to those of window w or clearing.  No two of these touch one buffer, and a buffer that is added to has
+    been cleared, in an earlier interval, since it was last read."""
+    rows = run_rules(tmp_path, """
+  for (uint32_t w = 0, buf = 0; w < 40; ++w, buf = next_sum_buffer(buf))
+    printf("%u %u\\n", buf, cleared_sum_buffer(buf));
+  printf("%u %u\\n", kSumBuffers, kSumBuffers);""")
+    n = rows.pop()[0]
+    clean = {b: True for b in range(n)}       # as the kernel starts
+    for w, (added, cleared) in enumerate(rows):
+        used = [added, cleared] + ([rows[w - 1][0]] if w else [])
+        assert len(set(used)) == len(used), f"window {w}: {used}"
+        assert all(0 <= b < n for b in used)
+        assert clean[added], f"window {w} adds to what an earlier one left"
+        clean[added] = False                  # read behind this interval's barrier
+        clean[cleared] = True
