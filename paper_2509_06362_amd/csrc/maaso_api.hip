@@ -17,6 +17,7 @@
 #include "probe_kernels.hpp"
 #include "profile_fit_kernels.hpp"
 #include "sweep_window_kernels.hpp"
+#include "sweep_block_kernels.hpp"
 #include "sweep_seq_kernels.hpp"
 #include "window_kernels.hpp"
 
@@ -295,6 +296,23 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
   }
   const uint64_t blocks = (uint64_t)a.n_cand * a.n_sets;
   if (blocks == 0 || blocks > 0x7fffffffull) return MAASO_E_SHAPE;
+  // Few candidates: a block per candidate, its lanes shared out over requests and instances.  Measured, this form
+  // against what the rules below choose (us per window, 64 slots, lengths and state as a loaded cluster's):
+  // 512 candidates, windows of 6: 1.44 times as fast, of 33: 2.1, of 256: 1.25, of 512: 0.85; 1024 candidates: 1.16, 1.35,
+  // 0.93, 0.82; 2048 candidates: 0.74, 0.92, 0.59 - but 1.2 at windows of 12 to 24.  Windows of up to four: 0.95 (8
+  // candidates) to 0.5.  Shortest queue, 8 candidates of 4 / 16 / 256 slots: windows of 12 1.04 / 1.6 / 1.7, of 24 0.91 /
+  // 1.36 / 1.1, of 65 1.0 / 0.98 / 0.6.
+  uint64_t longest_block = 0;
+  if (kSQ) longest_block = blocks > 1536u ? 0u : a.i_pad > 8u ? 24u : 16u;
+  else longest_block = blocks <= 768u ? 256u : blocks <= 1536u ? 64u : blocks <= 2560u && a.i_pad > 8u ? 32u : 0u;
+  const uint64_t shortest_block = kSQ ? 1u : blocks <= 1536u ? 5u : 9u;
+  if (per_window >= shortest_block && per_window <= longest_block) {
+    uint32_t lpr_log2 = 0;  // lanes per request: as many as a pass over the window has, and instances to walk
+    while (lpr_log2 < kMaxLprLog2 && (per_window << (lpr_log2 + 1u)) <= (uint64_t)kBlockThreads && (2u << lpr_log2) <= a.i_pad)
+      ++lpr_log2;
+    hipLaunchKernelGGL((sweep_block_kernel<kScore, kSQ>), dim3((uint32_t)blocks), dim3(kBlockThreads), lds, s, a, lpr_log2);
+    return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
+  }
   // Short windows go to the kernel whose lanes are the instances while a request is scored (no search for
   // the instances a request can be given, but all of them at every request).  Measured, lanes-are-requests
   // against it (2048 candidates, 2048 requests): 16 slots, windows of 8: 0.72 / 0.49 ms, of 16: 0.32 / 0.48;

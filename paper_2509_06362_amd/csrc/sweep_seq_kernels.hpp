@@ -281,20 +281,7 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : 4) void sweep_seq_kernel(
       for (unsigned long long todo = served[s]; todo != 0ull; todo &= todo - 1ull)
         pt = pt + lane_value(inv_tbt_first[s], (int)__builtin_ctzll(todo));
   }
-  if (lane == 0u && mine_c) {
-    rs.sat_count[c] = sat;
-    if (kScore) {
-      const float ps = (rs.n_req == 0u) ? 0.0f : (float)sat / (float)rs.n_req;
-      const float plat = (sat == 0u) ? 0.0f : ((float)wait_sum * 0x1p-20f) / (float)sat;
-      const float ptn = fminf(pt, a.gamma_t) / a.gamma_t;
-      const float pln = fmaxf(a.gamma_l - plat, 0.0f) / a.gamma_l;
-      const float sc = fmaf(a.alpha, ps, fmaf(a.beta, ptn, (1.0f - a.beta) * pln));
-      if (rs.phi_s) rs.phi_s[c] = ps;
-      if (rs.phi_t) rs.phi_t[c] = pt;
-      if (rs.phi_l) rs.phi_l[c] = plat;
-      if (rs.score) rs.score[c] = sc;
-    }
-  }
+  if (lane == 0u && mine_c) write_candidate<kScore>(a, rs, c, sat, wait_sum, pt);
 }
 
 // The distributor itself on short windows (one placement, requests in arrival order, down to one

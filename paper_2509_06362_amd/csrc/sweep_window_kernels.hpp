@@ -117,6 +117,24 @@ __device__ __forceinline__ RequestSide request_side(const RequestRaw& raw, uint3
   return q;
 }
 
+// One candidate's results: its admitted requests and, with kScore, the composite score - Phi = alpha * Phi_S^n +
+// beta * min(Phi_T, gamma_T) / gamma_T + (1 - beta) * max(gamma_L - Phi_L, 0) / gamma_L (Sec. IV-D, Eq. 6-8).
+template <bool kScore>
+__device__ __forceinline__ void write_candidate(const SweepWindowArgs& a, const SweepWindowSet& rs, uint32_t c,
+                                                uint32_t sat, unsigned long long wait_sum, float pt) {
+  rs.sat_count[c] = sat;
+  if (!kScore) return;
+  const float ps = (rs.n_req == 0u) ? 0.0f : (float)sat / (float)rs.n_req;
+  const float pl = (sat == 0u) ? 0.0f : ((float)wait_sum * 0x1p-20f) / (float)sat;
+  const float ptn = fminf(pt, a.gamma_t) / a.gamma_t;
+  const float pln = fmaxf(a.gamma_l - pl, 0.0f) / a.gamma_l;
+  const float sc = fmaf(a.alpha, ps, fmaf(a.beta, ptn, (1.0f - a.beta) * pln));
+  if (rs.phi_s) rs.phi_s[c] = ps;
+  if (rs.phi_t) rs.phi_t[c] = pt;
+  if (rs.phi_l) rs.phi_l[c] = pl;
+  if (rs.score) rs.score[c] = sc;
+}
+
 // Scores V requests of a lane against M <= kFew instances held in registers and adds what is admitted
 // to the caller's sums: cnt[i] (uniform) requests and acc[i] (per lane) prefill ticks on instance i, except
 // that the entries of instance 0 take everything admitted (the caller subtracts the others).  Who is
@@ -466,20 +484,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
       for (unsigned long long todo = lane_mask(served[s] != 0u); todo != 0ull; todo &= todo - 1ull)
         pt = pt + lane_value(inv_tbt_first[s], (int)__builtin_ctzll(todo));
   }
-  if (lane == 0u && mine_c && (NW == 1 || wave == 0u)) {
-    rs.sat_count[c] = sat;
-    if (kScore) {
-      const float ps = (rs.n_req == 0u) ? 0.0f : (float)sat / (float)rs.n_req;
-      const float pl = (sat == 0u) ? 0.0f : ((float)wait_sum * 0x1p-20f) / (float)sat;
-      const float ptn = fminf(pt, a.gamma_t) / a.gamma_t;
-      const float pln = fmaxf(a.gamma_l - pl, 0.0f) / a.gamma_l;
-      const float sc = fmaf(a.alpha, ps, fmaf(a.beta, ptn, (1.0f - a.beta) * pln));
-      if (rs.phi_s) rs.phi_s[c] = ps;
-      if (rs.phi_t) rs.phi_t[c] = pt;
-      if (rs.phi_l) rs.phi_l[c] = pl;
-      if (rs.score) rs.score[c] = sc;
-    }
-  }
+  if (lane == 0u && mine_c && (NW == 1 || wave == 0u)) write_candidate<kScore>(a, rs, c, sat, wait_sum, pt);
 }
 
 // Best candidate by score: largest score, lowest index on ties.  One block.

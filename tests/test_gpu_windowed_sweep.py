@@ -66,11 +66,11 @@ def test_windowed_sweep_edges(n_cand, i_pad, window, n_req, variant):
 
 
 @pytest.mark.parametrize("i_pad,window,n_windows,variant", [
-    (5, 65, 60, "alike"), (64, 200, 48, "mixed"), (128, 96, 48, "different"), (256, 130, 40, "different"),
+    (5, 300, 60, "alike"), (64, 257, 48, "mixed"), (128, 500, 48, "different"), (256, 700, 40, "different"),
     (33, 1024, 30, "alike"), (100, 1025, 24, "different"), (256, 1500, 24, "mixed"),
 ])
 def test_wavefronts_that_share_a_candidate_stay_alike(i_pad, window, n_windows, variant):
-    """Few candidates and windows of more than 64 requests: four wavefronts per candidate, one request a lane
+    """Few candidates and windows of more than 256 requests: four wavefronts per candidate, one request a lane
     below 1024 and four from there on.  Dozens of windows in bursts: over all slots windows with one to several
     instances to choose among, over two slots windows in which nobody can be admitted next to others."""
     n_req = window * n_windows - window // 3
@@ -96,19 +96,52 @@ def test_wavefronts_that_share_a_candidate_stay_alike(i_pad, window, n_windows, 
             chosen[c] += len(np.unique(of)) >= 2 if c == 0 else len(of) == 0
     assert (variant == "alike" or chosen[0] >= 3) and 2 <= chosen[1] <= n_windows - 2, chosen
     for policy in (0, 1):
-        wp = W.replace(w, policy=policy)
-        print(f"shared candidate I={i_pad} window={window} windows={n_windows} {variant} policy={policy}", flush=True)
-        dw = binding.DeviceWorkload(wp)
-        try:
-            cnt, _, best = dw.sweep(window=window)
-            sc = dw.score(*WEIGHTS, window=window)
-            torch.cuda.synchronize()
-            ref = oracle.placement_score(wp, *WEIGHTS, window=window)
-            assert np.array_equal(cnt.cpu().numpy().view(np.uint32), ref["sat_count"])
-            assert int(best.item()) == int(np.argmax(ref["sat_count"]))
-            for k in ("sat_count", "phi_s", "phi_t", "phi_l", "score"):
-                got = sc[k].cpu().numpy()
-                assert np.array_equal(got.view(np.uint32) if k == "sat_count" else got, ref[k]), k
-            assert binding.maaso_ctx_device_status(dw.ctx) == 0
-        finally:
-            dw.close()
+        check_against_oracle(W.replace(w, policy=policy), window, f"shared candidate windows={n_windows} {variant}")
+
+
+def check_against_oracle(w, window, what, status=0, ref_w=None):
+    print(f"{what} C={w.n_cand} I={w.i_pad} R={w.n_req} window={window} policy={w.policy}", flush=True)
+    dw = binding.DeviceWorkload(w)
+    try:
+        cnt, _, best = dw.sweep(window=window)
+        sc = dw.score(*WEIGHTS, window=window)
+        torch.cuda.synchronize()
+        ref = oracle.placement_score(w if ref_w is None else ref_w, *WEIGHTS, window=window)
+        assert np.array_equal(cnt.cpu().numpy().view(np.uint32), ref["sat_count"])
+        assert int(best.item()) == int(np.argmax(ref["sat_count"]))
+        for k in ("sat_count", "phi_s", "phi_t", "phi_l", "score"):
+            got = sc[k].cpu().numpy()
+            assert np.array_equal(got.view(np.uint32) if k == "sat_count" else got, ref[k]), k
+        assert binding.maaso_ctx_device_status(dw.ctx) == status
+    finally:
+        dw.close()
+
+
+@pytest.mark.parametrize("n_cand,i_pad,window,n_req,policy,variant", [
+    # one lane a request and several, passes that end inside and at a window, instances that do not fill a trip
+    (3, 1, 5, 61, 0, "mixed"), (4, 2, 6, 90, 0, "mixed"), (2, 17, 9, 200, 0, "mixed"), (3, 16, 16, 160, 0, "bad"),
+    (2, 64, 17, 300, 0, "mixed"), (2, 255, 64, 700, 0, "mixed"), (3, 256, 65, 800, 0, "mixed"), (5, 33, 128, 1000, 0, "bad"),
+    (2, 128, 129, 900, 0, "long"), (4, 5, 255, 1100, 0, "long"), (3, 70, 256, 1300, 0, "mixed"), (3, 70, 257, 1300, 0, "mixed"),
+    (6, 40, 9000, 200, 0, "mixed"), (2, 64, 4, 210, 0, "mixed"),
+    # most candidates that are taken this way at windows of 256, 64 and 32 requests, and one more
+    (768, 4, 70, 150, 0, "mixed"), (769, 4, 70, 150, 0, "mixed"), (1536, 3, 20, 70, 0, "mixed"), (1537, 9, 20, 70, 0, "mixed"),
+    (1537, 8, 20, 70, 0, "mixed"), (2560, 9, 9, 40, 0, "mixed"), (2561, 9, 9, 40, 0, "mixed"),
+    # shortest queue
+    (3, 1, 1, 40, 1, "mixed"), (2, 20, 3, 150, 1, "mixed"), (2, 8, 16, 330, 1, "bad"), (2, 8, 17, 330, 1, "mixed"),
+    (2, 64, 24, 330, 1, "bad"), (2, 64, 25, 330, 1, "mixed"),
+    (3, 256, 7, 200, 1, "long"), (1536, 3, 16, 70, 1, "mixed"), (1537, 3, 16, 70, 1, "mixed"),
+])
+def test_block_per_candidate_edges(n_cand, i_pad, window, n_req, policy, variant):
+    w = W.random_small(n_cand * 5 + i_pad + window, n_cand, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
+    w = W.replace(w, policy=policy)
+    ref_w, status = w, 0
+    if variant == "long":     # ticks beyond 32 bits
+        w = ref_w = W.replace(w, d_ttft=w.d_ttft * np.float32(1000.0), q_ticks=w.q_ticks * np.uint64(300),
+                              prompt_len=w.prompt_len * np.uint32(700))
+    elif variant == "bad":    # absent slots: as good as instances nobody can ever be admitted to
+        tp, q = w.tp_idx.copy(), w.q_ticks.copy()
+        w = W.replace(w, n_inst=np.full_like(w.n_inst, i_pad))
+        tp[:, i_pad // 2] = 9
+        q[:, i_pad // 2] = np.uint64(1 << 50)
+        ref_w, w, status = W.replace(w, q_ticks=q), W.replace(w, tp_idx=tp), 2
+    check_against_oracle(w, window, f"block per candidate {variant}", status, ref_w)
