@@ -8,11 +8,15 @@
 // admitted to at all (find_admissible: 1 to 4 in nineteen windows of twenty) and scores the requests,
 // lanes = requests, against those alone.
 //
+// What a window's admitted requests add up to is kept in registers where a few instances are left, and in
+// LDS where more are: an addition per request unless a whole wavefront chose one instance, then every lane
+// fetches its instances' sums (a trip per instance chosen before: 1024 candidates x 128 jittered slots,
+// windows of 256: 11.7 -> 9.4 us a window; every instance scored: 10.8).
+//
 // What bounds it: vector issue at windows of thousands (8192 candidates x 131,072 requests x 128
-// instances, windows of 4096: 26.8 ms with every instance scored, 1.9 ms now - 263 vector and 96 scalar
-// instructions per wavefront and 256 requests), the chain of one window after the other at short ones
-// (Alg. 2, 720 deployments x three sets, windows of 256: 2.6 -> 1.33 ms, 2.6 us per window of the
-// longest chain).
+// instances, windows of 4096: 26.8 ms with every instance scored, 1.83 ms now), the chain of one window
+// after the other at short ones (Alg. 2, 720 deployments x three sets, windows of 256: 2.6 -> 1.24 ms,
+// 2.4 us per window of the longest chain).
 #pragma once
 
 #include "assign_kernels.hpp"
@@ -210,19 +214,18 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
   __shared__ ClassRow cls[kMaxSlo];
   __shared__ float4 chunk_u[NW == 1 ? 2 : 1][NW == 1 ? kAssignThreads : 1];  // RequestSide in two arrays:
   __shared__ float4 chunk_w[NW == 1 ? 2 : 1][NW == 1 ? kAssignThreads : 1];  // no bank conflicts
-  // admitted sums of a window, NW > 1: three buffers in turn - one is added to, the one before is read,
-  // the one after is cleared
-  constexpr uint32_t kSums = NW > 1 ? kSumBuffers : 1u;
-  __shared__ uint32_t n_sum[kSums][NW > 1 ? 64 * S : 1];
-  __shared__ unsigned long long t_sum[kSums][NW > 1 ? 64 * S : 1];
+  // admitted sums of a window.  NW > 1: three buffers in turn - one is added to, the one before is read, the
+  // one after is cleared.  NW = 1: one per wavefront, for windows with more than a few instances.
+  constexpr uint32_t kSums = NW > 1 ? kSumBuffers : kAssignThreads / 64;
+  __shared__ uint32_t n_sum[kSums][64 * S];
+  __shared__ unsigned long long t_sum[kSums][64 * S];
 
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   if (tid < a.n_slo) cls[tid] = ClassRow{a.d_ttft[tid], a.d_tbt[tid], a.i_ttft[tid], a.i_tbt[tid]};
   for (uint32_t i = tid; i < 3u * a.cells; i += kAssignThreads) tab[i] = a.tab[i];
-  if (NW > 1)
-    for (uint32_t i = tid; i < kSums * 64u * S; i += kAssignThreads) { (&n_sum[0][0])[i] = 0u; (&t_sum[0][0])[i] = 0ull; }
+  for (uint32_t i = tid; i < kSums * 64u * S; i += kAssignThreads) { (&n_sum[0][0])[i] = 0u; (&t_sum[0][0])[i] = 0ull; }
   __syncthreads();
 
   // blocks of one request set first, then the next: a block never mixes sets
@@ -248,8 +251,9 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
     if (j < n)
       slot[s].load(a.mp, a.tp_idx[base + j], a.max_batch[base + j], a.occ[base + j], a.q_ticks[base + j]);
   }
-  uint32_t sat = 0;                    // uniform
-  unsigned long long wait_sum = 0ull;  // queue waits of the admitted requests, in ticks; uniform
+  // queue waits of the admitted requests, in ticks: of windows with few instances (uniform), of the others (of
+  // the lane's instances)
+  unsigned long long wait_sum = 0ull, wait_own = 0ull;
 
   const uint32_t R = rs.n_req;
   auto window_end = [&](uint32_t s0) __attribute__((always_inline)) { return R - s0 > rs.window ? s0 + rs.window : R; };
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
     if (f0 < R) f1 = window_end(f0);
   };
   RequestSide rq[V];
-  uint32_t cbuf = 0, buf = 0;
+  uint32_t cbuf = 0, buf = NW == 1 ? wave : 0u;
   auto next_chunk = [&](uint32_t to) __attribute__((always_inline)) {
     const RequestSide q = request_side(raw[0], a.n_slo, cls, a.status);
     chunk_u[to][NW == 1 ? tid : 0u] = q.u;
@@ -336,7 +340,6 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
     }
     // adds to the state: instance j (uniform) admitted `num` requests of `ticks` prefill in all
     auto admit = [&](uint32_t j, uint32_t num, unsigned long long ticks, float wait) __attribute__((always_inline)) {
-      sat += num;
       if (kScore) wait_sum += (unsigned long long)num * to_ticks(wait, a.bounds.narrow);
 #pragma unroll
       for (int s = 0; s < S; ++s)
@@ -380,28 +383,31 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const bool adm = best[v] >= 0.0f;  // admitted requests load their instance
+        const unsigned long long am = lane_mask(adm);
+        if (am == 0ull) continue;
         const unsigned long long ticks = adm ? to_ticks(bpre[v], a.bounds.narrow) : 0ull;
-        for (unsigned long long am = lane_mask(adm); am != 0ull;) {  // one trip per instance chosen
-          const uint32_t j = (uint32_t)__builtin_amdgcn_readlane((int)idx[v], (int)__builtin_ctzll(am));
-          const bool here = adm && idx[v] == j;
-          const unsigned long long held = lane_mask(here);
-          const unsigned long long tsum = wave_sum_ticks(here ? ticks : 0ull);
-          if (NW > 1) {
-            if (lane == 0u) {
-              atomicAdd(&n_sum[buf][j], (uint32_t)__popcll(held));
-              atomicAdd(&t_sum[buf][j], tsum);
-            }
-          } else {
-            float w = 0.0f;
-            if (kScore) {
-#pragma unroll
-              for (int s = 0; s < S; ++s)
-                if (j >> 6 == (uint32_t)s) w = lane_value(rec[s].wait, (int)(j & 63u));
-            }
-            admit(j, (uint32_t)__popcll(held), tsum, w);
+        const uint32_t one = (uint32_t)__builtin_amdgcn_readlane((int)idx[v], (int)__builtin_ctzll(am));
+        if (lane_mask(adm && idx[v] == one) == am) {  // all chose one instance
+          const unsigned long long tsum = wave_sum_ticks(ticks);
+          if (lane == 0u) {
+            atomicAdd(&n_sum[buf][one], (uint32_t)__popcll(am));
+            atomicAdd(&t_sum[buf][one], tsum);
           }
-          am &= ~held;
+        } else if (adm) {
+          atomicAdd(&n_sum[buf][idx[v]], 1u);
+          atomicAdd(&t_sum[buf][idx[v]], ticks);
         }
+      }
+    };
+    // ... and what they were given, every lane for its instances
+    auto close_any = [&](uint32_t from) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const uint32_t num = n_sum[from][s * 64 + lane];
+        slot[s].occ += (int32_t)num;
+        slot[s].q += t_sum[from][s * 64 + lane];
+        served[s] += num;
+        if (kScore && num != 0u) wait_own += (unsigned long long)num * to_ticks(rec[s].wait, a.bounds.narrow);
       }
     };
     auto close_few = [&]() __attribute__((always_inline)) {
@@ -438,7 +444,14 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
         cbuf ^= 1u;
         __syncthreads();
       }
-      close_few();
+      if (few) {
+        close_few();
+      } else if (m != 0u) {  // a wavefront's own LDS operations stay in order
+        __builtin_amdgcn_wave_barrier();
+        close_any(buf);
+#pragma unroll
+        for (int s = 0; s < S; ++s) { n_sum[buf][s * 64 + lane] = 0u; t_sum[buf][s * 64 + lane] = 0ull; }
+      }
     } else {
       for (uint32_t b0 = s0; b0 < e0; b0 = e0 - b0 > kBatch ? b0 + kBatch : e0) {
 #pragma unroll
@@ -456,13 +469,7 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
         for (int i = 0; i < kFew; ++i)
           if ((uint32_t)i < m) admit(fj[i], n_sum[buf][fj[i]], t_sum[buf][fj[i]], fr[i].wait);
       } else {
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-          for (unsigned long long todo = und.m[s]; todo != 0ull; todo &= todo - 1ull) {
-            const int l = (int)__builtin_ctzll(todo);
-            admit((uint32_t)(s * 64 + l), n_sum[buf][s * 64 + l], t_sum[buf][s * 64 + l],
-                  lane_value(rec[s].wait, l));
-          }
+        close_any(buf);
       }
       buf = next_sum_buffer(buf);
     }
@@ -476,8 +483,14 @@ __global__ __launch_bounds__(kAssignThreads, S <= 2 ? 4 : 3) void sweep_window_k
   }
 
   if (bad_slot != 0ull) raise_status(a.status, 2u);
+  uint32_t sat = 0;
+#pragma unroll
+  for (int s = 0; s < S; ++s) sat += served[s];
+  sat = wave_sum_u32(sat);
   float pt = 0.0f;
   if (kScore) {
+    for (int d = 32; d >= 1; d >>= 1) wait_own += __shfl_xor(wait_own, d);
+    wait_sum += wait_own;
     // Phi_T: 1 / tbt of the serving instances, added in index order
 #pragma unroll
     for (int s = 0; s < S; ++s)

@@ -145,3 +145,21 @@ def test_block_per_candidate_edges(n_cand, i_pad, window, n_req, policy, variant
         q[:, i_pad // 2] = np.uint64(1 << 50)
         ref_w, w, status = W.replace(w, q_ticks=q), W.replace(w, tp_idx=tp), 2
     check_against_oracle(w, window, f"block per candidate {variant}", status, ref_w)
+
+
+@pytest.mark.parametrize("n_cand,i_pad,window,n_req", [
+    (1540, 20, 40, 200), (1540, 70, 100, 450), (1540, 128, 150, 400), (1540, 256, 200, 450), (5, 256, 1100, 4000),
+])
+def test_windows_that_load_many_instances(n_cand, i_pad, window, n_req):
+    """Instances of which none is better than another in everything, and tight deadlines: more than a few stay in a
+    window and take requests, with a wavefront and with a block per candidate."""
+    w = W.random_small(n_cand + i_pad, n_cand, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
+    order = np.argsort(np.argsort(w.tp_idx, axis=1, kind="stable"), axis=1).astype(np.uint64)
+    w = W.replace(w, tbt_mode=1, n_inst=np.full_like(w.n_inst, i_pad), occ=np.zeros_like(w.occ), q_ticks=order * np.uint64(2000),
+                  max_batch=(64 - (order * np.uint64(60)) // np.uint64(i_pad)).astype(np.uint16),
+                  d_ttft=w.d_ttft * np.float32(0.1))
+    run = oracle.score_assign(w, cand=0, window=window)
+    first = run["chosen"][:window][run["slack"][:window] >= 0]
+    assert len(np.unique(first)) > 4
+    for policy in (0, 1):
+        check_against_oracle(W.replace(w, policy=policy), window, "many instances")
