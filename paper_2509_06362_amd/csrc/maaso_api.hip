@@ -466,34 +466,54 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   }
   ctx->counters_dirty = true;
   const bool small = R <= kSmallRequests;
-  // few candidates: every block knows all thresholds.  Measured, one launch against grouping first: 2 candidates x
-  // 91 slots x 92,049 requests, sixteen classes: 17.9 / 27.0 us; 16 x 32 x 2,000,000: 26.8 / 69; 64 x 8 x 500,000:
-  // 26.3 / 36; 128 x 4 x 262,144: equal.
-  const bool few = !small && C <= kFewCandidates && (uint64_t)C * I <= kFewSlots &&
-                   (C <= 64u || (uint64_t)C * R <= (1ull << 25));
+  // Few candidates: every block works out all thresholds and compares its share of the requests with them.
+  // Grouping first costs two more launches and two passes over the requests instead.  Both in nanoseconds, as
+  // fitted to 40 shapes: the one launch by trips of 256 slots (an evaluation per class each), candidates x
+  // classes and comparisons; the three by classes and requests.  Measured, one launch against three: 2 candidates
+  // x 91 slots x 92,049 requests, sixteen classes: 17.9 / 27.0 us; 16 x 32 x 2,000,000, three: 26.8 / 69; 55 x 17 x 158,856,
+  // one: 18.8 / 22.7; 17 x 34 x 310,617, sixteen: 31.0 / 35.0; 91 x 5 x 62,421, sixteen: 30.9 / 22.7; 79 x 41 x 6753, one:
+  // 24.7 / 16.9; 63 x 22 x 116,985, three: 23.8 / 21.5; 128 x 4 x 262,144, three: equal.
+  const uint64_t few_ns = 9000u + ((uint64_t)C * I + 255u) / 256u * (1100u + 360u * K) + 9u * (uint64_t)C * K / 2u +
+                          (uint64_t)C * R / 2500u;
+  const uint64_t grouped_ns = 17000u + 200u * K + (uint64_t)R * (260u + 12u * K) / 10000u;
+  const bool few = !small && C <= kFewCandidates && few_ns <= grouped_ns;
+  // Bins per class: a pass over all groups is most of what the grouping launches cost on some ten thousand
+  // requests, so no more than some 256 groups while bins stay below a few hundred requests and the look-ups
+  // of all candidates some megabytes (213 candidates x 32 slots x 7112 requests, sixteen classes: 26 -> 20 us;
+  // 45 x 34 x 7773: 26.4 -> 19.8).
+  LengthGroups groups{K, 0u};
+  while (groups.count() > 256u && (uint64_t)R << (groups.shift + 1u) <= (uint64_t)K * kLenBins << 7 &&
+         (uint64_t)C * R << (groups.shift + 1u) <= 1ull << 28)
+    ++groups.shift;
+  const uint32_t n_groups = groups.count();
   if (!small && !few) {
     GroupArgs g;
     g.prompt_len = rq->prompt_len;
     g.slo_class = rq->slo_class;
     g.n_req = R;
-    g.n_slo = K;
+    g.groups = groups;
     // 1024 requests a block fill the chip from 2^18 on; beyond 1024 blocks each takes more
     g.per_block = R > (1u << 20) ? (uint32_t)(((uint64_t)R + 1023u) / 1024u) : 1024u;
     g.hist = hist;
-    g.cursor = hist + (size_t)K * kLenBins;
+    g.cursor = hist + n_groups;
     g.offsets = offsets;
     g.sorted = static_cast<float*>(ws);
     g.status = ctx->status;
     const uint32_t blocks = (uint32_t)(((uint64_t)R + g.per_block - 1) / g.per_block);
-    hipLaunchKernelGGL(sweep_hist_kernel, dim3(blocks), dim3(kSweepThreads), 0, s, g);
-    hipLaunchKernelGGL(sweep_scatter_kernel, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+    if (groups.shift == 0u) {
+      hipLaunchKernelGGL(sweep_hist_kernel<true>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+      hipLaunchKernelGGL(sweep_scatter_kernel<true>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+    } else {
+      hipLaunchKernelGGL(sweep_hist_kernel<false>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+      hipLaunchKernelGGL(sweep_scatter_kernel<false>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+    }
     if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
   }
   CountArgs a;
   a.tab = ctx->tab;
   a.cells = ctx->cells;
   a.mp = model_params(ctx, prm);
-  a.n_slo = K;
+  a.groups = groups;
   std::memcpy(a.d_ttft, ctx->d_ttft, sizeof(a.d_ttft));
   std::memcpy(a.d_tbt, ctx->d_tbt, sizeof(a.d_tbt));
   a.n_cand = C;
@@ -525,18 +545,21 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   a.status = ctx->status;
   const uint32_t cap = (uint32_t)ctx->n_cu * 6u;  // 65,536 x 32 slots: 38 us with 6 blocks per compute unit, 43 with 4 or 8
   const dim3 grid(a.n_groups < cap ? a.n_groups : cap), block(kSweepThreads);
-  const size_t lds = ((size_t)K * kLenBins + 1u) * sizeof(uint32_t);
+  const size_t lds = ((size_t)n_groups + 1u) * sizeof(uint32_t);
   {
     TimedRegion timed(ctx, s);
     if (few) {
       const uint32_t tiles = (R + 1023u) / 1024u;  // four requests a thread
       hipLaunchKernelGGL(sweep_few_kernel, dim3(std::min(tiles, (uint32_t)ctx->n_cu * 4u)), block, 0, s, a);
     } else if (small) {
-      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<true, true>), grid, block, lds, s, a);
-      else hipLaunchKernelGGL((sweep_count_kernel<true, false>), grid, block, lds, s, a);
+      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<true, true, false>), grid, block, lds, s, a);
+      else hipLaunchKernelGGL((sweep_count_kernel<true, false, false>), grid, block, lds, s, a);
+    } else if (groups.shift == 0u) {
+      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true, true>), grid, block, lds, s, a);
+      else hipLaunchKernelGGL((sweep_count_kernel<false, false, true>), grid, block, lds, s, a);
     } else {
-      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true>), grid, block, lds, s, a);
-      else hipLaunchKernelGGL((sweep_count_kernel<false, false>), grid, block, lds, s, a);
+      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true, false>), grid, block, lds, s, a);
+      else hipLaunchKernelGGL((sweep_count_kernel<false, false, false>), grid, block, lds, s, a);
     }
   }
   ctx->last_evaluated = a.eval_total;

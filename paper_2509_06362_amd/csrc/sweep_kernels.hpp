@@ -14,7 +14,8 @@
 //
 // Launches:
 //   1. sweep_hist_kernel, 2. sweep_scatter_kernel - the prompt lengths grouped by (class, bin), 256 bins
-//      per class by the leading bits of the binary32 length (eight per octave), and the groups' offsets.
+//      per class by the leading bits of the binary32 length (eight per octave; two, four ... bins in one
+//      where there are many classes and few requests), and the groups' offsets.
 //   3. sweep_count_kernel - blocks take groups of candidates: a thread per instance slot evaluates the
 //      profile (Eq. 1 row, occupancy penalty, queue wait) and its thresholds, the largest per
 //      (candidate, class) meet in LDS, sixteen lanes per (candidate, class) add the group of the
@@ -23,8 +24,8 @@
 // With few candidates sweep_few_kernel is: every block compares its share of the requests with all thresholds.
 //
 // What bounds it: the instance slots' 15 bytes each and the latency of three short launches.  65,536
-// candidates x 32 slots x 16,384 requests: 457 -> 40 us; 8192 x 128 x 131,072: 5240 -> 43 us; 4096 x 32 x 65,536:
-// 127 -> 24 us; 37 x 13 x 1000: 18 -> 12 us (before: every pair evaluated on the vector units).
+// candidates x 32 slots x 16,384 requests: 457 -> 37 us; 8192 x 128 x 131,072: 5240 -> 40.6 us; 4096 x 32 x 65,536:
+// 127 -> 22 us; 37 x 13 x 1000: 18 -> 11 us (before: every pair evaluated on the vector units).
 #pragma once
 
 #include "device_model.hpp"
@@ -36,7 +37,7 @@ namespace maaso {
 constexpr int kSweepThreads = 256;  // 4 wavefronts
 constexpr int kWave = 64;
 constexpr int kMaxSlo = 16;
-constexpr uint32_t kLenBins = 256;              // per class
+constexpr uint32_t kLenBinsLog2 = 8, kLenBins = 1u << kLenBinsLog2;  // per class, or half as many, a quarter ... (LengthGroups)
 constexpr uint32_t kSmallRequests = 4096;       // grouped by every block for itself
 constexpr uint32_t kMaxGroup = 64;              // candidates a block works on at a time
 
@@ -108,14 +109,35 @@ __device__ __forceinline__ void copy_words(uint32_t* dst, const uint32_t* src, u
   }
 }
 
+// Groups of (class, bin): class k's are [k * bins, (k + 1) * bins).
+struct LengthGroups {
+  uint32_t n_slo;
+  uint32_t shift;  // kLenBins >> shift bins per class
+  __host__ __device__ __forceinline__ uint32_t bins() const { return kLenBins >> shift; }
+  __host__ __device__ __forceinline__ uint32_t count() const { return n_slo * bins(); }
+  __device__ __forceinline__ uint32_t of(uint32_t k, float L) const {
+    return (k << (kLenBinsLog2 - shift)) + (length_bin(L) >> shift);
+  }
+  // groups in a row that a thread of a block takes in a pass over all
+  __device__ __forceinline__ uint32_t per_thread() const { return (count() + kSweepThreads - 1u) / kSweepThreads; }
+};
+
+// kWhole: all kLenBins bins of a class (the usual case, a constant for the compiler).
+template <bool kWhole>
+__device__ __forceinline__ LengthGroups groups_of(LengthGroups g) {
+  if (kWhole) g.shift = 0u;
+  return g;
+}
+
 struct GroupArgs {
   const uint32_t* prompt_len;
   const uint8_t* slo_class;
-  uint32_t n_req, n_slo;
+  uint32_t n_req;
+  LengthGroups groups;
   uint32_t per_block;  // requests per block, contiguous
-  uint32_t* hist;      // [n_slo * kLenBins] zero on entry; the count kernel clears it again
-  uint32_t* cursor;    // [n_slo * kLenBins] as hist
-  uint32_t* offsets;   // [n_slo * kLenBins + 1]
+  uint32_t* hist;      // [groups] zero on entry; the count kernel clears it again
+  uint32_t* cursor;    // [groups] as hist
+  uint32_t* offsets;   // [groups + 1]
   float* sorted;       // [n_req]
   uint32_t* status;
 };
@@ -123,7 +145,7 @@ struct GroupArgs {
 // Calls f(group, length) for the requests [r0, r1) of this block whose class exists.
 template <bool kFlag, class F>
 __device__ __forceinline__ void for_requests(const uint32_t* prompt_len, const uint8_t* slo_class, uint32_t r0,
-                                             uint32_t r1, uint32_t n_slo, uint32_t* status, F f) {
+                                             uint32_t r1, const LengthGroups& groups, uint32_t* status, F f) {
   constexpr uint32_t U = 4;  // loads in flight per thread
   for (uint32_t base = r0; base < r1; base = r1 - base > U * kSweepThreads ? base + U * kSweepThreads : r1) {
     uint32_t k[U];
@@ -137,32 +159,36 @@ __device__ __forceinline__ void for_requests(const uint32_t* prompt_len, const u
     }
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u) {
-      if (k[u] < n_slo) f(k[u] * kLenBins + length_bin(L[u]), L[u]);
+      if (k[u] < groups.n_slo) f(groups.of(k[u], L[u]), L[u]);
       else if (kFlag && k[u] != 0xffffffffu) raise_status(status, 1u);
     }
   }
 }
 
+template <bool kWhole>
 __global__ __launch_bounds__(kSweepThreads) void sweep_hist_kernel(const GroupArgs a) {
   __shared__ uint32_t h[kMaxSlo * kLenBins];
-  const uint32_t n = a.n_slo * kLenBins;
+  const LengthGroups groups = groups_of<kWhole>(a.groups);
+  const uint32_t n = groups.count();
   for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads) h[i] = 0u;
   __syncthreads();
   const uint32_t r0 = blockIdx.x * a.per_block;  // the grid covers the requests without overflow
   const uint32_t r1 = a.n_req - r0 > a.per_block ? r0 + a.per_block : a.n_req;
-  for_requests<true>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
+  for_requests<true>(a.prompt_len, a.slo_class, r0, r1, groups, a.status,
                      [&](uint32_t g, float) { atomicAdd(&h[g], 1u); });
   lds_atomics_barrier();
   for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads)
     if (h[i] != 0u) atomicAdd(&a.hist[i], h[i]);
 }
 
+template <bool kWhole>
 __global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const GroupArgs a) {
   __shared__ uint32_t h[kMaxSlo * kLenBins];
   __shared__ uint32_t start[kMaxSlo * kLenBins / 16 * 17];
   __shared__ uint32_t part[kSweepThreads / kWave];
-  const uint32_t n = a.n_slo * kLenBins, tid = threadIdx.x;
-  // where each group starts: every block works it out from the totals, thread t for n_slo groups in a row (a
+  const LengthGroups groups = groups_of<kWhole>(a.groups);
+  const uint32_t n = groups.count(), per = kWhole ? groups.n_slo : groups.per_thread(), tid = threadIdx.x;
+  // where each group starts: every block works it out from the totals, thread t for `per` groups in a row (a
   // word of padding every sixteen keeps the threads' rows off each other's banks)
   auto padded = [](uint32_t i) { return i + (i >> 4); };
   constexpr uint32_t U = 8;  // trips to memory side by side
@@ -180,14 +206,15 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const Grou
   uint32_t held[kMaxSlo], sum = 0;
 #pragma unroll
   for (uint32_t q = 0; q < kMaxSlo; ++q) {
-    held[q] = start[padded(tid * a.n_slo + min(q, a.n_slo - 1u))];
-    sum += q < a.n_slo ? held[q] : 0u;
+    const uint32_t i = tid * per + min(q, per - 1u);
+    held[q] = start[padded(kWhole ? i : min(i, n - 1u))];
+    sum += q < per && (kWhole || i < n) ? held[q] : 0u;
   }
   uint32_t before = block_prefix(sum, part);
 #pragma unroll
   for (uint32_t q = 0; q < kMaxSlo; ++q)
-    if (q < a.n_slo) {
-      start[padded(tid * a.n_slo + q)] = before;
+    if (q < per && (kWhole || tid * per + q < n)) {
+      start[padded(tid * per + q)] = before;
       before += held[q];
     }
   if (blockIdx.x == 0u && tid == kSweepThreads - 1u) a.offsets[n] = before;
@@ -196,7 +223,7 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const Grou
     for (uint32_t i = tid; i < n; i += kSweepThreads) a.offsets[i] = start[padded(i)];
   const uint32_t r0 = blockIdx.x * a.per_block;
   const uint32_t r1 = a.n_req - r0 > a.per_block ? r0 + a.per_block : a.n_req;
-  for_requests<false>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
+  for_requests<false>(a.prompt_len, a.slo_class, r0, r1, groups, a.status,
                       [&](uint32_t g, float) { atomicAdd(&h[g], 1u); });
   lds_atomics_barrier();
   // this block's share of every group it has requests of, eight returning atomics a thread in flight
@@ -216,7 +243,7 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const Grou
     }
   }
   __syncthreads();
-  for_requests<false>(a.prompt_len, a.slo_class, r0, r1, a.n_slo, a.status,
+  for_requests<false>(a.prompt_len, a.slo_class, r0, r1, groups, a.status,
                       [&](uint32_t g, float L) { a.sorted[atomicAdd(&h[g], 1u)] = L; });
 }
 
@@ -305,7 +332,7 @@ struct CountArgs {
   const float* tab;  // three tables back to back, `cells` entries each
   uint32_t cells;
   ModelParams mp;
-  uint32_t n_slo;
+  LengthGroups groups;
   float d_ttft[kMaxSlo], d_tbt[kMaxSlo];
   uint32_t n_cand, i_pad;
   const uint32_t* n_inst;
@@ -318,7 +345,7 @@ struct CountArgs {
   const uint8_t* slo_class;
   const uint32_t* offsets;     // large form: groups and lengths from the two launches before
   const float* sorted;
-  uint32_t* clear;             // their histogram and cursors, 2 * n_slo * kLenBins words, cleared again
+  uint32_t* clear;             // their histogram and cursors, two words per group, cleared again
   uint32_t group, n_groups;    // candidates per group
   uint32_t* sat_count;
   float* sat_ratio;
@@ -345,10 +372,10 @@ __device__ __forceinline__ uint32_t row_sum_u32(uint32_t v) {
 
 // kSmall: at most kSmallRequests requests, grouped here.  kRows: i_pad is a multiple of 16, so the 16 lanes
 // of a DPP row hold slots of one candidate.
-template <bool kSmall, bool kRows>
+template <bool kSmall, bool kRows, bool kWhole>
 __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  uint32_t* off = reinterpret_cast<uint32_t*>(smem);                // [n_slo * kLenBins + 1]
+  uint32_t* off = reinterpret_cast<uint32_t*>(smem);                // [groups + 1]
   __shared__ float own[kSmall ? kSmallRequests : 1];                // the grouped lengths
   __shared__ uint32_t longest[kMaxGroup * kMaxSlo];                 // per (candidate, class) of the group
   __shared__ uint32_t cnt[kMaxGroup];
@@ -357,25 +384,27 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
   __shared__ unsigned long long ends[3][kSweepThreads / kWave];
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint32_t K = a.n_slo, I = a.i_pad, n = K * kLenBins;
+  const LengthGroups groups = groups_of<kWhole>(a.groups);
+  const uint32_t K = groups.n_slo, I = a.i_pad, n = groups.count(), bins = groups.bins();
   if (kSmall) {
     // counts at off[g + 1], then the groups' starts there; dealing the lengths out moves each to its
     // group's end, which is the next group's start
     for (uint32_t i = tid; i <= n; i += kSweepThreads) off[i] = 0u;
     __syncthreads();
-    for_requests<true>(a.prompt_len, a.slo_class, 0u, a.n_req, K, a.status,
+    for_requests<true>(a.prompt_len, a.slo_class, 0u, a.n_req, groups, a.status,
                        [&](uint32_t g, float) { atomicAdd(&off[g + 1u], 1u); });
     lds_atomics_barrier();
+    const uint32_t per = groups.per_thread(), g0 = min(tid * per, n), g1 = min(g0 + per, n);
     uint32_t sum = 0;
-    for (uint32_t q = 0; q < K; ++q) sum += off[tid * K + q + 1u];
+    for (uint32_t g = g0; g < g1; ++g) sum += off[g + 1u];
     uint32_t before = block_prefix(sum, part);
-    for (uint32_t q = 0; q < K; ++q) {
-      const uint32_t v = off[tid * K + q + 1u];
-      off[tid * K + q + 1u] = before;
+    for (uint32_t g = g0; g < g1; ++g) {
+      const uint32_t v = off[g + 1u];
+      off[g + 1u] = before;
       before += v;
     }
     __syncthreads();
-    for_requests<false>(a.prompt_len, a.slo_class, 0u, a.n_req, K, a.status,
+    for_requests<false>(a.prompt_len, a.slo_class, 0u, a.n_req, groups, a.status,
                         [&](uint32_t g, float L) { own[atomicAdd(&off[g + 1u], 1u)] = L; });
     __syncthreads();
   } else {
@@ -386,7 +415,7 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
   }
   if (tid < K)
     rows[tid] = make_float4(a.d_ttft[tid], a.d_tbt[tid],
-                            __uint_as_float(off[(tid + 1u) * kLenBins] - off[tid * kLenBins]), 0.0f);
+                            __uint_as_float(off[(tid + 1u) * bins] - off[tid * bins]), 0.0f);
   auto length_at = [&](uint32_t i) { return kSmall ? own[kSmall ? i : 0u] : a.sorted[i]; };
 
   unsigned long long best = 0ull;               // of this thread's candidates
@@ -461,7 +490,7 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
       uint32_t sum = 0;
       if (key != 0u) {
         const float X = __uint_as_float(key - 1u);
-        const uint32_t grp = k * kLenBins + length_bin(X);
+        const uint32_t grp = groups.of(k, X);
         const uint32_t b0 = off[grp], b1 = off[grp + 1u];
         constexpr uint32_t U = 8;
         for (uint32_t i = b0 + part_of; i < b1; i = b1 - i > (U << width) ? i + (U << width) : b1) {
@@ -473,7 +502,7 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
 #pragma unroll
           for (uint32_t u = 0; u < U; ++u) sum += L[u] <= X ? 1u : 0u;
         }
-        sum = row_sum_u32(sum) + (part_of == 0u ? b0 - off[k * kLenBins] : 0u);
+        sum = row_sum_u32(sum) + (part_of == 0u ? b0 - off[k * bins] : 0u);
       }
       if ((lane & 15u) == 0u && sum != 0u) atomicAdd(&cnt[cl], sum);
     }
@@ -510,9 +539,8 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
 }
 
 // The same counts in one launch where there are few candidates: every block works out the thresholds of all of
-// them (at most kFewSlots slots) and compares its share of the requests with each, a count per candidate from
-// the lanes' masks.  Grouping the lengths costs two launches and pays only where a length is looked up often.
-constexpr uint32_t kFewSlots = 512, kFewCandidates = 128;
+// them and compares its share of the requests with each, a count per candidate from the lanes' masks.  Grouping the lengths costs two launches and pays only where a length is looked up often.
+constexpr uint32_t kFewCandidates = 128;
 __global__ __launch_bounds__(kSweepThreads) void sweep_few_kernel(const CountArgs a) {
   __shared__ uint32_t longest[kMaxSlo * (kFewCandidates + 1u)];  // [class][candidate], rows of odd length
   __shared__ uint32_t cnt[kFewCandidates];
@@ -520,7 +548,7 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_few_kernel(const CountArg
   __shared__ unsigned long long ends[kSweepThreads / kWave];
   __shared__ uint32_t last;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint32_t K = a.n_slo, I = a.i_pad, C = a.n_cand, slots = C * I, pitch = C | 1u;
+  const uint32_t K = a.groups.n_slo, I = a.i_pad, C = a.n_cand, slots = C * I, pitch = C | 1u;
   constexpr uint32_t U = 4;
   const uint32_t per_trip = gridDim.x * U * kSweepThreads;  // the host keeps it far below 2^32
   // this block's first requests are on their way while the thresholds are worked out

@@ -83,3 +83,20 @@ def test_static_sweep_extreme_profiles(a_scale, p_scale, d_scale, n_cand):
                   prompt_len=np.floor(np.exp(rng.uniform(0, np.log(2.0 ** 24), 5000))).astype(np.uint32))
     print(f"static sweep a*{a_scale} p*{p_scale} D*{d_scale}", flush=True)
     check(w)
+
+
+@pytest.mark.parametrize("n_cand,i_pad,n_req,n_slo", [
+    # every number of bins a class can have: 128 (two classes) down to 16 (sixteen), in one launch and in three
+    (40, 12, 900, 2), (30, 9, 2000, 3), (25, 7, 3000, 7), (20, 20, 4096, 16), (150, 5, 5000, 2), (60, 33, 7000, 5),
+    (140, 12, 9000, 16), (70, 40, 30000, 9), (200, 3, 50000, 16),
+    # and all 256 where the look-ups would get too many
+    (2100, 6, 70000, 2),
+    # compared with every threshold: as many candidates as can be and one more; five trips of slots and six, which
+    # are grouped; one trip of sixteen classes' thresholds and two
+    (128, 4, 16384, 1), (129, 4, 16384, 1), (5, 256, 20000, 1), (6, 256, 20000, 1), (40, 40, 500000, 3), (8, 32, 6000, 16),
+    (9, 32, 6000, 16),
+])
+def test_static_sweep_groups(n_cand, i_pad, n_req, n_slo):
+    w = W.random_small(2 * n_cand + i_pad + n_req, n_cand, i_pad, n_req, n_slo=n_slo, b_cap=64, pen_kappa=0.5)
+    print(f"static sweep groups C={n_cand} I={i_pad} R={n_req} K={n_slo}", flush=True)
+    check(W.stressed(w, seed=n_slo))
