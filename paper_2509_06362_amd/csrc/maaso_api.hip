@@ -263,16 +263,17 @@ void fill_assign_args(AssignArgs& a, const maaso_ctx* ctx, const maaso_placement
 // least (state, evaluation and the choice of admissible instances are per wavefront) once there are
 // enough candidates to fill the device, and where a window is no more than its lanes; four shorten the walk
 // through the windows where they are not.
-// Measured, one wavefront against four: 8192 candidates, windows of 4096: 1.90 / 2.67 ms; 2160 units of
-// 256: 1.33 / 1.58 ms; 2000 of 65,536: 1.49 / 0.52 ms; 700 of 4096: 0.73 / 0.40 ms; 300 of 255:
-// 0.11 / 0.10 ms (8192 requests, 32 slots), of 128: 0.13 / 0.14 ms, of 64: 0.20 / 0.24 ms.
+// Measured, four wavefronts' time over one's, 4 / 32 / 256 slots: 400 candidates, windows of 80: 1.16 / 0.98 / 0.90; 780, of
+// 256: 1.43 / 1.08 / 0.92, of 512: 1.40 / 0.93 / 0.85; 1024, of 512: 1.41 / 0.94 / 0.92, of 1000: 1.34 / 0.83 / 0.81, of 2000:
+// 0.97 / 0.65 / 0.65; 1500, of 1000: 1.53 / 0.88 / 1.03, of 2000: 1.30 / 0.78 / 0.78; 3000, of 2000: 1.82 / 1.07 / 1.02, of 8000:
+// 1.16 / 0.84 / 0.94; 8192 of 4096: 1.4.  The line, units * units / 2048, runs between.
 // Requests per lane: as many as a window has for one pass (2000 candidates, 128 slots, 1 / 2 / 4: windows of 64
 // 0.73 / 0.78 / 0.88 ms, of 128 0.53 / 0.47 / 0.53 ms, of 192 0.44 / 0.42 / 0.37 ms, of 256
 // 0.42 / 0.35 / 0.30 ms); with four wavefronts one up to windows of 1024.
 template <bool kScore, bool kSQ, int S>
 void launch_sweep_window_s(const SweepWindowArgs& a, uint64_t per_window, size_t lds, hipStream_t s) {
   const uint64_t units = (uint64_t)a.n_cand * a.n_sets;
-  const bool alone = units >= 4096u || (units >= 1024u && per_window < 4096u) || per_window <= 64u;
+  const bool alone = units >= 4096u || per_window <= 64u || per_window <= units * units / 2048u;
   const dim3 b(kAssignThreads);
   const dim3 g((alone ? (a.n_cand + 3u) / 4u : a.n_cand) * a.n_sets);
   if (alone) {
@@ -283,6 +284,30 @@ void launch_sweep_window_s(const SweepWindowArgs& a, uint64_t per_window, size_t
     if (per_window >= 1024u) hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 4, 4, kSQ>), g, b, lds, s, a);
     else hipLaunchKernelGGL((sweep_window_kernel<kScore, S, 4, 1, kSQ>), g, b, lds, s, a);
   }
+}
+
+// The windows that a block per candidate (sweep_block_kernel) takes where there are few candidates.  Measured, the
+// forms chosen otherwise against it, 24 windows, mixed instances / jittered profiles and loaded instances:
+//   16 candidates, 16 slots, windows of 3, 5, 64, 256, 320: 0.99/0.97, 1.38/1.37, 1.78/1.80, 1.16/1.15, 0.89/0.91 times its
+//   time; 8 slots, 512: 0.96/0.95 (fresh jittered instances: 1.2); 128 slots, 64, 128, 192: 1.75/2.97, 1.24/1.61, 0.78/0.96;
+//   768: 32 slots, 5, 64, 256, 320: 1.16/1.20, 1.77/1.99, 1.09/1.20, 0.87/0.91; 256 slots, 128, 192: 1.16/1.60, 0.68/0.86;
+//   1024: 16 slots, 64, 128, 192: 1.37/1.51, 1.09/1.15, 0.93/0.92; 128 slots, 64, 96: 1.20/2.06, 0.86/1.28;
+//   1536: 64 slots, 5, 12, 64, 96: 0.86/0.86, 1.70/1.75, 1.23/1.66, 0.91/1.30; 2048: 12, 32, 48: 1.27/1.33, 1.24/1.76, 0.94/1.37,
+//   8 slots, 12: 0.94/0.97.
+// Shortest queue (loaded / jittered): 768 candidates, 8 slots, 64, 128, 256: 0.91/0.91, 1.08/1.10, 0.98/1.02; 32 slots, 128,
+// 192: 1.14/1.29, 0.89/1.03; 128 slots, 64, 96: 0.90/1.29, 0.85/1.21; 1024: 8 slots, 24, 48: 1.11/1.09, 0.96/0.94; 1536: 0.74/0.75.
+struct BlockWindows {
+  uint64_t shortest, longest;
+};
+BlockWindows block_windows(uint64_t blocks, uint32_t i_pad, bool shortest_queue) {
+  if (shortest_queue) {
+    if (blocks <= 768u) return {1u, i_pad <= 8u ? 256u : i_pad <= 32u ? 128u : 64u};
+    return {1u, blocks <= 1280u ? 32u : 0u};
+  }
+  if (blocks <= 768u) return {5u, i_pad <= 8u ? 512u : i_pad <= 64u ? 256u : 128u};
+  if (blocks <= 1024u) return {5u, i_pad > 12u && i_pad <= 64u ? 128u : 64u};
+  if (blocks <= 1536u) return {7u, 64u};
+  return {9u, blocks <= 2560u && i_pad > 12u ? 32u : 0u};
 }
 
 // The windowed sweep of every (request set, candidate); shapes are chosen by the set with the longest
@@ -296,30 +321,21 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
   }
   const uint64_t blocks = (uint64_t)a.n_cand * a.n_sets;
   if (blocks == 0 || blocks > 0x7fffffffull) return MAASO_E_SHAPE;
-  // Few candidates: a block per candidate, its lanes shared out over requests and instances.  Measured, this form
-  // against what the rules below choose (us per window, 64 slots, lengths and state as a loaded cluster's):
-  // 512 candidates, windows of 6: 1.44 times as fast, of 33: 2.1, of 256: 1.25, of 512: 0.85; 1024 candidates: 1.16, 1.35,
-  // 0.93, 0.82; 2048 candidates: 0.74, 0.92, 0.59 - but 1.2 at windows of 12 to 24.  Windows of up to four: 0.95 (8
-  // candidates) to 0.5.  Shortest queue, 8 candidates of 4 / 16 / 256 slots: windows of 12 1.04 / 1.6 / 1.7, of 24 0.91 /
-  // 1.36 / 1.1, of 65 1.0 / 0.98 / 0.6.
-  uint64_t longest_block = 0;
-  if (kSQ) longest_block = blocks > 1536u ? 0u : a.i_pad > 8u ? 24u : 16u;
-  else longest_block = blocks <= 768u ? 256u : blocks <= 1536u ? 64u : blocks <= 2560u && a.i_pad > 8u ? 32u : 0u;
-  const uint64_t shortest_block = kSQ ? 1u : blocks <= 1536u ? 5u : 9u;
-  if (per_window >= shortest_block && per_window <= longest_block) {
-    uint32_t lpr_log2 = 0;  // lanes per request: as many as a pass over the window has, and instances to walk
-    while (lpr_log2 < kMaxLprLog2 && (per_window << (lpr_log2 + 1u)) <= (uint64_t)kBlockThreads && (2u << lpr_log2) <= a.i_pad)
+  const BlockWindows bw = block_windows(blocks, a.i_pad, kSQ);
+  if (per_window >= bw.shortest && per_window <= bw.longest) {
+    uint32_t lpr_log2 = 0;  // lanes per request: as many as a pass over the window has, while a lane walks more than one trip
+    while (lpr_log2 < kMaxLprLog2 && (per_window << (lpr_log2 + 1u)) <= (uint64_t)kBlockThreads && (kBlockTrip << lpr_log2) < a.i_pad)
       ++lpr_log2;
     hipLaunchKernelGGL((sweep_block_kernel<kScore, kSQ>), dim3((uint32_t)blocks), dim3(kBlockThreads), lds, s, a, lpr_log2);
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
   // Short windows go to the kernel whose lanes are the instances while a request is scored (no search for
   // the instances a request can be given, but all of them at every request).  Measured, lanes-are-requests
-  // against it (2048 candidates, 2048 requests): 16 slots, windows of 8: 0.72 / 0.49 ms, of 16: 0.32 / 0.48;
-  // 32 slots, 8: 0.97 / 0.51, 16: 0.46 / 0.49; 64 slots, 16: 0.67 / 0.52, 32: 0.31 / 0.52; 128 slots, 16:
-  // 1.00 / 0.74, 32: 0.42 / 0.73; 256 slots, 16: 1.26 / 0.95, 32: 0.58 / 0.92.  512 and 8192 candidates
-  // cross over at the same windows.
-  const uint32_t short_window = a.i_pad > 32u ? 16u : 8u;
+  // against it, us per window of 2700 candidates: 16 slots, windows of 8: 4.75 / 3.07, of 16: 4.17 / 5.52; 32 slots, 8:
+  // 5.67 / 3.11, 16: 5.55 / 5.68; 64 slots, 16: 6.04 / 5.65, 24: 5.85 / 8.32; 128 slots, 16: 7.27 / 7.56; 256 slots, 16:
+  // 11.4 / 9.5, 24: 12.0 / 13.8.  On jittered profiles, where many instances stay, the search takes longer: 128 slots, 24:
+  // 13.1 / 11.0; 256 slots, 24: 22.1 / 13.9, 32: 21.7 / 17.9.  8000 candidates cross over at the same windows.
+  const uint32_t short_window = a.i_pad > 128u ? 24u : a.i_pad > 32u ? 16u : 8u;
   bool one_by_one = !kSQ;
   for (uint32_t k = 0; k < a.n_sets; ++k) one_by_one = one_by_one && a.sets[k].window <= short_window;
   if (one_by_one) {

@@ -40,12 +40,13 @@ __device__ __forceinline__ void argmax_group(float& s, int32_t& i, uint32_t log2
 
 // kSQ: the distributor's shortest-queue rule instead of the largest slack.  2^lpr_log2 lanes per request.
 constexpr int kBlockThreads = 256;  // one per instance slot
+constexpr uint32_t kBlockTrip = 4;  // records a lane reads ahead of their use
 constexpr uint32_t kMaxLprLog2 = 4;
 template <bool kScore, bool kSQ>
 __global__ __launch_bounds__(kBlockThreads) void sweep_block_kernel(const SweepWindowArgs a, uint32_t lpr_log2) {
   constexpr uint32_t T = kBlockThreads;
-  constexpr uint32_t U = 4;                          // records read ahead of their use
-  constexpr uint32_t kPad = U << kMaxLprLog2;        // records are padded to whole trips
+  constexpr uint32_t U = kBlockTrip;
+  constexpr uint32_t kPad = U << kMaxLprLog2;  // records are padded to whole trips
   const uint32_t lpr = 1u << lpr_log2, step = U << lpr_log2;
   extern __shared__ __align__(16) unsigned char smem[];
   float* tab = reinterpret_cast<float*>(smem);

@@ -66,7 +66,7 @@ def test_windowed_sweep_edges(n_cand, i_pad, window, n_req, variant):
 
 
 @pytest.mark.parametrize("i_pad,window,n_windows,variant", [
-    (5, 300, 60, "alike"), (64, 257, 48, "mixed"), (128, 500, 48, "different"), (256, 700, 40, "different"),
+    (9, 300, 60, "alike"), (64, 257, 48, "mixed"), (128, 500, 48, "different"), (256, 700, 40, "different"),
     (33, 1024, 30, "alike"), (100, 1025, 24, "different"), (256, 1500, 24, "mixed"),
 ])
 def test_wavefronts_that_share_a_candidate_stay_alike(i_pad, window, n_windows, variant):
@@ -123,13 +123,16 @@ def check_against_oracle(w, window, what, status=0, ref_w=None):
     (2, 64, 17, 300, 0, "mixed"), (2, 255, 64, 700, 0, "mixed"), (3, 256, 65, 800, 0, "mixed"), (5, 33, 128, 1000, 0, "bad"),
     (2, 128, 129, 900, 0, "long"), (4, 5, 255, 1100, 0, "long"), (3, 70, 256, 1300, 0, "mixed"), (3, 70, 257, 1300, 0, "mixed"),
     (6, 40, 9000, 200, 0, "mixed"), (2, 64, 4, 210, 0, "mixed"),
-    # most candidates that are taken this way at windows of 256, 64 and 32 requests, and one more
-    (768, 4, 70, 150, 0, "mixed"), (769, 4, 70, 150, 0, "mixed"), (1536, 3, 20, 70, 0, "mixed"), (1537, 9, 20, 70, 0, "mixed"),
-    (1537, 8, 20, 70, 0, "mixed"), (2560, 9, 9, 40, 0, "mixed"), (2561, 9, 9, 40, 0, "mixed"),
+    # the largest numbers of candidates and slots that are taken this way at windows of 256, 128, 64 and 32, and one more
+    (768, 4, 512, 600, 0, "mixed"), (768, 4, 513, 600, 0, "mixed"), (8, 9, 256, 600, 0, "mixed"), (8, 9, 257, 600, 0, "mixed"),
+    (769, 4, 70, 150, 0, "mixed"), (4, 65, 128, 300, 0, "mixed"),
+    (4, 65, 129, 300, 0, "mixed"), (1024, 13, 128, 150, 0, "mixed"), (1024, 12, 65, 150, 0, "mixed"), (1025, 13, 64, 140, 0, "mixed"),
+    (1536, 3, 7, 40, 0, "mixed"), (1536, 3, 6, 40, 0, "mixed"), (1537, 13, 32, 70, 0, "mixed"), (1537, 12, 32, 70, 0, "mixed"),
+    (2560, 13, 9, 40, 0, "mixed"), (2561, 13, 9, 40, 0, "mixed"),
     # shortest queue
-    (3, 1, 1, 40, 1, "mixed"), (2, 20, 3, 150, 1, "mixed"), (2, 8, 16, 330, 1, "bad"), (2, 8, 17, 330, 1, "mixed"),
-    (2, 64, 24, 330, 1, "bad"), (2, 64, 25, 330, 1, "mixed"),
-    (3, 256, 7, 200, 1, "long"), (1536, 3, 16, 70, 1, "mixed"), (1537, 3, 16, 70, 1, "mixed"),
+    (3, 1, 1, 40, 1, "mixed"), (2, 20, 3, 150, 1, "mixed"), (2, 8, 256, 530, 1, "bad"), (2, 9, 129, 530, 1, "mixed"),
+    (2, 32, 128, 330, 1, "mixed"), (2, 33, 64, 330, 1, "bad"), (2, 33, 65, 330, 1, "mixed"), (3, 256, 7, 200, 1, "long"),
+    (769, 5, 32, 70, 1, "mixed"), (769, 5, 33, 70, 1, "mixed"), (1280, 3, 16, 70, 1, "mixed"), (1281, 3, 16, 70, 1, "mixed"),
 ])
 def test_block_per_candidate_edges(n_cand, i_pad, window, n_req, policy, variant):
     w = W.random_small(n_cand * 5 + i_pad + window, n_cand, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
@@ -163,3 +166,24 @@ def test_windows_that_load_many_instances(n_cand, i_pad, window, n_req):
     assert len(np.unique(first)) > 4
     for policy in (0, 1):
         check_against_oracle(W.replace(w, policy=policy), window, "many instances")
+
+
+@pytest.mark.parametrize("n_cand,i_pad,window,variant", [
+    (2600, 129, 24, "mixed"), (2600, 129, 25, "mixed"), (2565, 128, 17, "different"), (2565, 9, 8, "mixed"),
+])
+def test_longest_short_windows_of_many_candidates(n_cand, i_pad, window, variant):
+    w = W.random_small(n_cand + i_pad, n_cand, i_pad, 3 * window + 5, n_slo=3, b_cap=64, pen_kappa=0.5)
+    if variant == "different":
+        q = w.tp_idx.astype(np.uint64) * np.uint64(1 << 19) + w.max_batch.astype(np.uint64) * np.uint64(4099)
+        w = W.replace(w, q_ticks=q, occ=np.zeros_like(w.occ), n_inst=np.full_like(w.n_inst, i_pad))
+    check_against_oracle(w, window, f"short windows {variant}")
+
+
+@pytest.mark.parametrize("n_cand,i_pad,window,n_req", [
+    (1024, 12, 512, 600), (1024, 12, 513, 600), (769, 66, 288, 350), (769, 66, 289, 350), (1449, 5, 1025, 1100),
+    (1448, 5, 1025, 1100), (4095, 3, 8190, 8300), (4096, 3, 8300, 8300),
+])
+def test_one_wavefront_per_candidate_or_four(n_cand, i_pad, window, n_req):
+    """Both sides of the line between the two, which runs with the square of the number of candidates."""
+    w = W.random_small(n_cand + i_pad, n_cand, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
+    check_against_oracle(w, window, "one wavefront or four")
