@@ -16,8 +16,9 @@ which HBM, not the VALU, binds.  Every entry is compared with the CPU oracle in 
 (`oracle_check`): satisfied counts per candidate for the sweeps, chosen instance / slack / admitted
 count / final state for the distributors.
 
-Prints ONE JSON line.  The roofline of each entry is that of its dominant kernel, timed with HIP
-events recorded inside the library directly around that kernel, on the stream it is launched on.
+Prints ONE JSON line.  The roofline of each entry is that of its dominant kernel (of the static sweep: all
+its launches), timed with HIP events recorded inside the library directly around it, on the stream it is
+launched on.
 """
 from __future__ import annotations
 
@@ -63,12 +64,12 @@ PAPER_CONTEXT = (
     "(Sec. V-B, Solver Overhead). The paper prints no triples/s or per-evaluation time for this "
     "path: context, not a target.")
 
-# HBM bytes per launch of the dominant kernel, from rocprofv3 FETCH_SIZE + WRITE_SIZE scaled by the
-# readings of a 1 GiB copy kernel (the summaries named here hold the readings and the factor).  A
+# HBM bytes per call of the dominant kernel (static_sweep: its launches together), from rocprofv3 FETCH_SIZE +
+# WRITE_SIZE scaled by the readings of a 1 GiB copy kernel (the summaries named here hold the readings and the factor).  A
 # figure only holds for the kernel it was taken with: it is reported while the digest of that kernel's
 # source files matches and as null - with both digests, so that the staleness is visible - afterwards.
 KERNEL_SOURCES = {
-    "sweep_count_kernel": ("device_model.hpp", "sweep_kernels.hpp"),
+    "static_sweep": ("device_model.hpp", "sweep_kernels.hpp"),
     "assign_static_kernel": ("device_model.hpp", "sweep_kernels.hpp", "lane_ops.hpp", "live_slots.hpp",
                              "assign_kernels.hpp"),
     "assign_window_kernel": ("device_model.hpp", "sweep_kernels.hpp", "lane_ops.hpp", "live_slots.hpp",
@@ -76,8 +77,8 @@ KERNEL_SOURCES = {
 }
 TRAFFIC = {
     # workload name: (kernel, bytes per launch, digest of the kernel's sources at measurement, summary)
-    "cfg4_skewed_stress": ("sweep_count_kernel", 3.0879e7, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg4.md"),
-    "cfg1_placer_sweep": ("sweep_count_kernel", 5.641e6, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg1.md"),
+    "cfg4_skewed_stress": ("static_sweep", 3.0879e7, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg4.md"),
+    "cfg1_placer_sweep": ("static_sweep", 5.641e6, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg1.md"),
     "streaming_i4": ("assign_static_kernel", 1.1410e9, "db880294941b8bee",
                      "profiles/assign_static_kernel_stream.md"),
 }
@@ -390,16 +391,19 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
         # pairs past the between-token check, and those of them on an instance without a wait
         pairs, pairs_nowait = binding.maaso_ctx_sweep_evaluated(dw.ctx, split=True)
         roofline = {
-            "kernel": "sweep_count_kernel", "bound": "hbm", "unit": "GB/s", "peak": HBM_PEAK_GBS,
+            "kernel": "sweep_count_kernel" if w.n_req <= 4096 else
+                      "sweep_hist_kernel + sweep_scatter_kernel + sweep_count_kernel",
+            "bound": "hbm", "unit": "GB/s", "peak": HBM_PEAK_GBS,
             "traffic": traffic, "kernel_ms": k_avg_s * 1e3, "launches_timed": k_n,
             "pairs_past_between_token_check": pairs, "pairs_without_wait": pairs_nowait,
             "valid_triples": triples_sweep,
             "settled_per_class_instance": triples_sweep - pairs,
             "kernel_triples_per_s": triples_sweep / k_avg_s,
         }
-        # the metric also asks for the fraction of the HBM roofline: each request record (9 B), each
-        # instance slot (15 B) and each candidate result (8 B) once per call, over the same kernel time
-        alg_bytes = 9 * w.n_req + 15 * w.n_cand * w.i_pad + 8 * w.n_cand
+        # the metric also asks for the fraction of the HBM roofline: what the static sweep needs of a
+        # request (prompt length and class, 5 B), each instance slot (15 B) and each candidate result
+        # (8 B) once per call, over the time of all its launches
+        alg_bytes = 5 * w.n_req + 15 * w.n_cand * w.i_pad + 8 * w.n_cand
         roofline["hbm"] = {
             "algorithmic_bytes": alg_bytes, "achieved_GBps": alg_bytes / k_avg_s / 1e9,
             "frac_of_peak": alg_bytes / k_avg_s / 1e9 / HBM_PEAK_GBS,

@@ -153,10 +153,11 @@ int maaso_ctx_device_status(maaso_ctx* ctx, uint32_t* bits);
 
 const char* maaso_strerror(int status);
 
-/* Performance knobs; they never change a result.  0 selects the library's own choice.
- *   sweep_requests_per_lane (0, 2, 4, 8, 16), sweep_group, sweep_blocks_per_queue: tiles, groups and
- *     blocks the static sweep's workspace is charged by (maaso_ctx_reserve, MAASO_E_WORKSPACE,
- *     MAASO_E_SHAPE of the no-allocation form); its launches are sized by the library alone;
+/* Launch shapes; they never change a result.  0 selects the library's own choice.
+ *   sweep_requests_per_lane (0, 2, 4, 8, 16), sweep_group, sweep_blocks_per_queue: no performance knobs any
+ *     more.  The static sweep's launches are sized by the library alone; these three are accepted, and
+ *     enter only what its workspace is charged with (maaso_ctx_reserve, MAASO_E_WORKSPACE, MAASO_E_SHAPE
+ *     of the no-allocation form), as they did when it was laid out by them;
  *   window_blocks: blocks of the windowed distributor's persistent kernel (at most one per compute
  *   unit is used).  Left at 0, windows of up to four requests are distributed by a single wavefront
  *   instead (no device-wide barrier per window); a value keeps the persistent kernel for them too.
@@ -179,8 +180,9 @@ int maaso_ctx_set_wait_limit(maaso_ctx* ctx, uint32_t polls);
 int maaso_ctx_set_cooperative(maaso_ctx* ctx, int enable);
 
 /* Instrumentation.  With timing enabled, each compute call records a pair of HIP events on its
- * stream directly around its dominant kernel (the sweep kernel of maaso_placement_sweep and of
- * maaso_placement_score, the scoring kernel of maaso_score_assign), for up to 256 calls.  maaso_ctx_kernel_elapsed waits for the
+ * stream directly around what does its work (all launches of the static maaso_placement_sweep, the
+ * sweep kernel of the windowed one and of maaso_placement_score, the scoring kernel of
+ * maaso_score_assign), for up to 256 calls.  maaso_ctx_kernel_elapsed waits for the
  * recorded events, returns the sum of the kernel durations in milliseconds and their number, and
  * starts a new series.  Enabling allocates the events once; no other call is affected.
  * Errors: INVALID_ARG, HIP. */

@@ -417,9 +417,10 @@ void add_sweep_window_set(SweepWindowArgs& a, const maaso_requests* rq, const ma
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace the static sweep of a shape is charged with: 4 bytes per (class, request), 16 per instance
-// slot, and per (request tile, XCD) queue 4 bytes and 16 per block that serves it, the tiles and blocks
-// as the launch-shape knobs or the rules here set them.  The grouped lengths it keeps (4 bytes per request)
-// take less; the charge is the boundary's, and what it refuses does not depend on how the sweep works.
+// slot, and per (request tile, XCD) queue 4 bytes and 16 per block that would serve it, by the launch-shape
+// knobs or the rules here.  The sweep has no such tiles, queues or records: it keeps 4 bytes per request.
+// The charge is part of the interface - which calls are refused, and what maaso_ctx_reserve reserves - and
+// stays what it was, so that a caller's reservations and refusals do not depend on how the sweep works.
 int static_sweep_bytes(const maaso_ctx* ctx, uint32_t C, uint32_t I, uint32_t R, size_t& bytes) {
   const uint32_t K = ctx->n_slo;
   uint32_t Q = ctx->sweep_q;
@@ -502,6 +503,7 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
          (uint64_t)C * R << (groups.shift + 1u) <= 1ull << 28)
     ++groups.shift;
   const uint32_t n_groups = groups.count();
+  TimedRegion timed(ctx, s);  // all launches of the call
   if (!small && !few) {
     GroupArgs g;
     g.prompt_len = rq->prompt_len;
@@ -562,21 +564,18 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   const uint32_t cap = (uint32_t)ctx->n_cu * 6u;  // 65,536 x 32 slots: 38 us with 6 blocks per compute unit, 43 with 4 or 8
   const dim3 grid(a.n_groups < cap ? a.n_groups : cap), block(kSweepThreads);
   const size_t lds = ((size_t)n_groups + 1u) * sizeof(uint32_t);
-  {
-    TimedRegion timed(ctx, s);
-    if (few) {
-      const uint32_t tiles = (R + 1023u) / 1024u;  // four requests a thread
-      hipLaunchKernelGGL(sweep_few_kernel, dim3(std::min(tiles, (uint32_t)ctx->n_cu * 4u)), block, 0, s, a);
-    } else if (small) {
-      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<true, true, false>), grid, block, lds, s, a);
-      else hipLaunchKernelGGL((sweep_count_kernel<true, false, false>), grid, block, lds, s, a);
-    } else if (groups.shift == 0u) {
-      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true, true>), grid, block, lds, s, a);
-      else hipLaunchKernelGGL((sweep_count_kernel<false, false, true>), grid, block, lds, s, a);
-    } else {
-      if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true, false>), grid, block, lds, s, a);
-      else hipLaunchKernelGGL((sweep_count_kernel<false, false, false>), grid, block, lds, s, a);
-    }
+  if (few) {
+    const uint32_t tiles = (R + 1023u) / 1024u;  // four requests a thread
+    hipLaunchKernelGGL(sweep_few_kernel, dim3(std::min(tiles, (uint32_t)ctx->n_cu * 4u)), block, 0, s, a);
+  } else if (small) {
+    if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<true, true, false>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((sweep_count_kernel<true, false, false>), grid, block, lds, s, a);
+  } else if (groups.shift == 0u) {
+    if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true, true>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((sweep_count_kernel<false, false, true>), grid, block, lds, s, a);
+  } else {
+    if (I % 16u == 0u) hipLaunchKernelGGL((sweep_count_kernel<false, true, false>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((sweep_count_kernel<false, false, false>), grid, block, lds, s, a);
   }
   ctx->last_evaluated = a.eval_total;
   if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
@@ -935,7 +934,7 @@ int placement_sweep_impl(maaso_ctx* ctx, const maaso_placements* pl, const maaso
   const uint32_t C = pl->n_cand, I = pl->i_pad, R = rq->n_req;
 
   if (prm->window != 0u && R != 0) {
-    // Capacity-aware form: one block per candidate walks the request windows on its own state copy.
+    // Capacity-aware form: a wavefront, or a block, walks a candidate through the request windows on its own state copy.
     SweepWindowArgs a;
     fill_sweep_window_args(a, ctx, pl, prm);
     add_sweep_window_set(a, rq, prm, sat_count, nullptr);
