@@ -77,9 +77,9 @@ KERNEL_SOURCES = {
 }
 TRAFFIC = {
     # workload name: (kernel, bytes per launch, digest of the kernel's sources at measurement, summary)
-    "cfg4_skewed_stress": ("static_sweep", 3.0879e7, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg4.md"),
-    "cfg1_placer_sweep": ("static_sweep", 5.641e6, "4a4d88dd875e78ec", "profiles/sweep_kernel_cfg1.md"),
-    "streaming_i4": ("assign_static_kernel", 1.1410e9, "db880294941b8bee",
+    "cfg4_skewed_stress": ("static_sweep", 2.0109e7, "5a5b7d6bc1c6fb0c", "profiles/sweep_kernel_cfg4.md"),
+    "cfg1_placer_sweep": ("static_sweep", 3.521e6, "5a5b7d6bc1c6fb0c", "profiles/sweep_kernel_cfg1.md"),
+    "streaming_i4": ("assign_static_kernel", 1.1410e9, "96006bed354a9fe9",
                      "profiles/assign_static_kernel_stream.md"),
 }
 

@@ -13,9 +13,9 @@
 // changed: for the row of slots that admitted a request, or for all of them in the rare window at whose
 // end a request completes.  What every window needs is the queued prefill (one conversion, one fma per
 // slot) and the comparison that shows that nothing completes (no division).  8192 candidates of 128
-// instances, 8192 requests one by one: 23.4 -> 9.6 ms, bound by issue (some 110 instructions a request
-// where 330 were); one placement of 64 instances: 0.56 -> 0.36 us per request, the chain of one request
-// after the other in a single wavefront, four to five cycles an instruction.
+// instances, 8192 requests one by one: 23.4 -> 9.6 ms, bound by issue (89 vector and 46 scalar instructions
+// a request, all told); one placement of 64 instances: 0.56 -> 0.36 us per request, the chain of one request
+// after the other in a single wavefront (49 vector and 31 scalar instructions, eleven cycles each on average).
 //
 // The arithmetic is the windowed kernel's, operation by operation, so the two agree bit for bit and
 // with the oracle's windowed distributor.  The shortest-queue rule is not offered here (its ranks

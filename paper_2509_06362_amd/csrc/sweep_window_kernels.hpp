@@ -6,7 +6,8 @@
 // and walks the windows by itself: no device-wide barrier.  Its lanes hold the instances (state, profile
 // evaluation, the drain between windows); per window it works out which instances a request can be
 // admitted to at all (find_admissible: 1 to 4 in nineteen windows of twenty) and scores the requests,
-// lanes = requests, against those alone.
+// lanes = requests, against those alone.  (Few candidates and windows of up to a few hundred requests have a
+// form of their own, sweep_block_kernels.hpp, and windows of a few requests another, sweep_seq_kernels.hpp.)
 //
 // What a window's admitted requests add up to is kept in registers where a few instances are left, and in
 // LDS where more are: an addition per request unless a whole wavefront chose one instance, then every lane
@@ -14,9 +15,10 @@
 // windows of 256: 11.7 -> 9.4 us a window; every instance scored: 10.8).
 //
 // What bounds it: vector issue at windows of thousands (8192 candidates x 131,072 requests x 128
-// instances, windows of 4096: 26.8 ms with every instance scored, 1.83 ms now), the chain of one window
-// after the other at short ones (Alg. 2, 720 deployments x three sets, windows of 256: 2.6 -> 1.24 ms,
-// 2.4 us per window of the longest chain).
+// instances, windows of 4096: 26.8 ms with every instance scored, 1.83 ms now; 238 vector and 90 scalar
+// instructions per wavefront and 256 requests), the chain of one window after the other at short ones
+// (Alg. 2, 720 deployments x three sets, windows of 256: 2.6 -> 1.24 ms, 2.4 us per window of the longest
+// chain; 214 vector and 155 scalar instructions per window).
 #pragma once
 
 #include "assign_kernels.hpp"

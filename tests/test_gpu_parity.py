@@ -45,7 +45,8 @@ def oracle_counts(w, cands, window=0, threads=8):
 
 def check_sweep(w, shapes=((0, 0, 0),), sampled=None, threshold=False):
     """GPU sweep vs the triple oracle (all candidates, or `sampled` ones) and optionally vs the
-    threshold-count route on all candidates."""
+    threshold-count route on all candidates.  `shapes`: settings of the sweep's three shape knobs, which
+    set what its workspace is charged with and must change nothing else."""
     dw = binding.DeviceWorkload(w)
     try:
         ref = None
@@ -1120,7 +1121,7 @@ def test_assign_static_unaligned_arrays_take_the_scalar_path():
 ])
 def test_sweep_with_fresh_and_loaded_instances_mixed(seed, n_cand, i_pad, n_req, fresh_share):
     """Instances without a queue wait and instances with one inside the same candidates, in every
-    proportion and with odd and even numbers of each: the sweep walks them in two loops."""
+    proportion and with odd and even numbers of each."""
     base = W.stressed(W.random_small(seed, n_cand, i_pad, n_req, n_slo=3, pen_kappa=0.5), seed=seed,
                       deadline_scale=0.04)   # tight: a fresh instance serves short prompts only
     rng = np.random.default_rng(seed)
