@@ -10,6 +10,11 @@ __device__ __forceinline__ float lane_value(float v, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
 
+// `old` with lane l (uniform) holding v (uniform): v_writelane, for which there is no builtin.
+__device__ int maaso_writelane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ int with_lane(int old, int l, int v) { return maaso_writelane(v, l, old); }
+__device__ __forceinline__ int with_lane(int old, int l, float v) { return with_lane(old, l, __builtin_bit_cast(int, v)); }
+
 // At the head of a branch that is hardly ever taken: keeps the compiler from working out both sides of
 // it and selecting.
 __device__ __forceinline__ void rare_path() { asm volatile(""); }

@@ -43,16 +43,18 @@ struct LiveSlot {
   }
 
   // stage_instance on the live state, up to the queued prefill: {a, p, tbt}, the expected service time and
-  // the wait for a slot past the batch cap.  `tab`: the three tables, `stride` entries each.  A slot
+  // the wait for a slot past the batch cap.  `tab`: the three tables, entry i of table k at i * kStep + k *
+  // stride.  A slot
   // outside the tables gets a record that is never chosen (an infinite wait) and drains with a service
   // time of one second; `bad` has its lane's bit.
+  template <uint32_t kStep = 1u>
   __device__ __forceinline__ void evaluate(const float* tab, uint32_t stride, const ModelParams& mp, SlotRecord& r,
                                            float& svc, float& past, unsigned long long& bad) const {
     bad = lane_mask(!configured | (occ < 0));
     const uint32_t arriving = (uint32_t)occ + 1u;
     uint32_t w = mp.tbt_mode == 1u ? B : min(arriving, B);
     if (bad != 0ull) w = in_mask(bad) ? 1u : w;
-    const uint32_t row = row0 + w;
+    const uint32_t row = kStep == 1u ? row0 + w : (row0 + w) * kStep;
     r.a = tab[row];
     r.p = tab[stride + row];
     r.tbt = tab[2u * stride + row];

@@ -339,12 +339,13 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
   bool one_by_one = !kSQ;
   for (uint32_t k = 0; k < a.n_sets; ++k) one_by_one = one_by_one && a.sets[k].window <= short_window;
   if (one_by_one) {
-    const dim3 g((a.n_cand + kSeqThreads / 64 - 1) / (kSeqThreads / 64) * a.n_sets);
-    const size_t lds_seq = lds + 3u * sizeof(float);  // one more row: slots without an instance
+    const uint32_t per_block = blocks > kSeqSpread && a.i_pad <= 128u ? kSeqThreads / 64 : 4u;  // wavefronts
+    const dim3 g((a.n_cand + per_block - 1u) / per_block * a.n_sets);
+    const size_t lds_seq = ((size_t)a.cells + 1u) * sizeof(float4);  // one more row: slots without an instance
     bool one = true;  // every set request by request
     for (uint32_t k = 0; k < a.n_sets; ++k) one = one && a.sets[k].window == 1u;
     if (!kSQ) {
-      const dim3 b(kSeqThreads);
+      const dim3 b(per_block * 64u);
       if (a.i_pad <= 64u) {
         if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1, true>), g, b, lds_seq, s, a);
         else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1>), g, b, lds_seq, s, a);
@@ -1319,7 +1320,7 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   // asks for the persistent kernel below whatever the window.
   const uint32_t short_window = pl->i_pad <= 128u ? 4u : 2u;
   if (prm->policy == 0u && prm->window <= short_window && ctx->window_blocks == 0u) {
-    const size_t lds = (size_t)3 * (ctx->cells + 1u) * sizeof(float);
+    const size_t lds = ((size_t)ctx->cells + 1u) * sizeof(float4);
     TimedRegion timed(ctx, s);
     if (pl->i_pad <= 64u) {
       if (lat) hipLaunchKernelGGL((assign_seq_kernel<true, 1>), dim3(1), dim3(64), lds, s, a, prm->window);

@@ -10,12 +10,17 @@
 // wavefront.  Requests come prepared (deadlines, the reciprocal of the end-to-end one) through LDS.
 //
 // An instance's profile evaluation depends on the requests on it alone, so it is redone only where they
-// changed: for the row of slots that admitted a request, or for all of them in the rare window at whose
-// end a request completes.  What every window needs is the queued prefill (one conversion, one fma per
-// slot) and the comparison that shows that nothing completes (no division).  8192 candidates of 128
-// instances, 8192 requests one by one: 23.4 -> 9.6 ms, bound by issue (89 vector and 46 scalar instructions
-// a request, all told); one placement of 64 instances: 0.56 -> 0.36 us per request, the chain of one request
-// after the other in a single wavefront (49 vector and 31 scalar instructions, eleven cycles each on average).
+// changed.  What every window needs is the queued prefill (one conversion, one fma per slot) and one
+// comparison that shows that nothing completes (no division).
+//
+// What bounds it: vector issue, with eight wavefronts per SIMD.  Measured there, cycles per wavefront
+// instruction: fma, add, sub, mul, mov, 32-bit add and saturating sub 2.3; all others - compare, convert,
+// min, DPP, lane reads and writes, anything with a scalar operand - 4.2, scalar instructions about 2 beside them.  So the
+// rules of NarrowSequence leave out conversions and compares first.  8192 candidates of 128 instances, 8192
+// requests one by one: 23.4 -> 9.7 ms with the profile evaluated where occupancy changed -> 6.3 ms with 32-bit queues
+// throughout, one lane evaluated per admission and the completion check on the scalar unit; 6000 x 60
+// slots, windows of 3: 338 -> 289 us; 9000 x 128, of 16: 388 -> 304 us.  Reading the next request ahead of its turn
+// costs its registers' moves: 8 candidates 446 -> 429 us, 16,384 902 -> 1013 us; not taken.
 //
 // The arithmetic is the windowed kernel's, operation by operation, so the two agree bit for bit and
 // with the oracle's windowed distributor.  The shortest-queue rule is not offered here (its ranks
@@ -30,16 +35,59 @@
 
 namespace maaso {
 
-constexpr int kSeqThreads = 256;  // four wavefronts = four candidates of a request set per block
+constexpr int kSeqThreads = 512;    // up to eight wavefronts = candidates of a request set per block
+constexpr uint32_t kSeqSpread = 1024;  // up to so many candidates a block takes four: they spread over the chip
 constexpr uint32_t kSeqChunk = 64;  // requests prepared at a time, by one of the block's wavefronts in turn
 
-// The three profile tables in LDS with one entry more each: the row of a slot without an instance, whose
-// prefill time is infinite.
-__device__ __forceinline__ void load_seq_tables(float* tab, const float* src, uint32_t cells) {
-  for (uint32_t i = threadIdx.x; i < 3u * (cells + 1u); i += blockDim.x) {
-    const uint32_t t = i / (cells + 1u), k = i - t * (cells + 1u);
-    tab[i] = k < cells ? src[t * cells + k] : (t == 0u ? INFINITY : 1.0f);
+// The three profile tables in LDS, a row {a, p, tbt, row_safe_ticks} per entry, and one row more: that of a
+// slot without an instance, whose prefill time is infinite and where nothing ever completes.
+__device__ __forceinline__ void load_seq_rows(float4* rows, const float* src, uint32_t cells, const ModelParams& mp,
+                                              uint32_t window) {
+  for (uint32_t i = threadIdx.x; i <= cells; i += blockDim.x) {
+    float4 r = make_float4(INFINITY, 1.0f, 1.0f, __uint_as_float(0xffffffffu));
+    if (i < cells) {
+      const float tbt = src[2u * cells + i];
+      r = make_float4(src[i], src[cells + i], tbt,
+                      __uint_as_float(row_safe_ticks(mp.s_bar, tbt, i % (mp.b_cap + 1u), window)));
+    }
+    rows[i] = r;
   }
+}
+
+// The request scored against every slot of the lane, and the largest slack over all instances, uniform: four DPP
+// steps settle each row of 16 lanes, two row broadcasts carry the rows' maxima into lane 63, one v_readlane
+// fetches it.
+template <int S>
+__device__ __forceinline__ float score_slots(const RequestSide& q, const SlotRecord (&rec)[S], float (&pre)[S],
+                                             float (&slack)[S], float (&ttft)[S], float (&e2e)[S]) {
+  const Deadlines d{q.u.y, q.u.z, q.w.z, q.w.x, q.w.y, q.w.w};
+  float m = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const Margins g = score_triple(rec[s].a, rec[s].p, rec[s].tbt, rec[s].wait, q.u.x, q.u.w, d);
+    pre[s] = g.pre;
+    slack[s] = g.slack;
+    ttft[s] = g.ttft;
+    e2e[s] = g.e2e;
+    m = s == 0 ? g.slack : max_no_nan(m, g.slack);
+  }
+  m = max_lanes<16>(m);
+  MAASO_DPP_FOLD_ROWS("v_max_f32_dpp", m, "row_bcast:15", "0xa");
+  MAASO_DPP_FOLD_ROWS("v_max_f32_dpp", m, "row_bcast:31", "0xc");
+  return lane_value(m, 63);
+}
+
+// The lowest index among the instances whose slack is `best` (above -inf): the first row of slots with a
+// holder, its first lane, from one lane mask per row on the scalar unit.
+template <int S>
+__device__ __forceinline__ uint32_t holder_of(const float (&slack)[S], float best) {
+  uint32_t j = 0;
+#pragma unroll
+  for (int s = S - 1; s >= 0; --s) {
+    const unsigned long long held = lane_mask(slack[s] == best);
+    if (held != 0ull) j = (uint32_t)s * 64u + (uint32_t)__builtin_ctzll(held);
+  }
+  return j;
 }
 
 // A placement in the lanes of one wavefront, taken through windows of requests.
@@ -63,22 +111,22 @@ struct Sequence {
       slot[s].row0 = cells - 1u;
     }
   }
-  __device__ __forceinline__ void evaluate(int s, const float* tab, uint32_t cells, const ModelParams& mp) {
+  __device__ __forceinline__ void evaluate(int s, const float4* rows, const ModelParams& mp) {
     unsigned long long b;
-    slot[s].evaluate(tab, cells + 1u, mp, rec[s], svc[s], past[s], b);
+    slot[s].template evaluate<4u>(reinterpret_cast<const float*>(rows), 1u, mp, rec[s], svc[s], past[s], b);
     if (b != 0ull) {  // (see close_window: a slot with a negative occupancy compares with no number)
       rare_path();
       if (slot[s].occ < 0) svc[s] = __builtin_nanf("");
       bad |= b;
     }
   }
-  __device__ __forceinline__ void begin(const float* tab, uint32_t cells, const ModelParams& mp) {
+  __device__ __forceinline__ void begin(const float4* rows, const ModelParams& mp) {
     bad = 0ull;
     dirty = 0u;
     wide = false;  // (an admission cannot make it true where narrow_queue holds)
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      evaluate(s, tab, cells, mp);
+      evaluate(s, rows, mp);
       wide |= slot[s].any_wide();
     }
   }
@@ -86,51 +134,21 @@ struct Sequence {
 #pragma unroll
     for (int s = 0; s < S; ++s) rec[s].wait = slot[s].wait_with(past[s], wide);
   }
-  // Largest slack of the request over all instances, uniform: four DPP steps settle each row of 16 lanes,
-  // two row broadcasts carry the rows' maxima into lane 63, one v_readlane fetches it.
-  __device__ __forceinline__ float score(const RequestSide& q) {
-    const Deadlines d{q.u.y, q.u.z, q.w.z, q.w.x, q.w.y, q.w.w};
-    float m = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const Margins g = score_triple(rec[s].a, rec[s].p, rec[s].tbt, rec[s].wait, q.u.x, q.u.w, d);
-      pre[s] = g.pre;
-      slack[s] = g.slack;
-      ttft[s] = g.ttft;
-      e2e[s] = g.e2e;
-      m = s == 0 ? g.slack : max_no_nan(m, g.slack);
-    }
-    m = max_lanes<16>(m);
-    MAASO_DPP_FOLD_ROWS("v_max_f32_dpp", m, "row_bcast:15", "0xa");
-    MAASO_DPP_FOLD_ROWS("v_max_f32_dpp", m, "row_bcast:31", "0xc");
-    return lane_value(m, 63);
-  }
-  // The lowest index among the instances whose slack is `best` (above -inf): the first row of slots with a
-  // holder, its first lane, from one lane mask per row on the scalar unit.
-  __device__ __forceinline__ uint32_t holder(float best) const {
-    uint32_t j = 0;
-#pragma unroll
-    for (int s = S - 1; s >= 0; --s) {
-      const unsigned long long held = lane_mask(slack[s] == best);
-      if (held != 0ull) j = (uint32_t)s * 64u + (uint32_t)__builtin_ctzll(held);
-    }
-    return j;
-  }
   // The request scored last is admitted to instance j = (s, l): it loads it at the window's end.
-  __device__ __forceinline__ void admit(int s, uint32_t l, uint32_t lane, const bool narrow) {
-    const bool me = l == lane;
-    const unsigned long long t = to_ticks(pre[s], narrow);
+  __device__ __forceinline__ int32_t occupancy(int s) const { return slot[s].occ; }
+  __device__ __forceinline__ uint64_t queue(int s) const { return slot[s].q; }
+  template <bool kOne>
+  __device__ __forceinline__ void admit(int s, uint32_t l, const float4*, const ModelParams&) {
+    const bool me = in_mask(1ull << l);
+    const unsigned long long t = to_ticks(pre[s], false);
     slot[s].occ += me ? 1 : 0;
     slot[s].q += me ? t : 0ull;
-    if (!narrow) {
-      rare_path();
-      wide |= slot[s].any_wide();
-    }
+    wide |= slot[s].any_wide();
     dirty |= 1u << s;
   }
   // `delta` ticks pass (`last`: nothing follows, no time passes).
-  __device__ __forceinline__ void close_window(uint32_t delta, bool last, const float* tab, uint32_t cells,
-                                               const ModelParams& mp) {
+  template <bool kOne>
+  __device__ __forceinline__ void close_window(uint32_t delta, uint32_t, bool last, const float4* rows, const ModelParams& mp) {
     if (!last) {
       const float dt = (float)delta * 0x1p-20f;
       float served[S];
@@ -160,119 +178,314 @@ struct Sequence {
     if (dirty != 0u) {
 #pragma unroll
       for (int s = 0; s < S; ++s)
-        if (dirty & (1u << s)) evaluate(s, tab, cells, mp);
+        if (dirty & (1u << s)) evaluate(s, rows, mp);
       dirty = 0u;
     }
   }
 };
 
-// kOne: every set's window is one request (the window length is then a constant).
-template <bool kScore, int S, bool kOne = false>
-__global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : 4) void sweep_seq_kernel(const SweepWindowArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  float* tab = reinterpret_cast<float*>(smem);
-  __shared__ ClassRow cls[kMaxSlo];
-  __shared__ float4 chunk_u[2][kSeqChunk], chunk_w[2][kSeqChunk];  // RequestSide
-  __shared__ uint32_t chunk_t[2][kSeqChunk];                       // arrival of the request behind it
+// The same placement where nothing needs 64 bits and every slot is inside the tables: the usual case, for which a
+// request costs some three fifths of what it costs above.  Queues are 32 bits.  What follows from an
+// instance's occupancy is evaluated for the one lane that admitted a request.  Whether a request completes
+// at a window's end is one comparison per row of slots with a number of ticks in which none can
+// (row_safe_ticks), with windows of one request a single scalar one with the least of them, kept as instances
+// fill up.
+template <int S>
+struct NarrowSequence {
+  uint32_t row0[S];        // byte offset of its strategy's first row
+  uint32_t B[S];           // batch cap
+  float invB[S];
+  uint32_t arr[S];         // requests on it, an arriving one included
+  uint32_t q[S];
+  SlotRecord rec[S];       // as evaluated when the window opened
+  float past[S];
+  uint32_t safe[S];
+  float pre[S], slack[S];  // of the request scored last
+  float ttft[S], e2e[S];
+  unsigned long long changed[S];  // lanes that admitted a request in this window
+  uint32_t safe_all, safe_next;   // windows of one request: the least of all, now and once the window has closed
 
-  const uint32_t tid = threadIdx.x;
-  const uint32_t lane = tid & 63u;
-  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-  if (tid < a.n_slo) cls[tid] = ClassRow{a.d_ttft[tid], a.d_tbt[tid], a.i_ttft[tid], a.i_tbt[tid]};
-  load_seq_tables(tab, a.tab, a.cells);
-  __syncthreads();
-
-  constexpr uint32_t kPerBlock = kSeqThreads / 64;
-  const uint32_t blocks_per_set = (a.n_cand + kPerBlock - 1u) / kPerBlock;
-  const uint32_t set = blockIdx.x / blocks_per_set;
-  const uint32_t c = (blockIdx.x - set * blocks_per_set) * kPerBlock + wave;
-  const bool mine_c = c < a.n_cand;  // a block's last wavefronts may have no candidate: they only prepare
-  const SweepWindowSet rs = resolve_set(a.sets[set]);
-  const size_t base = (size_t)c * a.i_pad;
-  const uint32_t n = mine_c ? min(a.n_inst[c], a.i_pad) : 0u;
-
-  Sequence<S> sq;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const uint32_t j = (uint32_t)s * 64u + lane;
-    uint32_t tp = 0, B = 1;
-    int32_t occ = 0;
-    uint64_t q = 0;
-    if (j < n) { tp = a.tp_idx[base + j]; B = a.max_batch[base + j]; occ = a.occ[base + j]; q = a.q_ticks[base + j]; }
-    sq.load(s, j < n, a.mp, a.cells, tp, B, occ, q);
+  // Whether a slot may be kept this way (`extra`: requests of the run).
+  __device__ __forceinline__ static bool fits(const ModelParams& mp, uint32_t tp, uint32_t b, int32_t occ, uint64_t q,
+                                              uint32_t extra) {
+    return tp < mp.n_tp && b != 0u && b <= mp.b_cap && occ >= 0 && occ < (1 << 30) && extra < (1u << 30) && (q >> 32) == 0ull;
   }
-  sq.begin(tab, a.cells, a.mp);
-  unsigned long long served[S];
-  float inv_tbt_first[S];
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    served[s] = 0ull;
-    inv_tbt_first[s] = kScore ? (in_mask(sq.bad) && sq.past[s] == INFINITY ? 0.0f : 1.0f / sq.rec[s].tbt) : 0.0f;
+  __device__ __forceinline__ void load(int s, bool present, const ModelParams& mp, uint32_t cells, uint32_t tp,
+                                       uint32_t b, int32_t o, uint64_t ticks) {
+    row0[s] = 16u * (present ? tp * (mp.b_cap + 1u) : cells - 1u);  // (an empty slot: on the extra row for good)
+    B[s] = present ? b : 1u;
+    invB[s] = 1.0f / (float)B[s];
+    arr[s] = present ? (uint32_t)o + 1u : 1u;
+    q[s] = present ? (uint32_t)ticks : 0u;
+    changed[s] = 0ull;
   }
-  uint32_t sat = 0;                    // uniform
-  unsigned long long wait_sum = 0ull;  // queue waits of the admitted requests, in ticks; uniform
+  __device__ __forceinline__ void evaluate(int s, const float4* rows, const ModelParams& mp) {
+    const uint32_t w = min(arr[s] | (0u - mp.tbt_mode), B[s]);  // (worst-case latencies: any number, so the cap)
+    const float4 r = *reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(rows) + (row0[s] + (w << 4)));
+    rec[s].a = r.x;
+    rec[s].p = r.y;
+    rec[s].tbt = r.z;
+    safe[s] = __float_as_uint(r.w);
+    if (mp.pen_kappa != 0.0f) {  // a factor of exactly one without a penalty
+      rare_path();
+      const float over = (float)__builtin_elementwise_sub_sat(4u * w, 3u * B[s]);  // > 0 iff the batch is > 75 % full
+      rec[s].tbt = rec[s].tbt * fmaf(mp.pen_kappa, over * invB[s], 1.0f);
+    }
+    const float ov = (float)__builtin_elementwise_sub_sat(arr[s], B[s]);  // requests beyond the batch cap
+    past[s] = (ov * invB[s]) * (mp.s_bar * rec[s].tbt);
+  }
+  // All rows, and the least of the ticks in which nothing completes.
+  __device__ __forceinline__ void begin(const float4* rows, const ModelParams& mp) {
+    uint32_t least = 0xffffffffu;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      evaluate(s, rows, mp);
+      least = min(least, safe[s]);
+    }
+    safe_all = safe_next = (uint32_t)__builtin_amdgcn_readfirstlane((int)min_lanes<64>(least));
+  }
+  __device__ __forceinline__ void open_window() {
+#pragma unroll
+    for (int s = 0; s < S; ++s) rec[s].wait = fmaf((float)q[s], 0x1p-20f, past[s]);
+  }
+  __device__ __forceinline__ int32_t occupancy(int s) const { return (int32_t)(arr[s] - 1u); }
+  __device__ __forceinline__ uint64_t queue(int s) const { return q[s]; }
+  // The request scored last is admitted to instance (s, l).  With windows of one request the instance is
+  // evaluated for the next one right away.
+  template <bool kOne>
+  __device__ __forceinline__ void admit(int s, uint32_t l, const float4* rows, const ModelParams& mp) {
+    changed[s] |= 1ull << l;
+    if (in_mask(1ull << l)) {
+      q[s] += (uint32_t)rintf(pre[s] * 1048576.0f);
+      arr[s] += 1u;
+      if (kOne) evaluate(s, rows, mp);
+    }
+    if (kOne) safe_next = min(safe_next, (uint32_t)__builtin_amdgcn_readlane((int)safe[s], (int)l));
+  }
+  // Requests complete, or may: the whole rule, against the service times that the window opened with.
+  template <bool kOne>
+  __device__ __forceinline__ void complete(uint32_t delta, const float4* rows, const ModelParams& mp) {
+    const float dt = (float)delta * 0x1p-20f;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if (kOne) {  // the admitting lane is a request ahead
+        const uint32_t one = in_mask(changed[s]) ? 1u : 0u;
+        arr[s] -= one;
+        evaluate(s, rows, mp);
+        arr[s] += one;
+      }
+      const int32_t occ = (int32_t)(arr[s] - 1u);
+      const float x = ((float)min(occ, (int32_t)B[s]) * dt) / (mp.s_bar * rec[s].tbt);
+      arr[s] -= (uint32_t)min(occ, (int32_t)floorf(fminf(x, 2147483520.0f)));
+      changed[s] = 0ull;
+    }
+    begin(rows, mp);
+  }
+  // `delta` ticks pass, none behind the last window; `at_most`: uniform, no fewer than those.
+  template <bool kOne>
+  __device__ __forceinline__ void close_window(uint32_t delta, uint32_t at_most, bool, const float4* rows, const ModelParams& mp) {
+    if (kOne) {
+#pragma unroll
+      for (int s = 0; s < S; ++s) q[s] = __builtin_elementwise_sub_sat(q[s], delta);
+      if (at_most >= safe_all && (uint32_t)__builtin_amdgcn_readfirstlane((int)delta) >= safe_all) {
+        rare_path();
+        complete<kOne>(delta, rows, mp);
+      } else {
+#pragma unroll
+        for (int s = 0; s < S; ++s) changed[s] = 0ull;
+        safe_all = safe_next;
+      }
+    } else {
+      unsigned long long some = 0ull;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        some |= lane_mask(delta >= safe[s]);
+        q[s] = __builtin_elementwise_sub_sat(q[s], delta);
+      }
+      if (some != 0ull) {
+        rare_path();
+        complete<kOne>(delta, rows, mp);
+      } else {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (changed[s] != 0ull) {
+            rare_path();
+            if (in_mask(changed[s])) evaluate(s, rows, mp);
+            changed[s] = 0ull;
+          }
+      }
+    }
+  }
+};
 
+// What a block's wavefronts share while they walk through a request set: two chunks of requests, and with windows
+// of one request the time behind each, else its arrival.
+struct SeqChunks {
+  float4 u[2][kSeqChunk], w[2][kSeqChunk];  // RequestSide
+  uint32_t t[2][kSeqChunk];
+  uint32_t t_max[2];  // kOne: the longest of a chunk's times
+};
+
+// One candidate through the windows of a request set.  served: per row of slots, the lanes that admitted a
+// request.  Every wavefront of the block calls it for the same set: they prepare the chunks in turn.
+// kOne: the window is one request (a constant).
+template <bool kScore, int S, bool kOne, class Seq>
+__device__ __forceinline__ void walk_windows(const SweepWindowArgs& a, const SweepWindowSet& rs, Seq& sq,
+                                             const float4* rows, const ClassRow* cls, SeqChunks& chunks, uint32_t lane,
+                                             uint32_t wave, uint32_t n_waves, unsigned long long (&served)[S],
+                                             uint32_t& sat, unsigned long long& wait_sum) {
   const uint32_t R = rs.n_req;
   const uint32_t W = kOne ? 1u : rs.window;
-  // Chunk k is prepared by wavefront k mod 4 from what it asked for four chunks earlier.
-  uint32_t f0 = wave * kSeqChunk;
+  // Chunk k is prepared by wavefront k mod n_waves from what it asked for n_waves chunks earlier.
+  uint32_t f0 = wave * kSeqChunk, turn = wave;
   RequestRaw raw{0u, 0u, kNoRequest};
-  uint32_t behind = 0;
+  uint32_t own = 0, behind = 0;
   auto fetch = [&]() __attribute__((always_inline)) {
     if (f0 >= R) return;
     raw = fetch_request(rs, f0, lane, R);
-    if (reads_arrival_behind(f0 + lane, R, W)) behind = rs.arrival_ticks[f0 + lane + 1u];
-    f0 = R - f0 > 4u * kSeqChunk ? f0 + 4u * kSeqChunk : R;
+    own = behind = 0u;
+    if (reads_arrival_behind(f0 + lane, R, W)) {
+      behind = rs.arrival_ticks[f0 + lane + 1u];
+      if (kOne) own = rs.arrival_ticks[f0 + lane];
+    }
+    f0 = R - f0 > n_waves * kSeqChunk ? f0 + n_waves * kSeqChunk : R;
   };
   auto prepare = [&](uint32_t to) __attribute__((always_inline)) {
     const RequestSide q = request_side(raw, a.n_slo, cls, a.status);
-    chunk_u[to][lane] = q.u;
-    chunk_w[to][lane] = q.w;
-    chunk_t[to][lane] = behind;
+    chunks.u[to][lane] = q.u;
+    chunks.w[to][lane] = q.w;
+    chunks.t[to][lane] = kOne ? behind - own : behind;
+    if (kOne) {
+      const uint32_t top = ~min_lanes<64>(~(behind - own));
+      if (lane == 0u) chunks.t_max[to] = top;
+    }
     fetch();
   };
   fetch();
   if (wave == 0u) prepare(0u);
   __syncthreads();
 
-  uint32_t t_open = R > W ? rs.arrival_ticks[0] : 0u;
+  uint32_t t_open = !kOne && R > W ? rs.arrival_ticks[0] : 0u;
   uint32_t in_window = 0;
-  for (uint32_t c0 = 0, k = 0; c0 < R; ++k) {
+  for (uint32_t c0 = 0, buf = 0; c0 < R; buf ^= 1u) {
     const uint32_t len = min(R - c0, kSeqChunk);
-    const uint32_t buf = k & 1u;
-    if (((k + 1u) & 3u) == wave && R - c0 > kSeqChunk) prepare(buf ^ 1u);
-    for (uint32_t i = 0; i < len; ++i) {
-      if (kOne || in_window == 0u) sq.open_window();
-      const RequestSide q{chunk_u[buf][i], chunk_w[buf][i]};
-      const float best = sq.score(q);
-      if (best >= 0.0f) {  // admitted
-        const uint32_t j = sq.holder(best), l = j & 63u;
-        sat += 1u;
+    turn = turn == 0u ? n_waves - 1u : turn - 1u;  // how many chunks until this wavefront's turn
+    if (turn == 0u && R - c0 > kSeqChunk) prepare(buf ^ 1u);
+    const uint32_t at_most = kOne ? (uint32_t)__builtin_amdgcn_readfirstlane((int)chunks.t_max[buf]) : 0xffffffffu;
+    unsigned long long admitted = 0ull;  // requests of the chunk, and (lane i) the wait of request i
+    int waits = 0;
+    unsigned long long bit = 1ull;
+    auto one_request = [&](const RequestSide& q, uint32_t i) __attribute__((always_inline)) {
+      const float best = score_slots<S>(q, sq.rec, sq.pre, sq.slack, sq.ttft, sq.e2e);
+      // (a slack is no number or minus zero under no input: its between-token margin is a number, and a
+      // difference from a deadline is +0 or far above the underflow)
+      if (__builtin_bit_cast(int, best) >= 0) {
+        const uint32_t j = holder_of<S>(sq.slack, best), l = j & 63u;
+        admitted |= bit;
 #pragma unroll
         for (int s = 0; s < S; ++s)
           if (j >> 6 == (uint32_t)s) {
             rare_path();  // (a branch per row of slots, not selects over all of them)
             if (kScore) {
               served[s] |= 1ull << l;
-              wait_sum += to_ticks(lane_value(sq.rec[s].wait, (int)l), a.bounds.narrow);
+              waits = with_lane(waits, (int)i, lane_value(sq.rec[s].wait, (int)l));
             }
-            sq.admit(s, l, lane, a.bounds.narrow_queue);
+            sq.template admit<kOne>(s, l, rows, a.mp);
           }
       }
-      const bool last = c0 + i + 1u == R;
-      if (kOne || ++in_window == W || last) {
-        const uint32_t t_end = chunk_t[buf][i];
-        sq.close_window(t_end - t_open, last, tab, a.cells, a.mp);
-        t_open = t_end;
-        in_window = 0u;
+      bit <<= 1;
+    };
+    if (kOne) {
+      for (uint32_t i = 0; i < len; ++i) {
+        const uint32_t passed = chunks.t[buf][i];
+        sq.open_window();
+        one_request(RequestSide{chunks.u[buf][i], chunks.w[buf][i]}, i);
+        sq.template close_window<true>(passed, at_most, c0 + i + 1u == R, rows, a.mp);
+      }
+    } else {
+      for (uint32_t i = 0; i < len;) {
+        if (in_window == 0u) sq.open_window();
+        const uint32_t stop = min(len, i + (W - in_window));  // of the window's requests in this chunk
+        in_window += stop - i;
+        do one_request(RequestSide{chunks.u[buf][i], chunks.w[buf][i]}, i);
+        while (++i < stop);
+        const bool last = c0 + stop == R;
+        if (in_window == W || last) {
+          const uint32_t t_end = chunks.t[buf][stop - 1u];
+          sq.template close_window<false>(last ? 0u : t_end - t_open, at_most, last, rows, a.mp);
+          t_open = t_end;
+          in_window = 0u;
+        }
       }
     }
+    sat += (uint32_t)__popcll(admitted);
+    if (kScore)
+      wait_sum += wave_sum_ticks(in_mask(admitted) ? to_ticks(__builtin_bit_cast(float, waits), a.bounds.narrow) : 0ull);
     c0 = R - c0 > kSeqChunk ? c0 + kSeqChunk : R;
     __syncthreads();
   }
+}
+
+// kOne: every set's window is one request.
+template <bool kScore, int S, bool kOne = false>
+__global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : (kScore ? 4 : 5)) void sweep_seq_kernel(const SweepWindowArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  float4* rows = reinterpret_cast<float4*>(smem);
+  __shared__ ClassRow cls[kMaxSlo];
+  __shared__ SeqChunks chunks;
+
+  const uint32_t tid = threadIdx.x;
+  const uint32_t lane = tid & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint32_t n_waves = blockDim.x >> 6;  // candidates of a block
+  const uint32_t blocks_per_set = (a.n_cand + n_waves - 1u) / n_waves;
+  const uint32_t set = blockIdx.x / blocks_per_set;
+  const uint32_t c = (blockIdx.x - set * blocks_per_set) * n_waves + wave;
+  const bool mine_c = c < a.n_cand;  // a block's last wavefronts may have no candidate: they only prepare
+  const SweepWindowSet rs = resolve_set(a.sets[set]);
+  if (tid < a.n_slo) cls[tid] = ClassRow{a.d_ttft[tid], a.d_tbt[tid], a.i_ttft[tid], a.i_tbt[tid]};
+  load_seq_rows(rows, a.tab, a.cells, a.mp, rs.window);
+
+  const size_t base = (size_t)c * a.i_pad;
+  const uint32_t n = mine_c ? min(a.n_inst[c], a.i_pad) : 0u;
+  uint32_t tp[S], B[S];
+  int32_t occ[S];
+  uint64_t q[S];
+  bool narrow = a.bounds.narrow_queue;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const uint32_t j = (uint32_t)s * 64u + lane;
+    tp[s] = 0u; B[s] = 1u; occ[s] = 0; q[s] = 0ull;
+    if (j < n) { tp[s] = a.tp_idx[base + j]; B[s] = a.max_batch[base + j]; occ[s] = a.occ[base + j]; q[s] = a.q_ticks[base + j]; }
+    narrow = narrow && NarrowSequence<S>::fits(a.mp, tp[s], B[s], occ[s], q[s], rs.n_req);
+  }
+  narrow = __syncthreads_and(narrow) != 0;  // (the rows are complete as well)
+
+  unsigned long long served[S], bad = 0ull;
+  float inv_tbt_first[S];
+  uint32_t sat = 0;                    // uniform
+  unsigned long long wait_sum = 0ull;  // queue waits of the admitted requests, in ticks; uniform
+#pragma unroll
+  for (int s = 0; s < S; ++s) served[s] = 0ull;
+  auto run = [&](auto& sq) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) sq.load(s, (uint32_t)s * 64u + lane < n, a.mp, a.cells, tp[s], B[s], occ[s], q[s]);
+    sq.begin(rows, a.mp);
+#pragma unroll
+    for (int s = 0; s < S; ++s) inv_tbt_first[s] = kScore ? (sq.past[s] == INFINITY ? 0.0f : 1.0f / sq.rec[s].tbt) : 0.0f;
+    walk_windows<kScore, S, kOne>(a, rs, sq, rows, cls, chunks, lane, wave, n_waves, served, sat, wait_sum);
+  };
+  if (narrow) {
+    NarrowSequence<S> sq;
+    run(sq);
+  } else {
+    Sequence<S> sq;
+    run(sq);
+    bad = sq.bad;
+  }
 
   // results of this (set, candidate): lane 0 writes them
-  if (sq.bad != 0ull && R != 0u) raise_status(a.status, 2u);  // (a lane without an instance is never bad)
+  if (bad != 0ull && rs.n_req != 0u) raise_status(a.status, 2u);  // (a lane without an instance is never bad)
   float pt = 0.0f;
   if (kScore) {
     // Phi_T: 1 / tbt of the serving instances, added in index order
@@ -289,117 +502,146 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : 4) void sweep_seq_kernel(
 // scheme, plus the per-request outputs.  One wavefront does all the work - the method is sequential
 // here - so this is about latency: no device-wide barrier per window.  The outputs of 64 requests are
 // collected one lane each and stored together.
+struct SeqOutputs {
+  int idx, slack, ttft, tbt, e2e;  // bit patterns; request c0 + lane in this lane
+};
+
+// A chunk of requests in LDS, and what of it stays in registers: its valid requests, the time behind each.
+struct AssignChunk {
+  float4 u[kSeqChunk + 1], w[kSeqChunk + 1];  // RequestSide; the last is read ahead and never used
+};
+
+template <bool kLat>
+__device__ __forceinline__ void store_outputs(const AssignArgs& a, uint32_t c0, uint32_t lane, unsigned long long live,
+                                              const SeqOutputs& o) {
+  const uint32_t r = c0 + lane;
+  if (r >= a.n_req) return;
+  const float slack = __builtin_bit_cast(float, o.slack), nanv = __builtin_nanf("");
+  const bool given = in_mask(live) && slack > -INFINITY;  // a class out of range, or no instance
+  if (a.chosen) a.chosen[r] = given ? o.idx : -1;
+  if (a.slack) a.slack[r] = given ? slack : -INFINITY;
+  if (kLat) {
+    if (a.ttft) a.ttft[r] = given ? __builtin_bit_cast(float, o.ttft) : nanv;
+    if (a.tbt) a.tbt[r] = given ? __builtin_bit_cast(float, o.tbt) : nanv;
+    if (a.e2e) a.e2e[r] = given ? __builtin_bit_cast(float, o.e2e) : nanv;
+  }
+}
+
+// Requests r0 .. r0 + 63 as they come from memory, with the arrivals of them and of those behind them.
+struct AssignRaw {
+  RequestRaw rq;
+  uint32_t own, behind;
+};
+__device__ __forceinline__ AssignRaw fetch_assign(const AssignArgs& a, uint32_t c0, uint32_t lane) {
+  const uint32_t r = c0 + lane;
+  AssignRaw x{{0u, 0u, kNoRequest}, 0u, 0u};
+  if (r < a.n_req) { x.rq.pl = a.prompt_len[r]; x.rq.ol = a.out_len[r]; x.rq.k = a.slo_class[r]; x.own = a.arrival_ticks[r]; }
+  x.behind = x.own;
+  if (r < a.n_req && a.n_req - r > 1u) x.behind = a.arrival_ticks[r + 1u];
+  return x;
+}
+
+// Windows of `window` requests, any state.
+template <bool kLat, int S, class Seq>
+__device__ __forceinline__ unsigned long long assign_windows(const AssignArgs& a, uint32_t window, Seq& sq, const float4* rows,
+                                                             const ClassRow* cls, AssignChunk& chunk, uint32_t lane) {
+  const uint32_t R = a.n_req;
+  unsigned long long sat = 0ull;
+  AssignRaw raw = fetch_assign(a, 0u, lane);
+  uint32_t in_window = 0, delta = 0;
+  for (uint32_t c0 = 0; c0 < R; c0 = R - c0 > kSeqChunk ? c0 + kSeqChunk : R) {
+    const uint32_t len = min(R - c0, kSeqChunk);
+    // one wavefront: its LDS operations stay in order, no barrier between the writes and the reads
+    const unsigned long long live = lane_mask(raw.rq.k < a.n_slo);
+    const RequestSide mine = request_side(raw.rq, a.n_slo, cls, a.status);
+    chunk.u[lane] = mine.u;
+    chunk.w[lane] = mine.w;
+    const uint32_t gap = raw.behind - raw.own;
+    if (R - c0 > kSeqChunk) raw = fetch_assign(a, c0 + kSeqChunk, lane);
+    SeqOutputs o{0, 0, 0, 0, 0};
+    for (uint32_t i = 0; i < len;) {
+      if (in_window == 0u) sq.open_window();
+      const uint32_t stop = min(len, i + (window - in_window));  // of the window's requests in this chunk
+      in_window += stop - i;
+      do {
+        const float best = score_slots<S>(RequestSide{chunk.u[i], chunk.w[i]}, sq.rec, sq.pre, sq.slack, sq.ttft, sq.e2e);
+        const uint32_t j = holder_of<S>(sq.slack, best), l = j & 63u;
+        o.idx = with_lane(o.idx, (int)i, (int)j);
+        o.slack = with_lane(o.slack, (int)i, best);
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (j >> 6 == (uint32_t)s) {
+            rare_path();
+            if (kLat) {  // what is reported about the chosen instance comes from the lane that holds it
+              o.ttft = with_lane(o.ttft, (int)i, lane_value(sq.ttft[s], (int)l));
+              o.tbt = with_lane(o.tbt, (int)i, lane_value(sq.rec[s].tbt, (int)l));
+              o.e2e = with_lane(o.e2e, (int)i, lane_value(sq.e2e[s], (int)l));
+            }
+            if (__builtin_bit_cast(int, best) >= 0) {  // admitted: it loads the instance; a blocked request does not
+              sat += 1ull;
+              sq.template admit<false>(s, l, rows, a.mp);
+            }
+          }
+        delta += (uint32_t)__builtin_amdgcn_readlane((int)gap, (int)i);
+      } while (++i < stop);
+      const bool last = c0 + stop == R;
+      if (in_window == window || last) {
+        const uint32_t passed = last ? 0u : delta;
+        sq.template close_window<false>(passed, passed, last, rows, a.mp);
+        in_window = 0u;
+        delta = 0u;
+      }
+    }
+    store_outputs<kLat>(a, c0, lane, live, o);
+  }
+  return sat;
+}
+
 template <bool kLat, int S>
 __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint32_t window) {
   extern __shared__ __align__(16) unsigned char smem[];
-  float* tab = reinterpret_cast<float*>(smem);
+  float4* rows = reinterpret_cast<float4*>(smem);
   __shared__ ClassRow cls[kMaxSlo];
-  __shared__ float4 chunk_u[kSeqChunk], chunk_w[kSeqChunk];  // RequestSide
-  __shared__ uint32_t chunk_t[kSeqChunk];                    // arrival of the request behind it
+  __shared__ AssignChunk chunk;
   const uint32_t lane = threadIdx.x;
   if (lane < a.n_slo) cls[lane] = ClassRow{a.d_ttft[lane], a.d_tbt[lane], a.i_ttft[lane], a.i_tbt[lane]};
-  load_seq_tables(tab, a.tab, a.cells);
+  load_seq_rows(rows, a.tab, a.cells, a.mp, window);
   __syncthreads();
 
   const PlacementRow row = select_row(a);
   const uint32_t n = row.n;
-  Sequence<S> sq;
+  uint32_t tp[S], B[S];
+  int32_t occ[S];
+  uint64_t q[S];
+  bool narrow = a.bounds.narrow_queue;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const uint32_t j = (uint32_t)s * 64u + lane;
-    uint32_t tp = 0, B = 1;
-    int32_t occ = 0;
-    uint64_t q = 0;
-    if (j < n) { tp = row.tp_idx[j]; B = row.max_batch[j]; occ = row.occ[j]; q = row.q_ticks[j]; }
-    sq.load(s, j < n, a.mp, a.cells, tp, B, occ, q);
+    tp[s] = 0u; B[s] = 1u; occ[s] = 0; q[s] = 0ull;
+    if (j < n) { tp[s] = row.tp_idx[j]; B[s] = row.max_batch[j]; occ[s] = row.occ[j]; q[s] = row.q_ticks[j]; }
+    narrow = narrow && NarrowSequence<S>::fits(a.mp, tp[s], B[s], occ[s], q[s], a.n_req);
   }
-  sq.begin(tab, a.cells, a.mp);
+  narrow = lane_mask(!narrow) == 0ull;
   unsigned long long sat = 0ull;  // uniform
-
-  const uint32_t R = a.n_req;
-  const uint32_t W = window;
-  auto fetch = [&](uint32_t c0, RequestRaw& raw, uint32_t& behind) __attribute__((always_inline)) {
-    const uint32_t r = c0 + lane;
-    raw = RequestRaw{0u, 0u, kNoRequest};
-    if (r < R) { raw.pl = a.prompt_len[r]; raw.ol = a.out_len[r]; raw.k = a.slo_class[r]; }
-    if (r + 1u < R) behind = a.arrival_ticks[r + 1u];
+  auto run = [&](auto& sq) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) sq.load(s, (uint32_t)s * 64u + lane < n, a.mp, a.cells, tp[s], B[s], occ[s], q[s]);
+    sq.begin(rows, a.mp);
+    sat = assign_windows<kLat, S>(a, window, sq, rows, cls, chunk, lane);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const uint32_t j = (uint32_t)s * 64u + lane;
+      if (j < n) { row.occ[j] = sq.occupancy(s); row.q_ticks[j] = sq.queue(s); }
+    }
   };
-  RequestRaw raw;
-  uint32_t behind = 0;
-  fetch(0u, raw, behind);
-  uint32_t t_open = R > W ? a.arrival_ticks[0] : 0u;
-  uint32_t in_window = 0;
-  const float nanv = __builtin_nanf("");
-  for (uint32_t c0 = 0; c0 < R; c0 = R - c0 > kSeqChunk ? c0 + kSeqChunk : R) {
-    const uint32_t len = min(R - c0, kSeqChunk);
-    // one wavefront: its LDS operations stay in order, no barrier between the writes and the reads
-    const unsigned long long live = lane_mask(raw.k < a.n_slo);
-    const RequestSide mine = request_side(raw, a.n_slo, cls, a.status);
-    chunk_u[lane] = mine.u;
-    chunk_w[lane] = mine.w;
-    chunk_t[lane] = behind;
-    if (R - c0 > kSeqChunk) fetch(c0 + kSeqChunk, raw, behind);
-    // outputs of the chunk, request c0 + lane in this lane
-    int32_t o_idx = -1;
-    float o_slack = -INFINITY, o_ttft = nanv, o_tbt = nanv, o_e2e = nanv;
-    for (uint32_t i = 0; i < len; ++i) {
-      if (in_window == 0u) sq.open_window();
-      const RequestSide q{chunk_u[i], chunk_w[i]};
-      if ((live >> i) & 1ull) {
-        const float best = sq.score(q);
-        if (best > -INFINITY) {
-          const uint32_t j = sq.holder(best);
-          const bool me = lane == i;
-          o_idx = me ? (int32_t)j : o_idx;
-          o_slack = me ? best : o_slack;
-          if (kLat) {  // what is reported about the chosen instance comes from the lane that holds it
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-              if (j >> 6 == (uint32_t)s) {
-                const int l = (int)(j & 63u);
-                const float w_ttft = lane_value(sq.ttft[s], l), w_tbt = lane_value(sq.rec[s].tbt, l),
-                            w_e2e = lane_value(sq.e2e[s], l);
-                o_ttft = me ? w_ttft : o_ttft;
-                o_tbt = me ? w_tbt : o_tbt;
-                o_e2e = me ? w_e2e : o_e2e;
-              }
-          }
-          if (best >= 0.0f) {  // admitted: it loads the instance; a blocked request does not
-            sat += 1ull;
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-              if (j >> 6 == (uint32_t)s) {
-                rare_path();
-                sq.admit(s, j & 63u, lane, a.bounds.narrow_queue);
-              }
-          }
-        }
-      }
-      const bool last = c0 + i + 1u == R;
-      if (++in_window == W || last) {
-        const uint32_t t_end = chunk_t[i];
-        sq.close_window(t_end - t_open, last, tab, a.cells, a.mp);
-        t_open = t_end;
-        in_window = 0u;
-      }
-    }
-    const uint32_t mine_r = c0 + lane;
-    if (mine_r < R) {
-      if (a.chosen) a.chosen[mine_r] = o_idx;
-      if (a.slack) a.slack[mine_r] = o_slack;
-      if (kLat) {
-        if (a.ttft) a.ttft[mine_r] = o_ttft;
-        if (a.tbt) a.tbt[mine_r] = o_tbt;
-        if (a.e2e) a.e2e[mine_r] = o_e2e;
-      }
-    }
+  if (narrow) {
+    NarrowSequence<S> sq;
+    run(sq);
+  } else {
+    Sequence<S> sq;
+    run(sq);
+    if (sq.bad != 0ull) raise_status(a.status, 2u);
   }
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const uint32_t j = (uint32_t)s * 64u + lane;
-    if (j < n) { row.occ[j] = sq.slot[s].occ; row.q_ticks[j] = sq.slot[s].q; }
-  }
-  if (sq.bad != 0ull) raise_status(a.status, 2u);
   if (lane == 0u && a.n_satisfied) *a.n_satisfied = sat;
 }
 

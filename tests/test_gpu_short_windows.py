@@ -1,0 +1,75 @@
+"""Windows of a few requests, one instance per lane: the sweep, the score and the distributor against the CPU
+oracle where their two forms meet (queues and slots that fit 32 bits and the tables, and ones that do not), at one
+row of slots per lane and several, at four and eight candidates a block, over arrivals so close that nothing
+completes between two windows, so far apart that something always does, and in bursts."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from paper_2509_06362_amd import binding, workloads as W  # noqa: E402
+from tests.test_gpu_windowed_sweep import check_against_oracle  # noqa: E402
+
+
+def workload(n_cand, i_pad, n_req, variant, gaps, **kw):
+    kw = dict(dict(n_slo=3, b_cap=64, pen_kappa=0.5), **kw)
+    w = W.random_small(n_cand * 3 + i_pad + n_req, n_cand, i_pad, n_req, **kw)
+    i = np.arange(n_req, dtype=np.uint64)
+    ticks = {"close": i * 300, "far": i * 900_001, "bursts": i * 100 + i // 37 * (11 << 20)}[gaps]
+    w = W.replace(w, arrival_ticks=ticks.astype(np.uint32))
+    if variant == "long":       # deadlines and queues beyond 32-bit ticks
+        w = W.replace(w, d_ttft=w.d_ttft * np.float32(1000.0), q_ticks=w.q_ticks * np.uint64(300),
+                      prompt_len=w.prompt_len * np.uint32(700))
+    elif variant == "wide":     # one queue of 2^32 ticks and more
+        q = w.q_ticks.copy()
+        q[:, -1] = np.uint64(5 << 32)
+        w = W.replace(w, q_ticks=q, n_inst=np.full_like(w.n_inst, i_pad))
+    elif variant == "full":     # batches past their cap
+        w = W.replace(w, occ=(w.max_batch.astype(np.int32) + np.arange(i_pad, dtype=np.int32) % 3))
+    return w
+
+
+CASES = [
+    (5, 1, 1, 130, "mixed", "close"), (5, 64, 1, 200, "mixed", "bursts"), (6, 65, 1, 129, "full", "far"),
+    (3, 128, 1, 150, "long", "bursts"), (3, 129, 1, 100, "mixed", "bursts"), (2, 256, 1, 190, "full", "close"),
+    (1030, 20, 1, 70, "full", "bursts"), (1026, 100, 1, 66, "mixed", "far"), (1025, 9, 2, 65, "wide", "bursts"),
+    (7, 33, 2, 131, "full", "bursts"), (4, 70, 3, 128, "mixed", "far"), (4, 200, 2, 121, "wide", "close"),
+    (2570, 40, 12, 100, "full", "bursts"), (4, 256, 4, 64, "full", "far"),
+]
+
+
+@pytest.mark.parametrize("n_cand,i_pad,window,n_req,variant,gaps", CASES)
+@pytest.mark.parametrize("kw", [{}, dict(pen_kappa=0.0, tbt_mode=1)])
+def test_sweep_and_score(n_cand, i_pad, window, n_req, variant, gaps, kw):
+    kw = dict(kw)
+    mode = kw.pop("tbt_mode", 0)
+    w = W.replace(workload(n_cand, i_pad, n_req, variant, gaps, **kw), tbt_mode=mode)
+    check_against_oracle(w, window, f"short windows {variant} {gaps} {kw}")
+
+
+@pytest.mark.parametrize("i_pad,window,n_req,variant,gaps", [
+    (1, 1, 65, "mixed", "close"), (3, 1, 64, "full", "far"), (64, 1, 333, "mixed", "bursts"), (64, 1, 300, "full", "close"),
+    (65, 1, 200, "full", "bursts"), (128, 1, 200, "long", "bursts"), (200, 1, 260, "full", "bursts"), (64, 1, 128, "wide", "far"),
+    (40, 2, 127, "full", "bursts"), (64, 4, 256, "full", "far"), (100, 3, 200, "mixed", "bursts"), (256, 2, 130, "full", "close"),
+    (64, 4, 255, "wide", "bursts"), (10, 1, 1, "mixed", "close"),
+])
+@pytest.mark.parametrize("mode,kappa", [(0, 0.5), (1, 0.0)])
+def test_distributor(i_pad, window, n_req, variant, gaps, mode, kappa):
+    w = W.replace(workload(2, i_pad, n_req, variant, gaps, pen_kappa=kappa), tbt_mode=mode)
+    print(f"short windows I={i_pad} R={n_req} window={window} {variant} {gaps} mode={mode}", flush=True)
+    dw = binding.DeviceWorkload(w)
+    try:
+        got = dw.assign(cand=1, window=window, latencies=True)
+        torch.cuda.synchronize()
+        ref = oracle.score_assign(w, cand=1, window=window)
+        for key in ("chosen", "slack", "ttft", "tbt", "e2e"):
+            assert np.array_equal(got[key].cpu().numpy(), ref[key], equal_nan=key != "chosen"), key
+        assert int(got["n_satisfied"].item()) == ref["n_satisfied"]
+        assert np.array_equal(got["occ"].cpu().numpy()[0], ref["occ"])
+        assert np.array_equal(got["q_ticks"].cpu().numpy()[0].view(np.uint64), ref["q_ticks"])
+        assert binding.maaso_ctx_device_status(dw.ctx) == 0
+    finally:
+        dw.close()

@@ -55,3 +55,31 @@ def test_sum_buffers_are_cleared_while_nobody_uses_them(tmp_path):
         assert clean[added], f"window {w} adds to what an earlier one left"
         clean[added] = False                  # read behind this interval's barrier
         clean[cleared] = True
+
+
+def test_nothing_completes_in_safe_ticks(tmp_path):
+    """One tick less than row_safe_ticks: the binary32 comparison that the windowed kernels make says that nothing
+    completes, over service times, batch rows and window lengths of all sizes; and the bound is not idle: within
+    1 % of the exact one where it is above some thousand ticks."""
+    rows = run_rules(tmp_path, """
+  uint64_t seed = 88172645463325252ull;
+  auto next = [&]() { seed ^= seed << 13; seed ^= seed >> 7; seed ^= seed << 17; return seed; };
+  auto unit = [&]() { return (float)(next() >> 40) * 0x1p-24f; };
+  int wrong = 0, loose = 0, tight = 0;
+  for (int k = 0; k < 2000000; ++k) {
+    const float s_bar = __builtin_exp2f(unit() * 24.0f - 2.0f), tbt = __builtin_exp2f(unit() * 16.0f - 14.0f);
+    const uint32_t w = 1u + (uint32_t)(next() % (k % 2 ? 300u : 65535u)), window = 1u + (uint32_t)(next() % 24u);
+    const float pen = k % 3 ? 1.0f : 1.0f + unit();
+    const uint32_t safe = row_safe_ticks(s_bar, tbt, w, window);
+    if (safe == 0u) continue;
+    const int run = (int)(w - 1u + window);
+    const float svc = s_bar * (tbt * pen);
+    const float served = (float)run * ((float)(safe - 1u) * 0x1p-20f);
+    wrong += !(served < svc);
+    const double exact = (double)s_bar * tbt / run * 1048576.0;
+    if (exact > 4000.0 && exact < 3.9e9) { ++tight; loose += (double)safe < 0.99 * exact; }
+  }
+  printf("%d %d %d\\n", wrong, loose, tight);
+  printf("%u %u %u\\n", row_safe_ticks(1e30f, 1e30f, 1u, 1u), row_safe_ticks(1e-30f, 1e-20f, 1u, 1u), row_safe_ticks(1.0f, 1.0f, 1u, 1u));""")
+    assert rows[0][0] == 0 and rows[0][1] == 0 and rows[0][2] > 100000
+    assert rows[1] == [4000000000, 0, 1048576 - 1024]
