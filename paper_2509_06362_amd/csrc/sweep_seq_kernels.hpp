@@ -93,6 +93,7 @@ __device__ __forceinline__ uint32_t holder_of(const float (&slack)[S], float bes
 // A placement in the lanes of one wavefront, taken through windows of requests.
 template <int S>
 struct Sequence {
+  static constexpr bool kNarrow = false;
   LiveSlot slot[S];
   SlotRecord rec[S];  // as evaluated when the window opened
   float svc[S], past[S];
@@ -192,6 +193,7 @@ struct Sequence {
 // fill up.
 template <int S>
 struct NarrowSequence {
+  static constexpr bool kNarrow = true;
   uint32_t row0[S];        // byte offset of its strategy's first row
   uint32_t B[S];           // batch cap
   float invB[S];
@@ -219,18 +221,28 @@ struct NarrowSequence {
     q[s] = present ? (uint32_t)ticks : 0u;
     changed[s] = 0ull;
   }
+  // The table row, and with the occupancy penalty the latency per token, of slot s with `load` requests on it.
+  __device__ __forceinline__ uint32_t batch(int s, uint32_t load, const ModelParams& mp) const {
+    return min(load | (0u - mp.tbt_mode), B[s]);  // (worst-case latencies: any number, so the cap)
+  }
+  __device__ __forceinline__ float4 row(int s, uint32_t w, const float4* rows) const {
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(rows) + (row0[s] + (w << 4)));
+  }
+  __device__ __forceinline__ float penalised(int s, float tbt, uint32_t w, const ModelParams& mp) const {
+    const float over = (float)__builtin_elementwise_sub_sat(4u * w, 3u * B[s]);  // > 0 iff the batch is > 75 % full
+    return tbt * fmaf(mp.pen_kappa, over * invB[s], 1.0f);
+  }
   __device__ __forceinline__ void evaluate(int s, const float4* rows, const ModelParams& mp) {
-    const uint32_t w = min(arr[s] | (0u - mp.tbt_mode), B[s]);  // (worst-case latencies: any number, so the cap)
-    const float4 r = *reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(rows) + (row0[s] + (w << 4)));
+    const uint32_t w = batch(s, arr[s], mp);
+    const float4 r = row(s, w, rows);
     rec[s].a = r.x;
     rec[s].p = r.y;
     rec[s].tbt = r.z;
-    safe[s] = __float_as_uint(r.w);
     if (mp.pen_kappa != 0.0f) {  // a factor of exactly one without a penalty
       rare_path();
-      const float over = (float)__builtin_elementwise_sub_sat(4u * w, 3u * B[s]);  // > 0 iff the batch is > 75 % full
-      rec[s].tbt = rec[s].tbt * fmaf(mp.pen_kappa, over * invB[s], 1.0f);
+      rec[s].tbt = penalised(s, r.z, w, mp);
     }
+    safe[s] = __float_as_uint(r.w);
     const float ov = (float)__builtin_elementwise_sub_sat(arr[s], B[s]);  // requests beyond the batch cap
     past[s] = (ov * invB[s]) * (mp.s_bar * rec[s].tbt);
   }
@@ -541,10 +553,100 @@ __device__ __forceinline__ AssignRaw fetch_assign(const AssignArgs& a, uint32_t 
   return x;
 }
 
-// Windows of `window` requests, any state.
-template <bool kLat, int S, class Seq>
+// The largest slack over the wavefront, uniform, and in the two wait states that a DPP operand needs behind the
+// instruction that wrote it (twelve of them): the prefill in ticks of a request admitted by this lane, and the
+// wait past the batch cap, (ov / B) * s_bar * tbt, of its instance if it does.
+__device__ __forceinline__ float max_beside(float slack, float pre, float tbt, uint32_t load, uint32_t B, float invB,
+                                            float s_bar, uint32_t& ticks, float& past) {
+  float m, ov;
+  asm("v_mul_f32 %[t], %[k], %[pre]\n\t"
+      "v_mul_f32 %[w], %[sb], %[tbt]\n\t"
+      "v_max_f32_dpp %[m], %[s], %[s] quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_rndne_f32 %[t], %[t]\n\t"
+      "v_sub_u32 %[o], %[n], %[b] clamp\n\t"
+      "v_max_f32_dpp %[m], %[m], %[m] quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cvt_u32_f32 %[t], %[t]\n\t"
+      "v_cvt_f32_u32 %[o], %[o]\n\t"
+      "v_max_f32_dpp %[m], %[m], %[m] row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_mul_f32 %[o], %[o], %[i]\n\t"
+      "s_nop 0\n\t"
+      "v_max_f32_dpp %[m], %[m], %[m] row_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_mul_f32 %[w], %[o], %[w]\n\t"
+      "s_nop 0\n\t"
+      "v_max_f32_dpp %[m], %[m], %[m] row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+      "s_nop 1\n\t"
+      "v_max_f32_dpp %[m], %[m], %[m] row_bcast:31 row_mask:0xc bank_mask:0xf"
+      : [m] "=&v"(m), [t] "=&v"(ticks), [w] "=&v"(past), [o] "=&v"(ov)
+      : [s] "v"(slack), [pre] "v"(pre), [tbt] "v"(tbt), [n] "v"(load), [b] "v"(B), [i] "v"(invB), [sb] "s"(s_bar),
+        [k] "s"(1048576.0f));
+  return lane_value(m, 63);
+}
+
+// A chunk of requests one by one, one slot per lane, while nothing completes: a chain of some sixty instructions
+// without a branch.  What bounds it is the length of that chain: alone on its SIMD a wavefront issues an
+// instruction every 4 cycles, whether it depends on the one before or not; a taken branch costs 20, a scalar
+// instruction behind the vector one that wrote its operand 16 to 24, a table row from LDS some 100.  16,384 requests,
+// 64 slots: 5.95 -> 4.94 ms with NarrowSequence (as it still is over more slots: 120: 0.59 -> 0.31 us per request) ->
+// 2.72 with the chain -> 2.35 (0.143 us per request) with two requests a trip and the waits filled.  What an instance will be once it has admitted one more request is worked out ahead, so
+// that the admission is a select; its row of the tables arrives while the next request is scored.
+template <bool kLat, bool kPenalty>
+__device__ __forceinline__ void assign_chain(const AssignArgs& a, NarrowSequence<1>& sq, const float4* rows,
+                                             const AssignChunk& chunk, uint32_t gap, uint32_t len, SeqOutputs& o) {
+  uint32_t w = sq.batch(0, sq.arr[0] + 1u, a.mp);
+  float4 next = sq.row(0, w, rows);
+  // request i, and the one that is `ahead` read meanwhile
+  auto step = [&](uint32_t i, const RequestSide& q, uint32_t ahead) __attribute__((always_inline)) {
+    const float wait = fmaf((float)sq.q[0], 0x1p-20f, sq.past[0]);
+    const Deadlines d{q.u.y, q.u.z, q.w.z, q.w.x, q.w.y, q.w.w};
+    const Margins g = score_triple(sq.rec[0].a, sq.rec[0].p, sq.rec[0].tbt, wait, q.u.x, q.u.w, d);
+    const float next_tbt = kPenalty ? sq.penalised(0, next.z, w, a.mp) : next.z;
+    const uint32_t load = sq.arr[0] + 1u;
+    uint32_t ticks;
+    float past;
+    const float best = max_beside(g.slack, g.pre, next_tbt, load, sq.B[0], sq.invB[0], a.mp.s_bar, ticks, past);
+    const unsigned long long held = lane_mask(g.slack == best);
+    // a scalar instruction waits some 16 cycles for a mask that a vector one wrote: what does not depend on it
+    // goes in between
+    __builtin_amdgcn_sched_barrier(0);
+    const RequestSide r{chunk.u[ahead], chunk.w[ahead]};
+    const uint32_t passed = (uint32_t)__builtin_amdgcn_readlane((int)gap, (int)i);
+    o.slack = with_lane(o.slack, (int)i, best);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t j = (uint32_t)__builtin_ctzll(held);  // (some lane holds it)
+    const unsigned long long takes = __builtin_bit_cast(int, best) >= 0 ? 1ull << j : 0ull;
+    if (kLat) {
+      o.ttft = with_lane(o.ttft, (int)i, lane_value(g.ttft, (int)j));
+      o.tbt = with_lane(o.tbt, (int)i, lane_value(sq.rec[0].tbt, (int)j));
+      o.e2e = with_lane(o.e2e, (int)i, lane_value(g.e2e, (int)j));
+    }
+    o.idx = with_lane(o.idx, (int)i, (int)j);
+    const bool me = in_mask(takes);
+    sq.arr[0] = me ? load : sq.arr[0];
+    w = sq.batch(0, sq.arr[0] + 1u, a.mp);
+    const float4 row = sq.row(0, w, rows);
+    __builtin_amdgcn_sched_barrier(0);  // (the read first: the next request's arithmetic hides it)
+    sq.q[0] = __builtin_elementwise_sub_sat(sq.q[0] + (me ? ticks : 0u), passed);
+    sq.rec[0].a = me ? next.x : sq.rec[0].a;
+    sq.rec[0].p = me ? next.y : sq.rec[0].p;
+    sq.rec[0].tbt = me ? next_tbt : sq.rec[0].tbt;
+    sq.past[0] = me ? past : sq.past[0];
+    next = row;
+    return r;
+  };
+  RequestSide q{chunk.u[0], chunk.w[0]};
+  uint32_t i = 0;
+  for (; i + 2u <= len; i += 2u) {  // two a trip: what the next one reads needs no moves
+    const RequestSide second = step(i, q, i + 1u);
+    q = step(i + 1u, second, i + 2u);
+  }
+  if (i < len) step(i, q, i + 1u);
+}
+
+// Windows of `window` requests (kOne: of one), any state.  `tbt_min`: least entry of the per-token latency table.
+template <bool kLat, int S, bool kOne, class Seq>
 __device__ __forceinline__ unsigned long long assign_windows(const AssignArgs& a, uint32_t window, Seq& sq, const float4* rows,
-                                                             const ClassRow* cls, AssignChunk& chunk, uint32_t lane) {
+                                                             const ClassRow* cls, AssignChunk& chunk, float tbt_min, uint32_t lane) {
+  constexpr bool kChain = kOne && S == 1 && Seq::kNarrow;
   const uint32_t R = a.n_req;
   unsigned long long sat = 0ull;
   AssignRaw raw = fetch_assign(a, 0u, lane);
@@ -556,12 +658,27 @@ __device__ __forceinline__ unsigned long long assign_windows(const AssignArgs& a
     const RequestSide mine = request_side(raw.rq, a.n_slo, cls, a.status);
     chunk.u[lane] = mine.u;
     chunk.w[lane] = mine.w;
-    const uint32_t gap = raw.behind - raw.own;
+    const uint32_t gap = raw.behind - raw.own;  // (none behind the last request)
     if (R - c0 > kSeqChunk) raw = fetch_assign(a, c0 + kSeqChunk, lane);
     SeqOutputs o{0, 0, 0, 0, 0};
-    for (uint32_t i = 0; i < len;) {
-      if (in_window == 0u) sq.open_window();
-      const uint32_t stop = min(len, i + (window - in_window));  // of the window's requests in this chunk
+    const uint32_t at_most = kOne ? (uint32_t)__builtin_amdgcn_readfirstlane((int)~min_lanes<64>(~gap)) : 0u;
+    bool done = false;
+    if constexpr (kChain) {
+      // nothing completes in this chunk: no gap in it reaches what the shortest service time allows with as
+      // many requests running as there may be by its end
+      const uint32_t run = min(sq.B[0], sq.arr[0] + kSeqChunk);
+      const uint32_t most = ~min_lanes<64>(~run);
+      if (at_most < (uint32_t)__builtin_amdgcn_readfirstlane((int)row_safe_ticks(a.mp.s_bar, tbt_min, most, 1u))) {
+        if (a.mp.pen_kappa != 0.0f) assign_chain<kLat, true>(a, sq, rows, chunk, gap, len, o);
+        else assign_chain<kLat, false>(a, sq, rows, chunk, gap, len, o);
+        done = true;
+      } else {
+        sq.begin(rows, a.mp);
+      }
+    }
+    for (uint32_t i = done ? len : 0u; i < len;) {
+      if (kOne || in_window == 0u) sq.open_window();
+      const uint32_t stop = kOne ? i + 1u : min(len, i + (window - in_window));  // of the window's requests in this chunk
       in_window += stop - i;
       do {
         const float best = score_slots<S>(RequestSide{chunk.u[i], chunk.w[i]}, sq.rec, sq.pre, sq.slack, sq.ttft, sq.e2e);
@@ -577,21 +694,20 @@ __device__ __forceinline__ unsigned long long assign_windows(const AssignArgs& a
               o.tbt = with_lane(o.tbt, (int)i, lane_value(sq.rec[s].tbt, (int)l));
               o.e2e = with_lane(o.e2e, (int)i, lane_value(sq.e2e[s], (int)l));
             }
-            if (__builtin_bit_cast(int, best) >= 0) {  // admitted: it loads the instance; a blocked request does not
-              sat += 1ull;
-              sq.template admit<false>(s, l, rows, a.mp);
-            }
+            // admitted: it loads the instance; a blocked request does not
+            if (__builtin_bit_cast(int, best) >= 0) sq.template admit<kOne>(s, l, rows, a.mp);
           }
         delta += (uint32_t)__builtin_amdgcn_readlane((int)gap, (int)i);
-      } while (++i < stop);
+      } while (++i < stop && !kOne);
       const bool last = c0 + stop == R;
-      if (in_window == window || last) {
+      if (kOne || in_window == window || last) {
         const uint32_t passed = last ? 0u : delta;
-        sq.template close_window<false>(passed, passed, last, rows, a.mp);
+        sq.template close_window<kOne>(passed, kOne ? at_most : passed, last, rows, a.mp);
         in_window = 0u;
         delta = 0u;
       }
     }
+    sat += (unsigned long long)__popcll(lane_mask(lane < len && o.slack >= 0));
     store_outputs<kLat>(a, c0, lane, live, o);
   }
   return sat;
@@ -607,6 +723,10 @@ __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint
   if (lane < a.n_slo) cls[lane] = ClassRow{a.d_ttft[lane], a.d_tbt[lane], a.i_ttft[lane], a.i_tbt[lane]};
   load_seq_rows(rows, a.tab, a.cells, a.mp, window);
   __syncthreads();
+  float tbt_min = INFINITY;  // over the rows that are read
+  for (uint32_t i = lane; i < a.cells; i += 64u)
+    if (i % (a.mp.b_cap + 1u) != 0u) tbt_min = fminf(tbt_min, rows[i].z);
+  tbt_min = -max_lanes<64>(-tbt_min);
 
   const PlacementRow row = select_row(a);
   const uint32_t n = row.n;
@@ -627,7 +747,8 @@ __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint
 #pragma unroll
     for (int s = 0; s < S; ++s) sq.load(s, (uint32_t)s * 64u + lane < n, a.mp, a.cells, tp[s], B[s], occ[s], q[s]);
     sq.begin(rows, a.mp);
-    sat = assign_windows<kLat, S>(a, window, sq, rows, cls, chunk, lane);
+    if (window == 1u) sat = assign_windows<kLat, S, true>(a, 1u, sq, rows, cls, chunk, tbt_min, lane);
+    else sat = assign_windows<kLat, S, false>(a, window, sq, rows, cls, chunk, tbt_min, lane);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const uint32_t j = (uint32_t)s * 64u + lane;
