@@ -29,7 +29,9 @@ constexpr uint32_t kMaxTimed = 256;
 // The context's small device block, in 32-bit words: [0] status, [32..35] evaluated pairs of the last
 // static sweep (all; those without a wait), [64..] the static distributor's admitted-count accumulators,
 // then the static sweep's SweepTotals; from kCounterWord on its histogram, cursors and group offsets.
+constexpr uint32_t kClassWord = 40;  // [kMaxSlo] requests of each class, between two launches of the static sweep
 constexpr uint32_t kSatWord = 64;
+static_assert(kClassWord + kMaxSlo <= kSatWord, "");
 constexpr uint32_t kTotalsWord = kSatWord + (1u + kSatLines) * kSatStride * 2u;
 constexpr uint32_t kCounterWord = kTotalsWord + (1u + kTotalsLines) * sizeof(SweepTotals) / 4u;
 constexpr uint32_t kHistWords = kMaxSlo * kLenBins;
@@ -471,7 +473,7 @@ size_t workspace_bound(const maaso_ctx* ctx, uint32_t C, uint32_t I, uint32_t R)
 
 // The launches of the static sweep; `ws` holds the grouped prompt lengths, 4 bytes per request.
 int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_requests* rq,
-                        const maaso_params* prm, void* ws, uint32_t* sat_count, float* sat_ratio,
+                        const maaso_params* prm, void* ws, size_t ws_bytes, uint32_t* sat_count, float* sat_ratio,
                         uint32_t* best_cand, hipStream_t s) {
   const uint32_t C = pl->n_cand, I = pl->i_pad, K = ctx->n_slo, R = rq->n_req;
   uint32_t* hist = ctx->status + kCounterWord;
@@ -479,6 +481,7 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   if (ctx->counters_dirty) {  // an earlier call failed between its launches
     hipLaunchKernelGGL(fill_u32_kernel, dim3(16), dim3(256), 0, s, ctx->status + kTotalsWord,
                        (kCounterWord - kTotalsWord) + 2u * kHistWords, 0u);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, ctx->status + kClassWord, (uint32_t)kMaxSlo, 0u);
     if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
     ctx->counters_dirty = false;
   }
@@ -504,7 +507,99 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
          (uint64_t)C * R << (groups.shift + 1u) <= 1ull << 28)
     ++groups.shift;
   const uint32_t n_groups = groups.count();
+  // a group of about 512 slots, two per thread, but no fewer than some 1024 groups while there are the
+  // candidates for it (four blocks per compute unit)
+  uint32_t G = (uint32_t)(((uint64_t)C + 1023u) / 1024u);
+  if (G > 512u / I) G = 512u / I;
+  if (G > kMaxGroup) G = kMaxGroup;
+  if (G == 0u) G = 1u;
+  const uint32_t cand_groups = (uint32_t)(((uint64_t)C + G - 1u) / G);
+  // Thresholds beside the grouping keep a word per (candidate, class) behind the lengths: where the workspace has
+  // room for them (next to any that holds the call's charge; with many classes, few slots and few requests it may not).
+  const uint32_t cap = (uint32_t)ctx->n_cu * 6u;  // 65,536 x 32 slots: 33.9 us with 6 blocks per compute unit, 35.0 with 5, 36.1 with 8
+  const uint32_t rank_cap = (uint32_t)ctx->n_cu * 8u;
+  const size_t at_longest = up256((size_t)R * sizeof(float)), at_pairs = at_longest + up256((size_t)C * K * sizeof(uint32_t));
+  const size_t at_best = at_pairs + up256((size_t)rank_cap * 2u * sizeof(uint64_t));
+  // (The one-launch form of up to 4096 requests keeps the atomics: settled apart it is 2 to 5 % slower at any size.)
+  // A fourth launch to settle the totals costs less than their delivery by atomics from a few hundred blocks on, the
+  // thresholds beside the dealing out pay with some 10^5 requests: 64 candidates x 99 slots x 4981 requests: 16.9 us in
+  // three launches, 18.2 in four; 67 x 32 x 4775: 17.5 / 18.0; 1039 x 6 x 8704: 18.7 / 18.5; 53 x 59 x 196,187: 26.7 / 24.7;
+  // 8974 x 8 x 151,529: 30.2 / 25.7; 59,250 x 3 x 188,741: 64 / 48.
+  const bool beside = !small && !few && (C >= 512u || R >= 1u << 16) && at_best + (size_t)rank_cap * sizeof(uint64_t) <= ws_bytes;
   TimedRegion timed(ctx, s);  // all launches of the call
+  if (beside) {
+    GroupArgs g;
+    g.prompt_len = rq->prompt_len;
+    g.slo_class = rq->slo_class;
+    g.n_req = R;
+    g.groups = groups;
+    g.per_block = R > (1u << 20) ? (uint32_t)(((uint64_t)R + 1023u) / 1024u) : 1024u;
+    g.hist = hist;
+    g.of_class = ctx->status + kClassWord;
+    g.cursor = hist + n_groups;
+    g.offsets = offsets;
+    g.sorted = static_cast<float*>(ws);
+    g.status = ctx->status;
+    const uint32_t blocks = (uint32_t)(((uint64_t)R + g.per_block - 1) / g.per_block);
+    ThresholdArgs t;
+    t.tab = ctx->tab;
+    t.cells = ctx->cells;
+    t.mp = model_params(ctx, prm);
+    t.n_slo = K;
+    std::memcpy(t.d_ttft, ctx->d_ttft, sizeof(t.d_ttft));
+    std::memcpy(t.d_tbt, ctx->d_tbt, sizeof(t.d_tbt));
+    t.n_cand = C;
+    t.i_pad = I;
+    t.n_inst = pl->n_inst;
+    t.tp_idx = pl->tp_idx;
+    t.max_batch = pl->max_batch;
+    t.occ = pl->occ;
+    t.q_ticks = reinterpret_cast<const uint64_t*>(pl->q_ticks);
+    t.group = G;
+    t.longest = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(ws) + at_longest);
+    t.status = ctx->status;
+    t.pairs = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(ws) + at_pairs);
+    t.of_class = ctx->status + kClassWord;
+    t.n_groups = cand_groups;
+    const size_t lds_g = (size_t)group_lds_words(n_groups) * sizeof(uint32_t);
+    const size_t lds = std::max(lds_g, (size_t)G * K * sizeof(uint32_t));
+    const bool rows = I % 16u == 0u, whole = groups.shift == 0u;
+    const uint32_t t_blocks = std::min(cand_groups, cap);
+    const dim3 pg(blocks + t_blocks), pb(kSweepThreads);
+    if (whole) hipLaunchKernelGGL(sweep_hist_kernel<true>, dim3(blocks), pb, lds_g, s, g);
+    else hipLaunchKernelGGL(sweep_hist_kernel<false>, dim3(blocks), pb, lds_g, s, g);
+    if (rows && whole) hipLaunchKernelGGL((sweep_prepare_kernel<true, true>), pg, pb, lds, s, g, t, blocks);
+    else if (rows) hipLaunchKernelGGL((sweep_prepare_kernel<true, false>), pg, pb, lds, s, g, t, blocks);
+    else if (whole) hipLaunchKernelGGL((sweep_prepare_kernel<false, true>), pg, pb, lds, s, g, t, blocks);
+    else hipLaunchKernelGGL((sweep_prepare_kernel<false, false>), pg, pb, lds, s, g, t, blocks);
+    RankArgs r;
+    r.groups = groups;
+    r.n_cand = C;
+    r.n_req = R;
+    r.longest = t.longest;
+    r.of_class = ctx->status + kClassWord;
+    r.block_best = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(ws) + at_best);
+    r.offsets = offsets;
+    r.sorted = g.sorted;
+    r.clear = hist;
+    uint32_t RG = (uint32_t)(((uint64_t)C + 2047u) / 2048u);
+    if (RG > kMaxGroup) RG = kMaxGroup;
+    r.group = RG;
+    r.n_groups = (uint32_t)(((uint64_t)C + RG - 1u) / RG);
+    r.sat_count = sat_count;
+    r.sat_ratio = sat_ratio;
+    unsigned long long* eval_total = reinterpret_cast<unsigned long long*>(ctx->status + 32);
+    const dim3 rg(std::min(r.n_groups, rank_cap));
+    const size_t lds_r = ((size_t)n_groups + 1u) * sizeof(uint32_t);
+    if (whole) hipLaunchKernelGGL(sweep_rank_kernel<true>, rg, dim3(kSweepThreads), lds_r, s, r);
+    else hipLaunchKernelGGL(sweep_rank_kernel<false>, rg, dim3(kSweepThreads), lds_r, s, r);
+    hipLaunchKernelGGL(sweep_settle_kernel, dim3(1), dim3(1024), 0, s, r.block_best, rg.x, t.pairs, t_blocks, best_cand, eval_total);
+    ctx->last_evaluated = eval_total;
+    if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
+    ctx->counters_dirty = false;
+    return MAASO_OK;
+  }
+  const size_t lds_g = (size_t)group_lds_words(n_groups) * sizeof(uint32_t);
   if (!small && !few) {
     GroupArgs g;
     g.prompt_len = rq->prompt_len;
@@ -514,17 +609,18 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
     // 1024 requests a block fill the chip from 2^18 on; beyond 1024 blocks each takes more
     g.per_block = R > (1u << 20) ? (uint32_t)(((uint64_t)R + 1023u) / 1024u) : 1024u;
     g.hist = hist;
+    g.of_class = nullptr;
     g.cursor = hist + n_groups;
     g.offsets = offsets;
     g.sorted = static_cast<float*>(ws);
     g.status = ctx->status;
     const uint32_t blocks = (uint32_t)(((uint64_t)R + g.per_block - 1) / g.per_block);
     if (groups.shift == 0u) {
-      hipLaunchKernelGGL(sweep_hist_kernel<true>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
-      hipLaunchKernelGGL(sweep_scatter_kernel<true>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+      hipLaunchKernelGGL(sweep_hist_kernel<true>, dim3(blocks), dim3(kSweepThreads), lds_g, s, g);
+      hipLaunchKernelGGL(sweep_scatter_kernel<true>, dim3(blocks), dim3(kSweepThreads), lds_g, s, g);
     } else {
-      hipLaunchKernelGGL(sweep_hist_kernel<false>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
-      hipLaunchKernelGGL(sweep_scatter_kernel<false>, dim3(blocks), dim3(kSweepThreads), 0, s, g);
+      hipLaunchKernelGGL(sweep_hist_kernel<false>, dim3(blocks), dim3(kSweepThreads), lds_g, s, g);
+      hipLaunchKernelGGL(sweep_scatter_kernel<false>, dim3(blocks), dim3(kSweepThreads), lds_g, s, g);
     }
     if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
   }
@@ -548,21 +644,14 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   a.offsets = offsets;
   a.sorted = static_cast<const float*>(ws);
   a.clear = hist;
-  // a group of about 512 slots, two per thread, but no fewer than some 1024 groups while there are the
-  // candidates for it (four blocks per compute unit)
-  uint32_t G = (uint32_t)(((uint64_t)C + 1023u) / 1024u);
-  if (G > 512u / I) G = 512u / I;
-  if (G > kMaxGroup) G = kMaxGroup;
-  if (G == 0u) G = 1u;
   a.group = G;
-  a.n_groups = (uint32_t)(((uint64_t)C + G - 1u) / G);
+  a.n_groups = cand_groups;
   a.sat_count = sat_count;
   a.sat_ratio = sat_ratio;
   a.best_cand = best_cand;
   a.totals = reinterpret_cast<SweepTotals*>(ctx->status + kTotalsWord);
   a.eval_total = reinterpret_cast<unsigned long long*>(ctx->status + 32);
   a.status = ctx->status;
-  const uint32_t cap = (uint32_t)ctx->n_cu * 6u;  // 65,536 x 32 slots: 38 us with 6 blocks per compute unit, 43 with 4 or 8
   const dim3 grid(a.n_groups < cap ? a.n_groups : cap), block(kSweepThreads);
   const size_t lds = ((size_t)n_groups + 1u) * sizeof(uint32_t);
   if (few) {
@@ -957,11 +1046,12 @@ int placement_sweep_impl(maaso_ctx* ctx, const maaso_placements* pl, const maaso
   if (static_scratch) {
     if (!ctx->scratch_ptr) return MAASO_E_HIP;
     if (bytes > (size_t)MAASO_NOALLOC_SCRATCH_BYTES) return MAASO_E_SHAPE;
-    return launch_static_sweep(ctx, pl, rq, prm, ctx->scratch_ptr, sat_count, sat_ratio, best_cand, s);
+    return launch_static_sweep(ctx, pl, rq, prm, ctx->scratch_ptr, (size_t)MAASO_NOALLOC_SCRATCH_BYTES, sat_count, sat_ratio,
+                               best_cand, s);
   }
   rc = need_workspace(ctx, bytes);
   if (rc != MAASO_OK) return rc;
-  return launch_static_sweep(ctx, pl, rq, prm, ctx->ws, sat_count, sat_ratio, best_cand, s);
+  return launch_static_sweep(ctx, pl, rq, prm, ctx->ws, ctx->ws_bytes, sat_count, sat_ratio, best_cand, s);
 }
 
 }  // namespace

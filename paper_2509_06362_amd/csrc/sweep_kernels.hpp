@@ -16,16 +16,21 @@
 //   1. sweep_hist_kernel, 2. sweep_scatter_kernel - the prompt lengths grouped by (class, bin), 256 bins
 //      per class by the leading bits of the binary32 length (eight per octave; two, four ... bins in one
 //      where there are many classes and few requests), and the groups' offsets.
-//   3. sweep_count_kernel - blocks take groups of candidates: a thread per instance slot evaluates the
-//      profile (Eq. 1 row, occupancy penalty, queue wait) and its thresholds, the largest per
-//      (candidate, class) meet in LDS, sixteen lanes per (candidate, class) add the group of the
-//      threshold's bin to the lengths below it.  The last block to finish writes the best candidate.
-// Up to kSmallRequests requests the third launch is the only one: every block groups them in its own LDS.
-// With few candidates sweep_few_kernel is: every block compares its share of the requests with all thresholds.
+//      Beside the second (sweep_prepare_kernel): blocks take groups of candidates, a thread per instance slot
+//      evaluates the profile (Eq. 1 row, occupancy penalty, queue wait) and its thresholds, the largest per
+//      (candidate, class) meet in LDS.
+//   3. sweep_rank_kernel - sixteen lanes per (candidate, class) add the group of the threshold's bin to the
+//      lengths below it.  4. sweep_settle_kernel - the best candidate.
+// Up to kSmallRequests requests sweep_count_kernel does all of it in one launch: every block groups them in its own
+// LDS, and the last block to finish writes the best candidate.  It is also the third launch where the thresholds
+// have no room in the workspace, or with some hundred candidates and few requests.
+// With few candidates sweep_few_kernel is the only launch: every block compares its share of the requests with all
+// thresholds.
 //
-// What bounds it: the instance slots' 15 bytes each and the latency of three short launches.  65,536
-// candidates x 32 slots x 16,384 requests: 457 -> 37 us; 8192 x 128 x 131,072: 5240 -> 40.6 us; 4096 x 32 x 65,536:
-// 127 -> 22 us; 37 x 13 x 1000: 18 -> 11 us (before: every pair evaluated on the vector units).
+// What bounds it: the instance slots' 15 bytes each and the latency of four short launches.  65,536
+// candidates x 32 slots x 16,384 requests: 457 -> 36.2 -> 33.9 us; 8192 x 128 x 131,072: 5240 -> 38.8 -> 33.8 us; 4096 x 32 x
+// 65,536: 127 -> 22.1 -> 20.2 us; 37 x 13 x 1000: 18 -> 11 us (every pair evaluated on the vector units; thresholds in the
+// third launch; beside the second).  Of the 33.8: grouping 5, dealing out and thresholds 20, ranks 7, totals 4.
 #pragma once
 
 #include "device_model.hpp"
@@ -136,6 +141,7 @@ struct GroupArgs {
   LengthGroups groups;
   uint32_t per_block;  // requests per block, contiguous
   uint32_t* hist;      // [groups] zero on entry; the count kernel clears it again
+  uint32_t* of_class;  // [n_slo] requests of each class, as hist; or null
   uint32_t* cursor;    // [groups] as hist
   uint32_t* offsets;   // [groups + 1]
   float* sorted;       // [n_req]
@@ -165,9 +171,13 @@ __device__ __forceinline__ void for_requests(const uint32_t* prompt_len, const u
   }
 }
 
+// LDS words of the two below for n groups.
+constexpr uint32_t group_lds_words(uint32_t n) { return n + (n + 15u) / 16u * 17u; }
+
 template <bool kWhole>
-__global__ __launch_bounds__(kSweepThreads) void sweep_hist_kernel(const GroupArgs a) {
-  __shared__ uint32_t h[kMaxSlo * kLenBins];
+__device__ __forceinline__ void count_groups(const GroupArgs& a, uint32_t* h) {
+  __shared__ uint32_t of_class[kMaxSlo];
+  if (threadIdx.x < kMaxSlo) of_class[threadIdx.x] = 0u;
   const LengthGroups groups = groups_of<kWhole>(a.groups);
   const uint32_t n = groups.count();
   for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads) h[i] = 0u;
@@ -178,15 +188,20 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_hist_kernel(const GroupAr
                      [&](uint32_t g, float) { atomicAdd(&h[g], 1u); });
   lds_atomics_barrier();
   for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads)
-    if (h[i] != 0u) atomicAdd(&a.hist[i], h[i]);
+    if (h[i] != 0u) {
+      atomicAdd(&a.hist[i], h[i]);
+      if (a.of_class) atomicAdd(&of_class[i / groups.bins()], h[i]);
+    }
+  if (!a.of_class) return;
+  lds_atomics_barrier();
+  if (threadIdx.x < groups.n_slo && of_class[threadIdx.x] != 0u) atomicAdd(&a.of_class[threadIdx.x], of_class[threadIdx.x]);
 }
 
 template <bool kWhole>
-__global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const GroupArgs a) {
-  __shared__ uint32_t h[kMaxSlo * kLenBins];
-  __shared__ uint32_t start[kMaxSlo * kLenBins / 16 * 17];
+__device__ __forceinline__ void deal_out(const GroupArgs& a, uint32_t* h) {
   __shared__ uint32_t part[kSweepThreads / kWave];
   const LengthGroups groups = groups_of<kWhole>(a.groups);
+  uint32_t* start = h + groups.count();
   const uint32_t n = groups.count(), per = kWhole ? groups.n_slo : groups.per_thread(), tid = threadIdx.x;
   // where each group starts: every block works it out from the totals, thread t for `per` groups in a row (a
   // word of padding every sixteen keeps the threads' rows off each other's banks)
@@ -245,6 +260,18 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const Grou
   __syncthreads();
   for_requests<false>(a.prompt_len, a.slo_class, r0, r1, groups, a.status,
                       [&](uint32_t g, float L) { a.sorted[atomicAdd(&h[g], 1u)] = L; });
+}
+
+template <bool kWhole>
+__global__ __launch_bounds__(kSweepThreads) void sweep_hist_kernel(const GroupArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  count_groups<kWhole>(a, reinterpret_cast<uint32_t*>(smem));
+}
+
+template <bool kWhole>
+__global__ __launch_bounds__(kSweepThreads) void sweep_scatter_kernel(const GroupArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  deal_out<kWhole>(a, reinterpret_cast<uint32_t*>(smem));
 }
 
 // The longest prompt whose first-token latency meets the deadline, as the bits of its binary32 value plus
@@ -535,6 +562,233 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_count_kernel(const CountA
       a.eval_total[1] = f;
       if (a.best_cand) *a.best_cand = ~(uint32_t)(b & 0xffffffffull);
     }
+  }
+}
+
+// The large form in four launches: the grouping's two, the second with the thresholds beside it - they need the
+// requests of each class, not the groups, and a hundred blocks of 1024 requests leave most of the chip idle for the
+// 7 us that dealing the lengths out takes - then the ranks, then a block that settles the totals.  (Delivered by
+// atomics from the rank kernel's 2048 blocks, over 32 cache lines, the totals were 5 us and more of its 12 to 17.
+// Thresholds beside the first launch as well, 20 / 40 / 60 % of them: 65,536 x 32 slots 36.9 / 35.2 / 35.2 us against 33.6
+// with none; tables in LDS and slots read a trip ahead: 8192 x 128 slots 22.7 us for this launch instead of 19.8.)
+struct ThresholdArgs {
+  const float* tab;
+  uint32_t cells;
+  ModelParams mp;
+  uint32_t n_slo;
+  float d_ttft[kMaxSlo], d_tbt[kMaxSlo];
+  uint32_t n_cand, i_pad;
+  const uint32_t* n_inst;
+  const uint8_t* tp_idx;
+  const uint16_t* max_batch;
+  const int32_t* occ;
+  const uint64_t* q_ticks;
+  const uint32_t* of_class;    // [n_slo] requests of each class
+  uint32_t group, n_groups;    // candidates per group
+  uint32_t* longest;           // [n_cand][n_slo] largest longest_prompt of the candidate's slots
+  unsigned long long* pairs;   // [blocks][2] (request, instance) pairs past the between-token check: all, without a wait
+  uint32_t* status;
+};
+
+template <bool kRows>
+__device__ __forceinline__ void find_thresholds(const ThresholdArgs& a, uint32_t* longest, uint32_t block, uint32_t blocks) {
+  __shared__ float4 rows[kMaxSlo];
+  __shared__ unsigned long long ends[2][kSweepThreads / kWave];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t K = a.n_slo, I = a.i_pad;
+  if (tid < K) rows[tid] = make_float4(a.d_ttft[tid], a.d_tbt[tid], __uint_as_float(a.of_class[tid]), 0.0f);
+  unsigned long long pairs = 0ull, fresh = 0ull;  // of this thread's slots
+  for (uint32_t g = block; g < a.n_groups; g = a.n_groups - g > blocks ? g + blocks : a.n_groups) {
+    const uint32_t c0 = g * a.group;
+    const uint32_t nc = min(a.group, a.n_cand - c0);
+    const uint32_t slots = nc * I;
+    for (uint32_t i = tid; i < nc * K; i += kSweepThreads) longest[i] = 0u;
+    __syncthreads();
+    // two slots a thread at a time, everything read before anything is used
+    constexpr uint32_t U = 2;
+    for (uint32_t s0 = wave * 64u; s0 < slots; s0 += U * kSweepThreads) {
+      uint32_t cl[U], tp[U], B[U], n_inst[U];
+      int32_t occ[U];
+      uint64_t q[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t s = min(s0 + u * kSweepThreads + lane, slots - 1u);
+        cl[u] = s / I;
+        const size_t at = (size_t)c0 * I + s;
+        n_inst[u] = a.n_inst[c0 + cl[u]];
+        tp[u] = a.tp_idx[at]; B[u] = a.max_batch[at]; occ[u] = a.occ[at]; q[u] = a.q_ticks[at];
+      }
+      Staged st[U];
+      float inv_p[U];
+      uint32_t reached[U];  // requests whose class the slot's between-token latency suits
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t s = s0 + u * kSweepThreads + lane;
+        st[u] = Staged{1.0f, 1.0f, INFINITY, 1.0f, INFINITY};  // absent: suits no class
+        if (s < slots && s - cl[u] * I < n_inst[u] &&
+            !stage_instance(a.tab, a.cells, a.mp, tp[u], B[u], occ[u], q[u], st[u]))
+          raise_status(a.status, 2u);
+        inv_p[u] = __builtin_amdgcn_rcpf(st[u].p);
+        reached[u] = 0u;
+      }
+      for (uint32_t k = 0; k < K; ++k) {
+        const float4 row = rows[k];  // deadlines, requests of the class
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+          const bool in_time = st[u].tbt <= row.y;
+          if (lane_mask(in_time) == 0ull) continue;
+          reached[u] += in_time ? __float_as_uint(row.z) : 0u;
+          uint32_t key = longest_prompt(st[u].a, st[u].p, st[u].wait, row.x, inv_p[u], in_time);
+          if (kRows) {
+            key = row_max_u32(key);
+            if ((lane & 15u) == 0u && key != 0u) atomicMax(&longest[cl[u] * K + k], key);
+          } else if (key != 0u) {
+            atomicMax(&longest[cl[u] * K + k], key);
+          }
+        }
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        pairs += reached[u];
+        fresh += st[u].wait == 0.0f ? reached[u] : 0u;
+      }
+    }
+    lds_atomics_barrier();
+    for (uint32_t i = tid; i < nc * K; i += kSweepThreads) a.longest[(size_t)c0 * K + i] = longest[i];
+    __syncthreads();
+  }
+  for (int d = 32; d >= 1; d >>= 1) {
+    pairs += __shfl_xor(pairs, d);
+    fresh += __shfl_xor(fresh, d);
+  }
+  if (lane == 0u) { ends[0][wave] = pairs; ends[1][wave] = fresh; }
+  __syncthreads();
+  if (tid < 2u) {
+    unsigned long long v = 0ull;
+    for (int w = 0; w < kSweepThreads / kWave; ++w) v += ends[tid][w];
+    a.pairs[2u * block + tid] = v;
+  }
+}
+
+template <bool kRows, bool kWhole>
+__global__ __launch_bounds__(kSweepThreads) void sweep_prepare_kernel(const GroupArgs g, const ThresholdArgs t, uint32_t group_blocks) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t* lds = reinterpret_cast<uint32_t*>(smem);
+  if (blockIdx.x < group_blocks) deal_out<kWhole>(g, lds);
+  else find_thresholds<kRows>(t, lds, blockIdx.x - group_blocks, gridDim.x - group_blocks);
+}
+
+struct RankArgs {
+  LengthGroups groups;
+  uint32_t n_cand, n_req;
+  const uint32_t* longest;         // [n_cand][n_slo]
+  const uint32_t* offsets;
+  const float* sorted;
+  uint32_t* clear;                 // histogram and cursors, two words per group, cleared again
+  uint32_t* of_class;              // ... and the requests of each class
+  uint32_t group, n_groups;        // candidates per group
+  uint32_t* sat_count;
+  float* sat_ratio;
+  unsigned long long* block_best;  // [blocks] (count << 32) | ~candidate, the largest
+};
+
+// The lengths below the threshold's bin, and those of the bin that are not above it: 2^width lanes per (candidate,
+// class).
+template <bool kWhole>
+__global__ __launch_bounds__(kSweepThreads) void sweep_rank_kernel(const RankArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t* off = reinterpret_cast<uint32_t*>(smem);                // [groups + 1]
+  __shared__ uint32_t longest[kMaxGroup * kMaxSlo];
+  __shared__ uint32_t cnt[kMaxGroup];
+  __shared__ unsigned long long ends[kSweepThreads / kWave];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const LengthGroups groups = groups_of<kWhole>(a.groups);
+  const uint32_t K = groups.n_slo, n = groups.count(), bins = groups.bins();
+  copy_words(off, a.offsets, n + 1u);
+  if (blockIdx.x == 0u) {
+    for (uint32_t i = tid; i < 2u * n; i += kSweepThreads) a.clear[i] = 0u;
+    if (tid < K) a.of_class[tid] = 0u;
+  }
+  unsigned long long best = 0ull;
+  for (uint32_t g = blockIdx.x; g < a.n_groups; g = a.n_groups - g > gridDim.x ? g + gridDim.x : a.n_groups) {
+    const uint32_t c0 = g * a.group;
+    const uint32_t nc = min(a.group, a.n_cand - c0);
+    const uint32_t tasks = nc * K;
+    for (uint32_t i = tid; i < tasks; i += kSweepThreads) longest[i] = a.longest[(size_t)c0 * K + i];
+    if (tid < nc) cnt[tid] = 0u;
+    __syncthreads();
+    const uint32_t width = tasks > 8u ? 4u : tasks > 4u ? 5u : tasks > 2u ? 6u : tasks > 1u ? 7u : 8u;
+    const uint32_t part_of = tid & ((1u << width) - 1u), per_pass = kSweepThreads >> width;
+    constexpr uint32_t U = 8;  // lengths in flight (two tasks side by side: 34.4 against 34.3 us, four: 37.4)
+    for (uint32_t t = tid >> width; t < tasks; t += per_pass) {
+      const uint32_t key = longest[t];
+      const uint32_t cl = t / K, k = t - cl * K;
+      uint32_t sum = 0;
+      if (key != 0u) {
+        const float X = __uint_as_float(key - 1u);
+        const uint32_t grp = groups.of(k, X);
+        const uint32_t b0 = off[grp], b1 = off[grp + 1u];
+        for (uint32_t i = b0 + part_of; i < b1; i = b1 - i > (U << width) ? i + (U << width) : b1) {
+          float L[U];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) L[u] = (u << width) < b1 - i ? a.sorted[i + (u << width)] : INFINITY;
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) sum += L[u] <= X ? 1u : 0u;
+        }
+        sum = row_sum_u32(sum) + (part_of == 0u ? b0 - off[k * bins] : 0u);
+      }
+      if ((lane & 15u) == 0u && sum != 0u) atomicAdd(&cnt[cl], sum);
+    }
+    lds_atomics_barrier();
+    if (tid < nc) {
+      const uint32_t c = c0 + tid, v = cnt[tid];
+      a.sat_count[c] = v;
+      if (a.sat_ratio) a.sat_ratio[c] = a.n_req ? (float)v / (float)a.n_req : 0.0f;
+      const unsigned long long kc = ((unsigned long long)v << 32) | (unsigned long long)(~c);
+      best = kc > best ? kc : best;
+    }
+    __syncthreads();
+  }
+  for (int d = 32; d >= 1; d >>= 1) {
+    const unsigned long long o = __shfl_xor(best, d);
+    best = o > best ? o : best;
+  }
+  if (lane == 0u) ends[wave] = best;
+  __syncthreads();
+  if (tid == 0u) {
+    for (int w = 1; w < kSweepThreads / kWave; ++w) best = ends[w] > best ? ends[w] : best;
+    a.block_best[blockIdx.x] = best;
+  }
+}
+
+// The best candidate and the pairs from what the blocks left.  One block.
+__global__ __launch_bounds__(1024) void sweep_settle_kernel(const unsigned long long* block_best, uint32_t n_best,
+                                                            const unsigned long long* pairs, uint32_t n_pairs,
+                                                            uint32_t* best_cand, unsigned long long* eval_total) {
+  __shared__ unsigned long long ends[3][1024 / kWave];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  unsigned long long best = 0ull, all = 0ull, fresh = 0ull;
+#pragma unroll 4
+  for (uint32_t i = tid; i < n_best; i += 1024u) best = block_best[i] > best ? block_best[i] : best;
+#pragma unroll 4
+  for (uint32_t i = tid; i < n_pairs; i += 1024u) { all += pairs[2u * i]; fresh += pairs[2u * i + 1u]; }
+  for (int d = 32; d >= 1; d >>= 1) {
+    const unsigned long long o = __shfl_xor(best, d);
+    best = o > best ? o : best;
+    all += __shfl_xor(all, d);
+    fresh += __shfl_xor(fresh, d);
+  }
+  if (lane == 0u) { ends[0][wave] = best; ends[1][wave] = all; ends[2][wave] = fresh; }
+  __syncthreads();
+  if (tid == 0u) {
+    for (int w = 1; w < 1024 / kWave; ++w) {
+      best = ends[0][w] > best ? ends[0][w] : best;
+      all += ends[1][w];
+      fresh += ends[2][w];
+    }
+    eval_total[0] = all;
+    eval_total[1] = fresh;
+    if (best_cand) *best_cand = ~(uint32_t)(best & 0xffffffffull);
   }
 }
 

@@ -38,6 +38,11 @@ def check(w):
     (9, 256, 5121, 3), (1, 64, 9000, 16), (40, 33, 4095, 8), (2100, 32, 4100, 3),
     # compared with every threshold (up to 128 candidates of 512 slots together), or grouped
     (128, 4, 5000, 16), (129, 3, 5000, 16), (2, 256, 4097, 5), (3, 171, 4097, 5), (37, 13, 20481, 1),
+    # thresholds beside the grouping or behind it: either side of 512 candidates and of 65,536 requests, rows of slots
+    # that fill 16 lanes and not, several groups of candidates a block, more blocks than deliver at once, and (the last)
+    # thresholds that the no-allocation scratch has no room for
+    (511, 20, 4100, 16), (512, 20, 4100, 16), (512, 16, 4097, 2), (140, 48, 65535, 2), (140, 48, 65536, 2), (129, 5, 70001, 3),
+    (5000, 1, 4097, 16), (1900, 255, 4099, 1), (140_000, 1, 4200, 16),
 ])
 def test_static_sweep_edges(n_cand, i_pad, n_req, n_slo):
     w = W.random_small(n_cand + 3 * i_pad + n_req, n_cand, i_pad, n_req, n_slo=n_slo, b_cap=64, pen_kappa=0.5)
