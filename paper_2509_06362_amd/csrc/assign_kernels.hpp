@@ -171,7 +171,8 @@ __device__ __forceinline__ RequestVec load_request_vec(const AssignArgs& a, uint
 
 // kSQ: shortest-queue rule; the lists or `rrank` (registers, with NREG) hold the instances'
 // queue_rank_value, and the slack written out is the chosen instance's own.
-template <bool kLat, int V, int NREG, bool kSQ>
+// kAll: `adm` is the placement itself.
+template <bool kLat, int V, int NREG, bool kSQ, bool kAll>
 __device__ __forceinline__ uint32_t assign_requests(const AssignArgs& a, uint64_t r0, uint32_t n,
                                                     const float4* __restrict__ recs,
                                                     const ClassRow* __restrict__ cls,
@@ -267,10 +268,10 @@ __device__ __forceinline__ uint32_t assign_requests(const AssignArgs& a, uint64_
     bool blocked = false;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      idx[v] = idx[v] >= 0 ? (int32_t)adm.idx[idx[v]] : -1;
+      if (!kAll) idx[v] = idx[v] >= 0 ? (int32_t)adm.idx[idx[v]] : -1;
       blocked |= !(best[v] >= 0.0f);
     }
-    if (rep.n && lane_mask(blocked) != 0ull) {  // some lane has a request that nothing can serve
+    if (!kAll && rep.n && lane_mask(blocked) != 0ull) {  // some lane has a request that nothing can serve
       float top[V];
       int32_t at[V];
 #pragma unroll
@@ -338,60 +339,55 @@ __device__ __forceinline__ uint32_t assign_requests(const AssignArgs& a, uint64_
   return sat;
 }
 
-// Listing takes a wavefront about as long as comparing a thread's requests with this many instances: up to
-// there all of them are compared with all requests (31 jittered slots, 316,707 requests, one group of four a
-// thread: 17.6 us with lists, 14.0 without; 49 slots, 6145 requests: 14.2 and 16.4).
-constexpr uint32_t kListPays = 32;
-
-// Lists the instances of a staged placement that matter (one wavefront).
-template <bool kSQ>
-__device__ __forceinline__ void list_candidates(const AssignArgs& a, const float4* recs, const int32_t* occ_s,
-                                                uint32_t n, uint32_t lane, float4* adm_recs, uint32_t* adm_idx,
-                                                float* adm_rank, float4* rep_recs, uint32_t* rep_idx,
-                                                uint32_t* sizes) {
-  SlotRecord rec[4];
-  int32_t occ[4];
-  float rank[4];
+// Lists instances of a staged placement, one wavefront, S slots per lane (no more than it takes to hold the
+// placement: 64 instances listed with four slots per lane were 1.1 us slower).  kReport: those that can be reported for
+// a blocked request, else those that a request can be admitted to.
+template <int S, bool kSQ, bool kReport>
+__device__ __forceinline__ void list_candidates(const AdmissionBounds& bounds, const float4* recs, const int32_t* occ_s,
+                                                  uint32_t n, uint32_t lane, float4* out_recs, uint32_t* out_idx,
+                                                  float* out_rank, uint32_t* size) {
+  SlotRecord rec[S];
+  int32_t occ[S];
+  float rank[S];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < S; ++s) {
     const uint32_t j = min((uint32_t)s * 64u + lane, n ? n - 1u : 0u);
     const float4 r = recs[j];
     rec[s] = SlotRecord{r.x, r.y, r.z, r.w};
-    occ[s] = kSQ ? occ_s[j] : 0;
+    occ[s] = kSQ && !kReport ? occ_s[j] : 0;
   }
-  InstanceSet<4> adm, rep;
-  find_admissible<4, kSQ>(rec, occ, n, lane, a.bounds, adm);
-  find_undominated<4>(rec, n, lane, rep);
-  if (kSQ) queue_ranks<4>(occ, adm, lane, rank);
-  uint32_t base_a = 0, base_r = 0;
+  InstanceSet<S> set;
+  if (kReport) {
+    find_undominated<S>(rec, n, lane, set);
+  } else {
+    find_admissible<S, kSQ>(rec, occ, n, lane, bounds, set);
+    if (kSQ) queue_ranks<S>(occ, set, lane, rank);
+  }
+  uint32_t base = 0;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const unsigned long long below = (1ull << lane) - 1ull;
-    const float4 r = make_float4(rec[s].a, rec[s].p, rec[s].tbt, rec[s].wait);
-    if (in_mask(adm.m[s])) {
-      const uint32_t at = base_a + (uint32_t)__popcll(adm.m[s] & below);
-      adm_recs[at] = r;
-      adm_idx[at] = (uint32_t)s * 64u + lane;
-      if (kSQ) adm_rank[at] = rank[s];
+  for (int s = 0; s < S; ++s) {
+    if (in_mask(set.m[s])) {
+      const uint32_t at = base + (uint32_t)__popcll(set.m[s] & ((1ull << lane) - 1ull));
+      out_recs[at] = make_float4(rec[s].a, rec[s].p, rec[s].tbt, rec[s].wait);
+      out_idx[at] = (uint32_t)s * 64u + lane;
+      if (kSQ && !kReport) out_rank[at] = rank[s];
     }
-    if (in_mask(rep.m[s])) {
-      const uint32_t at = base_r + (uint32_t)__popcll(rep.m[s] & below);
-      rep_recs[at] = r;
-      rep_idx[at] = (uint32_t)s * 64u + lane;
-    }
-    base_a += (uint32_t)__popcll(adm.m[s]);
-    base_r += (uint32_t)__popcll(rep.m[s]);
+    base += (uint32_t)__popcll(set.m[s]);
   }
-  if (lane == 0u) { sizes[0] = base_a; sizes[1] = base_r; }
+  if (lane == 0u) *size = base;
 }
 
 // V = 4 needs 16-byte aligned request and output arrays (slo_class 4-byte aligned); the host checks.
 // NREG > 0 requires n_inst <= NREG (the host checks against the i_pad it was given).
-template <bool kLat, int V, int NREG, bool kSQ>
+// LIST (with NREG = 0): slots per lane of the wavefronts that list the instances, as many as i_pad takes; 0: nothing
+// is listed, every request is compared with all instances (largest slack only).
+template <bool kLat, int V, int NREG, bool kSQ, int LIST>
 __global__ __launch_bounds__(kAssignThreads) void assign_static_kernel(const AssignArgs a) {
-  __shared__ float4 recs[256];
+  __shared__ float4 recs[256 + (NREG ? 0 : 3)];  // whole trips of four are read
   __shared__ ClassRow cls[kMaxSlo];
-  constexpr int kList = NREG ? 1 : 256 + 3;  // whole trips of four are read
+  constexpr bool kAll = NREG == 0 && LIST == 0;
+  constexpr int kList = LIST ? 256 + 3 : 1;
+  static_assert(!kAll || !kSQ, "ranks come with a list");
   __shared__ float4 adm_recs[kList], rep_recs[kList];
   __shared__ uint32_t adm_idx[kList], rep_idx[kList], sizes[2];
   __shared__ float adm_rank[kSQ ? kList : 1];
@@ -418,19 +414,16 @@ __global__ __launch_bounds__(kAssignThreads) void assign_static_kernel(const Ass
   if (NREG) {
     if (kSQ)
       for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) rankv[j] = queue_rank_value(occ_s, n, j);
-  } else if (n_vec <= stride * (kListPays / max(n, 1u))) {  // groups per thread x instances
-    for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
-      adm_recs[j] = recs[j];
-      adm_idx[j] = j;
-      if (kSQ) adm_rank[j] = queue_rank_value(occ_s, n, j);
-    }
-    if (threadIdx.x == 0u) { sizes[0] = n; sizes[1] = 0u; }
-  } else if (threadIdx.x < 64u) {
-    list_candidates<kSQ>(a, recs, occ_s, n, threadIdx.x, adm_recs, adm_idx, adm_rank, rep_recs, rep_idx, sizes);
+  } else if (kAll) {
+  } else if (threadIdx.x < 64u) {  // the two lists side by side, a wavefront each
+    list_candidates<LIST ? LIST : 1, kSQ, false>(a.bounds, recs, occ_s, n, threadIdx.x, adm_recs, adm_idx, adm_rank, &sizes[0]);
+  } else if (threadIdx.x < 128u) {
+    list_candidates<LIST ? LIST : 1, kSQ, true>(a.bounds, recs, occ_s, n, threadIdx.x - 64u, rep_recs, rep_idx, nullptr, &sizes[1]);
   }
   __syncthreads();
-  const CandidateList adm{adm_recs, adm_idx, adm_rank, NREG ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)sizes[0])};
-  const CandidateList rep{rep_recs, rep_idx, nullptr, NREG ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)sizes[1])};
+  const CandidateList adm{kAll ? recs : adm_recs, kAll ? nullptr : adm_idx, adm_rank,
+                          NREG ? 0u : kAll ? n : (uint32_t)__builtin_amdgcn_readfirstlane((int)sizes[0])};
+  const CandidateList rep{rep_recs, rep_idx, nullptr, LIST ? (uint32_t)__builtin_amdgcn_readfirstlane((int)sizes[1]) : 0u};
   float4 rreg[NREG ? NREG : 1];
   float rrank[NREG ? NREG : 1];
 #pragma unroll
@@ -445,16 +438,16 @@ __global__ __launch_bounds__(kAssignThreads) void assign_static_kernel(const Ass
     // always has loads in flight (the loop is otherwise load -> wait -> compute -> store)
     for (uint64_t g = g0; g < n_vec; g += stride) {
       if (g + stride < n_vec) nxt = load_request_vec(a, (g + stride) * V);
-      sat += assign_requests<kLat, V, NREG, kSQ>(a, g * V, n, recs, cls, adm, rep, rreg, rrank, &cur);
+      sat += assign_requests<kLat, V, NREG, kSQ, kAll>(a, g * V, n, recs, cls, adm, rep, rreg, rrank, &cur);
       cur = nxt;
     }
   } else {
     for (uint64_t g = g0; g < n_vec; g += stride)
-      sat += assign_requests<kLat, V, NREG, kSQ>(a, g * V, n, recs, cls, adm, rep, rreg, rrank);
+      sat += assign_requests<kLat, V, NREG, kSQ, kAll>(a, g * V, n, recs, cls, adm, rep, rreg, rrank);
   }
   if (V > 1 && blockIdx.x == 0) {  // the ragged tail, one request per thread
     const uint64_t r = n_vec * V + threadIdx.x;
-    if (r < a.n_req) sat += assign_requests<kLat, 1, NREG, kSQ>(a, r, n, recs, cls, adm, rep, rreg, rrank);
+    if (r < a.n_req) sat += assign_requests<kLat, 1, NREG, kSQ, kAll>(a, r, n, recs, cls, adm, rep, rreg, rrank);
   }
   // Admitted count: wavefront shuffle, block sum in LDS, then ONE returning device-scope atomic per
   // block on a 64-bit word the library owns and keeps at zero between calls: the block's count goes

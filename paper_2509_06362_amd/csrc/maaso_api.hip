@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 
 #include "assign_kernels.hpp"
 #include "sweep_kernels.hpp"
@@ -1383,23 +1384,33 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
     const uint32_t cap = (uint32_t)ctx->n_cu * (few ? 3u : 8u);
     if (blocks > cap) blocks = cap;
     TimedRegion timed(ctx, s);
-#define MAASO_LAUNCH_STATIC(LAT, V, NREG)                                                          \
-  do {                                                                                             \
-    if (prm->policy)                                                                               \
-      hipLaunchKernelGGL((assign_static_kernel<LAT, V, NREG, true>), dim3(blocks),                 \
-                         dim3(kAssignThreads), 0, s, a);                                           \
-    else                                                                                           \
-      hipLaunchKernelGGL((assign_static_kernel<LAT, V, NREG, false>), dim3(blocks),                \
-                         dim3(kAssignThreads), 0, s, a);                                           \
-  } while (0)
-    if (vec) {
-      if (few) { if (lat) MAASO_LAUNCH_STATIC(true, 4, 8); else MAASO_LAUNCH_STATIC(false, 4, 8); }
-      else     { if (lat) MAASO_LAUNCH_STATIC(true, 4, 0); else MAASO_LAUNCH_STATIC(false, 4, 0); }
-    } else {
-      if (few) { if (lat) MAASO_LAUNCH_STATIC(true, 1, 8); else MAASO_LAUNCH_STATIC(false, 1, 8); }
-      else     { if (lat) MAASO_LAUNCH_STATIC(true, 1, 0); else MAASO_LAUNCH_STATIC(false, 1, 0); }
-    }
-#undef MAASO_LAUNCH_STATIC
+    // How wide the listing of instances gets, and where comparing all of them is quicker: few slots, and a part of
+    // the threads with a second group of requests.  Measured, all / listed, largest slack, jittered profiles: 9
+    // slots, 1,500,000 requests (one group): 11.5 / 10.4 us; 2,500,000 (one or two): 15.6 / 18.0; 5,000,000: 25.1 / 22.6; 12
+    // slots: 12.7 / 10.2, 16.9 / 19.5, - / 22.6; 16 slots: 14.2 / 10.7, 19.4 / 19.9.  Shortest queue, 9 slots: 16.9 / 12.0, 21.2 / 18.9.
+    const uint64_t n_vec = (uint64_t)R / (vec ? 4u : 1u), stride = (uint64_t)blocks * kAssignThreads;
+    const bool all = !prm->policy && pl->i_pad <= 16u && n_vec > stride && n_vec <= 2u * stride;
+    const int list = few || all ? 0 : pl->i_pad <= 64u ? 1 : pl->i_pad <= 128u ? 2 : 4;
+    auto launch = [&](auto lat_, auto v_, auto nreg_, auto sq_, auto list_) {
+      hipLaunchKernelGGL((assign_static_kernel<lat_(), v_(), nreg_(), sq_(), list_()>), dim3(blocks), dim3(kAssignThreads), 0, s, a);
+    };
+    auto by_list = [&](auto lat_, auto v_, auto sq_) {
+      if (few) launch(lat_, v_, std::integral_constant<int, 8>{}, sq_, std::integral_constant<int, 0>{});
+      else if (list == 0) launch(lat_, v_, std::integral_constant<int, 0>{}, std::false_type{}, std::integral_constant<int, 0>{});
+      else if (list == 1) launch(lat_, v_, std::integral_constant<int, 0>{}, sq_, std::integral_constant<int, 1>{});
+      else if (list == 2) launch(lat_, v_, std::integral_constant<int, 0>{}, sq_, std::integral_constant<int, 2>{});
+      else launch(lat_, v_, std::integral_constant<int, 0>{}, sq_, std::integral_constant<int, 4>{});
+    };
+    auto by_policy = [&](auto lat_, auto v_) {
+      if (prm->policy) by_list(lat_, v_, std::true_type{});
+      else by_list(lat_, v_, std::false_type{});
+    };
+    auto by_width = [&](auto lat_) {
+      if (vec) by_policy(lat_, std::integral_constant<int, 4>{});
+      else by_policy(lat_, std::integral_constant<int, 1>{});
+    };
+    if (lat) by_width(std::true_type{});
+    else by_width(std::false_type{});
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
 

@@ -17,9 +17,17 @@ from paper_2509_06362_amd import binding, workloads as W  # noqa: E402
     (9, 1000, "mixed"), (64, 32768, "mixed"), (64, 32769, "mixed"), (256, 33000, "different"),
     (65, 40001, "alike"), (128, 2051, "different"), (200, 36000, "blocked"), (33, 5, "blocked"),
     (16, 70000, "bad"), (256, 3000, "different blocked"), (70, 3001, "different blocked"),
+    # listed with one, two and four slots per lane; and few slots with a second group of requests for a part of the
+    # threads, where nothing is listed, next to one group, two, and one slot more
+    (63, 700, "different"), (65, 700, "different blocked"), (128, 900, "mixed"), (129, 900, "different"), (12, 300, "blocked"),
+    (9, 2_097_152, "different"), (9, 2_097_160, "blocked"), (16, 2_100_003, "different blocked"), (17, 2_100_000, "different"),
+    (10, 4_194_309, "mixed"),
 ])
 def test_static_distributor_lists(i_pad, n_req, variant):
-    w = W.random_small(i_pad + n_req, 1, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=0.5)
+    few = min(n_req, 100_003)   # (the generator's arrivals end at 2^32 ticks: more requests repeat these)
+    w = W.random_small(i_pad + n_req, 1, i_pad, few, n_slo=3, b_cap=64, pen_kappa=0.5)
+    if n_req != few:
+        w = W.replace(w, arrival_ticks=None, **{k: np.resize(getattr(w, k), n_req) for k in ("prompt_len", "out_len", "slo_class")})
     w = W.replace(w, n_inst=np.full(1, i_pad, np.uint32))
     if variant == "alike":
         w = W.replace(w, tp_idx=np.full_like(w.tp_idx, 2), max_batch=np.full_like(w.max_batch, 8),
