@@ -159,8 +159,9 @@ const char* maaso_strerror(int status);
  *     enter only what its workspace is charged with (maaso_ctx_reserve, MAASO_E_WORKSPACE, MAASO_E_SHAPE
  *     of the no-allocation form), as they did when it was laid out by them;
  *   window_blocks: blocks of the windowed distributor's persistent kernel (at most one per compute
- *   unit is used).  Left at 0, windows of up to four requests are distributed by a single wavefront
- *   instead (no device-wide barrier per window); a value keeps the persistent kernel for them too.
+ *   unit is used).  Left at 0, windows of up to ten requests (five with more than 128 instance slots) are
+ *   distributed by a single wavefront instead (no device-wide barrier per window); a value keeps the
+ *   persistent kernel for them too.
  * Errors: INVALID_ARG. */
 int maaso_ctx_set_launch_shape(maaso_ctx* ctx, uint32_t sweep_requests_per_lane, uint32_t sweep_group,
                                uint32_t sweep_blocks_per_queue, uint32_t window_blocks);
@@ -296,7 +297,7 @@ typedef struct {
  * requests: occupancy and queued prefill ticks are added, the queue drains by the arrival time that
  * passed, and min(W,B) * elapsed / (s_bar * tbt_j) requests complete; blocked requests add no load.
  * After the last window the load is added and nothing drains.  window >= R behaves as one window.
- * Windows of more than four requests run in one persistent kernel whose blocks meet at a device-wide
+ * Windows of more than ten requests run in one persistent kernel whose blocks meet at a device-wide
  * barrier after every window, so all of them must be resident together: the kernel is launched
  * cooperatively, which the runtime either guarantees or refuses (MAASO_E_RESIDENCY, nothing ran).
  * Errors: INVALID_ARG, SHAPE, WORKSPACE, RESIDENCY, BUSY, HIP - all detected on the host. */

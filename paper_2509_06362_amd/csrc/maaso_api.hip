@@ -1415,12 +1415,14 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   }
 
   // Short windows (down to one request per window, the online distributor taken literally): one
-  // wavefront with the instances in its lanes and no device-wide barrier.  Measured per request, the
-  // persistent kernel against one wavefront: window 1: 1.98 / 0.41 us (64 slots), 2.20 / 0.80 (256); window 4:
-  // 0.51 / 0.30, 0.57 / 0.54; window 8: 0.27 / 0.28, 0.30 / 0.49.  The window_blocks knob set to a value
-  // asks for the persistent kernel below whatever the window.
-  const uint32_t short_window = pl->i_pad <= 128u ? 4u : 2u;
-  if (prm->policy == 0u && prm->window <= short_window && ctx->window_blocks == 0u) {
+  // wavefront with the instances in its lanes and no device-wide barrier.  Measured, the persistent kernel's time
+  // over one wavefront's: windows of 5 / 8 / 10 / 12 requests: 4 slots: 1.87 / 1.28 / 1.05 / 0.91, 64: 2.01 / 1.39 / 1.17 / 1.02, 100:
+  // 1.60 / 1.09 / 0.93 / 0.80, 128: 1.59 / 1.08 / 0.91; of 3 / 4 / 5 / 6: 200: 1.87 / 1.52 / 1.27 / 1.09, 256: 1.67 / 1.35 / 1.15 / 0.99.
+  // The window_blocks knob set to a value asks for the persistent kernel below whatever the window, and so does
+  // its profile for the windows that it describes.
+  const uint32_t short_window = pl->i_pad <= 64u ? 10u : pl->i_pad <= 128u ? 8u : 5u;
+  const bool profiled = ctx->window_profile && prm->window > (pl->i_pad <= 128u ? 4u : 2u);
+  if (prm->policy == 0u && prm->window <= short_window && ctx->window_blocks == 0u && !profiled) {
     const size_t lds = ((size_t)ctx->cells + 1u) * sizeof(float4);
     TimedRegion timed(ctx, s);
     if (pl->i_pad <= 64u) {

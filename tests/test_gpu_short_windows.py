@@ -55,6 +55,9 @@ def test_sweep_and_score(n_cand, i_pad, window, n_req, variant, gaps, kw):
     (65, 1, 200, "full", "bursts"), (128, 1, 200, "long", "bursts"), (200, 1, 260, "full", "bursts"), (64, 1, 128, "wide", "far"),
     (40, 2, 127, "full", "bursts"), (64, 4, 256, "full", "far"), (100, 3, 200, "mixed", "bursts"), (256, 2, 130, "full", "close"),
     (64, 4, 255, "wide", "bursts"), (10, 1, 1, "mixed", "close"),
+    # the longest windows that one wavefront takes, and one request more
+    (64, 10, 205, "full", "bursts"), (64, 11, 205, "mixed", "bursts"), (65, 8, 200, "mixed", "far"), (128, 9, 200, "full", "bursts"),
+    (129, 5, 130, "full", "bursts"), (256, 6, 130, "mixed", "close"), (33, 7, 140, "wide", "far"), (5, 9, 70, "long", "bursts"),
 ])
 @pytest.mark.parametrize("mode,kappa", [(0, 0.5), (1, 0.0)])
 def test_distributor(i_pad, window, n_req, variant, gaps, mode, kappa):
