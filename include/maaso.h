@@ -135,7 +135,8 @@ void maaso_ctx_destroy(maaso_ctx* ctx);
  * i_pad instance slots and max_req requests is refused with MAASO_E_WORKSPACE, whatever launch shape
  * it takes (set the launch-shape knobs before reserving: more blocks per queue need more).  The
  * workspace is charged, for the static sweep, with 4*K*R bytes of prompt lengths, 16 bytes per instance
- * slot and its queues (it keeps 4*R of them); 12 KiB for the windowed distributor;
+ * slot and its queues (it keeps 4*R of them, and 4*C*K and some 50 KiB for thresholds and bests where
+ * there is room); 12 KiB for the windowed distributor;
  * 4 bytes per 1024 requests for maaso_split_by_slo.  The windowed sweep, the scores and the static
  * distributor use none.  Never shrinks.  A set-up call: it synchronises the device and reallocates
  * when the workspace has to grow.  Errors: INVALID_ARG, SHAPE, HIP, NOMEM, BUSY. */
@@ -159,7 +160,7 @@ const char* maaso_strerror(int status);
  *     enter only what its workspace is charged with (maaso_ctx_reserve, MAASO_E_WORKSPACE, MAASO_E_SHAPE
  *     of the no-allocation form), as they did when it was laid out by them;
  *   window_blocks: blocks of the windowed distributor's persistent kernel (at most one per compute
- *   unit is used).  Left at 0, windows of up to ten requests (five with more than 128 instance slots) are
+ *   unit is used).  Left at 0, windows of up to ten requests (eight beyond 64 instance slots, five beyond 128) are
  *   distributed by a single wavefront instead (no device-wide barrier per window); a value keeps the
  *   persistent kernel for them too.
  * Errors: INVALID_ARG. */
@@ -297,7 +298,8 @@ typedef struct {
  * requests: occupancy and queued prefill ticks are added, the queue drains by the arrival time that
  * passed, and min(W,B) * elapsed / (s_bar * tbt_j) requests complete; blocked requests add no load.
  * After the last window the load is added and nothing drains.  window >= R behaves as one window.
- * Windows of more than ten requests run in one persistent kernel whose blocks meet at a device-wide
+ * Windows of more than ten requests (eight beyond 64 instance slots, five beyond 128) run in one
+ * persistent kernel whose blocks meet at a device-wide
  * barrier after every window, so all of them must be resident together: the kernel is launched
  * cooperatively, which the runtime either guarantees or refuses (MAASO_E_RESIDENCY, nothing ran).
  * Errors: INVALID_ARG, SHAPE, WORKSPACE, RESIDENCY, BUSY, HIP - all detected on the host. */
