@@ -333,12 +333,17 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
   // Short windows go to the kernel whose lanes are the instances while a request is scored (no search for
-  // the instances a request can be given, but all of them at every request).  Measured, lanes-are-requests
-  // against it, us per window of 2700 candidates: 16 slots, windows of 8: 4.75 / 3.07, of 16: 4.17 / 5.52; 32 slots, 8:
-  // 5.67 / 3.11, 16: 5.55 / 5.68; 64 slots, 16: 6.04 / 5.65, 24: 5.85 / 8.32; 128 slots, 16: 7.27 / 7.56; 256 slots, 16:
-  // 11.4 / 9.5, 24: 12.0 / 13.8.  On jittered profiles, where many instances stay, the search takes longer: 128 slots, 24:
-  // 13.1 / 11.0; 256 slots, 24: 22.1 / 13.9, 32: 21.7 / 17.9.  8000 candidates cross over at the same windows.
-  const uint32_t short_window = a.i_pad > 128u ? 24u : a.i_pad > 32u ? 16u : 8u;
+  // the instances a request can be given, but all of them at every request).  Measured, the lanes-are-requests kernel's
+  // time over its (least of three layouts, jittered and smooth profiles, loaded and fresh instances; 2700 candidates, the
+  // lines lie lower for these than for 9000 or 20000): 8 slots, windows of 12: 1.06, 13: 1.04, 16: 0.88; 12 slots, 14: 1.08, 16:
+  // 0.97; 16 slots, 16: 1.11, 20: 0.92; 24 slots, 20: 1.04; 32 slots, 20: 1.18; 40 slots, 24: 1.06; 48 slots, 24: 1.11, 28: 0.96;
+  // 64 slots, 24: 1.19, 28: 1.02, 34: 0.85; 80 slots, 24: 1.04; 100 slots, 24: 1.10, 28: 0.98; 136 slots, 28: 1.06; 200 slots,
+  // 28: 1.09, 34: 0.90.  With the score's sums, which cost it more: 8 slots, 12: 1.02; 16 slots, 16: 1.03; 24 slots, 20: 0.96;
+  // 40 slots, 24: 0.97; 64 slots, 24: 1.09; 80 slots, 24: 0.92; 136 slots, 28: 0.96 (9000: 0.90).  (The block form ahead of it
+  // takes few candidates.)
+  const uint32_t I = a.i_pad;
+  const uint32_t short_window = I >= 40u ? (I > 128u ? (kScore ? 24u : 28u) : (kScore ? 20u : 24u))
+                                : I >= 24u ? (kScore ? 18u : 20u) : I >= 16u ? 16u : I >= 8u ? 12u : 8u;
   bool one_by_one = !kSQ;
   for (uint32_t k = 0; k < a.n_sets; ++k) one_by_one = one_by_one && a.sets[k].window <= short_window;
   if (one_by_one) {

@@ -38,6 +38,9 @@ CASES = [
     (1030, 20, 1, 70, "full", "bursts"), (1026, 100, 1, 66, "mixed", "far"), (1025, 9, 2, 65, "wide", "bursts"),
     (7, 33, 2, 131, "full", "bursts"), (4, 70, 3, 128, "mixed", "far"), (4, 200, 2, 121, "wide", "close"),
     (2570, 40, 12, 100, "full", "bursts"), (4, 256, 4, 64, "full", "far"),
+    # the longest windows of a line, and a request more (more candidates than a block each is used for)
+    (2561, 8, 12, 73, "full", "bursts"), (2561, 16, 16, 81, "mixed", "far"), (2561, 24, 20, 101, "long", "bursts"),
+    (2561, 40, 24, 130, "wide", "close"), (2561, 40, 25, 130, "full", "bursts"), (2561, 129, 28, 60, "full", "far"),
 ]
 
 
