@@ -152,7 +152,8 @@ struct AdmissionBounds {
   // the largest first-token deadline is below kNarrowSeconds and no wait can come out as no number: the
   // ticks of an admitted request's wait or prefill, and the sum of four prefills, fit 32 bits
   bool narrow;
-  // the same, and the queue of an instance that admits all of a window stays below 2^32 ticks
+  // the same, the queue of an instance that admits all of a window stays below 2^32 ticks, and no service time
+  // is zero
   bool narrow_queue;
 };
 

@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cfloat>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -50,7 +51,7 @@ struct maaso_ctx {
   int device;
   uint32_t n_tp, b_cap, cells, n_slo;
   float d_ttft[kMaxSlo], d_tbt[kMaxSlo], i_ttft[kMaxSlo], i_tbt[kMaxSlo];
-  float tbt_max;        // largest entry of the per-token latency table
+  float tbt_min, tbt_max;  // least and largest entry of the per-token latency table
   float* tab;           // device: three tables back to back, then tp_degree [n_tp] as uint32
   bool has_degree;      // the profile came with GPUs-per-instance figures
   uint32_t* status;     // device status word
@@ -199,6 +200,8 @@ ModelParams model_params(const maaso_ctx* ctx, const maaso_params* prm) {
 // AdmissionBounds::narrow (per_window = 0) and narrow_queue.  The occupancy penalty is at most 1 + pen_kappa;
 // a finite service time leaves no 0 * inf in a wait.  An instance admits while its wait is within the
 // largest first-token deadline D, and so is each prefill: its queue ends a window below D * (1 + window).
+// narrow_queue also takes a service time that is not zero in binary32: NarrowSequence lets no time pass behind the
+// last window and relies on nothing completing in none.
 bool narrow_ticks(const maaso_ctx* ctx, const maaso_params* prm, uint64_t per_window) {
   double d = 0.0;
   for (uint32_t k = 0; k < ctx->n_slo; ++k) d = std::max(d, (double)ctx->d_ttft[k]);
@@ -215,7 +218,8 @@ AdmissionBounds admission_bounds(const maaso_ctx* ctx, const maaso_params* prm) 
   b.e_ttft = b.d_ttft * 0x1p-20f;
   b.e_tbt = b.d_tbt * 0x1p-20f;
   b.narrow = narrow_ticks(ctx, prm, 0u);
-  b.narrow_queue = narrow_ticks(ctx, prm, prm->window ? prm->window : MAASO_MAX_REQUESTS);
+  b.narrow_queue = (double)prm->s_bar * (double)ctx->tbt_min >= (double)FLT_MIN &&
+                   narrow_ticks(ctx, prm, prm->window ? prm->window : MAASO_MAX_REQUESTS);
   return b;
 }
 
@@ -871,9 +875,13 @@ int maaso_profile_tables_load(const maaso_profile_desc* d, int device, maaso_ctx
   ctx->cells = cells;
   ctx->n_slo = d->n_slo;
   ctx->spin_limit = 1u << 22;
+  ctx->tbt_min = INFINITY;
   for (uint32_t t = 0; t < d->n_tp; ++t)
-    for (uint32_t b = 1; b <= d->b_cap; ++b)
-      ctx->tbt_max = std::max(ctx->tbt_max, d->tbt[(size_t)t * (d->b_cap + 1u) + b]);
+    for (uint32_t b = 1; b <= d->b_cap; ++b) {
+      const float tbt = d->tbt[(size_t)t * (d->b_cap + 1u) + b];
+      ctx->tbt_min = std::min(ctx->tbt_min, tbt);
+      ctx->tbt_max = std::max(ctx->tbt_max, tbt);
+    }
   for (uint32_t k = 0; k < kMaxSlo; ++k) {
     const bool live = k < d->n_slo;
     ctx->d_ttft[k] = live ? d->d_ttft[k] : 1.0f;

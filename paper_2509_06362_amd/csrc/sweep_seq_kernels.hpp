@@ -293,7 +293,8 @@ struct NarrowSequence {
     }
     begin(rows, mp);
   }
-  // `delta` ticks pass, none behind the last window; `at_most`: uniform, no fewer than those.
+  // `delta` ticks pass, none behind the last window, where nothing completes (narrow_queue: no service time is zero);
+  // `at_most`: uniform, no fewer than those.
   template <bool kOne>
   __device__ __forceinline__ void close_window(uint32_t delta, uint32_t at_most, bool, const float4* rows, const ModelParams& mp) {
     if (kOne) {

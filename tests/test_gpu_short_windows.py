@@ -79,3 +79,28 @@ def test_distributor(i_pad, window, n_req, variant, gaps, mode, kappa):
         assert binding.maaso_ctx_device_status(dw.ctx) == 0
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("i_pad,window,n_req", [(4, 5, 3), (4, 1, 3), (40, 1, 130), (64, 3, 128), (70, 1, 65), (100, 8, 90),
+                                                (200, 1, 64), (130, 5, 12), (4, 60, 300)])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("s_bar,tbt", [(1e-40, 1e-6), (1e-30, 1e-20)])
+def test_nothing_completes_behind_the_last_window(i_pad, window, n_req, mode, s_bar, tbt):
+    """A service time that is zero in binary32: all requests complete between two windows, however short the time, and
+    none behind the last one, where no time passes."""
+    w = workload(2, i_pad, n_req, "full", "close", n_slo=3)
+    w = W.replace(w, n_inst=np.full_like(w.n_inst, i_pad), s_bar=np.float32(s_bar), tbt=np.full_like(w.tbt, tbt), tbt_mode=mode)
+    print(f"zero service time I={i_pad} R={n_req} window={window} mode={mode} s_bar={s_bar}", flush=True)
+    dw = binding.DeviceWorkload(w)
+    try:
+        got = dw.assign(cand=1, window=window)
+        torch.cuda.synchronize()
+        ref = oracle.score_assign(w, cand=1, window=window)
+        assert n_req > window or int(ref["occ"].sum()) == int(w.occ[1].sum()) + ref["n_satisfied"] > 0
+        for key in ("chosen", "slack"):
+            assert np.array_equal(got[key].cpu().numpy(), ref[key]), key
+        assert int(got["n_satisfied"].item()) == ref["n_satisfied"]
+        assert np.array_equal(got["occ"].cpu().numpy()[0], ref["occ"])
+        assert np.array_equal(got["q_ticks"].cpu().numpy()[0].view(np.uint64), ref["q_ticks"])
+    finally:
+        dw.close()
