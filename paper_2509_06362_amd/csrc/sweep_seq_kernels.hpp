@@ -102,6 +102,7 @@ struct Sequence {
   unsigned long long bad;  // lanes with a slot outside the tables, over the whole run
   uint32_t dirty;          // rows of slots whose occupancy changed in this window
   bool wide;               // some queue holds 2^32 ticks or more
+  bool narrow;             // narrow_queue: an admission cannot make `wide` true, a prefill's ticks fit 32 bits
 
   __device__ __forceinline__ void load(int s, bool present, const ModelParams& mp, uint32_t cells, uint32_t tp,
                                        uint32_t b, int32_t occ, uint64_t q) {
@@ -124,7 +125,7 @@ struct Sequence {
   __device__ __forceinline__ void begin(const float4* rows, const ModelParams& mp) {
     bad = 0ull;
     dirty = 0u;
-    wide = false;  // (an admission cannot make it true where narrow_queue holds)
+    wide = false;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       evaluate(s, rows, mp);
@@ -141,10 +142,13 @@ struct Sequence {
   template <bool kOne>
   __device__ __forceinline__ void admit(int s, uint32_t l, const float4*, const ModelParams&) {
     const bool me = in_mask(1ull << l);
-    const unsigned long long t = to_ticks(pre[s], false);
+    const unsigned long long t = to_ticks(pre[s], narrow);
     slot[s].occ += me ? 1 : 0;
     slot[s].q += me ? t : 0ull;
-    wide |= slot[s].any_wide();
+    if (!narrow) {
+      rare_path();
+      wide |= slot[s].any_wide();
+    }
     dirty |= 1u << s;
   }
   // `delta` ticks pass (`last`: nothing follows, no time passes).
@@ -493,6 +497,7 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : (kScore ? 4 : 5)) void sw
     run(sq);
   } else {
     Sequence<S> sq;
+    sq.narrow = a.bounds.narrow_queue;
     run(sq);
     bad = sq.bad;
   }
@@ -761,6 +766,7 @@ __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint
     run(sq);
   } else {
     Sequence<S> sq;
+    sq.narrow = a.bounds.narrow_queue;
     run(sq);
     if (sq.bad != 0ull) raise_status(a.status, 2u);
   }
