@@ -27,6 +27,8 @@
 // need every instance's queue length); the windowed kernel serves it.
 #pragma once
 
+#include <type_traits>
+
 #include "sweep_window_kernels.hpp"
 #include "window_kernels.hpp"
 #include "window_rules.hpp"
@@ -102,7 +104,6 @@ struct Sequence {
   unsigned long long bad;  // lanes with a slot outside the tables, over the whole run
   uint32_t dirty;          // rows of slots whose occupancy changed in this window
   bool wide;               // some queue holds 2^32 ticks or more
-  bool narrow;             // narrow_queue: an admission cannot make `wide` true, a prefill's ticks fit 32 bits
 
   __device__ __forceinline__ void load(int s, bool present, const ModelParams& mp, uint32_t cells, uint32_t tp,
                                        uint32_t b, int32_t occ, uint64_t q) {
@@ -136,17 +137,23 @@ struct Sequence {
 #pragma unroll
     for (int s = 0; s < S; ++s) rec[s].wait = slot[s].wait_with(past[s], wide);
   }
-  // The request scored last is admitted to instance j = (s, l): it loads it at the window's end.
   __device__ __forceinline__ int32_t occupancy(int s) const { return slot[s].occ; }
   __device__ __forceinline__ uint64_t queue(int s) const { return slot[s].q; }
-  template <bool kOne>
-  __device__ __forceinline__ void admit(int s, uint32_t l, const float4*, const ModelParams&) {
+  // The request scored last is admitted to instance j = (s, l): it loads it at the window's end.  `narrow`:
+  // narrow_queue, so that no admission makes `wide` true and a prefill's ticks fit 32 bits; the constant
+  // std::false_type where that is not asked.
+  template <bool kOne, class Narrow>
+  __device__ __forceinline__ void admit(int s, uint32_t l, const float4*, const ModelParams&, const Narrow narrow) {
     const bool me = in_mask(1ull << l);
     const unsigned long long t = to_ticks(pre[s], narrow);
     slot[s].occ += me ? 1 : 0;
     slot[s].q += me ? t : 0ull;
-    if (!narrow) {
-      rare_path();
+    if constexpr (std::is_same_v<Narrow, bool>) {
+      if (!narrow) {
+        rare_path();
+        wide |= slot[s].any_wide();
+      }
+    } else {
       wide |= slot[s].any_wide();
     }
     dirty |= 1u << s;
@@ -268,8 +275,8 @@ struct NarrowSequence {
   __device__ __forceinline__ uint64_t queue(int s) const { return q[s]; }
   // The request scored last is admitted to instance (s, l).  With windows of one request the instance is
   // evaluated for the next one right away.
-  template <bool kOne>
-  __device__ __forceinline__ void admit(int s, uint32_t l, const float4* rows, const ModelParams& mp) {
+  template <bool kOne, class Narrow>
+  __device__ __forceinline__ void admit(int s, uint32_t l, const float4* rows, const ModelParams& mp, Narrow) {
     changed[s] |= 1ull << l;
     if (in_mask(1ull << l)) {
       q[s] += (uint32_t)rintf(pre[s] * 1048576.0f);
@@ -407,7 +414,7 @@ __device__ __forceinline__ void walk_windows(const SweepWindowArgs& a, const Swe
               served[s] |= 1ull << l;
               waits = with_lane(waits, (int)i, lane_value(sq.rec[s].wait, (int)l));
             }
-            sq.template admit<kOne>(s, l, rows, a.mp);
+            sq.template admit<kOne>(s, l, rows, a.mp, (bool)a.bounds.narrow_queue);
           }
       }
       bit <<= 1;
@@ -497,7 +504,6 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : (kScore ? 4 : 5)) void sw
     run(sq);
   } else {
     Sequence<S> sq;
-    sq.narrow = a.bounds.narrow_queue;
     run(sq);
     bad = sq.bad;
   }
@@ -701,7 +707,7 @@ __device__ __forceinline__ unsigned long long assign_windows(const AssignArgs& a
               o.e2e = with_lane(o.e2e, (int)i, lane_value(sq.e2e[s], (int)l));
             }
             // admitted: it loads the instance; a blocked request does not
-            if (__builtin_bit_cast(int, best) >= 0) sq.template admit<kOne>(s, l, rows, a.mp);
+            if (__builtin_bit_cast(int, best) >= 0) sq.template admit<kOne>(s, l, rows, a.mp, std::false_type{});
           }
         delta += (uint32_t)__builtin_amdgcn_readlane((int)gap, (int)i);
       } while (++i < stop && !kOne);
@@ -766,7 +772,6 @@ __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint
     run(sq);
   } else {
     Sequence<S> sq;
-    sq.narrow = a.bounds.narrow_queue;
     run(sq);
     if (sq.bad != 0ull) raise_status(a.status, 2u);
   }
