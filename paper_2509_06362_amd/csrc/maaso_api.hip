@@ -320,7 +320,7 @@ BlockWindows block_windows(uint64_t blocks, uint32_t i_pad, bool shortest_queue)
 // The windowed sweep of every (request set, candidate); shapes are chosen by the set with the longest
 // windows (the choice never changes a result).
 template <bool kScore, bool kSQ>
-int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
+int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, hipStream_t s) {
   uint64_t per_window = 0;
   for (uint32_t k = 0; k < a.n_sets; ++k) {
     const uint64_t pw = a.sets[k].window < a.sets[k].n_req ? a.sets[k].window : a.sets[k].n_req;
@@ -351,9 +351,18 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
   bool one_by_one = !kSQ;
   for (uint32_t k = 0; k < a.n_sets; ++k) one_by_one = one_by_one && a.sets[k].window <= short_window;
   if (one_by_one) {
-    const uint32_t per_block = blocks > kSeqSpread && a.i_pad <= 128u ? kSeqThreads / 64 : 4u;  // wavefronts
-    const dim3 g((a.n_cand + per_block - 1u) / per_block * a.n_sets);
     const size_t lds_seq = ((size_t)a.cells + 1u) * sizeof(float4);  // one more row: slots without an instance
+    // Wavefronts per block: eight (tables and requests shared by more, 2 to 3 % faster where both spread as well), four
+    // where that leaves fewer on the fullest compute unit and the tables leave room for its blocks.  64 slots, eight / four, us:
+    // 3000 candidates one by one 73.5 / 66.2, windows of 3: 69.4 / 64.3; 5000: 92.6 / 84.8; 9000: 140 / 132; 128 slots, 6000: 128 / 132;
+    // 8192: 158 / 162, with tables of 1028 cells (seven blocks of four at a time) 158 / 171.
+    auto fullest = [&](uint32_t waves) {  // blocks on it
+      return ((uint64_t)((a.n_cand + waves - 1u) / waves) * a.n_sets + n_cu - 1u) / n_cu;
+    };
+    const uint32_t fit = std::min(kSeqLds / (uint32_t)(lds_seq + kSeqShared), 8u);
+    const bool four = a.i_pad > 128u || (fullest(4u) < 2u * fullest(8u) && (fit == 8u || fullest(4u) <= fit));
+    const uint32_t per_block = four ? 4u : kSeqThreads / 64;
+    const dim3 g((a.n_cand + per_block - 1u) / per_block * a.n_sets);
     bool one = true;  // every set request by request
     for (uint32_t k = 0; k < a.n_sets; ++k) one = one && a.sets[k].window == 1u;
     if (!kSQ) {
@@ -378,9 +387,11 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, hipStream_t s) {
 }
 
 template <bool kScore>
-int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, size_t lds, hipStream_t s) {
-  return policy ? launch_sweep_window_v<kScore, true>(a, lds, s)
-                : launch_sweep_window_v<kScore, false>(a, lds, s);
+int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, const maaso_ctx* ctx, hipStream_t s) {
+  const size_t lds = (size_t)3 * ctx->cells * sizeof(float);  // profile tables
+  const uint32_t n_cu = (uint32_t)ctx->n_cu;
+  return policy ? launch_sweep_window_v<kScore, true>(a, lds, n_cu, s)
+                : launch_sweep_window_v<kScore, false>(a, lds, n_cu, s);
 }
 
 // Everything but the request sets.
@@ -733,7 +744,7 @@ int launch_score_sets(maaso_ctx* ctx, const maaso_placements* pl, uint32_t n_set
   a.gamma_l = wts->gamma_l;
   {
     TimedRegion timed(ctx, s);
-    const int rc = launch_sweep_window<true>(a, prm->policy, (size_t)3 * ctx->cells * sizeof(float), s);
+    const int rc = launch_sweep_window<true>(a, prm->policy, ctx, s);
     if (rc != MAASO_OK) return rc;
   }
   for (uint32_t k = 0; k < n_sets; ++k)
@@ -1044,7 +1055,7 @@ int placement_sweep_impl(maaso_ctx* ctx, const maaso_placements* pl, const maaso
     add_sweep_window_set(a, rq, prm, sat_count, nullptr);
     {
       TimedRegion timed(ctx, s);
-      rc = launch_sweep_window<false>(a, prm->policy, (size_t)3 * ctx->cells * sizeof(float), s);
+      rc = launch_sweep_window<false>(a, prm->policy, ctx, s);
       if (rc != MAASO_OK) return rc;
     }
     hipLaunchKernelGGL(sweep_finalize_kernel, dim3(1), dim3(1024), 0, s, sat_count, C, R, sat_ratio,

@@ -38,7 +38,7 @@
 namespace maaso {
 
 constexpr int kSeqThreads = 512;    // up to eight wavefronts = candidates of a request set per block
-constexpr uint32_t kSeqSpread = 1024;  // up to so many candidates a block takes four: they spread over the chip
+constexpr uint32_t kSeqLds = 160u << 10;  // LDS of a compute unit
 constexpr uint32_t kSeqChunk = 64;  // requests prepared at a time, by one of the block's wavefronts in turn
 
 // The three profile tables in LDS, a row {a, p, tbt, row_safe_ticks} per entry, and one row more: that of a
@@ -349,6 +349,7 @@ struct SeqChunks {
   uint32_t t[2][kSeqChunk];
   uint32_t t_max[2];  // kOne: the longest of a chunk's times
 };
+constexpr uint32_t kSeqShared = sizeof(SeqChunks) + kMaxSlo * sizeof(ClassRow);  // of a block beside the tables
 
 // One candidate through the windows of a request set.  served: per row of slots, the lanes that admitted a
 // request.  Every wavefront of the block calls it for the same set: they prepare the chunks in turn.
