@@ -365,18 +365,22 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, h
     const dim3 g((a.n_cand + per_block - 1u) / per_block * a.n_sets);
     bool one = true;  // every set request by request
     for (uint32_t k = 0; k < a.n_sets; ++k) one = one && a.sets[k].window == 1u;
-    if (!kSQ) {
+    if constexpr (!kSQ) {
       const dim3 b(per_block * 64u);
-      if (a.i_pad <= 64u) {
-        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1, true>), g, b, lds_seq, s, a);
-        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 1>), g, b, lds_seq, s, a);
-      } else if (a.i_pad <= 128u) {
-        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 2, true>), g, b, lds_seq, s, a);
-        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 2>), g, b, lds_seq, s, a);
-      } else {
-        if (one) hipLaunchKernelGGL((sweep_seq_kernel<kScore, 4, true>), g, b, lds_seq, s, a);
-        else hipLaunchKernelGGL((sweep_seq_kernel<kScore, 4>), g, b, lds_seq, s, a);
-      }
+      auto launch = [&](auto s_, auto one_, auto fits_) {
+        hipLaunchKernelGGL((sweep_seq_kernel<kScore, s_(), one_(), fits_()>), g, b, lds_seq, s, a);
+      };
+      auto by_form = [&](auto s_, auto one_) {
+        if (a.bounds.narrow_queue) launch(s_, one_, std::true_type{});
+        else launch(s_, one_, std::false_type{});
+      };
+      auto by_slots = [&](auto one_) {
+        if (a.i_pad <= 64u) by_form(std::integral_constant<int, 1>{}, one_);
+        else if (a.i_pad <= 128u) by_form(std::integral_constant<int, 2>{}, one_);
+        else by_form(std::integral_constant<int, 4>{}, one_);
+      };
+      if (one) by_slots(std::true_type{});
+      else by_slots(std::false_type{});
     }
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }

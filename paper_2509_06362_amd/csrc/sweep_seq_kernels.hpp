@@ -27,8 +27,6 @@
 // need every instance's queue length); the windowed kernel serves it.
 #pragma once
 
-#include <type_traits>
-
 #include "sweep_window_kernels.hpp"
 #include "window_kernels.hpp"
 #include "window_rules.hpp"
@@ -93,7 +91,9 @@ __device__ __forceinline__ uint32_t holder_of(const float (&slack)[S], float bes
 }
 
 // A placement in the lanes of one wavefront, taken through windows of requests.
-template <int S>
+// kFits: narrow_queue holds, so that no admission makes `wide` true and a prefill's ticks fit 32 bits (false is always
+// right).
+template <int S, bool kFits = false>
 struct Sequence {
   static constexpr bool kNarrow = false;
   LiveSlot slot[S];
@@ -139,23 +139,14 @@ struct Sequence {
   }
   __device__ __forceinline__ int32_t occupancy(int s) const { return slot[s].occ; }
   __device__ __forceinline__ uint64_t queue(int s) const { return slot[s].q; }
-  // The request scored last is admitted to instance j = (s, l): it loads it at the window's end.  `narrow`:
-  // narrow_queue, so that no admission makes `wide` true and a prefill's ticks fit 32 bits; the constant
-  // std::false_type where that is not asked.
-  template <bool kOne, class Narrow>
-  __device__ __forceinline__ void admit(int s, uint32_t l, const float4*, const ModelParams&, const Narrow narrow) {
+  // The request scored last is admitted to instance j = (s, l): it loads it at the window's end.
+  template <bool kOne>
+  __device__ __forceinline__ void admit(int s, uint32_t l, const float4*, const ModelParams&) {
     const bool me = in_mask(1ull << l);
-    const unsigned long long t = to_ticks(pre[s], narrow);
+    const unsigned long long t = to_ticks(pre[s], kFits);
     slot[s].occ += me ? 1 : 0;
     slot[s].q += me ? t : 0ull;
-    if constexpr (std::is_same_v<Narrow, bool>) {
-      if (!narrow) {
-        rare_path();
-        wide |= slot[s].any_wide();
-      }
-    } else {
-      wide |= slot[s].any_wide();
-    }
+    if (!kFits) wide |= slot[s].any_wide();
     dirty |= 1u << s;
   }
   // `delta` ticks pass (`last`: nothing follows, no time passes).
@@ -275,8 +266,8 @@ struct NarrowSequence {
   __device__ __forceinline__ uint64_t queue(int s) const { return q[s]; }
   // The request scored last is admitted to instance (s, l).  With windows of one request the instance is
   // evaluated for the next one right away.
-  template <bool kOne, class Narrow>
-  __device__ __forceinline__ void admit(int s, uint32_t l, const float4* rows, const ModelParams& mp, Narrow) {
+  template <bool kOne>
+  __device__ __forceinline__ void admit(int s, uint32_t l, const float4* rows, const ModelParams& mp) {
     changed[s] |= 1ull << l;
     if (in_mask(1ull << l)) {
       q[s] += (uint32_t)rintf(pre[s] * 1048576.0f);
@@ -415,7 +406,7 @@ __device__ __forceinline__ void walk_windows(const SweepWindowArgs& a, const Swe
               served[s] |= 1ull << l;
               waits = with_lane(waits, (int)i, lane_value(sq.rec[s].wait, (int)l));
             }
-            sq.template admit<kOne>(s, l, rows, a.mp, (bool)a.bounds.narrow_queue);
+            sq.template admit<kOne>(s, l, rows, a.mp);
           }
       }
       bit <<= 1;
@@ -451,8 +442,8 @@ __device__ __forceinline__ void walk_windows(const SweepWindowArgs& a, const Swe
   }
 }
 
-// kOne: every set's window is one request.
-template <bool kScore, int S, bool kOne = false>
+// kOne: every set's window is one request.  kFits: narrow_queue.
+template <bool kScore, int S, bool kOne, bool kFits>
 __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : (kScore ? 4 : 5)) void sweep_seq_kernel(const SweepWindowArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   float4* rows = reinterpret_cast<float4*>(smem);
@@ -476,7 +467,7 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : (kScore ? 4 : 5)) void sw
   uint32_t tp[S], B[S];
   int32_t occ[S];
   uint64_t q[S];
-  bool narrow = a.bounds.narrow_queue;
+  bool narrow = kFits;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const uint32_t j = (uint32_t)s * 64u + lane;
@@ -500,11 +491,11 @@ __global__ __launch_bounds__(kSeqThreads, S <= 2 ? 8 : (kScore ? 4 : 5)) void sw
     for (int s = 0; s < S; ++s) inv_tbt_first[s] = kScore ? (sq.past[s] == INFINITY ? 0.0f : 1.0f / sq.rec[s].tbt) : 0.0f;
     walk_windows<kScore, S, kOne>(a, rs, sq, rows, cls, chunks, lane, wave, n_waves, served, sat, wait_sum);
   };
-  if (narrow) {
+  if (kFits && narrow) {
     NarrowSequence<S> sq;
     run(sq);
   } else {
-    Sequence<S> sq;
+    Sequence<S, kFits> sq;
     run(sq);
     bad = sq.bad;
   }
@@ -708,7 +699,7 @@ __device__ __forceinline__ unsigned long long assign_windows(const AssignArgs& a
               o.e2e = with_lane(o.e2e, (int)i, lane_value(sq.e2e[s], (int)l));
             }
             // admitted: it loads the instance; a blocked request does not
-            if (__builtin_bit_cast(int, best) >= 0) sq.template admit<kOne>(s, l, rows, a.mp, std::false_type{});
+            if (__builtin_bit_cast(int, best) >= 0) sq.template admit<kOne>(s, l, rows, a.mp);
           }
         delta += (uint32_t)__builtin_amdgcn_readlane((int)gap, (int)i);
       } while (++i < stop && !kOne);
