@@ -160,8 +160,9 @@ const char* maaso_strerror(int status);
  *     enter only what its workspace is charged with (maaso_ctx_reserve, MAASO_E_WORKSPACE, MAASO_E_SHAPE
  *     of the no-allocation form), as they did when it was laid out by them;
  *   window_blocks: blocks of the windowed distributor's persistent kernel (at most one per compute
- *   unit is used).  Left at 0, windows of up to ten requests (eight beyond 64 instance slots, five beyond 128) are
- *   distributed by a single wavefront instead (no device-wide barrier per window); a value keeps the
+ *   unit is used).  Left at 0, windows of up to ten requests (eight beyond 64 instance slots, five beyond 128;
+ *   eight, six and four where the largest first-token deadline D reaches 512 s, or D * (1 + window) 4095 s)
+ *   are distributed by a single wavefront instead (no device-wide barrier per window); a value keeps the
  *   persistent kernel for them too.
  * Errors: INVALID_ARG. */
 int maaso_ctx_set_launch_shape(maaso_ctx* ctx, uint32_t sweep_requests_per_lane, uint32_t sweep_group,
@@ -211,7 +212,7 @@ int maaso_probe_valu(int device, uint32_t pattern, uint32_t trips, double* lane_
                      uint32_t* instructions_per_trip);
 
 /* Where the windowed distributor's time goes.  With profiling enabled, a maaso_score_assign call that
- * runs the persistent windowed kernel (window > 4, policy 0, no latency outputs) has block 0 sum the
+ * runs the persistent windowed kernel (window > 4, > 2 beyond 128 slots, policy 0, no latency outputs) has block 0 sum the
  * shader clock cycles it spends, per window, on: [0] evaluating the instances' profiles for the
  * window's state, [1] scoring its share of the window's requests, [2] exchanging the admitted load
  * with the other blocks (device-wide barrier included), [3] advancing the state; [4] is the whole
@@ -298,8 +299,8 @@ typedef struct {
  * requests: occupancy and queued prefill ticks are added, the queue drains by the arrival time that
  * passed, and min(W,B) * elapsed / (s_bar * tbt_j) requests complete; blocked requests add no load.
  * After the last window the load is added and nothing drains.  window >= R behaves as one window.
- * Windows of more than ten requests (eight beyond 64 instance slots, five beyond 128) run in one
- * persistent kernel whose blocks meet at a device-wide
+ * Windows of more than ten requests (fewer with many instance slots or very long deadlines, see
+ * maaso_ctx_set_launch_shape) run in one persistent kernel whose blocks meet at a device-wide
  * barrier after every window, so all of them must be resident together: the kernel is launched
  * cooperatively, which the runtime either guarantees or refuses (MAASO_E_RESIDENCY, nothing ran).
  * Errors: INVALID_ARG, SHAPE, WORKSPACE, RESIDENCY, BUSY, HIP - all detected on the host. */

@@ -336,18 +336,8 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, h
     hipLaunchKernelGGL((sweep_block_kernel<kScore, kSQ>), dim3((uint32_t)blocks), dim3(kBlockThreads), lds, s, a, lpr_log2);
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
-  // Short windows go to the kernel whose lanes are the instances while a request is scored (no search for
-  // the instances a request can be given, but all of them at every request).  Measured, the lanes-are-requests kernel's
-  // time over its (least of three layouts, jittered and smooth profiles, loaded and fresh instances; 2700 candidates, the
-  // lines lie lower for these than for 9000 or 20000): 8 slots, windows of 12: 1.06, 13: 1.04, 16: 0.88; 12 slots, 14: 1.08, 16:
-  // 0.97; 16 slots, 16: 1.11, 20: 0.92; 24 slots, 20: 1.04; 32 slots, 20: 1.18; 40 slots, 24: 1.06; 48 slots, 24: 1.11, 28: 0.96;
-  // 64 slots, 24: 1.19, 28: 1.02, 34: 0.85; 80 slots, 24: 1.04; 100 slots, 24: 1.10, 28: 0.98; 136 slots, 28: 1.06; 200 slots,
-  // 28: 1.09, 34: 0.90.  With the score's sums, which cost it more: 8 slots, 12: 1.02; 16 slots, 16: 1.03; 24 slots, 20: 0.96;
-  // 40 slots, 24: 0.97; 64 slots, 24: 1.09; 80 slots, 24: 0.92; 136 slots, 28: 0.96 (9000: 0.90).  (The block form ahead of it
-  // takes few candidates.)
-  const uint32_t I = a.i_pad;
-  const uint32_t short_window = I >= 40u ? (I > 128u ? (kScore ? 24u : 28u) : (kScore ? 20u : 24u))
-                                : I >= 24u ? (kScore ? 18u : 20u) : I >= 16u ? 16u : I >= 8u ? 12u : 8u;
+  // Short windows go to the kernel whose lanes are the instances (the block form ahead of it takes few candidates).
+  const uint32_t short_window = sweep_short_window(a.i_pad, kScore, a.bounds.narrow_queue);
   bool one_by_one = !kSQ;
   for (uint32_t k = 0; k < a.n_sets; ++k) one_by_one = one_by_one && a.sets[k].window <= short_window;
   if (one_by_one) {
@@ -1443,12 +1433,10 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   }
 
   // Short windows (down to one request per window, the online distributor taken literally): one
-  // wavefront with the instances in its lanes and no device-wide barrier.  Measured, the persistent kernel's time
-  // over one wavefront's: windows of 5 / 8 / 10 / 12 requests: 4 slots: 1.87 / 1.28 / 1.05 / 0.91, 64: 2.01 / 1.39 / 1.17 / 1.02, 100:
-  // 1.60 / 1.09 / 0.93 / 0.80, 128: 1.59 / 1.08 / 0.91; of 3 / 4 / 5 / 6: 200: 1.87 / 1.52 / 1.27 / 1.09, 256: 1.67 / 1.35 / 1.15 / 0.99.
+  // wavefront with the instances in its lanes and no device-wide barrier.
   // The window_blocks knob set to a value asks for the persistent kernel below whatever the window, and so does
   // its profile for the windows that it describes.
-  const uint32_t short_window = pl->i_pad <= 64u ? 10u : pl->i_pad <= 128u ? 8u : 5u;
+  const uint32_t short_window = assign_short_window(pl->i_pad, a.bounds.narrow_queue);
   const bool profiled = ctx->window_profile && prm->window > (pl->i_pad <= 128u ? 4u : 2u);
   if (prm->policy == 0u && prm->window <= short_window && ctx->window_blocks == 0u && !profiled) {
     const size_t lds = ((size_t)ctx->cells + 1u) * sizeof(float4);

@@ -32,4 +32,34 @@ constexpr uint32_t row_safe_ticks(float s_bar, float tbt, uint32_t w, uint32_t w
   return x < 4e9f ? (uint32_t)x : 4000000000u;
 }
 
+// The longest windows of a windowed sweep or score that go to the kernel whose lanes are the instances while a request
+// is scored (no search for the instances a request can be given, but all of them at every request).  `narrow`: queues
+// fit 32 bits (AdmissionBounds::narrow_queue), so its 32-bit form runs wherever the slots allow it; else its general form.
+// Measured, the lanes-are-requests kernel's time over its, least of three layouts (jittered and smooth profiles, loaded and
+// fresh instances) and of 2700 and 9000 candidates:
+//   32 bits: 8 slots, windows of 12: 1.13, 13: 1.08, 16: 0.92; 16 slots, 16: 1.16, 20: 0.96; 24 slots, 20: 1.08; 32 slots, 20: 1.18;
+//   40 slots, 24: 1.10, 28: 0.94; 64 slots, 24: 1.18, 28: 1.02; 100 slots, 24: 1.15, 28: 0.98; 136 slots, 28: 1.03; 200 slots, 28:
+//   1.05, 34: 0.88.  With the score's sums, which cost it more: 8 slots, 12: 1.14; 16 slots, 16: 1.17; 24 slots, 20: 1.12; 40 slots,
+//   24: 1.09; 64 slots, 24: 1.20; 136 slots, 28: 1.01; 200 slots, 28: 1.11.
+//   General (first-token deadlines of 600 s): 4 slots, 6: 1.08, 8: 0.90; 8 slots, 9: 1.03, 10: 0.94; 12 slots, 10: 1.07; 16 slots, 12:
+//   1.02, 14: 0.89; 24 slots, 12: 1.11, 14: 0.98; 32 slots, 14: 1.07, 16: 0.97; 40 slots, 16: 1.01, 18: 0.92; 64 slots, 16: 1.11, 18: 0.99;
+//   100 slots, 18: 1.08, 20: 0.98; 128 slots, 18: 1.11; 136 slots, 20: 1.04, 24: 0.87; 200 slots, 24: 0.97; 256 slots, 24: 1.03, 26: 0.96.
+constexpr uint32_t sweep_short_window(uint32_t i_pad, bool score, bool narrow) {
+  if (!narrow)
+    return i_pad >= 192u ? 24u : i_pad > 128u ? 20u : i_pad >= 100u ? 18u : i_pad >= 40u ? 16u
+           : i_pad >= 32u ? 14u : i_pad >= 16u ? 12u : i_pad >= 8u ? 9u : 6u;
+  if (i_pad >= 40u) return i_pad > 128u ? (score ? 24u : 28u) : (score ? 20u : 24u);
+  return i_pad >= 24u ? (score ? 18u : 20u) : i_pad >= 16u ? 16u : i_pad >= 8u ? 12u : 8u;
+}
+
+// The same for the distributor, one wavefront against the persistent kernel.  Measured, the persistent kernel's time
+// over one wavefront's, 32 bits: windows of 5 / 8 / 10 / 12 requests: 4 slots: 1.87 / 1.28 / 1.05 / 0.91, 64: 2.01 / 1.39 / 1.17 /
+// 1.02, 100: 1.60 / 1.09 / 0.93 / 0.80, 128: 1.59 / 1.08 / 0.91; of 3 / 4 / 5 / 6: 200: 1.87 / 1.52 / 1.27 / 1.09, 256: 1.67 / 1.35 / 1.15 /
+// 0.99.  General: of 7 / 8 / 9: 4 slots: 1.19 / 1.08 / 0.97, 64: 1.16 / 1.04 / 0.97; of 5 / 6 / 7: 65: 1.26 / 1.08 / 0.95, 128: 1.21 /
+// 1.04 / 0.92; of 4 / 5: 129: 1.16 / 0.98, 256: 1.10 / 0.94.
+constexpr uint32_t assign_short_window(uint32_t i_pad, bool narrow) {
+  if (!narrow) return i_pad <= 64u ? 8u : i_pad <= 128u ? 6u : 4u;
+  return i_pad <= 64u ? 10u : i_pad <= 128u ? 8u : 5u;
+}
+
 }  // namespace maaso

@@ -41,6 +41,10 @@ CASES = [
     # the longest windows of a line, and a request more (more candidates than a block each is used for)
     (2561, 8, 12, 73, "full", "bursts"), (2561, 16, 16, 81, "mixed", "far"), (2561, 24, 20, 101, "long", "bursts"),
     (2561, 40, 24, 130, "wide", "close"), (2561, 40, 25, 130, "full", "bursts"), (2561, 129, 28, 60, "full", "far"),
+    # deadlines beyond 32-bit ticks: the general form's own longest windows, and a request more
+    (2561, 7, 6, 40, "long", "bursts"), (2561, 8, 10, 70, "long", "bursts"), (2561, 33, 14, 90, "long", "far"),
+    (2561, 33, 15, 90, "long", "bursts"), (2561, 60, 16, 130, "long", "bursts"), (2561, 100, 19, 90, "long", "far"),
+    (2561, 130, 20, 70, "long", "bursts"), (2561, 200, 25, 60, "long", "close"),
 ]
 
 
@@ -61,6 +65,8 @@ def test_sweep_and_score(n_cand, i_pad, window, n_req, variant, gaps, kw):
     # the longest windows that one wavefront takes, and one request more
     (64, 10, 205, "full", "bursts"), (64, 11, 205, "mixed", "bursts"), (65, 8, 200, "mixed", "far"), (128, 9, 200, "full", "bursts"),
     (129, 5, 130, "full", "bursts"), (256, 6, 130, "mixed", "close"), (33, 7, 140, "wide", "far"), (5, 9, 70, "long", "bursts"),
+    (64, 8, 150, "long", "bursts"), (65, 6, 150, "long", "far"), (128, 7, 150, "long", "bursts"), (129, 4, 100, "long", "bursts"),
+    (256, 5, 100, "long", "close"),
 ])
 @pytest.mark.parametrize("mode,kappa", [(0, 0.5), (1, 0.0)])
 def test_distributor(i_pad, window, n_req, variant, gaps, mode, kappa):

@@ -1,5 +1,6 @@
-"""The index rules of the windowed sweeps (window_rules.hpp), compiled for the CPU and run through every
-small case: which arrivals a set's windows read, and which buffer of admitted sums is free to be cleared."""
+"""The rules of the windowed sweeps (window_rules.hpp), compiled for the CPU and run through every small case:
+which arrivals a set's windows read, which buffer of admitted sums is free to be cleared, in how many ticks nothing
+completes, and the longest windows that a wavefront with the instances in its lanes takes."""
 import shutil
 import subprocess
 from pathlib import Path
@@ -83,3 +84,21 @@ def test_nothing_completes_in_safe_ticks(tmp_path):
   printf("%u %u %u\\n", row_safe_ticks(1e30f, 1e30f, 1u, 1u), row_safe_ticks(1e-30f, 1e-20f, 1u, 1u), row_safe_ticks(1.0f, 1.0f, 1u, 1u));""")
     assert rows[0][0] == 0 and rows[0][1] == 0 and rows[0][2] > 100000
     assert rows[1] == [4000000000, 0, 1048576 - 1024]
+
+
+def test_longest_short_windows(tmp_path):
+    """The general form, which runs where queues do not fit 32 bits, is slower per request: its windows are never longer
+    than the 32-bit form's, never where it was measured slower than the kernel it would replace by 10 % and more, and a window of
+    one request is always short."""
+    rows = run_rules(tmp_path, """
+  for (uint32_t i = 1; i <= 256; ++i)
+    printf("%u %u %u %u %u %u %u\\n", i, sweep_short_window(i, false, true), sweep_short_window(i, false, false),
+           sweep_short_window(i, true, true), sweep_short_window(i, true, false), assign_short_window(i, true),
+           assign_short_window(i, false));""")
+    slower = {4: 8, 8: 11, 16: 15, 24: 16, 32: 18, 40: 20, 64: 20, 100: 24, 128: 24, 136: 24, 200: 28, 256: 28}  # windows, sweep
+    assert [r[0] for r in rows] == list(range(1, 257))
+    for i, sweep, sweep_general, score, score_general, assign, assign_general in rows:
+        assert 1 <= sweep_general <= sweep and 1 <= score_general <= score <= sweep and 1 <= assign_general <= assign
+        if i in slower:
+            assert sweep_general < slower[i] and score_general < slower[i]
+        assert assign_general < (9 if i <= 64 else 7 if i <= 128 else 6)
