@@ -1,7 +1,8 @@
 """Windows of a few requests, one instance per lane: the sweep, the score and the distributor against the CPU
 oracle where their two forms meet (queues and slots that fit 32 bits and the tables, and ones that do not), at one
 row of slots per lane and several, at four and eight candidates a block, over arrivals so close that nothing
-completes between two windows, so far apart that something always does, and in bursts."""
+completes between two windows, so far apart that something always does, in bursts, and in chunks of both kinds in turn; service
+times of zero; slots and requests that are flagged."""
 import numpy as np
 import pytest
 
@@ -110,3 +111,99 @@ def test_nothing_completes_behind_the_last_window(i_pad, window, n_req, mode, s_
         assert np.array_equal(got["q_ticks"].cpu().numpy()[0].view(np.uint64), ref["q_ticks"])
     finally:
         dw.close()
+
+
+def safe_ticks(s_bar, tbt, run):
+    """row_safe_ticks for windows of one request."""
+    f = np.float32
+    return int(f(f(s_bar) * f(tbt)) / f(run) * f(1048576.0 * (1.0 - 2.0 ** -10)))
+
+
+@pytest.mark.parametrize("latencies", [True, False])
+@pytest.mark.parametrize("mode,kappa", [(0, 0.5), (0, 0.0), (1, 0.5)])
+@pytest.mark.parametrize("i_pad,tail", [(64, 17), (5, 64), (23, 1)])
+def test_chain_and_completing_steps_in_turn(i_pad, tail, mode, kappa, latencies):
+    """One request per window on up to 64 slots: chunks of 64 requests in which nothing can complete, which take the chain,
+    and chunks with gaps in which requests do, in turn.  The instances start empty and the gaps are shorter than the
+    service time of a single request, so what completes does so for the requests that the chain admitted."""
+    chunks = "CLCCLLCLC"
+    n_req = 64 * (len(chunks) - 1) + tail
+    w = W.random_small(i_pad + tail, 1, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=kappa, queued=False)
+    w = W.replace(w, n_inst=np.full_like(w.n_inst, i_pad), occ=np.zeros_like(w.occ), tbt_mode=mode,
+                  max_batch=np.maximum(w.max_batch, 32).astype(np.uint16), prompt_len=np.minimum(w.prompt_len, 64).astype(np.uint32),
+                  d_tbt=w.d_tbt * np.float32(4.0))
+    least = float(w.tbt[:, 1:].min())
+    alone = safe_ticks(w.s_bar, least, 1)
+    gap = np.full(n_req, 300, dtype=np.uint64)
+    for k, c in enumerate(chunks):
+        if c == "L":
+            at = 64 * k + np.array([0, 1, 20, 31, 62, 63])[k % 3:]
+            gap[at] = np.uint64(alone * 9 // 10)
+    assert 300 < safe_ticks(w.s_bar, least, 64) <= safe_ticks(w.s_bar, least, 32) < alone * 9 // 10  # chain; steps
+    w = W.replace(w, arrival_ticks=(np.cumsum(gap) - gap).astype(np.uint32))
+    print(f"chain and steps I={i_pad} R={n_req} mode={mode} kappa={kappa} latencies={latencies}", flush=True)
+    ref = oracle.score_assign(w, cand=0, window=1)
+    assert 0 < int(ref["occ"].sum()) < ref["n_satisfied"] // 2  # requests completed
+    dw = binding.DeviceWorkload(w)
+    try:
+        got = dw.assign(window=1, latencies=latencies)
+        torch.cuda.synchronize()
+        for key in ("chosen", "slack") + (("ttft", "tbt", "e2e") if latencies else ()):
+            assert np.array_equal(got[key].cpu().numpy(), ref[key], equal_nan=key != "chosen"), key
+        assert int(got["n_satisfied"].item()) == ref["n_satisfied"]
+        assert np.array_equal(got["occ"].cpu().numpy()[0], ref["occ"])
+        assert np.array_equal(got["q_ticks"].cpu().numpy()[0].view(np.uint64), ref["q_ticks"])
+        assert binding.maaso_ctx_device_status(dw.ctx) == 0
+    finally:
+        dw.close()
+
+
+@pytest.mark.parametrize("i_pad,window,n_req", [(64, 1, 200), (64, 3, 150), (40, 10, 205), (65, 4, 130), (128, 8, 200), (130, 2, 90),
+                                                (256, 5, 130), (100, 1, 130)])
+@pytest.mark.parametrize("latencies", [True, False])
+def test_flagged_slots_and_requests(i_pad, window, n_req, latencies):
+    """Slots outside the tables, a negative occupancy and requests of an unknown class, at the short windows of every
+    number of slots per lane: one wavefront and the persistent kernel give the same, and the oracle's values where it
+    has any (a slot that nobody can be admitted to stands for one outside the tables, an endless prompt for an unknown
+    class)."""
+    w = workload(1, i_pad, n_req, "mixed", "bursts")
+    tp, B, q = w.tp_idx.copy(), w.max_batch.copy(), w.q_ticks.copy()
+    out = [0, i_pad // 2]
+    q[:, out] = np.uint64(1 << 50)
+    odd = np.arange(5, n_req, 37)
+    prompt, cls = w.prompt_len.copy(), w.slo_class.copy()
+    prompt[odd] = 16777215
+    w = W.replace(w, n_inst=np.full_like(w.n_inst, i_pad), prompt_len=prompt)
+    ref = oracle.score_assign(W.replace(w, q_ticks=q), cand=0, window=window)
+    assert (ref["slack"][odd] < 0).all() and ref["n_satisfied"] > 0
+    tp[:, 0] = 9
+    B[:, i_pad // 2] = 65
+    cls[odd] = 200
+    bad = W.replace(w, tp_idx=tp, max_batch=B, slo_class=cls)
+    neg = bad.occ.copy()
+    neg[:, i_pad - 1] = -3
+    keys = ("chosen", "slack") + (("ttft", "tbt", "e2e") if latencies else ())
+    for what, x in (("outside", bad), ("negative", W.replace(bad, occ=neg))):
+        got = []
+        for blocks in (0, 1):
+            print(f"flagged {what} I={i_pad} window={window} R={n_req} blocks={blocks} latencies={latencies}", flush=True)
+            dw = binding.DeviceWorkload(x)
+            try:
+                binding.maaso_ctx_set_launch_shape(dw.ctx, 0, 0, 0, blocks)
+                g = dw.assign(window=window, latencies=latencies)
+                torch.cuda.synchronize()
+                got.append({k: g[k].cpu().numpy() for k in keys + ("occ", "q_ticks", "n_satisfied")})
+                assert binding.maaso_ctx_device_status(dw.ctx) == 3
+            finally:
+                dw.close()
+        for k in got[0]:
+            assert np.array_equal(got[0][k], got[1][k], equal_nan=got[0][k].dtype.kind == "f"), (what, k)
+        assert (got[0]["chosen"][odd] == -1).all() and np.isneginf(got[0]["slack"][odd]).all()
+        if what == "outside":
+            known = np.setdiff1d(np.arange(n_req), odd)
+            for k in keys:
+                assert np.array_equal(got[0][k][known], ref[k][known], equal_nan=k != "chosen"), k
+            assert int(got[0]["n_satisfied"].item()) == ref["n_satisfied"]
+            inside = np.setdiff1d(np.arange(i_pad), out)
+            assert np.array_equal(got[0]["occ"][0][inside], ref["occ"][inside])
+            assert np.array_equal(got[0]["q_ticks"][0].view(np.uint64)[inside], ref["q_ticks"][inside])
