@@ -10,9 +10,16 @@ __device__ __forceinline__ float lane_value(float v, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
 
-// `old` with lane l (uniform) holding v (uniform): v_writelane, for which there is no builtin.
+// `old` with lane l (uniform) holding v (uniform): v_writelane.  Where the compiler has no builtin for it, the
+// intrinsic by its name, which carries the type since LLVM 19; with any other compiler a compare and a select.
+#if __has_builtin(__builtin_amdgcn_writelane)
+__device__ __forceinline__ int with_lane(int old, int l, int v) { return __builtin_amdgcn_writelane(v, l, old); }
+#elif __clang_major__ >= 19
 __device__ int maaso_writelane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
 __device__ __forceinline__ int with_lane(int old, int l, int v) { return maaso_writelane(v, l, old); }
+#else
+__device__ __forceinline__ int with_lane(int old, int l, int v) { return (int)__lane_id() == l ? v : old; }
+#endif
 __device__ __forceinline__ int with_lane(int old, int l, float v) { return with_lane(old, l, __builtin_bit_cast(int, v)); }
 
 // At the head of a branch that is hardly ever taken: keeps the compiler from working out both sides of
