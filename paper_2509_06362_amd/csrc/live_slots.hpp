@@ -153,7 +153,8 @@ struct AdmissionBounds {
   // ticks of an admitted request's wait or prefill, and the sum of four prefills, fit 32 bits
   bool narrow;
   // the same, the queue of an instance that admits all of a window stays below 2^32 ticks, and no service time
-  // is zero
+  // is zero.  NarrowSequence keeps queues in 32 bits on the strength of this alone: an instance admits only while its
+  // wait, and so its queue, is within the largest first-token deadline D, and adds at most D per request of the window.
   bool narrow_queue;
 };
 

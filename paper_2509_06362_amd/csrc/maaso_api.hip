@@ -531,7 +531,7 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   const uint32_t cand_groups = (uint32_t)(((uint64_t)C + G - 1u) / G);
   // Thresholds beside the grouping keep a word per (candidate, class) behind the lengths: where the workspace has
   // room for them (next to any that holds the call's charge; with many classes, few slots and few requests it may not).
-  const uint32_t cap = (uint32_t)ctx->n_cu * 6u;  // 65,536 x 32 slots: 33.9 us with 6 blocks per compute unit, 35.0 with 5, 36.1 with 8
+  const uint32_t cap = (uint32_t)ctx->n_cu * 6u;  // 65,536 x 32 slots, the same inputs repeated: 33.8 us with 6 blocks per compute unit, 35.1 with 5, 36.4 with 8
   const uint32_t rank_cap = (uint32_t)ctx->n_cu * 8u;
   const size_t at_longest = up256((size_t)R * sizeof(float)), at_pairs = at_longest + up256((size_t)C * K * sizeof(uint32_t));
   const size_t at_best = at_pairs + up256((size_t)rank_cap * 2u * sizeof(uint64_t));

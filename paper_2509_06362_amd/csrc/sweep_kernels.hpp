@@ -27,10 +27,12 @@
 // With few candidates sweep_few_kernel is the only launch: every block compares its share of the requests with all
 // thresholds.
 //
-// What bounds it: the instance slots' 15 bytes each and the latency of four short launches.  65,536
-// candidates x 32 slots x 16,384 requests: 457 -> 36.2 -> 33.9 us; 8192 x 128 x 131,072: 5240 -> 38.8 -> 33.8 us; 4096 x 32 x
-// 65,536: 127 -> 22.1 -> 20.2 us; 37 x 13 x 1000: 18 -> 11 us (every pair evaluated on the vector units; thresholds in the
-// third launch; beside the second).  Of the 33.8: grouping 5, dealing out and thresholds 20, ranks 7, totals 4.
+// What bounds it: the latency of four short launches, each dependent on the one before, and in the second the thresholds.
+// 65,536 candidates x 32 slots x 16,384 requests: 457 -> 36.2 -> 33.8 us; 8192 x 128 x 131,072: 5240 -> 38.5 -> 33.8 us;
+// 4096 x 32 x 65,536: 127 -> 22.1 -> 21.0 us (every pair evaluated on the vector units; thresholds in the third launch;
+// beside the second), the same inputs again and again; with others at every call 37.1 -> 35.0, 40.6 -> 35.8, 22.2 -> 20.0.
+// 37 x 13 x 1000: 18 -> 11 us.  The launches by themselves, in a kernel trace with each one's start (which is why they add up
+// to more): grouping 3.4 / 5.2 / 3.5, dealing out and thresholds 16.8 / 19.6 / 7.4, ranks 12.0 / 6.6 / 5.8, totals 4.
 #pragma once
 
 #include "device_model.hpp"

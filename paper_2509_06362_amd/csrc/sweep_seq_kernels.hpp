@@ -17,10 +17,15 @@
 // instruction: fma, add, sub, mul, mov, 32-bit add and saturating sub 2.3; all others - compare, convert,
 // min, DPP, lane reads and writes, anything with a scalar operand - 4.2, scalar instructions about 2 beside them.  So the
 // rules of NarrowSequence leave out conversions and compares first.  8192 candidates of 128 instances, 8192
-// requests one by one: 23.4 -> 9.7 ms with the profile evaluated where occupancy changed -> 6.3 ms with 32-bit queues
-// throughout, one lane evaluated per admission and the completion check on the scalar unit; 6000 x 60
-// slots, windows of 3: 338 -> 289 us; 9000 x 128, of 16: 388 -> 304 us.  Reading the next request ahead of its turn
+// requests one by one: 23.4 -> 9.5 ms with the profile evaluated where occupancy changed -> 6.1 ms with 32-bit queues
+// throughout, one lane evaluated per admission and the completion check on the scalar unit (93 -> 62 vector and 49 -> 29
+// scalar instructions a request); 1000 requests, 6000 x 60 slots, windows of 3: 453 -> 385 us; 9000 x 128, of 16: 798 -> 593 us.
+// Reading the next request ahead of its turn
 // costs its registers' moves: 8 candidates 446 -> 429 us, 16,384 902 -> 1013 us; not taken.
+//
+// A block has one form for all of its candidates (they meet at barriers while they prepare requests): one slot that does not
+// fit - 2^32 ticks queued, a negative occupancy, outside the tables - puts all four or eight on the general one.  With one
+// such slot in every eighth candidate and in each, 3000 candidates, windows of 3, us: 16 slots 63 -> 68 -> 69, 128: 87 -> 96 -> 99.
 //
 // The arithmetic is the windowed kernel's, operation by operation, so the two agree bit for bit and
 // with the oracle's windowed distributor.  The shortest-queue rule is not offered here (its ranks
@@ -590,7 +595,7 @@ __device__ __forceinline__ float max_beside(float slack, float pre, float tbt, u
 // without a branch.  What bounds it is the length of that chain: alone on its SIMD a wavefront issues an
 // instruction every 4 cycles, whether it depends on the one before or not; a taken branch costs 20, a scalar
 // instruction behind the vector one that wrote its operand 16 to 24, a table row from LDS some 100.  16,384 requests,
-// 64 slots: 5.95 -> 4.94 ms with NarrowSequence (as it still is over more slots: 120: 0.59 -> 0.31 us per request) ->
+// 64 slots: 5.95 -> 4.94 ms with NarrowSequence (as it still is over more slots: 120: 0.54 -> 0.29 us per request) ->
 // 2.72 with the chain -> 2.35 (0.143 us per request) with two requests a trip and the waits filled.  What an instance will be once it has admitted one more request is worked out ahead, so
 // that the admission is a select; its row of the tables arrives while the next request is scored.
 template <bool kLat, bool kPenalty>
