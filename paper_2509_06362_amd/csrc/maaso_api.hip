@@ -1441,16 +1441,20 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   if (prm->policy == 0u && prm->window <= short_window && ctx->window_blocks == 0u && !profiled) {
     const size_t lds = ((size_t)ctx->cells + 1u) * sizeof(float4);
     TimedRegion timed(ctx, s);
-    if (pl->i_pad <= 64u) {
-      if (lat) hipLaunchKernelGGL((assign_seq_kernel<true, 1>), dim3(1), dim3(64), lds, s, a, prm->window);
-      else hipLaunchKernelGGL((assign_seq_kernel<false, 1>), dim3(1), dim3(64), lds, s, a, prm->window);
-    } else if (pl->i_pad <= 128u) {
-      if (lat) hipLaunchKernelGGL((assign_seq_kernel<true, 2>), dim3(1), dim3(64), lds, s, a, prm->window);
-      else hipLaunchKernelGGL((assign_seq_kernel<false, 2>), dim3(1), dim3(64), lds, s, a, prm->window);
-    } else {
-      if (lat) hipLaunchKernelGGL((assign_seq_kernel<true, 4>), dim3(1), dim3(64), lds, s, a, prm->window);
-      else hipLaunchKernelGGL((assign_seq_kernel<false, 4>), dim3(1), dim3(64), lds, s, a, prm->window);
-    }
+    auto launch = [&](auto lat_, auto s_, auto fits_) {
+      hipLaunchKernelGGL((assign_seq_kernel<lat_(), s_(), fits_()>), dim3(1), dim3(64), lds, s, a, prm->window);
+    };
+    auto by_form = [&](auto lat_, auto s_) {
+      if (a.bounds.narrow_queue) launch(lat_, s_, std::true_type{});
+      else launch(lat_, s_, std::false_type{});
+    };
+    auto by_slots = [&](auto lat_) {
+      if (pl->i_pad <= 64u) by_form(lat_, std::integral_constant<int, 1>{});
+      else if (pl->i_pad <= 128u) by_form(lat_, std::integral_constant<int, 2>{});
+      else by_form(lat_, std::integral_constant<int, 4>{});
+    };
+    if (lat) by_slots(std::true_type{});
+    else by_slots(std::false_type{});
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
 

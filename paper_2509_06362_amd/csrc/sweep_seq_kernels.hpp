@@ -98,7 +98,7 @@ __device__ __forceinline__ uint32_t holder_of(const float (&slack)[S], float bes
 // A placement in the lanes of one wavefront, taken through windows of requests.
 // kFits: narrow_queue holds, so that no admission makes `wide` true and a prefill's ticks fit 32 bits (false is always
 // right).
-template <int S, bool kFits = false>
+template <int S, bool kFits>
 struct Sequence {
   static constexpr bool kNarrow = false;
   LiveSlot slot[S];
@@ -722,7 +722,8 @@ __device__ __forceinline__ unsigned long long assign_windows(const AssignArgs& a
   return sat;
 }
 
-template <bool kLat, int S>
+// kFits: narrow_queue.
+template <bool kLat, int S, bool kFits>
 __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint32_t window) {
   extern __shared__ __align__(16) unsigned char smem[];
   float4* rows = reinterpret_cast<float4*>(smem);
@@ -742,7 +743,7 @@ __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint
   uint32_t tp[S], B[S];
   int32_t occ[S];
   uint64_t q[S];
-  bool narrow = a.bounds.narrow_queue;
+  bool narrow = kFits;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const uint32_t j = (uint32_t)s * 64u + lane;
@@ -764,11 +765,11 @@ __global__ __launch_bounds__(64) void assign_seq_kernel(const AssignArgs a, uint
       if (j < n) { row.occ[j] = sq.occupancy(s); row.q_ticks[j] = sq.queue(s); }
     }
   };
-  if (narrow) {
+  if (kFits && narrow) {
     NarrowSequence<S> sq;
     run(sq);
   } else {
-    Sequence<S> sq;
+    Sequence<S, kFits> sq;
     run(sq);
     if (sq.bad != 0ull) raise_status(a.status, 2u);
   }
