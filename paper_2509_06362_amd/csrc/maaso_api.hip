@@ -345,7 +345,7 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, h
     // Wavefronts per block: eight (tables and requests shared by more, 2 to 3 % faster where both spread as well), four
     // where that leaves fewer on the fullest compute unit and the tables leave room for its blocks.  64 slots, eight / four, us:
     // 3000 candidates one by one 73.5 / 66.2, windows of 3: 69.4 / 64.3; 5000: 92.6 / 84.8; 9000: 140 / 132; 128 slots, 6000: 128 / 132;
-    // 8192: 158 / 162, with tables of 1028 cells (seven blocks of four at a time) 158 / 171.
+    // 8192: 158 / 161, with tables of 1028 cells (seven blocks of four at a time) 159 / 173.
     auto fullest = [&](uint32_t waves) {  // blocks on it
       return ((uint64_t)((a.n_cand + waves - 1u) / waves) * a.n_sets + n_cu - 1u) / n_cu;
     };
