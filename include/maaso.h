@@ -136,7 +136,8 @@ void maaso_ctx_destroy(maaso_ctx* ctx);
  * it takes (set the launch-shape knobs before reserving: more blocks per queue need more).  The
  * workspace is charged, for the static sweep, with 4*K*R bytes of prompt lengths, 16 bytes per instance
  * slot and its queues (it keeps 4*R of them, and 4*C*K and some 50 KiB for thresholds and bests where
- * there is room); 12 KiB for the windowed distributor;
+ * there is room, which the charge leaves except with many classes, few slots and few requests, and a
+ * reservation for more requests gives; without it the call is somewhat slower); 12 KiB for the windowed distributor;
  * 4 bytes per 1024 requests for maaso_split_by_slo.  The windowed sweep, the scores and the static
  * distributor use none.  Never shrinks.  A set-up call: it synchronises the device and reallocates
  * when the workspace has to grow.  Errors: INVALID_ARG, SHAPE, HIP, NOMEM, BUSY. */

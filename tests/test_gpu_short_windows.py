@@ -207,3 +207,11 @@ def test_flagged_slots_and_requests(i_pad, window, n_req, latencies):
             inside = np.setdiff1d(np.arange(i_pad), out)
             assert np.array_equal(got[0]["occ"][0][inside], ref["occ"][inside])
             assert np.array_equal(got[0]["q_ticks"][0].view(np.uint64)[inside], ref["q_ticks"][inside])
+
+
+@pytest.mark.parametrize("n_cand,b_cap", [(2561, 511), (4300, 511), (4300, 64), (6000, 255)])
+@pytest.mark.parametrize("window", [1, 3])
+def test_wavefronts_per_block(n_cand, b_cap, window):
+    """Blocks of four wavefronts and of eight: which spread better, and tables that leave room for fewer than eight
+    blocks of four on a compute unit."""
+    check_against_oracle(workload(n_cand, 3, 20, "full", "bursts", b_cap=b_cap), window, f"blocks b_cap={b_cap}")
