@@ -138,8 +138,10 @@ void maaso_ctx_destroy(maaso_ctx* ctx);
  * slot and its queues (it keeps 4*R of them, and 4*C*K and some 50 KiB for thresholds and bests where
  * there is room, which the charge leaves except with many classes, few slots and few requests, and a
  * reservation for more requests gives; without it the call is somewhat slower); 12 KiB for the windowed distributor;
- * 4 bytes per 1024 requests for maaso_split_by_slo.  The windowed sweep, the scores and the static
- * distributor use none.  Never shrinks.  A set-up call: it synchronises the device and reallocates
+ * 4 bytes per 1024 requests for maaso_split_by_slo.  The static distributor uses none.  The windowed sweep and the
+ * scores are charged with none: with many candidates and windows of some hundred requests they lay the requests out in
+ * it where there is room and the stream is not being captured (some 9 bytes a request, more with short windows and many
+ * classes), and are somewhat slower without.  Never shrinks.  A set-up call: it synchronises the device and reallocates
  * when the workspace has to grow.  Errors: INVALID_ARG, SHAPE, HIP, NOMEM, BUSY. */
 int maaso_ctx_reserve(maaso_ctx* ctx, uint32_t max_cand, uint32_t i_pad, uint32_t max_req);
 

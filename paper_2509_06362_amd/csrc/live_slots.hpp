@@ -163,8 +163,9 @@ __device__ __forceinline__ void find_admissible(const SlotRecord (&rec)[S], cons
                                                 const AdmissionBounds& lim, InstanceSet<S>& und) {
 #pragma unroll
   for (int s = 0; s < S; ++s)
-    und.m[s] = lane_mask(((uint32_t)s * 64u + lane < n) & (rec[s].tbt <= lim.d_tbt) &
-                        !(rec[s].wait + rec[s].a > lim.d_ttft));
+    und.m[s] = lane_mask((uint32_t)s * 64u + lane < n) & lane_mask(rec[s].tbt <= lim.d_tbt) &
+               lane_mask(!(rec[s].wait + rec[s].a > lim.d_ttft));
+  if (und.count() <= 1u) return;  // nobody to remove
   uint32_t steps = 0;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
@@ -175,16 +176,15 @@ __device__ __forceinline__ void find_admissible(const SlotRecord (&rec)[S], cons
       const int32_t ko = kSQ ? (int32_t)__builtin_amdgcn_readlane(occ[s], b) : 0;
 #pragma unroll
       for (int t = 0; t < S; ++t) {
-        const bool ap = (k.a <= rec[t].a) & (k.p <= rec[t].p);
-        const bool le = ap & (k.tbt <= rec[t].tbt) & (k.wait <= rec[t].wait);
+        const unsigned long long ap = lane_mask(k.a <= rec[t].a) & lane_mask(k.p <= rec[t].p);
+        const unsigned long long le = ap & lane_mask(k.tbt <= rec[t].tbt) & lane_mask(k.wait <= rec[t].wait);
         // lanes behind instance k in index order
         const unsigned long long behind = t > s ? ~0ull : (t == s ? ~1ull << b : 0ull);
         unsigned long long gone;
         if (kSQ) {
-          gone = lane_mask(le & (ko < occ[t])) | (lane_mask(le & (ko == occ[t])) & behind);
+          gone = le & (lane_mask(ko < occ[t]) | (lane_mask(ko == occ[t]) & behind));
         } else {
-          gone = (lane_mask(le) & behind) |
-                 lane_mask(ap & (t_above <= rec[t].tbt) & (w_above <= rec[t].wait));
+          gone = (le & behind) | (ap & lane_mask(t_above <= rec[t].tbt) & lane_mask(w_above <= rec[t].wait));
         }
         und.m[t] &= ~gone;
       }
@@ -209,8 +209,8 @@ __device__ __forceinline__ void find_undominated(const SlotRecord (&rec)[S], uin
       const SlotRecord k = rec[s].of_lane(b);
 #pragma unroll
       for (int t = s; t < S; ++t) {
-        unsigned long long gone = lane_mask((k.a <= rec[t].a) & (k.p <= rec[t].p) & (k.tbt <= rec[t].tbt) &
-                                            (k.wait <= rec[t].wait));
+        unsigned long long gone = lane_mask(k.a <= rec[t].a) & lane_mask(k.p <= rec[t].p) & lane_mask(k.tbt <= rec[t].tbt) &
+                                  lane_mask(k.wait <= rec[t].wait);
         if (t == s) gone &= ~1ull << b;  // those behind it, not itself
         und.m[t] &= ~gone;
       }

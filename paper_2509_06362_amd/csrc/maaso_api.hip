@@ -20,6 +20,7 @@
 #include "profile_fit_kernels.hpp"
 #include "sweep_window_kernels.hpp"
 #include "sweep_block_kernels.hpp"
+#include "sweep_ordered_kernels.hpp"
 #include "sweep_seq_kernels.hpp"
 #include "window_kernels.hpp"
 
@@ -317,10 +318,66 @@ BlockWindows block_windows(uint64_t blocks, uint32_t i_pad, bool shortest_queue)
   return {9u, blocks <= 2560u && i_pad > 12u ? 32u : 0u};
 }
 
+inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Where a launch over windows keeps its requests laid out by class and length (ordered_windows.hpp), in a workspace.
+struct OrderedPlan {
+  OrderArgs order;
+  OrderedSets sets;
+  uint32_t blocks;   // of the launch that lays them out
+  uint32_t threads;
+  size_t lds, bytes;
+};
+
+// Of request set `t`, of which n_windows windows are laid out at `at` (moved behind them).
+OrderedSet plan_set(const SweepWindowSet& t, uint32_t n_slo, uint32_t size_log2, uint64_t n_windows, unsigned char*& at) {
+  const uint32_t per_window = std::min(t.window, t.n_req);
+  OrderedSet o;
+  o.segments = (per_window + kSegment - 1u) / kSegment;
+  o.size_log2 = size_log2;
+  o.batches = o.segments * segment_batches(std::min(per_window, kSegment), n_slo, 1u << size_log2);
+  auto take = [&](size_t bytes) {
+    unsigned char* p = at;
+    at += up256(bytes);
+    return p;
+  };
+  const size_t slots = (size_t)n_windows * o.batches << size_log2;
+  o.len = reinterpret_cast<float*>(take(slots * sizeof(float)));
+  o.out = reinterpret_cast<float*>(take(slots * sizeof(float)));
+  o.batch = reinterpret_cast<Batch*>(take((size_t)n_windows * o.batches * sizeof(Batch)));
+  o.gap = reinterpret_cast<uint32_t*>(take((size_t)n_windows * sizeof(uint32_t)));
+  return o;
+}
+
+// All sets of `a` in a workspace of ws_bytes; false where they do not fit.
+bool plan_ordered(const SweepWindowArgs& a, uint32_t size_log2, void* ws, size_t ws_bytes, OrderedPlan& plan) {
+  plan.order.n_slo = a.n_slo;
+  plan.order.status = a.status;
+  plan.order.n_sets = a.n_sets;
+  unsigned char* at = static_cast<unsigned char*>(ws);
+  uint64_t blocks = 0;
+  uint32_t segment = 1u;
+  for (uint32_t k = 0; k < a.n_sets; ++k) {
+    const SweepWindowSet& t = a.sets[k];
+    const uint64_t n_windows = ((uint64_t)t.n_req + t.window - 1u) / t.window;
+    plan.order.first[k] = (uint32_t)blocks;
+    plan.order.sets[k] = t;
+    plan.order.to[k] = plan.sets.set[k] = plan_set(t, a.n_slo, size_log2, n_windows, at);
+    blocks += n_windows * plan.order.to[k].segments;
+    if (blocks > 1u << 24) return false;
+    segment = std::max(segment, std::min(std::min(t.window, t.n_req), kSegment));
+  }
+  plan.blocks = (uint32_t)blocks;
+  plan.threads = segment <= 256u * kOrderPer ? 256u : 1024u;
+  plan.lds = order_lds(segment, a.n_slo, 1u << size_log2);
+  plan.bytes = (size_t)(at - static_cast<unsigned char*>(ws));
+  return plan.bytes <= ws_bytes && plan.bytes < (size_t)1 << 32;
+}
+
 // The windowed sweep of every (request set, candidate); shapes are chosen by the set with the longest
 // windows (the choice never changes a result).
 template <bool kScore, bool kSQ>
-int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, hipStream_t s) {
+int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, void* ws, size_t ws_bytes, hipStream_t s) {
   uint64_t per_window = 0;
   for (uint32_t k = 0; k < a.n_sets; ++k) {
     const uint64_t pw = a.sets[k].window < a.sets[k].n_req ? a.sets[k].window : a.sets[k].n_req;
@@ -328,6 +385,23 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, h
   }
   const uint64_t blocks = (uint64_t)a.n_cand * a.n_sets;
   if (blocks == 0 || blocks > 0x7fffffffull) return MAASO_E_SHAPE;
+  // Laid out by class and length: in batches of 16 where a window then is two groups at most, else of 64 (8192 candidates,
+  // windows of 4096, batches of 32: 2 % slower).  The kernels below where the workspace has no room.
+  OrderedPlan plan;
+  const bool small = per_window <= kSegment && segment_batches((uint32_t)per_window, a.n_slo, 16u) <= 32u;
+  if (ws && a.bounds.narrow && sweep_lays_out(blocks, a.n_sets, a.i_pad, per_window, kSQ) &&
+      plan_ordered(a, small ? 4u : 6u, ws, ws_bytes, plan)) {
+    hipLaunchKernelGGL(order_requests_kernel, dim3(plan.blocks), dim3(plan.threads), plan.lds, s, plan.order);
+    const dim3 g((a.n_cand + 3u) / 4u * a.n_sets), b(kAssignThreads);
+    auto launch = [&](auto s_) {
+      if (small) hipLaunchKernelGGL((sweep_ordered_kernel<kScore, s_(), 4, true, kSQ>), g, b, lds, s, a, plan.sets);
+      else hipLaunchKernelGGL((sweep_ordered_kernel<kScore, s_(), 6, false, kSQ>), g, b, lds, s, a, plan.sets);
+    };
+    if (a.i_pad <= 64u) launch(std::integral_constant<int, 1>{});
+    else if (a.i_pad <= 128u) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 4>{});
+    return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
+  }
   const BlockWindows bw = block_windows(blocks, a.i_pad, kSQ);
   if (per_window >= bw.shortest && per_window <= bw.longest) {
     uint32_t lpr_log2 = 0;  // lanes per request: as many as a pass over the window has, while a lane walks more than one trip
@@ -381,11 +455,17 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, h
 }
 
 template <bool kScore>
-int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, const maaso_ctx* ctx, hipStream_t s) {
+int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, const maaso_ctx* ctx, bool may_use_ws, hipStream_t s) {
   const size_t lds = (size_t)3 * ctx->cells * sizeof(float);  // profile tables
   const uint32_t n_cu = (uint32_t)ctx->n_cu;
-  return policy ? launch_sweep_window_v<kScore, true>(a, lds, n_cu, s)
-                : launch_sweep_window_v<kScore, false>(a, lds, n_cu, s);
+  void* ws = nullptr;
+  if (may_use_ws) {
+    // A captured launch may run later beside other work of the context: it keeps nothing in the workspace.
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hip_ok(hipStreamIsCapturing(s, &capturing)) && capturing == hipStreamCaptureStatusNone) ws = ctx->ws;
+  }
+  return policy ? launch_sweep_window_v<kScore, true>(a, lds, n_cu, ws, ctx->ws_bytes, s)
+                : launch_sweep_window_v<kScore, false>(a, lds, n_cu, ws, ctx->ws_bytes, s);
 }
 
 // Everything but the request sets.
@@ -431,8 +511,6 @@ void add_sweep_window_set(SweepWindowArgs& a, const maaso_requests* rq, const ma
   t.phi_l = out ? out->phi_l : nullptr;
   t.score = out ? out->score : nullptr;
 }
-
-inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace the static sweep of a shape is charged with: 4 bytes per (class, request), 16 per instance
 // slot, and per (request tile, XCD) queue 4 bytes and 16 per block that would serve it, by the launch-shape
@@ -738,7 +816,7 @@ int launch_score_sets(maaso_ctx* ctx, const maaso_placements* pl, uint32_t n_set
   a.gamma_l = wts->gamma_l;
   {
     TimedRegion timed(ctx, s);
-    const int rc = launch_sweep_window<true>(a, prm->policy, ctx, s);
+    const int rc = launch_sweep_window<true>(a, prm->policy, ctx, true, s);
     if (rc != MAASO_OK) return rc;
   }
   for (uint32_t k = 0; k < n_sets; ++k)
@@ -1049,7 +1127,7 @@ int placement_sweep_impl(maaso_ctx* ctx, const maaso_placements* pl, const maaso
     add_sweep_window_set(a, rq, prm, sat_count, nullptr);
     {
       TimedRegion timed(ctx, s);
-      rc = launch_sweep_window<false>(a, prm->policy, ctx, s);
+      rc = launch_sweep_window<false>(a, prm->policy, ctx, !static_scratch, s);
       if (rc != MAASO_OK) return rc;
     }
     hipLaunchKernelGGL(sweep_finalize_kernel, dim3(1), dim3(1024), 0, s, sat_count, C, R, sat_ratio,

@@ -15,10 +15,11 @@
 // windows of 256: 11.7 -> 9.4 us a window; every instance scored: 10.8).
 //
 // What bounds it: vector issue at windows of thousands (8192 candidates x 131,072 requests x 128
-// instances, windows of 4096: 26.8 ms with every instance scored, 1.83 ms now; 238 vector and 90 scalar
+// instances, windows of 4096: 26.8 ms with every instance scored, 1.83 ms here; 238 vector and 90 scalar
 // instructions per wavefront and 256 requests), the chain of one window after the other at short ones
 // (Alg. 2, 720 deployments x three sets, windows of 256: 2.6 -> 1.24 ms, 2.4 us per window of the longest
-// chain; 214 vector and 155 scalar instructions per window).
+// chain; 214 vector and 155 scalar instructions per window).  Both of these now go to sweep_ordered_kernels.hpp; this kernel
+// keeps the shapes on the other side of sweep_lays_out, deadlines of 512 s and more, and captured launches.
 #pragma once
 
 #include "assign_kernels.hpp"

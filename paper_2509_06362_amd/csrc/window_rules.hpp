@@ -62,4 +62,23 @@ constexpr uint32_t assign_short_window(uint32_t i_pad, bool narrow) {
   return i_pad <= 64u ? 10u : i_pad <= 128u ? 8u : 5u;
 }
 
+// Whether the windowed sweep of `units` (set, candidate) pairs lays its windows' requests out by class and length first
+// (sweep_ordered_kernels.hpp).  That saves the look at most requests of a window, and costs a launch and, per
+// window and instance, bounds over its batches: it pays with windows of some hundred requests and candidates enough
+// to hide a wavefront's trips to memory.  Measured, the other kernels' time over it, least and most of 4 to 256 slots, jittered
+// fresh instances with three classes and loaded ones with eight, largest slack | shortest queue:
+//   9000 candidates: windows of 128: 0.76-1.21 | 1.19, 256: 1.08-1.45 | 1.50-1.56, 512: 1.55-1.84 | 1.82-1.90, 4096: 4.68-6.96 | 3.87-4.03;
+//   2000: 256: 0.91-1.12 | 1.28, 320: 1.23-1.61 | 1.70-1.99, 512: 1.06-1.55, 1024: 1.37-2.26, 16,384: 2.56-3.76 | 2.39-3.17;
+//   720: 256: 0.78-1.14 | 1.08-1.33, 320: 1.12-1.56, 512: 0.98-1.35, 1024: 1.05-1.38, 256 slots 0.90-1.04, 4096: 1.48-2.17 | 1.25-1.43;
+//   500: 1024: 0.78-1.31, 2048: 1.11-1.60 | 1.25-1.46; 100: 2048: 0.97-1.50, 4096: 1.18-1.56 | 0.86-1.13, 16,384: 1.08-1.59; 1: 4096: 0.84-1.72.
+// Where several sets are scored (Alg. 2, over growth chains of equal instances) few instances count: 720 candidates, three
+// sets, windows of 256: 1.75.
+constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, uint64_t per_window, bool shortest_queue) {
+  if (per_window < 256u || units < 64u) return false;
+  if (units >= 1000u) return per_window > 256u || n_sets > 1u || units >= 4096u || shortest_queue;
+  if (units >= 720u) return per_window > 256u && (i_pad <= 128u || per_window >= 2048u);
+  if (units >= 400u) return per_window >= 2048u;
+  return per_window >= 4096u && !shortest_queue;
+}
+
 }  // namespace maaso
