@@ -418,7 +418,9 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
         ops = ASSIGN_LANEOPS_PER_TRIPLE * triples_assign
         hbm_frac = nbytes / k_avg_s / 1e9 / HBM_PEAK_GBS
         alu_frac = ops / k_avg_s / 1e12 / VALU_PEAK_TLANEOPS
-        kname = "assign_window_kernel" if w.window else "assign_static_kernel"
+        kname = "assign_static_kernel"
+        if w.window:  # which form takes the call: the library's own choice for this shape, or the persistent kernel asked for
+            kname = "assign_window_kernel" if args.window_blocks else "order_requests + assign_states + assign_recorded kernels"
         roofline = {
             "kernel": kname, "bound": "hbm", "achieved": nbytes / k_avg_s / 1e9,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hbm_frac, "traffic": traffic,
@@ -431,16 +433,15 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
                                 "is windows x per-window latency")
             roofline["windows"] = n_win
             roofline["us_per_window"] = k_avg_s * 1e6 / n_win
-            # where a window's time goes: one more call with the kernel's profiling variant (block 0
-            # sums its cycles per phase); shares of its loop, scaled to the unprofiled time per window
+            # where a window's time goes in the persistent kernel: one more call with its profiling variant (block 0
+            # sums its cycles per phase), cycles per window
             binding.maaso_ctx_window_profile(dw.ctx, True)
             dominant()
             ph = binding.maaso_ctx_window_phases(dw.ctx)
             binding.maaso_ctx_window_profile(dw.ctx, False)
             if ph["loop"]:
-                roofline["phase_us_per_window"] = {
-                    k: ph[k] / ph["loop"] * roofline["us_per_window"]
-                    for k in ("stage", "score", "exchange", "update")}
+                roofline["persistent_kernel_cycles_per_window"] = {
+                    k: ph[k] / n_win for k in ("stage", "score", "exchange", "update", "loop")}
         elif w.n_req < (1 << 20):
             roofline["note"] = "launch latency: a single short kernel"
     roofline["traffic_info"] = traffic_info

@@ -165,8 +165,10 @@ const char* maaso_strerror(int status);
  *   window_blocks: blocks of the windowed distributor's persistent kernel (at most one per compute
  *   unit is used).  Left at 0, windows of up to ten requests (eight beyond 64 instance slots, five beyond 128;
  *   eight, six and four where the largest first-token deadline D reaches 512 s, or D * (1 + window) 4095 s)
- *   are distributed by a single wavefront instead (no device-wide barrier per window); a value keeps the
- *   persistent kernel for them too.
+ *   are distributed by a single wavefront instead (no device-wide barrier per window), and with few slots,
+ *   the shortest-queue rule or windows of thousands (D below 512 s) the state is taken through the windows by one block, and the
+ *   requests are scored against what each window met, in launches of their own, laid out in the workspace; a
+ *   value keeps the persistent kernel for all of them.
  * Errors: INVALID_ARG. */
 int maaso_ctx_set_launch_shape(maaso_ctx* ctx, uint32_t sweep_requests_per_lane, uint32_t sweep_group,
                                uint32_t sweep_blocks_per_queue, uint32_t window_blocks);
@@ -187,7 +189,7 @@ int maaso_ctx_set_cooperative(maaso_ctx* ctx, int enable);
 
 /* Instrumentation.  With timing enabled, each compute call records a pair of HIP events on its
  * stream directly around what does its work (all launches of the static maaso_placement_sweep, the
- * sweep kernel of the windowed one and of maaso_placement_score, the scoring kernel of
+ * launches of the windowed one and of maaso_placement_score, the scoring kernel or launches of
  * maaso_score_assign), for up to 256 calls.  maaso_ctx_kernel_elapsed waits for the
  * recorded events, returns the sum of the kernel durations in milliseconds and their number, and
  * starts a new series.  Enabling allocates the events once; no other call is affected.
@@ -302,8 +304,8 @@ typedef struct {
  * requests: occupancy and queued prefill ticks are added, the queue drains by the arrival time that
  * passed, and min(W,B) * elapsed / (s_bar * tbt_j) requests complete; blocked requests add no load.
  * After the last window the load is added and nothing drains.  window >= R behaves as one window.
- * Windows of more than ten requests (fewer with many instance slots or very long deadlines, see
- * maaso_ctx_set_launch_shape) run in one persistent kernel whose blocks meet at a device-wide
+ * Windows of more than ten requests (fewer with many instance slots or very long deadlines; not those that are
+ * taken in launches of their own, see maaso_ctx_set_launch_shape) run in one persistent kernel whose blocks meet at a device-wide
  * barrier after every window, so all of them must be resident together: the kernel is launched
  * cooperatively, which the runtime either guarantees or refuses (MAASO_E_RESIDENCY, nothing ran).
  * Errors: INVALID_ARG, SHAPE, WORKSPACE, RESIDENCY, BUSY, HIP - all detected on the host. */

@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "assign_kernels.hpp"
+#include "assign_ordered_kernels.hpp"
 #include "sweep_kernels.hpp"
 #include "partition_kernels.hpp"
 #include "probe_kernels.hpp"
@@ -1443,6 +1444,104 @@ int maaso_score_assign_selected(maaso_ctx* ctx, const maaso_placements* pl, cons
 
 namespace {
 
+// The windowed distributor in launches over the requests laid out, as many windows at a time as the workspace
+// takes.  kNotTaken, nothing launched, where that are too few.
+constexpr int kNotTaken = 1;
+int launch_assign_ordered(maaso_ctx* ctx, const AssignArgs& a, const maaso_placements* pl, const maaso_requests* rq,
+                          const maaso_params* prm, const maaso_assign_out* out, bool lat, hipStream_t s) {
+  const uint32_t R = rq->n_req, I = pl->i_pad, size_log2 = 6;
+  SweepWindowSet set{};
+  set.n_req = R;
+  set.window = prm->window;
+  const uint64_t n_windows = ((uint64_t)R + prm->window - 1u) / prm->window;
+  // of one window; the arrays' starts are rounded up
+  unsigned char* at = nullptr;
+  const OrderedSet one = plan_set(set, a.n_slo, size_log2, 1u, at);
+  const uint64_t places = (uint64_t)one.batches << size_log2;
+  const uint64_t per_window = places * 8u + (uint64_t)one.batches * sizeof(Batch) + 4u + (uint64_t)I * 20u;
+  const uint64_t room = ctx->ws_bytes > 8192u ? ctx->ws_bytes - 8192u : 0u;
+  uint64_t at_once = std::min(room / per_window, n_windows);
+  at_once = std::min(at_once, (uint64_t)(1u << 24) / one.segments);
+  if (at_once == 0u || (at_once < n_windows && at_once < 64u)) return kNotTaken;
+  auto al = [](const void* p, uintptr_t m) { return (reinterpret_cast<uintptr_t>(p) & m) == 0; };
+  const bool vec = prm->window % 4u == 0u && al(rq->prompt_len, 15) && al(rq->out_len, 15) && al(rq->slo_class, 3) &&
+                   al(out->chosen, 15) && al(out->slack, 15) && al(out->ttft, 15) && al(out->tbt, 15) && al(out->e2e, 15);
+  const uint32_t window = std::min(prm->window, R);
+  const uint32_t per_pass = kAssignThreads * (vec ? 4u : 1u);
+  const uint32_t per_block = std::min((window + per_pass - 1u) / per_pass, 4u) * per_pass;
+  const uint32_t per_window_blocks = (window + per_block - 1u) / per_block;
+  if ((uint64_t)per_window_blocks * at_once > 0x7fffffffull) return kNotTaken;
+  const uint32_t segment = std::min(window, kSegment);
+  TimedRegion timed(ctx, s);
+  for (uint64_t w0 = 0; w0 < n_windows; w0 += at_once) {
+    const uint32_t count = (uint32_t)std::min(at_once, n_windows - w0);
+    const size_t skip = (size_t)w0 * prm->window;
+    OrderArgs o;
+    o.n_slo = a.n_slo;
+    o.status = a.status;
+    o.n_sets = 1u;
+    o.first[0] = 0u;
+    SweepWindowSet& t = o.sets[0];
+    t = SweepWindowSet{};
+    t.n_req = (uint32_t)(R - skip);
+    t.window = prm->window;
+    t.prompt_len = rq->prompt_len + skip;
+    t.out_len = rq->out_len + skip;
+    t.slo_class = rq->slo_class + skip;
+    t.arrival_ticks = rq->arrival_ticks + skip;
+    at = static_cast<unsigned char*>(ctx->ws);
+    SweepWindowSet whole = t;
+    whole.n_req = R;  // (windows of one size, also where the rest is shorter than one)
+    o.to[0] = plan_set(whole, a.n_slo, size_log2, count, at);
+    StateRun run;
+    run.n_req = R;
+    run.window = prm->window;
+    run.w0 = (uint32_t)w0;
+    run.n_windows = count;
+    run.recs = reinterpret_cast<float4*>(at);
+    at += up256((size_t)count * I * sizeof(float4));
+    run.occ = reinterpret_cast<int32_t*>(at);
+    hipLaunchKernelGGL(order_requests_kernel, dim3(count * o.to[0].segments), dim3(segment <= 256u * kOrderPer ? 256u : 1024u),
+                       order_lds(segment, a.n_slo, 1u << size_log2), s, o);
+    const size_t lds = (size_t)3 * ctx->cells * sizeof(float);
+    auto states = [&](auto s_, auto sq_) {
+      hipLaunchKernelGGL((assign_states_kernel<s_(), 4, sq_()>), dim3(1), dim3(5 * 64), lds, s, a, o.to[0], run);
+    };
+    auto states_by_slots = [&](auto sq_) {
+      if (I <= 64u) states(std::integral_constant<int, 1>{}, sq_);
+      else if (I <= 128u) states(std::integral_constant<int, 2>{}, sq_);
+      else states(std::integral_constant<int, 4>{}, sq_);
+    };
+    if (prm->policy) states_by_slots(std::true_type{});
+    else states_by_slots(std::false_type{});
+    if (a.chosen || a.slack || lat) {
+      const int list = I <= 16u && !prm->policy ? 0 : I <= 64u ? 1 : I <= 128u ? 2 : 4;
+      const dim3 g(count * per_window_blocks), b(kAssignThreads);
+      auto launch = [&](auto lat_, auto v_, auto sq_, auto list_) {
+        hipLaunchKernelGGL((assign_recorded_kernel<lat_(), v_(), sq_(), list_()>), g, b, 0, s, a, run, per_window_blocks, per_block);
+      };
+      auto by_list = [&](auto lat_, auto v_, auto sq_) {
+        if (list == 0) launch(lat_, v_, std::false_type{}, std::integral_constant<int, 0>{});
+        else if (list == 1) launch(lat_, v_, sq_, std::integral_constant<int, 1>{});
+        else if (list == 2) launch(lat_, v_, sq_, std::integral_constant<int, 2>{});
+        else launch(lat_, v_, sq_, std::integral_constant<int, 4>{});
+      };
+      auto by_policy = [&](auto lat_, auto v_) {
+        if (prm->policy) by_list(lat_, v_, std::true_type{});
+        else by_list(lat_, v_, std::false_type{});
+      };
+      auto by_width = [&](auto lat_) {
+        if (vec) by_policy(lat_, std::integral_constant<int, 4>{});
+        else by_policy(lat_, std::integral_constant<int, 1>{});
+      };
+      if (lat) by_width(std::true_type{});
+      else by_width(std::false_type{});
+    }
+    if (!hip_ok(hipGetLastError())) return MAASO_E_HIP;
+  }
+  return MAASO_OK;
+}
+
 int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t* cand_sel,
                       const maaso_requests* rq, const maaso_params* prm, const maaso_assign_out* out,
                       void* hip_stream) {
@@ -1534,6 +1633,14 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
     if (lat) by_slots(std::true_type{});
     else by_slots(std::false_type{});
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
+  }
+
+  // Few slots, or long windows: in launches over the requests laid out.  The window_blocks knob and the profile ask for
+  // the persistent kernel here too.
+  const bool ordered = a.bounds.narrow && assign_lays_out(pl->i_pad, prm->window < R ? prm->window : R, prm->policy != 0u);
+  if (ordered && ctx->window_blocks == 0u && !(ctx->window_profile && !prm->policy && !lat)) {
+    const int done = launch_assign_ordered(ctx, a, pl, rq, prm, out, lat, s);
+    if (done != kNotTaken) return done;
   }
 
   // Windowed: one persistent kernel; all blocks must be resident at once (one per compute unit at

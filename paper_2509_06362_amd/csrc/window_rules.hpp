@@ -81,4 +81,22 @@ constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, u
   return per_window >= 4096u && !shortest_queue;
 }
 
+// The same for the distributor (assign_ordered_kernels.hpp, against the persistent kernel): the chain of windows
+// is then one block's, which looks for the instances that count and bounds their slacks one after the other, so it pays
+// with few slots, or with windows that are much to score.  Measured, the persistent kernel's time over it, some hundred windows,
+// least and most of empty smooth and loaded jittered instances:
+//   largest slack: 2 slots: windows of 11 to 16,384: 2.5-5.6; 8 slots: 32: 0.97-2.8, 48: 1.26-3.9, 512: 2.4-4.8, 16,384: 1.8-2.6; 16 slots: 256:
+//   0.99-4.2, 512: 1.39-4.1, 16,384: 1.38-2.1; 64 slots: 1024: 0.82-2.8, 2048: 1.02-2.9, 4096: 1.36-3.3, 16,384: 1.04-1.4, 32,768: 0.43-0.53; 128
+//   slots: 2048: 0.76-2.0, 4096: 1.14-2.5, 8192: 1.44-2.4, 16,384: 0.79-0.97; 256 slots: 4096: 0.97-1.55, 8192: 1.12-1.51.
+//   Shortest queue: 8 slots: 11: 2.7, 512: 5.8; 64 slots: 11: 0.88, 16: 1.15, 64: 3.7, 4096: 5.6, 16,384: 2.1, 32,768: 0.73; 128 slots: 16: 1.00, 32: 1.57,
+//   8192: 4.2, 16,384: 1.55; 256 slots: 11: 1.27, 128: 2.1, 4096: 3.4, 16,384: 2.1.
+constexpr bool assign_lays_out(uint32_t i_pad, uint64_t per_window, bool shortest_queue) {
+  if (shortest_queue) return per_window >= (i_pad <= 16u ? 11u : i_pad <= 64u ? 16u : 32u) && per_window <= 16384u;
+  if (i_pad <= 2u) return per_window >= 11u && per_window <= 16384u;
+  if (i_pad <= 8u) return per_window >= 48u && per_window <= 16384u;
+  if (i_pad <= 16u) return per_window >= 512u && per_window <= 16384u;
+  if (i_pad <= 64u) return per_window >= 2048u && per_window <= 16384u;
+  return per_window >= (i_pad <= 128u ? 4096u : 8192u) && per_window <= 8192u;
+}
+
 }  // namespace maaso

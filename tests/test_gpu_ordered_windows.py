@@ -1,6 +1,6 @@
 """Windows laid out by class and prompt length, against the CPU oracle: sizes around the batches (16 and 64
-requests), the groups of 256 and the segments of 4096 requests, empty and single classes, ties on the between-token margin, and prefills
-beyond eight seconds."""
+requests), the groups of 256 and the segments of 4096 requests, empty and single classes, ties on the between-token margin, prefills
+beyond eight seconds, classes out of range, and a stream that takes more than one round of launches."""
 import numpy as np
 import pytest
 
@@ -66,6 +66,106 @@ def test_sweep_and_score(n_cand, i_pad, n_slo, window, n_req, variant):
             assert binding.maaso_ctx_device_status(dw.ctx) == 0
         finally:
             dw.close()
+
+
+def check_assign(w, window, latencies, out_of_range=False):
+    dw = binding.DeviceWorkload(w)
+    try:
+        print(f"laid-out assign I={w.i_pad} R={w.n_req} window={window} policy={w.policy}", flush=True)
+        got = dw.assign(window=window, latencies=latencies)
+        torch.cuda.synchronize()
+        assert binding.maaso_ctx_device_status(dw.ctx) == (1 if out_of_range else 0)
+        ref = oracle.score_assign(w, window=window)
+        for k in ("chosen", "slack") + (("ttft", "tbt", "e2e") if latencies else ()):
+            assert np.array_equal(got[k].cpu().numpy(), ref[k], equal_nan=True), k
+        assert int(got["n_satisfied"].item()) == ref["n_satisfied"]
+        assert np.array_equal(got["occ"].cpu().numpy()[0], ref["occ"])
+        assert np.array_equal(got["q_ticks"].cpu().numpy()[0].view(np.uint64), ref["q_ticks"])
+    finally:
+        dw.close()
+
+
+@pytest.mark.parametrize("i_pad,n_slo,window,n_req,policy,variant", [
+    (2, 3, 11, 500, 0, "mixed"), (1, 1, 64, 1000, 0, "alike"), (8, 3, 48, 999, 0, "mixed"), (8, 16, 4096, 9001, 0, "long"),
+    (16, 3, 512, 2600, 0, "mixed"), (16, 3, 1001, 5000, 0, "alike"), (40, 5, 2048, 7000, 0, "zeros"), (64, 3, 4097, 12_500, 0, "mixed"),
+    (64, 8, 16_384, 20_000, 0, "one length"), (100, 3, 4096, 9000, 0, "mixed"), (256, 3, 8192, 17_000, 0, "mixed"),
+    (16, 3, 11, 300, 1, "mixed"), (64, 3, 16, 330, 1, "mixed"), (100, 8, 32, 700, 1, "alike"), (256, 3, 333, 2000, 1, "mixed"),
+    (200, 16, 4096, 9000, 1, "long"), (3, 3, 16_384, 16_000, 1, "one class"),
+])
+def test_distributor(i_pad, n_slo, window, n_req, policy, variant):
+    w = variant_of(W.random_small(7 * i_pad + window, 1, i_pad, n_req, n_slo=n_slo, b_cap=64, jitter=variant != "alike"), variant)
+    w = W.replace(w, policy=policy, n_inst=np.full_like(w.n_inst, max(1, i_pad - 1)))
+    check_assign(w, window, latencies=policy == 1 or i_pad % 16 == 0)
+    # no instances at all, then requests of a class that does not exist (given to nobody)
+    check_assign(W.replace(w, n_inst=np.zeros_like(w.n_inst)), window, latencies=True)
+    cls = w.slo_class.copy()
+    cls[:: 7] = 200
+    dw = binding.DeviceWorkload(W.replace(w, slo_class=cls))
+    try:
+        got = dw.assign(window=window)
+        torch.cuda.synchronize()
+        assert binding.maaso_ctx_device_status(dw.ctx) == 1
+        binding.maaso_ctx_set_launch_shape(dw.ctx, 0, 0, 0, 2)  # the persistent kernel, on the state as it was given
+        exp = binding.DeviceWorkload(W.replace(w, slo_class=cls))
+        binding.maaso_ctx_set_launch_shape(exp.ctx, 0, 0, 0, 2)
+        ref = exp.assign(window=window)
+        torch.cuda.synchronize()
+        assert (got["chosen"][:: 7] == -1).all()
+        for k in ("chosen", "slack", "n_satisfied", "occ", "q_ticks"):
+            assert torch.equal(got[k], ref[k]), k
+        exp.close()
+    finally:
+        dw.close()
+
+
+def test_distributor_overloaded_then_idle():
+    """Queues of minutes build up in the first windows, most windows admit nothing, and pauses let the instances admit
+    again: windows are skipped, and taken up again, in every order."""
+    for seed, rate in ((3, 3000.0), (4, 60.0), (5, 900.0)):
+        w = W.random_small(seed, 1, 8, 40_000, b_cap=16, queued=False)
+        gaps = W.rng_for(seed, 5).exponential(1.0 / rate, size=w.n_req)
+        gaps[:: 6000] += 200.0
+        ticks = np.minimum(np.cumsum(gaps) * (1 << 20), 2.0 ** 32 - 1).astype(np.uint32)
+        w = W.replace(w, arrival_ticks=ticks, n_inst=np.full_like(w.n_inst, 8))
+        for policy in (0, 1):
+            check_assign(W.replace(w, policy=policy), 100, latencies=False)
+
+
+def test_distributor_in_rounds():
+    """More windows than the workspace takes at a time: the state, and the count, go from one round to the next."""
+    n = 11 * 9000 + 5
+    w = W.random_small(12, 1, 2, n, n_slo=16, b_cap=32)
+    w = W.replace(w, n_inst=np.full_like(w.n_inst, 2))
+    # a window of 11 requests of sixteen classes takes 16 batches of 64 places and their bounds
+    assert 9000 * 16 * (64 * 8 + 16) > 64 << 20
+    check_assign(w, 11, latencies=True)
+
+
+def test_distributor_unaligned_arrays_and_state_alone():
+    """Arrays at odd addresses (one request per thread), and a call that asks for the count alone."""
+    w = W.random_small(21, 1, 8, 4001, b_cap=32)
+    w = W.replace(w, n_inst=np.full_like(w.n_inst, 8))
+    ref = oracle.score_assign(w, window=64)
+    dw = binding.DeviceWorkload(w)
+    try:
+        up = lambda x, v: torch.from_numpy(np.concatenate([np.zeros(1, x.dtype), x]).view(v)).cuda()[1:]
+        rq = dict(n_req=w.n_req, prompt_len=up(w.prompt_len, np.int32), out_len=up(w.out_len, np.int32),
+                  slo_class=up(w.slo_class, np.uint8), arrival_ticks=up(w.arrival_ticks, np.int32))
+        pl = lambda: dict(n_cand=1, i_pad=8, n_inst=dw.n_inst, tp_idx=dw.tp_idx, max_batch=dw.max_batch,
+                          occ=dw.occ.clone(), q_ticks=dw.q_ticks.clone())
+        prm = dict(dw.param_args(), window=64)
+        chosen = torch.empty(w.n_req + 1, dtype=torch.int32, device="cuda")[1:]
+        count = torch.empty(1, dtype=torch.int64, device="cuda")
+        binding.maaso_score_assign(dw.ctx, **pl(), **rq, **prm, chosen=chosen, n_satisfied=count)
+        torch.cuda.synchronize()
+        assert np.array_equal(chosen.cpu().numpy(), ref["chosen"]) and int(count.item()) == ref["n_satisfied"]
+        live = pl()
+        binding.maaso_score_assign(dw.ctx, **live, **rq, **prm, n_satisfied=count.zero_())
+        torch.cuda.synchronize()
+        assert int(count.item()) == ref["n_satisfied"]
+        assert np.array_equal(live["occ"].cpu().numpy()[0], ref["occ"])
+    finally:
+        dw.close()
 
 
 def test_captured_sweep_keeps_off_the_workspace():
