@@ -160,7 +160,8 @@ __global__ __launch_bounds__((NW + 1) * 64) void assign_states_kernel(const Assi
                 atomicAdd(&t_sum[buf][j], t_j);
               }
             };
-            score_window<S, NW, kLog2, kSQ, kFirst, false>(deal, os, w, batch, len, cls, rec, occ, und, give);
+            score_window<S, NW, kLog2, kSQ, kFirst, false, false>(deal, os, w, batch, len, cls, rec, occ, und, nullptr, 0u,
+                                                                  [](uint32_t) { return 0u; }, give);
           }
           const uint32_t free = cleared_sum_buffer(buf);  // clean before anyone passes this barrier
           if (tid < 64u * S) { n_sum[free][tid] = 0u; t_sum[free][tid] = 0ull; }

@@ -352,6 +352,8 @@ OrderedSet plan_set(const SweepWindowSet& t, uint32_t n_slo, uint32_t size_log2,
 
 // All sets of `a` in a workspace of ws_bytes; false where they do not fit.
 bool plan_ordered(const SweepWindowArgs& a, uint32_t size_log2, void* ws, size_t ws_bytes, OrderedPlan& plan) {
+  plan.sets.ticks = nullptr;
+  plan.sets.row_ticks = 0u;
   plan.order.n_slo = a.n_slo;
   plan.order.status = a.status;
   plan.order.n_sets = a.n_sets;
@@ -394,9 +396,24 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, v
       plan_ordered(a, small ? 4u : 6u, ws, ws_bytes, plan)) {
     hipLaunchKernelGGL(order_requests_kernel, dim3(plan.blocks), dim3(plan.threads), plan.lds, s, plan.order);
     const dim3 g((a.n_cand + 3u) / 4u * a.n_sets), b(kAssignThreads);
+    TicksArgs t;
+    t.n_batches = (uint32_t)(((uint64_t)a.sets[0].n_req + a.sets[0].window - 1u) / a.sets[0].window) * plan.sets.set[0].batches;
+    const bool table = !small && a.n_sets == 1u && sweep_sums_batches(a.i_pad, per_window) &&
+                       up256(plan.bytes) + (uint64_t)t.n_batches * a.cells * sizeof(uint32_t) <= ws_bytes;
+    if (table) {
+      t.tab = a.tab;
+      t.cells = a.cells;
+      t.len = plan.sets.set[0].len;
+      t.batch = plan.sets.set[0].batch;
+      t.ticks = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(ws) + up256(plan.bytes));
+      plan.sets.ticks = t.ticks;
+      plan.sets.row_ticks = t.n_batches;
+      hipLaunchKernelGGL(batch_ticks_kernel, dim3((t.n_batches / 4u + 3u) / 4u, (a.cells + 63u) / 64u), dim3(256), 0, s, t);
+    }
     auto launch = [&](auto s_) {
-      if (small) hipLaunchKernelGGL((sweep_ordered_kernel<kScore, s_(), 4, true, kSQ>), g, b, lds, s, a, plan.sets);
-      else hipLaunchKernelGGL((sweep_ordered_kernel<kScore, s_(), 6, false, kSQ>), g, b, lds, s, a, plan.sets);
+      if (small) hipLaunchKernelGGL((sweep_ordered_kernel<kScore, s_(), 4, true, kSQ, false>), g, b, lds, s, a, plan.sets);
+      else if (table) hipLaunchKernelGGL((sweep_ordered_kernel<kScore, s_(), 6, false, kSQ, true>), g, b, lds, s, a, plan.sets);
+      else hipLaunchKernelGGL((sweep_ordered_kernel<kScore, s_(), 6, false, kSQ, false>), g, b, lds, s, a, plan.sets);
     };
     if (a.i_pad <= 64u) launch(std::integral_constant<int, 1>{});
     else if (a.i_pad <= 128u) launch(std::integral_constant<int, 2>{});

@@ -168,6 +168,18 @@ __global__ __launch_bounds__(1024) void order_requests_kernel(const OrderArgs a)
   }
 }
 
+// Prefill ticks of every batch on every row of the profile tables, where so many candidates are to be scored that each row
+// serves a batch many times: ticks[row * n_batches + b].  A batch whose longest prompt takes eight seconds and more on
+// a row has no sum here, and none is looked up.
+struct TicksArgs {
+  const float* tab;
+  uint32_t cells;
+  const float* len;
+  const Batch* batch;
+  uint32_t n_batches;  // of all windows, whole groups
+  uint32_t* ticks;
+};
+
 // How the NW wavefronts that share a window take its batches of 2^kLog2 requests: groups in turn, 64 batches a pass.
 template <int NW, int kLog2>
 struct Dealt {
@@ -193,6 +205,27 @@ struct Dealt {
 // addition rounds x to ticks, to nearest even as rint does, and leaves them in the low bits.
 constexpr float kTickBase = 8.0f;
 __device__ __forceinline__ uint32_t tick_bits(float pre) { return __float_as_uint(pre + kTickBase); }
+
+// A wavefront takes a group of four batches of 64, four requests per lane, through 64 rows.
+__global__ __launch_bounds__(256) void batch_ticks_kernel(const TicksArgs a) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t g = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (4u * g >= a.n_batches) return;
+  const f32x4 len = reinterpret_cast<const f32x4*>(a.len)[(size_t)g * 64u + lane];
+  const uint32_t b = 4u * g + (lane >> 4), filler = 64u - a.batch[b].n();
+  const uint32_t r0 = blockIdx.y * 64u, rows = min(64u, a.cells - r0);
+  const uint32_t own = r0 + min(lane, rows - 1u);
+  const float own_a = a.tab[own], own_p = a.tab[a.cells + own];
+  uint32_t* to = a.ticks + (size_t)r0 * a.n_batches + b;
+  for (uint32_t r = 0; r < rows; ++r, to += a.n_batches) {
+    const float ra = lane_value(own_a, (int)r), rp = lane_value(own_p, (int)r);
+    const uint32_t t = row_sum_u32(tick_bits(fmaf(rp, len.x, ra)) + tick_bits(fmaf(rp, len.y, ra)) +
+                                   tick_bits(fmaf(rp, len.z, ra)) + tick_bits(fmaf(rp, len.w, ra)));
+    // the places behind a batch's last request hold length 0: they counted with the prefill of none
+    if ((lane & 15u) == 0u)
+      *to = t - 64u * __float_as_uint(kTickBase) - filler * (tick_bits(ra) - __float_as_uint(kTickBase));
+  }
+}
 
 // What each lane's batch comes to: kOpen, kNobody, or the instance that takes all of it.
 constexpr uint32_t kOpen = 0xffffffffu, kNobody = 0xfffffffeu;
@@ -271,11 +304,13 @@ __device__ __forceinline__ uint32_t group_ticks(const f32x4& len, uint32_t bits,
 // uniform: instance j takes num requests of `ticks` prefill in all.
 // `batch`: the lane's of the first pass; `len`: its lengths in the wavefront's first kFirst groups, the only ones there are
 // with kOnly.  A wavefront asks for both ahead of the evaluation of its instances.
-template <int S, int NW, int kLog2, bool kSQ, int kFirst, bool kOnly, class Give>
+// kTable: what batches add up to is in `ticks` (of this window; row_ticks entries on for every row of the tables), and row_of(j)
+// says which row instance j is on.
+template <int S, int NW, int kLog2, bool kSQ, int kFirst, bool kOnly, bool kTable, class Give, class RowOf>
 __device__ __forceinline__ void score_window(const Dealt<NW, kLog2>& deal, const OrderedSet& os, uint32_t w, f32x4 batch,
                                              const f32x4 (&len)[kFirst ? kFirst : 1], const ClassRow* cls,
                                              const SlotRecord (&rec)[S], const int32_t (&occ)[S], const InstanceSet<S>& set,
-                                             Give&& give) {
+                                             const uint32_t* ticks, uint32_t row_ticks, RowOf&& row_of, Give&& give) {
   static_assert(kFirst <= (int)Dealt<NW, kLog2>::kPass, "of the first pass");
   constexpr uint32_t kSize = 1u << kLog2, kIn = kGroup >> kLog2;
   const uint32_t lane = deal.lane;
@@ -293,6 +328,18 @@ __device__ __forceinline__ void score_window(const Dealt<NW, kLog2>& deal, const
       const uint32_t j = (uint32_t)__builtin_amdgcn_readlane((int)to, (int)__builtin_ctzll(todo));
       const unsigned long long mask = lane_mask(to == j);
       todo &= ~mask;
+      if constexpr (kTable) {
+        const uint32_t t = in_mask(mask) ? ticks[(size_t)row_of(j) * row_ticks + deal.batch(pass, lane)] : 0u;
+        uint32_t n = in_mask(mask) ? b.n() : 0u, sum = t & 0x3ffffffu;
+        wave_sum_pair(n, sum);
+        unsigned long long all = sum;
+        if (lane_mask(t >> 26 != 0u) != 0ull) {
+          rare_path();
+          all += (unsigned long long)wave_sum_u32(t >> 26) << 26;
+        }
+        give(j, n, all);
+        continue;
+      }
       float a = lane_value(rec[0].a, (int)(j & 63u)), p = lane_value(rec[0].p, (int)(j & 63u));
 #pragma unroll
       for (int s = 1; s < S; ++s)

@@ -3,11 +3,12 @@
 // without the block's barriers and without a look at most requests.
 //
 // What bounds it: vector issue where candidates fill the chip (8192 candidates x 131,072 requests x 128 instances, windows
-// of 4096: 1.87 -> 0.67 ms; 3808 -> 1340 vector instructions per wavefront and window, two fifths of them the additions of prefills);
+// of 4096: 1.87 -> 0.67 ms with the batches' prefills added up here, 0.52 with their sums looked up, which a launch of 27 us
+// works out for all rows of the tables; 3808 -> 1340 -> 900 vector instructions per wavefront and window);
 // the chain of one window after the other where they do not (Alg. 2, 720 deployments x three sets, windows of 256: 1.25 -> 0.70 ms, 3100
-// cycles per window of the longest chain: instances 490, search 780, scoring 1530, state 290).  At 72 registers and fewer, up to seven
-// or eight wavefronts share a SIMD; the first form, which kept the lengths of a window in registers and had a code path per number
-// of instances, spilled and was no faster than before.
+// cycles per window of the longest chain: instances 490, search 780, scoring 1530, state 290).  Registers are held to what six or
+// seven wavefronts a SIMD take; the first form, which kept the lengths of a window in registers and had a code path per number
+// of instances, spilled and was no faster than before.  Batches of 32: 0.58 ms (half as many requests left open, but a pass more).
 #pragma once
 
 #include "ordered_windows.hpp"
@@ -18,12 +19,14 @@ namespace maaso {
 
 struct OrderedSets {
   OrderedSet set[kMaxSweepSets];
+  const uint32_t* ticks;  // kTable: batch_ticks_kernel's, of the only set
+  uint32_t row_ticks;     // its batches
 };
 
 // kSmall: a window is two groups at most.
 // (four wavefronts a SIMD with kSmall: held to eight, scalars spill and the chain gets longer)
-template <bool kScore, int S, int kLog2, bool kSmall, bool kSQ>
-__global__ __launch_bounds__(kAssignThreads, kSmall ? 4 : S <= 2 ? 7 : 4) void sweep_ordered_kernel(const SweepWindowArgs a,
+template <bool kScore, int S, int kLog2, bool kSmall, bool kSQ, bool kTable>
+__global__ __launch_bounds__(kAssignThreads, kSmall ? 4 : S == 1 ? 7 : S == 2 ? 6 : 4) void sweep_ordered_kernel(const SweepWindowArgs a,
                                                                                        const OrderedSets o) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* tab = reinterpret_cast<float*>(smem);
@@ -94,7 +97,18 @@ __global__ __launch_bounds__(kAssignThreads, kSmall ? 4 : S <= 2 ? 7 : 4) void s
         for (int s = 0; s < S; ++s)
           if (j == (uint32_t)s * 64u + lane) { num[s] += n_j; ticks[s] += t_j; }
       };
-      score_window<S, 1, kLog2, kSQ, kFirst, kSmall>(deal, os, w, batch, len, cls, rec, occ, und, give);
+      auto row_of = [&](uint32_t j) __attribute__((always_inline)) {
+        uint32_t row = 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (j >> 6 == (uint32_t)s) {
+            const uint32_t eff = min(((uint32_t)occ[s] + 1u) | (0u - a.mp.tbt_mode), slot[s].B);
+            row = (uint32_t)__builtin_amdgcn_readlane((int)(slot[s].row0 + eff), (int)(j & 63u));
+          }
+        return row;
+      };
+      const uint32_t* table = kTable ? o.ticks + (size_t)w * os.batches : nullptr;
+      score_window<S, 1, kLog2, kSQ, kFirst, kSmall, kTable>(deal, os, w, batch, len, cls, rec, occ, und, table, o.row_ticks, row_of, give);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         slot[s].occ += (int32_t)num[s];

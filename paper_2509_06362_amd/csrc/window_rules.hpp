@@ -81,6 +81,15 @@ constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, u
   return per_window >= 4096u && !shortest_queue;
 }
 
+// Whether the prefills of every batch are then summed up ahead, on every row of the tables (batch_ticks_kernel): a launch of some
+// 0.8 us per 4096 requests and thousand rows, for which a settled batch costs a look-up.  Measured, without the sums over with
+// them, fresh jittered instances and 516 rows / loaded ones and 1028: 64 slots, 1100 candidates: windows of 512: 0.99 / 1.00, 1024: 1.03 / 1.04,
+// 4096: 1.21 / 1.19, 16,384: 1.72 / 1.49; 9000: 512: 1.05 / 1.05, 1024: 1.06 / 1.08, 4096: 1.21 / 1.22; 300: 4096: 1.28 / 1.20; 4 slots, 1100: 1024: 0.80,
+// 4096: 1.00 / 0.85, 16,384: 1.41 / 1.06; 9000: 1.16 / 1.00, 16,384: 1.72 / 1.30.
+constexpr bool sweep_sums_batches(uint32_t i_pad, uint64_t per_window) {
+  return per_window >= (i_pad >= 32u ? 2048u : 16384u);
+}
+
 // The same for the distributor (assign_ordered_kernels.hpp, against the persistent kernel): the chain of windows
 // is then one block's, which looks for the instances that count and bounds their slacks one after the other, so it pays
 // with few slots, or with windows that are much to score.  Measured, the persistent kernel's time over it, some hundred windows,

@@ -44,6 +44,9 @@ def variant_of(w, variant):
     (1000, 70, 3, 500, 700, "mixed"), (1000, 130, 3, 300, 400, "alike"),        # two and four slots a lane
     (400, 3, 3, 2048, 4100, "one length"), (64, 5, 5, 4095, 8190, "mixed"), (64, 4, 3, 4096, 8193, "long"),
     (65, 4, 16, 4097, 9000, "zeros"), (64, 140, 3, 8200, 8300, "alike"), (4100, 2, 3, 256, 300, "mixed"),
+    # with the sums of batches worked out ahead
+    (400, 40, 3, 2048, 4100, "long"), (64, 33, 16, 4100, 8300, "one length"), (64, 70, 2, 2500, 5100, "alike"),
+    (64, 4, 3, 16_384, 16_900, "mixed"),
     (1000, 3, 3, 5000, 300, "mixed"),                                           # one window, shorter than its size
 ])
 def test_sweep_and_score(n_cand, i_pad, n_slo, window, n_req, variant):
