@@ -61,6 +61,7 @@ struct maaso_ctx {
   void* ws;             // device workspace: sized at load, resized only by maaso_ctx_reserve
   size_t ws_bytes;
   uint32_t ws_allocations;  // how often the workspace has been allocated (load counts as one)
+  bool ws_captured;     // a captured launch works in the workspace, and may replay beside any later call
   // one call at a time: the host part of a call is exclusive, and a call on another stream than the
   // context's previous call is ordered behind it with an event
   std::atomic<int> in_call;
@@ -122,6 +123,16 @@ struct TimedRegion {
 // Compute calls never allocate: a call whose shape needs more than the context holds is refused.
 int need_workspace(const maaso_ctx* ctx, size_t bytes) {
   return bytes <= ctx->ws_bytes ? MAASO_OK : MAASO_E_WORKSPACE;
+}
+
+bool is_captured(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hip_ok(hipStreamIsCapturing(s, &status)) && status != hipStreamCaptureStatusNone;
+}
+
+// Before launches that work in the workspace and are charged for it.
+void enter_workspace(maaso_ctx* ctx, hipStream_t s) {
+  if (!ctx->ws_captured && is_captured(s)) ctx->ws_captured = true;
 }
 
 // Set-up only (load, maaso_ctx_reserve): (re)allocates the workspace when it is too small.
@@ -476,12 +487,9 @@ template <bool kScore>
 int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, const maaso_ctx* ctx, bool may_use_ws, hipStream_t s) {
   const size_t lds = (size_t)3 * ctx->cells * sizeof(float);  // profile tables
   const uint32_t n_cu = (uint32_t)ctx->n_cu;
-  void* ws = nullptr;
-  if (may_use_ws) {
-    // A captured launch may run later beside other work of the context: it keeps nothing in the workspace.
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hip_ok(hipStreamIsCapturing(s, &capturing)) && capturing == hipStreamCaptureStatusNone) ws = ctx->ws;
-  }
+  // Calls that are charged with no workspace keep out of it while it holds what another call may still need: a captured
+  // launch may run beside any later call, and the windowed distributor's profile is read from it.
+  void* ws = may_use_ws && !ctx->ws_captured && !ctx->window_profiled && !is_captured(s) ? ctx->ws : nullptr;
   return policy ? launch_sweep_window_v<kScore, true>(a, lds, n_cu, ws, ctx->ws_bytes, s)
                 : launch_sweep_window_v<kScore, false>(a, lds, n_cu, ws, ctx->ws_bytes, s);
 }
@@ -872,6 +880,7 @@ int launch_split(maaso_ctx* ctx, const maaso_requests* rq, uint32_t tight_classe
   a.arrival_ticks = rq->arrival_ticks;
   a.tight_classes = tight_classes;
   a.n_slo = ctx->n_slo;
+  enter_workspace(ctx, s);
   a.block_tight = static_cast<uint32_t*>(ctx->ws);
   a.n_tight = n_tight;
   a.prompt_out = prompt_len_out;
@@ -1166,6 +1175,7 @@ int placement_sweep_impl(maaso_ctx* ctx, const maaso_placements* pl, const maaso
   }
   rc = need_workspace(ctx, bytes);
   if (rc != MAASO_OK) return rc;
+  if (R > kSmallRequests) enter_workspace(ctx, s);  // (fewer are not grouped there)
   return launch_static_sweep(ctx, pl, rq, prm, ctx->ws, ctx->ws_bytes, sat_count, sat_ratio, best_cand, s);
 }
 
@@ -1652,12 +1662,16 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
 
+  enter_workspace(ctx, s);
   // Few slots, or long windows: in launches over the requests laid out.  The window_blocks knob and the profile ask for
   // the persistent kernel here too.
   const bool ordered = a.bounds.narrow && assign_lays_out(pl->i_pad, prm->window < R ? prm->window : R, prm->policy != 0u);
   if (ordered && ctx->window_blocks == 0u && !(ctx->window_profile && !prm->policy && !lat)) {
     const int done = launch_assign_ordered(ctx, a, pl, rq, prm, out, lat, s);
-    if (done != kNotTaken) return done;
+    if (done != kNotTaken) {
+      ctx->window_profiled = false;
+      return done;
+    }
   }
 
   // Windowed: one persistent kernel; all blocks must be resident at once (one per compute unit at

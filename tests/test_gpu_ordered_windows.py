@@ -194,3 +194,41 @@ def test_captured_sweep_keeps_off_the_workspace():
                 assert torch.equal(x, y)
     finally:
         dw.close()
+
+
+def test_windowed_sweep_keeps_off_a_workspace_that_others_need():
+    """Beside a captured static sweep that replays, and behind a profiled distributor call whose figures are read later."""
+    w = W.random_small(33, 1200, 6, 9000, b_cap=32)
+    dw = binding.DeviceWorkload(w)
+    try:
+        pl = dict(n_cand=1, i_pad=6, n_inst=dw.n_inst[:1], tp_idx=dw.tp_idx[:1], max_batch=dw.max_batch[:1],
+                  occ=dw.occ[:1].clone(), q_ticks=dw.q_ticks[:1].clone())
+        binding.maaso_ctx_window_profile(dw.ctx, True)
+        binding.maaso_score_assign(dw.ctx, **pl, **dw.request_args(), **{**dw.param_args(), "policy": 0}, window=3000,
+                                   arrival_ticks=dw.arrival_ticks, n_satisfied=torch.zeros(1, dtype=torch.int64, device="cuda"))
+        before = binding.maaso_ctx_window_phases(dw.ctx)
+        assert before["windows"] == 3
+        windowed = dw.sweep(window=300)
+        torch.cuda.synchronize()
+        assert binding.maaso_ctx_window_phases(dw.ctx) == before
+        binding.maaso_ctx_window_profile(dw.ctx, False)
+
+        s = torch.cuda.Stream()
+        static = dw.sweep(stream=s)
+        torch.cuda.synchronize()
+        out = tuple(torch.empty_like(x) for x in static)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            dw.sweep(out=out, stream=s)
+        for _ in range(3):
+            for x in out:
+                x.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s):
+                g.replay()
+            again = dw.sweep(window=300)
+            torch.cuda.synchronize()
+            for x, y in zip(out + again, static + windowed):
+                assert torch.equal(x, y)
+    finally:
+        dw.close()
