@@ -461,7 +461,8 @@ int maaso_resource_partition(maaso_ctx* ctx, uint32_t n_gpus, const float* phi_t
  * candidates keep each other.  n_kept[g] (DEVICE, [n_groups]) counts the retained candidates of
  * group g.  group_offsets (DEVICE, [n_groups+1]) must be non-decreasing with its last entry at most
  * n_cand; a group that is not raises MAASO_DEV_BAD_CHAIN, gets n_kept 0 and leaves keep untouched.
- * Candidates outside every group are not written.  Errors: INVALID_ARG, SHAPE, BUSY, HIP. */
+ * Candidates outside every group are not written; where offsets that run backwards let groups overlap, keep goes by the
+ * last group that holds the candidate.  Errors: INVALID_ARG, SHAPE, BUSY, HIP. */
 int maaso_batch_size_prune(maaso_ctx* ctx, uint32_t n_cand, const uint32_t* group_offsets,
                            uint32_t n_groups, const uint32_t* sat_count, const float* latency,
                            uint8_t* keep, uint32_t* n_kept, void* hip_stream);

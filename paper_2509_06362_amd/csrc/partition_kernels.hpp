@@ -227,6 +227,15 @@ struct PruneArgs {
 
 constexpr int kPruneTile = 256;
 
+// Whether a group behind g holds candidate i as well (offsets that run backwards let groups overlap).
+__device__ inline bool held_later(const PruneArgs& a, uint32_t g, uint32_t i) {
+  for (uint32_t h = g + 1u; h < a.n_groups; ++h) {
+    const uint32_t h1 = a.group_offsets[h + 1u];
+    if (a.group_offsets[h] <= i && i < h1 && h1 <= a.n_cand) return true;
+  }
+  return false;
+}
+
 // One block per group.  Candidate i goes when it meets no request's SLO, or when another candidate
 // of its group is at least as good in both respects and better in one: sat_j >= sat_i and
 // lat_j <= lat_i with one of them strict.  Equal candidates keep each other; a NaN latency compares
@@ -241,6 +250,10 @@ __global__ __launch_bounds__(kPruneTile) void batch_prune_kernel(const PruneArgs
     if (tid == 0u) { raise_status(a.status, 8u); a.n_kept[g] = 0u; }
     return;
   }
+  // A candidate of several groups goes by the last of them, whichever block ends first.
+  bool overlaps = false;
+  for (uint32_t h = g + 1u + tid; h < a.n_groups; h += kPruneTile) overlaps |= a.group_offsets[h] < o1;
+  overlaps = __syncthreads_or(overlaps) != 0;
   uint32_t kept = 0;
   for (uint32_t base = o0; base < o1; base += kPruneTile) {  // uniform trip count: barriers inside
     const uint32_t i = base + tid;
@@ -260,7 +273,7 @@ __global__ __launch_bounds__(kPruneTile) void batch_prune_kernel(const PruneArgs
       }
     }
     const bool k = mine && sat_i != 0u && !dominated;
-    if (mine) a.keep[i] = k ? 1u : 0u;
+    if (mine && !(overlaps && held_later(a, g, i))) a.keep[i] = k ? 1u : 0u;
     kept += k ? 1u : 0u;
   }
   for (int d = 32; d >= 1; d >>= 1) kept += __shfl_xor(kept, d);

@@ -1612,3 +1612,20 @@ def test_valu_probe_reports_a_plausible_rate():
     with pytest.raises(binding.MaasoError) as e:
         binding.maaso_probe_valu(0, 0)
     assert e.value.status == -1
+
+
+def test_batch_size_prune_of_overlapping_groups():
+    """Offsets that run backwards: a candidate of several groups goes by the last, however the blocks end.  The first
+    group is the longest to prune, so it ends last."""
+    rng = np.random.default_rng(19)
+    n = 900
+    sat = rng.integers(0, 9, n).astype(np.uint32)
+    lat = rng.random(n).astype(np.float32)
+    offsets = [0, n, 3, 300, 100, 700]
+    ref_keep, ref_n = oracle.batch_size_prune(offsets, sat, lat)
+    dw = binding.DeviceWorkload(W.config0())
+    try:
+        keep, n_kept = prune_on_gpu(dw.ctx, dw.prompt_len.device, offsets, sat, lat)
+        assert np.array_equal(keep, ref_keep) and np.array_equal(n_kept, ref_n)
+    finally:
+        dw.close()
