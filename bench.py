@@ -379,7 +379,7 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
     traffic, traffic_info = measured_traffic(w.name)
     if kind == "sweep" and sweep_window:
         roofline = {
-            "kernel": "sweep_seq_kernel" if sweep_window == 1 else "sweep_window_kernel", "bound": "alu",
+            "kernel": "sweep_seq_kernel" if sweep_window == 1 else "order_requests + batch_ticks + sweep_ordered kernels", "bound": "alu",
             "achieved": None, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlaneop/s", "frac": None,
             "traffic": traffic, "kernel_ms": k_avg_s * 1e3, "launches_timed": k_n,
             "kernel_triples_per_s": triples_sweep / k_avg_s,
@@ -585,7 +585,7 @@ def bench_alg2(args) -> int:
                            "Alg. 1's selection per set, partition scan; |R_t| stays on the device",
                    "partition": {"g_t": int(part[0]), "g_l": int(part[1]),
                                  "heterogeneous": int(part[2]), "phi_opt": float(res["phi_opt"].item())}},
-        "roofline": {"kernel": "sweep_window_kernel", "bound": "latency", "achieved": None, "peak": None,
+        "roofline": {"kernel": "order_requests + sweep_ordered kernels", "bound": "latency", "achieved": None, "peak": None,
                      "unit": None, "frac": None, "traffic": None,
                      "kernel_ms": k_ms / max(k_n, 1), "launches_timed": k_n,
                      "kernel_triples_per_s": triples_step / k_total_s,
