@@ -69,7 +69,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void assign_states_kernel(const Assi
   uint32_t buf = 0;
   SlotRecord rec[S];
   float svc[S];
-  uint32_t at_w[S];  // effective batch that rec and svc were evaluated at
+  uint32_t at_w[S];  // effective batch that rec and svc were evaluated at; 0: at none
 #pragma unroll
   for (int s = 0; s < S; ++s) at_w[s] = 0u;
   // The windows, for a wavefront that scores and for the one that writes: each waits for its own memory operations only.
@@ -100,7 +100,7 @@ __global__ __launch_bounds__((NW + 1) * 64) void assign_states_kernel(const Assi
           unsigned long long bad;
           slot[s].evaluate(tab, a.cells, a.mp, rec[s], svc[s], past, bad);
           bad_slot |= bad;
-          at_w[s] = eff;
+          at_w[s] = in_mask(bad) ? 0u : eff;  // a record that stands in for none is not kept (an occupancy may return from below zero)
         }
         rec[s].wait = slot[s].wait_with(past, slot[s].any_wide());
         near |= lane_mask(!(rec[s].wait > reach)) & lane_mask((uint32_t)s * 64u + lane < n);

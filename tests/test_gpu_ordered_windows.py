@@ -121,6 +121,39 @@ def test_distributor(i_pad, n_slo, window, n_req, policy, variant):
         dw.close()
 
 
+@pytest.mark.parametrize("i_pad,window,n_req,policy", [
+    (8, 48, 400, 0), (16, 512, 2600, 0), (64, 2048, 6200, 0), (8, 11, 200, 1), (64, 16, 330, 1), (100, 32, 500, 1), (256, 33, 500, 1),
+])
+@pytest.mark.parametrize("mode,kappa", [(0, 0.5), (1, 0.0)])
+@pytest.mark.parametrize("pause", [0, 4 << 20])
+def test_distributor_with_flagged_slots(i_pad, window, n_req, policy, mode, kappa, pause):
+    """Slots outside the tables, and occupancies below zero that time brings back, with a batch cap of one, one that the next
+    window's batch is at once, and one that it grows to: as the persistent kernel, which evaluates every slot at every window."""
+    w = W.random_small(5 * i_pad + window, 1, i_pad, n_req, n_slo=3, b_cap=64, pen_kappa=kappa)
+    i = np.arange(n_req, dtype=np.uint64)
+    tp, B, occ, q = w.tp_idx.copy(), w.max_batch.copy(), w.occ.copy(), w.q_ticks.copy()
+    back = [1, 2, 3, i_pad - 1]  # slots that come back
+    q[:, 5:] += np.uint64(60 << 20)  # most others are busy
+    B[:, back], occ[:, back], q[:, back] = [1, 8, 64, 16], [-3, -5, -2, -3], 0
+    tp[:, 0], B[:, i_pad // 2] = 9, 65
+    w = W.replace(w, policy=policy, tbt_mode=mode, tp_idx=tp, max_batch=B, occ=occ, q_ticks=q, n_inst=np.full_like(w.n_inst, i_pad),
+                  arrival_ticks=(i * 300 + i // window * np.uint64(pause)).astype(np.uint32))
+    got = []
+    for blocks in (0, 1):
+        print(f"flagged slots I={i_pad} window={window} R={n_req} policy={policy} mode={mode} pause={pause} blocks={blocks}", flush=True)
+        dw = binding.DeviceWorkload(w)
+        try:
+            binding.maaso_ctx_set_launch_shape(dw.ctx, 0, 0, 0, blocks)
+            got.append(dw.assign(window=window))
+            torch.cuda.synchronize()
+            assert binding.maaso_ctx_device_status(dw.ctx) == 2
+        finally:
+            dw.close()
+    assert np.isin(got[1]["chosen"].cpu().numpy(), back).any()
+    for k in got[0]:
+        assert np.array_equal(got[0][k].cpu().numpy(), got[1][k].cpu().numpy(), equal_nan=got[0][k].is_floating_point()), k
+
+
 def test_distributor_overloaded_then_idle():
     """Queues of minutes build up in the first windows, most windows admit nothing, and pauses let the instances admit
     again: windows are skipped, and taken up again, in every order."""
