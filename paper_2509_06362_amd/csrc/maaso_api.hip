@@ -1382,7 +1382,15 @@ int maaso_batch_size_prune(maaso_ctx* ctx, uint32_t n_cand, const uint32_t* grou
   a.keep = keep;
   a.n_kept = n_kept;
   a.status = ctx->status;
-  hipLaunchKernelGGL(batch_prune_kernel, dim3(n_groups), dim3(kPruneTile), 0, s, a);
+  const bool small = prune_in_fours(n_cand, n_groups);
+  if (small) hipLaunchKernelGGL(batch_prune_small_kernel, dim3(n_groups / 4u + (n_groups % 4u != 0u ? 1u : 0u)), dim3(kPruneTile), 0, s, a);
+  else if (n_groups <= kPruneSingle) hipLaunchKernelGGL((batch_prune_kernel<true>), dim3(n_groups), dim3(kPruneTile), 0, s, a);
+  else hipLaunchKernelGGL((batch_prune_kernel<false>), dim3(n_groups), dim3(kPruneTile), 0, s, a);
+  if (n_groups > (small ? kPruneLook : kPruneSingle)) {
+    const uint32_t per_block = std::max(8u * (uint32_t)kPruneTile, (uint32_t)(((uint64_t)n_groups + 1023u) / 1024u));
+    hipLaunchKernelGGL(prune_overlaps_kernel, dim3((uint32_t)(((uint64_t)n_groups + per_block - 1u) / per_block)), dim3(kPruneTile), 0, s, a,
+                       per_block);
+  }
   return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
 }
 

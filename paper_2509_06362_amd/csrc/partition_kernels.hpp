@@ -227,7 +227,23 @@ struct PruneArgs {
 
 constexpr int kPruneTile = 256;
 
-// Whether a group behind g holds candidate i as well (offsets that run backwards let groups overlap).
+// Offsets that run backwards let groups overlap; a candidate of several goes by the last of them.  Up to kPruneSingle groups
+// every block looks through the offsets behind its own for a step backwards.  That grows with the square of their number, so with
+// more of them prune_overlaps_kernel looks behind this one, once, and small groups go four to a block, a wavefront each, which
+// pays for looking.  Us, without any look and a block per group / with every block looking / this: of 7 candidates, 2048 groups: 5.3 /
+// 5.5 / 5.4, 8192: 9.1 / 18.6 / 8.5, 65,536: 57 / 564 / 30, 262,144: 242 / 8439 / 133; of 65, 24: 6.3 / 6.8 / 6.7, 2048: 12.0 / 13.2 /
+// 13.2, 2100: 13.2 / 14.1 / 15.1; of 100, 8192: 53 / 62 / 55, 32,768: 197 / 321 / 198; of 0 to 59, 1500: 8.4 / 9.4 / 7.1.
+constexpr uint32_t kPruneSingle = 2048;
+constexpr uint32_t kPruneLook = 8192;  // groups up to which the blocks of four look as well
+
+// Whether groups go four to a block.  In us, a block per group / four to a block: 33 candidates each, 1100 groups 6.6 / 6.1, 2048: 8.8 / 6.4; 65 each,
+// 1100: 9.8 / 10.6, 2048: 13.4 / 11.1; 0 to 119 each, 1100: 13.0 / 16.8, 2048: 16.8 / 17.8, 8192: 43 / 35; 0 to 239 each, 2048: 30 / 59.
+constexpr bool prune_in_fours(uint32_t n_cand, uint32_t n_groups) {
+  const uint32_t each = n_cand / n_groups;
+  return each <= 64u && n_groups > (each <= 32u ? 1024u : kPruneSingle);
+}
+
+// Whether a group behind g holds candidate i as well.
 __device__ inline bool held_later(const PruneArgs& a, uint32_t g, uint32_t i) {
   for (uint32_t h = g + 1u; h < a.n_groups; ++h) {
     const uint32_t h1 = a.group_offsets[h + 1u];
@@ -236,24 +252,20 @@ __device__ inline bool held_later(const PruneArgs& a, uint32_t g, uint32_t i) {
   return false;
 }
 
-// One block per group.  Candidate i goes when it meets no request's SLO, or when another candidate
+// A block prunes group g = [o0, o1).  Candidate i goes when it meets no request's SLO, or when another candidate
 // of its group is at least as good in both respects and better in one: sat_j >= sat_i and
 // lat_j <= lat_i with one of them strict.  Equal candidates keep each other; a NaN latency compares
 // false either way, so such a candidate neither removes another nor is removed by one.
-__global__ __launch_bounds__(kPruneTile) void batch_prune_kernel(const PruneArgs a) {
+// kLook: back(), asked once, says whether offsets run backwards behind g as far as this thread has seen; a candidate that a later
+// group holds is then left to that one.
+template <bool kLook, class Back>
+__device__ inline void prune_group(const PruneArgs& a, uint32_t g, uint32_t o0, uint32_t o1, Back&& back) {
   __shared__ uint32_t t_sat[kPruneTile];
   __shared__ float t_lat[kPruneTile];
   __shared__ uint32_t wave_kept[kPruneTile / 64];
-  const uint32_t g = blockIdx.x, tid = threadIdx.x;
-  const uint32_t o0 = a.group_offsets[g], o1 = a.group_offsets[g + 1];
-  if (o0 > o1 || o1 > a.n_cand) {  // not a group: flagged, nothing written but its count
-    if (tid == 0u) { raise_status(a.status, 8u); a.n_kept[g] = 0u; }
-    return;
-  }
-  // A candidate of several groups goes by the last of them, whichever block ends first.
-  bool overlaps = false;
-  for (uint32_t h = g + 1u + tid; h < a.n_groups; h += kPruneTile) overlaps |= a.group_offsets[h] < o1;
-  overlaps = __syncthreads_or(overlaps) != 0;
+  __shared__ uint32_t overlaps;
+  const uint32_t tid = threadIdx.x;
+  if (kLook && tid == 0u) overlaps = 0u;
   uint32_t kept = 0;
   for (uint32_t base = o0; base < o1; base += kPruneTile) {  // uniform trip count: barriers inside
     const uint32_t i = base + tid;
@@ -264,6 +276,7 @@ __global__ __launch_bounds__(kPruneTile) void batch_prune_kernel(const PruneArgs
     for (uint32_t jb = o0; jb < o1; jb += kPruneTile) {
       __syncthreads();
       if (jb + tid < o1) { t_sat[tid] = a.sat_count[jb + tid]; t_lat[tid] = a.latency[jb + tid]; }
+      if (kLook && base == o0 && jb == o0 && back()) overlaps = 1u;
       __syncthreads();
       const uint32_t n = min((uint32_t)kPruneTile, o1 - jb);
       for (uint32_t j = 0; j < n; ++j) {
@@ -273,7 +286,7 @@ __global__ __launch_bounds__(kPruneTile) void batch_prune_kernel(const PruneArgs
       }
     }
     const bool k = mine && sat_i != 0u && !dominated;
-    if (mine && !(overlaps && held_later(a, g, i))) a.keep[i] = k ? 1u : 0u;
+    if (mine && !(kLook && overlaps != 0u && held_later(a, g, i))) a.keep[i] = k ? 1u : 0u;
     kept += k ? 1u : 0u;
   }
   for (int d = 32; d >= 1; d >>= 1) kept += __shfl_xor(kept, d);
@@ -283,6 +296,109 @@ __global__ __launch_bounds__(kPruneTile) void batch_prune_kernel(const PruneArgs
     uint32_t t = 0;
     for (int w = 0; w < kPruneTile / 64; ++w) t += wave_kept[w];
     a.n_kept[g] = t;
+  }
+}
+
+// [o0, o1) is not a group: flagged, nothing written but its count.
+__device__ inline bool is_group(const PruneArgs& a, uint32_t g, uint32_t o0, uint32_t o1, bool first) {
+  if (o0 <= o1 && o1 <= a.n_cand) return true;
+  if (first) { raise_status(a.status, 8u); a.n_kept[g] = 0u; }
+  return false;
+}
+
+// One block per group, at most kPruneSingle of them or large ones.
+template <bool kLook>
+__global__ __launch_bounds__(kPruneTile) void batch_prune_kernel(const PruneArgs a) {
+  const uint32_t g = blockIdx.x, tid = threadIdx.x;
+  constexpr int kTimes = kLook ? (int)(kPruneSingle / kPruneTile) : 0;
+  uint32_t from[kTimes + 1], to[kTimes + 1];  // asked for here, looked at where the group's candidates are waited for
+#pragma unroll
+  for (int u = 0; u < kTimes; ++u) {
+    from[u] = to[u] = 0u;
+    if (g + 1u + (uint32_t)u * kPruneTile >= a.n_groups) continue;
+    const uint32_t h = min(g + 1u + (uint32_t)u * kPruneTile + tid, a.n_groups);
+    from[u] = a.group_offsets[h - 1u];
+    to[u] = a.group_offsets[h];
+  }
+  const uint32_t o0 = a.group_offsets[g], o1 = a.group_offsets[g + 1u];
+  if (!is_group(a, g, o0, o1, tid == 0u)) return;
+  prune_group<kLook>(a, g, o0, o1, [&]() __attribute__((always_inline)) {
+    bool back = false;
+#pragma unroll
+    for (int u = 0; u < kTimes; ++u) {
+      asm volatile("" : "+v"(from[u]), "+v"(to[u]));
+      back |= from[u] > to[u];
+    }
+    return back;
+  });
+}
+
+// Small groups, four to a block: a wavefront each, up to two candidates in a lane; a larger one among the four is the block's, as above.
+__global__ __launch_bounds__(kPruneTile) void batch_prune_small_kernel(const PruneArgs a) {
+  constexpr uint32_t V = 2;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t g0 = blockIdx.x * 4u, g = g0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  bool back = false;
+  if (a.n_groups <= kPruneLook) {
+#pragma unroll 4
+    for (uint32_t h = g0 + 1u + tid; h < a.n_groups; h += kPruneTile) back |= a.group_offsets[h - 1u] > a.group_offsets[h];
+    back = __syncthreads_or(back) != 0;
+  }
+  if (g < a.n_groups) {
+    const uint32_t o0 = a.group_offsets[g], o1 = a.group_offsets[g + 1u];
+    if (is_group(a, g, o0, o1, lane == 0u) && o1 - o0 <= 64u * V) {
+      const uint32_t n = o1 - o0;
+      uint32_t sat[V], kept = 0;
+      float lat[V];
+#pragma unroll
+      for (uint32_t v = 0; v < V; ++v) {
+        const bool mine = 64u * v + lane < n;
+        sat[v] = mine ? a.sat_count[o0 + 64u * v + lane] : 0u;
+        lat[v] = mine ? a.latency[o0 + 64u * v + lane] : 0.0f;
+      }
+#pragma unroll
+      for (uint32_t v = 0; v < V; ++v) {
+        if (64u * v >= n) continue;
+        bool dominated = false;
+#pragma unroll
+        for (uint32_t u = 0; u < V; ++u) {
+          const uint32_t end = n > 64u * u ? min(n - 64u * u, 64u) : 0u;
+          for (uint32_t j = 0; j < end; ++j) {
+            const uint32_t sat_j = (uint32_t)__builtin_amdgcn_readlane((int)sat[u], (int)j);
+            const float lat_j = lane_value(lat[u], (int)j);
+            dominated |= (sat_j >= sat[v]) & (lat_j <= lat[v]) & ((sat_j > sat[v]) | (lat_j < lat[v]));
+          }
+        }
+        const uint32_t i = o0 + 64u * v + lane;
+        const bool mine = 64u * v + lane < n, k = mine && sat[v] != 0u && !dominated;
+        if (mine && !(back && held_later(a, g, i))) a.keep[i] = k ? 1u : 0u;
+        kept += (uint32_t)__popcll(lane_mask(k));
+      }
+      if (lane == 0u) a.n_kept[g] = kept;
+    }
+  }
+  for (uint32_t i = 0; i < 4u && g0 + i < a.n_groups; ++i) {  // (the same for the whole block)
+    const uint32_t o0 = a.group_offsets[g0 + i], o1 = a.group_offsets[g0 + i + 1u];
+    if (o0 > o1 || o1 > a.n_cand || o1 - o0 <= 64u * V) continue;
+    __syncthreads();  // the one before has been counted
+    prune_group<true>(a, g0 + i, o0, o1, [&]() { return back; });
+  }
+}
+
+// Behind either, where the blocks have not looked: every block looks through a part of the offsets, and one that finds
+// a step backwards prunes all groups again, in turn.  Several that do write the same values in the same order, so the last
+// write of any of them is the last group's.
+__global__ __launch_bounds__(kPruneTile) void prune_overlaps_kernel(const PruneArgs a, uint32_t per_block) {
+  const uint64_t g0 = (uint64_t)blockIdx.x * per_block, g1 = min(g0 + per_block, (uint64_t)a.n_groups);
+  bool back = false;
+#pragma unroll 8
+  for (uint64_t g = g0 + threadIdx.x; g < g1; g += kPruneTile) back |= a.group_offsets[g] > a.group_offsets[g + 1u];
+  if (__syncthreads_or(back) == 0) return;
+  for (uint32_t g = 0; g < a.n_groups; ++g) {
+    const uint32_t o0 = a.group_offsets[g], o1 = a.group_offsets[g + 1];
+    if (o0 > o1 || o1 > a.n_cand) continue;
+    __syncthreads();  // the group before has been written, and its shared memory read
+    prune_group<false>(a, g, o0, o1, []() { return false; });
   }
 }
 

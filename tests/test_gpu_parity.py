@@ -1629,3 +1629,58 @@ def test_batch_size_prune_of_overlapping_groups():
         assert np.array_equal(keep, ref_keep) and np.array_equal(n_kept, ref_n)
     finally:
         dw.close()
+
+
+def test_batch_size_prune_of_many_groups():
+    """More groups than a block each, and than every block looks through: in order, and with steps backwards, one at each end and
+    in between; small ones, and large ones among them."""
+    rng = np.random.default_rng(23)
+    dw = binding.DeviceWorkload(W.config0())
+    try:
+        for groups, large in ((1024, 0), (1025, 40), (2048, 0), (2049, 0), (2051, 300), (2200, 128), (5000, 65), (8192, 129), (8195, 64)):
+            n = 3 * groups
+            sat = rng.integers(0, 5, n).astype(np.uint32)
+            lat = rng.integers(0, 6, n).astype(np.float32)
+            valid = np.sort(rng.integers(0, n + 1, groups + 1))
+            if large:  # groups of that many among the others
+                at = int(valid[groups // 3])
+                valid[groups // 3 + 1:] = np.maximum(valid[groups // 3 + 1:], min(at + large, n))
+            backwards = valid.copy()
+            for at in (1, groups // 2, groups):
+                backwards[at] = max(0, int(backwards[at]) - 40)
+            for offsets in (valid, backwards):
+                print(f"prune of {groups} groups, backwards {bool((np.diff(offsets) < 0).any())}", flush=True)
+                ref_keep, ref_n = oracle.batch_size_prune(offsets, sat, lat)
+                keep, n_kept = prune_on_gpu(dw.ctx, dw.prompt_len.device, offsets, sat, lat)
+                assert np.array_equal(keep, ref_keep) and np.array_equal(n_kept, ref_n)
+                status = binding.maaso_ctx_device_status(dw.ctx)
+                assert status == (8 if (np.diff(offsets) < 0).any() else 0)
+    finally:
+        dw.close()
+
+
+def test_batch_size_prune_grows_with_the_number_of_groups():
+    """Four times the groups take some four times as long: not every block may look through all of them."""
+    dw = binding.DeviceWorkload(W.config0())
+    dev = dw.prompt_len.device
+    best = {}
+    try:
+        for groups in (65_536, 262_144):
+            offsets = (torch.arange(groups + 1, device=dev) * 2).to(torch.int32)
+            sat = torch.ones(2 * groups, dtype=torch.int32, device=dev)
+            lat = torch.rand(2 * groups, device=dev)
+            keep = torch.empty(2 * groups, dtype=torch.uint8, device=dev)
+            n_kept = torch.empty(groups, dtype=torch.int32, device=dev)
+            for _ in range(6):
+                t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                t0.record()
+                binding.maaso_batch_size_prune(dw.ctx, n_cand=2 * groups, group_offsets=offsets, sat_count=sat, latency=lat,
+                                               keep=keep, n_kept=n_kept)
+                t1.record()
+                torch.cuda.synchronize()
+                best[groups] = min(best.get(groups, 1e9), t0.elapsed_time(t1))
+            assert int(n_kept.sum()) == int(keep.sum()) >= groups
+    finally:
+        dw.close()
+    print(f"prune: {best}", flush=True)
+    assert best[262_144] < 8.0 * best[65_536]
