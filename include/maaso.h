@@ -139,9 +139,11 @@ void maaso_ctx_destroy(maaso_ctx* ctx);
  * there is room, which the charge leaves except with many classes, few slots and few requests, and a
  * reservation for more requests gives; without it the call is somewhat slower); 12 KiB for the windowed distributor;
  * 4 bytes per 1024 requests for maaso_split_by_slo.  The static distributor uses none.  The windowed sweep and the
- * scores are charged with none: with many candidates and windows of some hundred requests they lay the requests out in
- * it where there is room and the stream is not being captured (some 9 bytes a request, more with short windows and many
- * classes), and are somewhat slower without.  Never shrinks.  A set-up call: it synchronises the device and reallocates
+ * scores are charged with none.  With many candidates and windows of some hundred requests they lay the requests out at
+ * its end: some 9 bytes a request (more with short windows and many classes), and with windows of 2048 and more
+ * n_tp * (b_cap + 1) / 16 bytes a request for prefill sums.  They keep out of what the calls above have used since it was
+ * allocated (but for a windowed distributor that was not captured).  Where there is no room left for the sums, or for the
+ * requests, and in a stream that is being captured, the call is slower.  Never shrinks.  A set-up call: it synchronises the device and reallocates
  * when the workspace has to grow.  Errors: INVALID_ARG, SHAPE, HIP, NOMEM, BUSY. */
 int maaso_ctx_reserve(maaso_ctx* ctx, uint32_t max_cand, uint32_t i_pad, uint32_t max_req);
 

@@ -61,7 +61,7 @@ struct maaso_ctx {
   void* ws;             // device workspace: sized at load, resized only by maaso_ctx_reserve
   size_t ws_bytes;
   uint32_t ws_allocations;  // how often the workspace has been allocated (load counts as one)
-  bool ws_captured;     // a captured launch works in the workspace, and may replay beside any later call
+  size_t ws_low;        // bytes at its start that calls charged for them have used: a captured one may replay beside any later call
   // one call at a time: the host part of a call is exclusive, and a call on another stream than the
   // context's previous call is ordered behind it with an event
   std::atomic<int> in_call;
@@ -130,9 +130,11 @@ bool is_captured(hipStream_t s) {
   return hip_ok(hipStreamIsCapturing(s, &status)) && status != hipStreamCaptureStatusNone;
 }
 
-// Before launches that work in the workspace and are charged for it.
-void enter_workspace(maaso_ctx* ctx, hipStream_t s) {
-  if (!ctx->ws_captured && is_captured(s)) ctx->ws_captured = true;
+// Calls that are charged with no workspace, the windowed sweep and the scores, lay requests out at its end, and keep out of what charged
+// calls have used at its start: one that was captured may replay beside any later call, and the windowed distributor's profile is
+// read from there later.  Whether a call is captured is not asked (0.2 to 0.3 us of a static sweep's 20).
+void use_workspace(maaso_ctx* ctx, size_t bytes) {
+  if (bytes > ctx->ws_low) ctx->ws_low = bytes;
 }
 
 // Set-up only (load, maaso_ctx_reserve): (re)allocates the workspace when it is too small.
@@ -142,7 +144,7 @@ int alloc_workspace(maaso_ctx* ctx, size_t bytes) {
     if (!hip_ok(hipDeviceSynchronize())) return MAASO_E_HIP;
     (void)hipFree(ctx->ws);
     ctx->ws = nullptr;
-    ctx->ws_bytes = 0;
+    ctx->ws_bytes = ctx->ws_low = 0;
   }
   const size_t want = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
   if (!hip_ok(hipMalloc(&ctx->ws, want))) { ctx->ws = nullptr; return MAASO_E_NOMEM; }
@@ -361,14 +363,14 @@ OrderedSet plan_set(const SweepWindowSet& t, uint32_t n_slo, uint32_t size_log2,
   return o;
 }
 
-// All sets of `a` in a workspace of ws_bytes; false where they do not fit.
-bool plan_ordered(const SweepWindowArgs& a, uint32_t size_log2, void* ws, size_t ws_bytes, OrderedPlan& plan) {
+// All sets of `a` from `from` on (null: how much that is, alone); false where there is no room for them.
+bool plan_ordered(const SweepWindowArgs& a, uint32_t size_log2, unsigned char* from, size_t room, OrderedPlan& plan) {
   plan.sets.ticks = nullptr;
   plan.sets.row_ticks = 0u;
   plan.order.n_slo = a.n_slo;
   plan.order.status = a.status;
   plan.order.n_sets = a.n_sets;
-  unsigned char* at = static_cast<unsigned char*>(ws);
+  unsigned char* at = from;
   uint64_t blocks = 0;
   uint32_t segment = 1u;
   for (uint32_t k = 0; k < a.n_sets; ++k) {
@@ -384,14 +386,14 @@ bool plan_ordered(const SweepWindowArgs& a, uint32_t size_log2, void* ws, size_t
   plan.blocks = (uint32_t)blocks;
   plan.threads = segment <= 256u * kOrderPer ? 256u : 1024u;
   plan.lds = order_lds(segment, a.n_slo, 1u << size_log2);
-  plan.bytes = (size_t)(at - static_cast<unsigned char*>(ws));
-  return plan.bytes <= ws_bytes && plan.bytes < (size_t)1 << 32;
+  plan.bytes = (size_t)(at - from);
+  return up256(plan.bytes) <= room && plan.bytes < (size_t)1 << 32;
 }
 
 // The windowed sweep of every (request set, candidate); shapes are chosen by the set with the longest
 // windows (the choice never changes a result).
 template <bool kScore, bool kSQ>
-int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, void* ws, size_t ws_bytes, hipStream_t s) {
+int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, unsigned char* end, size_t room, hipStream_t s) {
   uint64_t per_window = 0;
   for (uint32_t k = 0; k < a.n_sets; ++k) {
     const uint64_t pw = a.sets[k].window < a.sets[k].n_req ? a.sets[k].window : a.sets[k].n_req;
@@ -400,23 +402,26 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, v
   const uint64_t blocks = (uint64_t)a.n_cand * a.n_sets;
   if (blocks == 0 || blocks > 0x7fffffffull) return MAASO_E_SHAPE;
   // Laid out by class and length: in batches of 16 where a window then is two groups at most, else of 64 (8192 candidates,
-  // windows of 4096, batches of 32: 2 % slower).  The kernels below where the workspace has no room.
+  // windows of 4096, batches of 32: 2 % slower).  The kernels below where there is no room, and in a captured launch, which may
+  // replay while another call has its requests laid out.
   OrderedPlan plan;
   const bool small = per_window <= kSegment && segment_batches((uint32_t)per_window, a.n_slo, 16u) <= 32u;
-  if (ws && a.bounds.narrow && sweep_lays_out(blocks, a.n_sets, a.i_pad, per_window, kSQ) &&
-      plan_ordered(a, small ? 4u : 6u, ws, ws_bytes, plan)) {
-    hipLaunchKernelGGL(order_requests_kernel, dim3(plan.blocks), dim3(plan.threads), plan.lds, s, plan.order);
-    const dim3 g((a.n_cand + 3u) / 4u * a.n_sets), b(kAssignThreads);
+  if (end && a.bounds.narrow && sweep_lays_out(blocks, a.n_sets, a.i_pad, per_window, kSQ) &&
+      plan_ordered(a, small ? 4u : 6u, nullptr, room, plan) && !is_captured(s)) {
     TicksArgs t;
     t.n_batches = (uint32_t)(((uint64_t)a.sets[0].n_req + a.sets[0].window - 1u) / a.sets[0].window) * plan.sets.set[0].batches;
-    const bool table = !small && a.n_sets == 1u && sweep_sums_batches(a.i_pad, per_window) &&
-                       up256(plan.bytes) + (uint64_t)t.n_batches * a.cells * sizeof(uint32_t) <= ws_bytes;
+    const uint64_t with_table = up256(plan.bytes) + (uint64_t)t.n_batches * a.cells * sizeof(uint32_t);
+    const bool table = !small && a.n_sets == 1u && sweep_sums_batches(a.i_pad, per_window) && up256(with_table) <= room;
+    unsigned char* at = end - up256(table ? (size_t)with_table : plan.bytes);
+    plan_ordered(a, small ? 4u : 6u, at, room, plan);
+    hipLaunchKernelGGL(order_requests_kernel, dim3(plan.blocks), dim3(plan.threads), plan.lds, s, plan.order);
+    const dim3 g((a.n_cand + 3u) / 4u * a.n_sets), b(kAssignThreads);
     if (table) {
       t.tab = a.tab;
       t.cells = a.cells;
       t.len = plan.sets.set[0].len;
       t.batch = plan.sets.set[0].batch;
-      t.ticks = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(ws) + up256(plan.bytes));
+      t.ticks = reinterpret_cast<uint32_t*>(at + up256(plan.bytes));
       plan.sets.ticks = t.ticks;
       plan.sets.row_ticks = t.n_batches;
       hipLaunchKernelGGL(batch_ticks_kernel, dim3((t.n_batches / 4u + 3u) / 4u, (a.cells + 63u) / 64u), dim3(256), 0, s, t);
@@ -484,14 +489,13 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, v
 }
 
 template <bool kScore>
-int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, const maaso_ctx* ctx, bool may_use_ws, hipStream_t s) {
+int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, const maaso_ctx* ctx, bool may_lay_out, hipStream_t s) {
   const size_t lds = (size_t)3 * ctx->cells * sizeof(float);  // profile tables
   const uint32_t n_cu = (uint32_t)ctx->n_cu;
-  // Calls that are charged with no workspace keep out of it while it holds what another call may still need: a captured
-  // launch may run beside any later call, and the windowed distributor's profile is read from it.
-  void* ws = may_use_ws && !ctx->ws_captured && !ctx->window_profiled && !is_captured(s) ? ctx->ws : nullptr;
-  return policy ? launch_sweep_window_v<kScore, true>(a, lds, n_cu, ws, ctx->ws_bytes, s)
-                : launch_sweep_window_v<kScore, false>(a, lds, n_cu, ws, ctx->ws_bytes, s);
+  unsigned char* end = may_lay_out ? static_cast<unsigned char*>(ctx->ws) + ctx->ws_bytes : nullptr;  // (whole MiB)
+  const size_t room = ctx->ws_bytes - std::min(up256(ctx->ws_low), ctx->ws_bytes);
+  return policy ? launch_sweep_window_v<kScore, true>(a, lds, n_cu, end, room, s)
+                : launch_sweep_window_v<kScore, false>(a, lds, n_cu, end, room, s);
 }
 
 // Everything but the request sets.
@@ -644,7 +648,9 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   // thresholds beside the dealing out pay with some 10^5 requests: 64 candidates x 99 slots x 4981 requests: 16.9 us in
   // three launches, 18.2 in four; 67 x 32 x 4775: 17.5 / 18.0; 1039 x 6 x 8704: 18.7 / 18.5; 53 x 59 x 196,187: 26.7 / 24.7;
   // 8974 x 8 x 151,529: 30.2 / 25.7; 59,250 x 3 x 188,741: 64 / 48.
-  const bool beside = !small && !few && (C >= 512u || R >= 1u << 16) && at_best + (size_t)rank_cap * sizeof(uint64_t) <= ws_bytes;
+  const size_t with_best = at_best + (size_t)rank_cap * sizeof(uint64_t);
+  const bool beside = !small && !few && (C >= 512u || R >= 1u << 16) && with_best <= ws_bytes;
+  if (ws == ctx->ws && !small && !few) use_workspace(ctx, beside ? with_best : at_longest);
   TimedRegion timed(ctx, s);  // all launches of the call
   if (beside) {
     GroupArgs g;
@@ -880,7 +886,7 @@ int launch_split(maaso_ctx* ctx, const maaso_requests* rq, uint32_t tight_classe
   a.arrival_ticks = rq->arrival_ticks;
   a.tight_classes = tight_classes;
   a.n_slo = ctx->n_slo;
-  enter_workspace(ctx, s);
+  use_workspace(ctx, ((size_t)n_blocks + 1u) * sizeof(uint32_t));
   a.block_tight = static_cast<uint32_t*>(ctx->ws);
   a.n_tight = n_tight;
   a.prompt_out = prompt_len_out;
@@ -1175,7 +1181,6 @@ int placement_sweep_impl(maaso_ctx* ctx, const maaso_placements* pl, const maaso
   }
   rc = need_workspace(ctx, bytes);
   if (rc != MAASO_OK) return rc;
-  if (R > kSmallRequests) enter_workspace(ctx, s);  // (fewer are not grouped there)
   return launch_static_sweep(ctx, pl, rq, prm, ctx->ws, ctx->ws_bytes, sat_count, sat_ratio, best_cand, s);
 }
 
@@ -1507,6 +1512,7 @@ int launch_assign_ordered(maaso_ctx* ctx, const AssignArgs& a, const maaso_place
   const uint32_t per_window_blocks = (window + per_block - 1u) / per_block;
   if ((uint64_t)per_window_blocks * at_once > 0x7fffffffull) return kNotTaken;
   const uint32_t segment = std::min(window, kSegment);
+  if (is_captured(s)) use_workspace(ctx, ctx->ws_bytes - room + at_once * per_window);
   TimedRegion timed(ctx, s);
   for (uint64_t w0 = 0; w0 < n_windows; w0 += at_once) {
     const uint32_t count = (uint32_t)std::min(at_once, n_windows - w0);
@@ -1670,7 +1676,6 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
     return hip_ok(hipGetLastError()) ? MAASO_OK : MAASO_E_HIP;
   }
 
-  enter_workspace(ctx, s);
   // Few slots, or long windows: in launches over the requests laid out.  The window_blocks knob and the profile ask for
   // the persistent kernel here too.
   const bool ordered = a.bounds.narrow && assign_lays_out(pl->i_pad, prm->window < R ? prm->window : R, prm->policy != 0u);
@@ -1686,6 +1691,7 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   // most).  Each request is spread over LPR lanes so that a window fills the blocks.
   rc = need_workspace(ctx, sizeof(WindowWs));
   if (rc != MAASO_OK) return rc;
+  use_workspace(ctx, sizeof(WindowWs));
   WindowWs* ws = static_cast<WindowWs*>(ctx->ws);
   const uint32_t per_window = prm->window < R ? prm->window : R;
   // More blocks shorten a window's scoring (more lanes per request, shorter instance walks) and

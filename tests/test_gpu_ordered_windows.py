@@ -265,3 +265,88 @@ def test_windowed_sweep_keeps_off_a_workspace_that_others_need():
                 assert torch.equal(x, y)
     finally:
         dw.close()
+
+
+def laid_out_sweep_us(dw, window):
+    dw.sweep(window=window)
+    best = float("inf")
+    for _ in range(6):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        dw.sweep(window=window)
+        t1.record()
+        torch.cuda.synchronize()
+        best = min(best, t0.elapsed_time(t1) * 1e3)
+    return best
+
+
+def test_a_capture_leaves_later_sweeps_as_fast():
+    """A captured static sweep, and a distributor's profile that is still to be read, cost later windowed sweeps nothing (without
+    their windows laid out they take some three times as long)."""
+    w = W.random_small(34, 4000, 32, 40_960, b_cap=32)
+    dw = binding.DeviceWorkload(w)
+    try:
+        before = laid_out_sweep_us(dw, 4096)
+        s = torch.cuda.Stream()
+        out = dw.sweep(stream=s)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            dw.sweep(out=out, stream=s)
+        captured = laid_out_sweep_us(dw, 4096)
+        pl = dict(n_cand=1, i_pad=32, n_inst=dw.n_inst[:1], tp_idx=dw.tp_idx[:1], max_batch=dw.max_batch[:1],
+                  occ=dw.occ[:1].clone(), q_ticks=dw.q_ticks[:1].clone())
+        binding.maaso_ctx_window_profile(dw.ctx, True)
+        binding.maaso_score_assign(dw.ctx, **pl, **dw.request_args(), **{**dw.param_args(), "policy": 0}, window=3000,
+                                   arrival_ticks=dw.arrival_ticks, n_satisfied=torch.zeros(1, dtype=torch.int64, device="cuda"))
+        profiled = laid_out_sweep_us(dw, 4096)
+        print(f"windowed sweep: {before:.0f} us, behind a capture {captured:.0f}, with a profile held {profiled:.0f}", flush=True)
+        assert captured < 1.5 * before and profiled < 1.5 * before
+    finally:
+        dw.close()
+
+
+@pytest.mark.parametrize("i_pad,window,policy", [(2, 64, 0), (6, 1024, 0), (32, 256, 1)])
+def test_captured_distributor_replays_beside_other_calls(i_pad, window, policy):
+    """The laid-out distributor, captured: every replay gives the eager result, with windowed sweeps laid out in between."""
+    w = W.random_small(35 + i_pad, 1200, i_pad, 9000, b_cap=32)
+    w = W.replace(w, policy=policy, n_inst=np.full_like(w.n_inst, i_pad))
+    dw = binding.DeviceWorkload(w)
+    try:
+        start = dict(occ=dw.occ[:1].clone(), q_ticks=dw.q_ticks[:1].clone())
+        live = {k: v.clone() for k, v in start.items()}
+        out = dict(chosen=torch.empty(w.n_req, dtype=torch.int32, device="cuda"), slack=torch.empty(w.n_req, device="cuda"),
+                   n_satisfied=torch.empty(1, dtype=torch.int64, device="cuda"))
+        s = torch.cuda.Stream()
+
+        def call():
+            binding.maaso_score_assign(dw.ctx, n_cand=1, i_pad=i_pad, n_inst=dw.n_inst[:1], tp_idx=dw.tp_idx[:1],
+                                       max_batch=dw.max_batch[:1], **live, **dw.request_args(), **dw.param_args(), window=window,
+                                       arrival_ticks=dw.arrival_ticks, **out, stream=s)
+
+        call()
+        torch.cuda.synchronize()
+        eager = {k: v.clone() for k, v in {**out, **live}.items()}
+        ref = oracle.score_assign(w, window=window)
+        assert np.array_equal(eager["chosen"].cpu().numpy(), ref["chosen"])
+        windowed = [x.clone() for x in dw.sweep(window=300)]
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            call()
+        for _ in range(3):
+            for k, v in start.items():
+                live[k].copy_(v)
+            for v in out.values():
+                v.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s):
+                g.replay()
+            again = dw.sweep(window=300)
+            torch.cuda.synchronize()
+            for k, v in {**out, **live}.items():
+                assert torch.equal(v, eager[k]), k
+            for x, y in zip(again, windowed):
+                assert torch.equal(x, y)
+    finally:
+        dw.close()
