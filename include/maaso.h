@@ -167,9 +167,9 @@ const char* maaso_strerror(int status);
  *   window_blocks: blocks of the windowed distributor's persistent kernel (at most one per compute
  *   unit is used).  Left at 0, windows of up to ten requests (eight beyond 64 instance slots, five beyond 128;
  *   eight, six and four where the largest first-token deadline D reaches 512 s, or D * (1 + window) 4095 s)
- *   are distributed by a single wavefront instead (no device-wide barrier per window), and with few slots,
- *   the shortest-queue rule or windows of thousands (D below 512 s) the state is taken through the windows by one block, and the
- *   requests are scored against what each window met, in launches of their own, laid out in the workspace; a
+ *   are distributed by a single wavefront instead (no device-wide barrier per window).  With few slots,
+ *   the shortest-queue rule or long streams of windows of thousands (D below 512 s) the state is taken through the windows by one block,
+ *   and the requests are scored against what each window met, in launches of their own, laid out in the workspace.  A
  *   value keeps the persistent kernel for all of them.
  * Errors: INVALID_ARG. */
 int maaso_ctx_set_launch_shape(maaso_ctx* ctx, uint32_t sweep_requests_per_lane, uint32_t sweep_group,

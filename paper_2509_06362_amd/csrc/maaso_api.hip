@@ -394,10 +394,11 @@ bool plan_ordered(const SweepWindowArgs& a, uint32_t size_log2, unsigned char* f
 // windows (the choice never changes a result).
 template <bool kScore, bool kSQ>
 int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, unsigned char* end, size_t room, hipStream_t s) {
-  uint64_t per_window = 0;
+  uint64_t per_window = 0, n_windows = 0;
   for (uint32_t k = 0; k < a.n_sets; ++k) {
     const uint64_t pw = a.sets[k].window < a.sets[k].n_req ? a.sets[k].window : a.sets[k].n_req;
     if (pw > per_window) per_window = pw;
+    n_windows = std::max(n_windows, ((uint64_t)a.sets[k].n_req + a.sets[k].window - 1u) / a.sets[k].window);
   }
   const uint64_t blocks = (uint64_t)a.n_cand * a.n_sets;
   if (blocks == 0 || blocks > 0x7fffffffull) return MAASO_E_SHAPE;
@@ -406,12 +407,12 @@ int launch_sweep_window_v(const SweepWindowArgs& a, size_t lds, uint32_t n_cu, u
   // replay while another call has its requests laid out.
   OrderedPlan plan;
   const bool small = per_window <= kSegment && segment_batches((uint32_t)per_window, a.n_slo, 16u) <= 32u;
-  if (end && a.bounds.narrow && sweep_lays_out(blocks, a.n_sets, a.i_pad, per_window, kSQ) &&
+  if (end && a.bounds.narrow && sweep_lays_out(blocks, a.n_sets, a.i_pad, per_window, n_windows, kSQ) &&
       plan_ordered(a, small ? 4u : 6u, nullptr, room, plan) && !is_captured(s)) {
     TicksArgs t;
     t.n_batches = (uint32_t)(((uint64_t)a.sets[0].n_req + a.sets[0].window - 1u) / a.sets[0].window) * plan.sets.set[0].batches;
     const uint64_t with_table = up256(plan.bytes) + (uint64_t)t.n_batches * a.cells * sizeof(uint32_t);
-    const bool table = !small && a.n_sets == 1u && sweep_sums_batches(a.i_pad, per_window) && up256(with_table) <= room;
+    const bool table = !small && a.n_sets == 1u && sweep_sums_batches(a.i_pad, per_window, n_windows) && up256(with_table) <= room;
     unsigned char* at = end - up256(table ? (size_t)with_table : plan.bytes);
     plan_ordered(a, small ? 4u : 6u, at, room, plan);
     hipLaunchKernelGGL(order_requests_kernel, dim3(plan.blocks), dim3(plan.threads), plan.lds, s, plan.order);
@@ -1678,7 +1679,8 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
 
   // Few slots, or long windows: in launches over the requests laid out.  The window_blocks knob and the profile ask for
   // the persistent kernel here too.
-  const bool ordered = a.bounds.narrow && assign_lays_out(pl->i_pad, prm->window < R ? prm->window : R, prm->policy != 0u);
+  const bool ordered = a.bounds.narrow && assign_lays_out(pl->i_pad, prm->window < R ? prm->window : R,
+                                                          ((uint64_t)R + prm->window - 1u) / prm->window, prm->policy != 0u);
   if (ordered && ctx->window_blocks == 0u && !(ctx->window_profile && !prm->policy && !lat)) {
     const int done = launch_assign_ordered(ctx, a, pl, rq, prm, out, lat, s);
     if (done != kNotTaken) {

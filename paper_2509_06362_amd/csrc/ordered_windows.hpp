@@ -168,8 +168,8 @@ __global__ __launch_bounds__(1024) void order_requests_kernel(const OrderArgs a)
   }
 }
 
-// Prefill ticks of every batch on every row of the profile tables, where so many candidates are to be scored that each row
-// serves a batch many times: ticks[row * n_batches + b].  A batch whose longest prompt takes eight seconds and more on
+// Prefill ticks of every batch on every row of the profile tables, where windows are long and requests many (sweep_sums_batches):
+// ticks[row * n_batches + b].  A batch whose longest prompt takes eight seconds and more on
 // a row has no sum here, and none is looked up.
 struct TicksArgs {
   const float* tab;

@@ -62,50 +62,82 @@ constexpr uint32_t assign_short_window(uint32_t i_pad, bool narrow) {
   return i_pad <= 64u ? 10u : i_pad <= 128u ? 8u : 5u;
 }
 
-// Whether the windowed sweep of `units` (set, candidate) pairs lays its windows' requests out by class and length first
-// (sweep_ordered_kernels.hpp).  That saves the look at most requests of a window, and costs a launch and, per
-// window and instance, bounds over its batches: it pays with windows of some hundred requests and candidates enough
-// to hide a wavefront's trips to memory.  Measured, the other kernels' time over it, least and most of 4 to 256 slots, jittered
-// fresh instances with three classes and loaded ones with eight, largest slack | shortest queue:
-//   9000 candidates: windows of 128: 0.76-1.21 | 1.19, 256: 1.08-1.45 | 1.50-1.56, 512: 1.55-1.84 | 1.82-1.90, 4096: 4.68-6.96 | 3.87-4.03;
-//   2000: 256: 0.91-1.12 | 1.28, 320: 1.23-1.61 | 1.70-1.99, 512: 1.06-1.55, 1024: 1.37-2.26, 16,384: 2.56-3.76 | 2.39-3.17;
-//   720: 256: 0.78-1.14 | 1.08-1.33, 320: 1.12-1.56, 512: 0.98-1.35, 1024: 1.05-1.38, 256 slots 0.90-1.04, 4096: 1.48-2.17 | 1.25-1.43;
-//   500: 1024: 0.78-1.31, 2048: 1.11-1.60 | 1.25-1.46; 100: 2048: 0.97-1.50, 4096: 1.18-1.56 | 0.86-1.13, 16,384: 1.08-1.59; 1: 4096: 0.84-1.72.
-// Where several sets are scored (Alg. 2, over growth chains of equal instances) few instances count: 720 candidates, three
-// sets, windows of 256: 1.75.
-constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, uint64_t per_window, bool shortest_queue) {
+// Whether the windowed sweep of `units` (set, candidate) pairs lays its windows' requests out by class and length first (sweep_ordered_kernels.hpp).
+// That saves the look at most requests of a window, and costs a launch of some 10 us, with the batches' sums another, and per window and instance
+// bounds over its batches.  It pays with windows of some hundred requests, with candidates enough to hide a wavefront's trips to memory, and with
+// windows enough to earn the launches and the first windows, in which most instances still admit: some 12 * 2^20 requests times candidates.
+// Measured, the other kernels' time over it, least and most of empty, fresh, loaded and stressed instances, smooth and jittered profiles, three and
+// eight classes, by number of windows, largest slack:
+//   64 slots: 64 candidates, windows of 4096: 1: 0.60-1.05, 4: 0.81-1.23, 8: 1.06-1.53, 16: 1.25-1.85; 512, of 2048: 1: 0.68-0.93, 8: 0.99-1.44, 16:
+//   1.11-1.74; 512, of 4096: 2: 0.81-1.31, 4: 1.15-1.52; 1024, of 320: 4: 1.00-1.30, 8: 1.15-1.43; of 512: 8: 0.95-1.30, 16: 1.01-1.39; of 1024: 8:
+//   0.96-1.46, 16: 1.15-1.62; of 2048: 2: 0.76-1.44, 4: 0.99-1.72; of 4096: 1: 0.80-1.31, 2: 1.02-1.72; of 16,384: 1: 0.84-2.02, 2: 1.05-2.73; 4096,
+//   of 256: 8: 0.92-1.01, 16: 0.97-1.07, 64: 1.13-1.28; of 512: 4: 0.92-1.33, 8: 1.05-1.43; of 1024: 2: 1.06-1.70; of 4096: 1: 1.43-3.10, 16:
+//   4.25-6.73; 8192, of 512: 4: 1.08-1.52; of 4096: 1: 1.92-4.15.
+//   4 slots: 4096, of 512: 8: 0.99-1.10, 16: 1.20-1.37.  256 slots: 64, of 16,384: 4: 0.89-1.98; 1024, of 512: 4: 1.00-1.53; of 2048: 2: 1.04-1.78.
+//   Shortest queue, 64 slots: 512, of 2048: 1: 1.04-1.08; 1024, of 320: 1.09-1.13, of 4096: 1.38-1.60; 4096, of 512: 1.05-1.22.
+// Several sets (Alg. 2: growth chains of equal instances against three): 1134 deployments and sets, windows of 256: 16: 1.03, 32: 1.14; of 512: 16:
+// 1.00, 32: 1.12; 2160, of 256: 16: 1.00, 64: 1.28; of 4096: 1: 1.00; 558 and fewer, of 4096: 16: 0.79-1.08, 32: 0.92-1.6. The line was laid where
+// the mean of a shape over these is above one and its least not below 0.8: of 1125 measured shapes on this side, least below 0.9: 7.
+constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, uint64_t per_window, uint64_t n_windows, bool shortest_queue) {
   if (per_window < 256u || units < 64u) return false;
-  if (units >= 1000u) return per_window > 256u || n_sets > 1u || units >= 4096u || shortest_queue;
-  if (units >= 720u) return per_window > 256u && (i_pad <= 128u || per_window >= 2048u);
-  if (units >= 400u) return per_window >= 2048u;
-  return per_window >= 4096u && !shortest_queue;
+  const bool candidates = units >= 1000u  ? per_window > 256u || n_sets > 1u || units >= 4096u || shortest_queue
+                          : units >= 720u ? per_window > 256u && (i_pad <= 128u || per_window >= 2048u)
+                          : units >= 400u ? per_window >= 2048u
+                                          : per_window >= 4096u && !shortest_queue;
+  if (!candidates) return false;
+  if (n_sets > 1u && units < 2000u && per_window >= 1024u) return n_windows >= 32u && units >= 400u;
+  if (n_windows >= (units < 400u ? 32u : 16u)) return true;
+  uint64_t gain = 1;
+  if (shortest_queue) gain = i_pad >= 64u ? 8u : i_pad >= 16u ? 4u : per_window >= 1024u ? 2u : 1u;
+  else if (per_window > 256u && i_pad > 8u) gain = i_pad > 128u ? 4u : per_window >= 1024u ? 2u : 1u;
+  const uint64_t work = units * n_windows * (per_window < 32768u ? per_window : 32768u) * gain;
+  if (per_window >= 16384u) return n_windows >= 4u || work >= 45u << 20;
+  return work >= (per_window > 256u && per_window < 465u ? 6u << 20 : 12u << 20);
 }
 
-// Whether the prefills of every batch are then summed up ahead, on every row of the tables (batch_ticks_kernel): a launch of some
-// 0.8 us per 4096 requests and thousand rows, for which a settled batch costs a look-up.  Measured, without the sums over with
-// them, fresh jittered instances and 516 rows / loaded ones and 1028: 64 slots, 1100 candidates: windows of 512: 0.99 / 1.00, 1024: 1.03 / 1.04,
-// 4096: 1.21 / 1.19, 16,384: 1.72 / 1.49; 9000: 512: 1.05 / 1.05, 1024: 1.06 / 1.08, 4096: 1.21 / 1.22; 300: 4096: 1.28 / 1.20; 4 slots, 1100: 1024: 0.80,
-// 4096: 1.00 / 0.85, 16,384: 1.41 / 1.06; 9000: 1.16 / 1.00, 16,384: 1.72 / 1.30.
-constexpr bool sweep_sums_batches(uint32_t i_pad, uint64_t per_window) {
-  return per_window >= (i_pad >= 32u ? 2048u : 16384u);
+// Whether the prefills of every batch are then summed up ahead, on every row of the tables (batch_ticks_kernel): a launch of some 0.8 us per 4096
+// requests and thousand rows and what it waits for, for which a settled batch costs a look-up, whatever the number of candidates.  Measured, without
+// the sums over with them, 64 to 4096 candidates, by number of windows: 64 slots, windows of 2048: 1: 0.68-0.85, 4: 0.87-0.99, 8: 0.98-1.17, 16:
+// 1.05-1.42, 64: 1.09-1.78; 4096: 2: 0.87-0.97, 4: 0.97-1.24, 16: 1.11-1.83; 16,384: 1: 0.95-1.30, 4: 1.15-2.15; 256 slots: 2048: 8: 0.97-1.08, 64:
+// 1.04-1.36; 16,384: 1: 0.95-1.21; 4 slots: 2048: 64: 0.69-0.95; 4096: 16: 0.83-1.19; 16,384: 1: 0.94-1.31, 4: 1.12-2.29.
+constexpr bool sweep_sums_batches(uint32_t i_pad, uint64_t per_window, uint64_t n_windows) {
+  return per_window >= (i_pad >= 32u ? 2048u : 16384u) && per_window * n_windows >= 16384u;
 }
 
-// The same for the distributor (assign_ordered_kernels.hpp, against the persistent kernel): the chain of windows
-// is then one block's, which looks for the instances that count and bounds their slacks one after the other, so it pays
-// with few slots, or with windows that are much to score.  Measured, the persistent kernel's time over it, some hundred windows,
-// least and most of empty smooth and loaded jittered instances:
-//   largest slack: 2 slots: windows of 11 to 16,384: 2.5-5.6; 8 slots: 32: 0.97-2.8, 48: 1.26-3.9, 512: 2.4-4.8, 16,384: 1.8-2.6; 16 slots: 256:
-//   0.99-4.2, 512: 1.39-4.1, 16,384: 1.38-2.1; 64 slots: 1024: 0.82-2.8, 2048: 1.02-2.9, 4096: 1.36-3.3, 16,384: 1.04-1.4, 32,768: 0.43-0.53; 128
-//   slots: 2048: 0.76-2.0, 4096: 1.14-2.5, 8192: 1.44-2.4, 16,384: 0.79-0.97; 256 slots: 4096: 0.97-1.55, 8192: 1.12-1.51.
-//   Shortest queue: 8 slots: 11: 2.7, 512: 5.8; 64 slots: 11: 0.88, 16: 1.15, 64: 3.7, 4096: 5.6, 16,384: 2.1, 32,768: 0.73; 128 slots: 16: 1.00, 32: 1.57,
-//   8192: 4.2, 16,384: 1.55; 256 slots: 11: 1.27, 128: 2.1, 4096: 3.4, 16,384: 2.1.
-constexpr bool assign_lays_out(uint32_t i_pad, uint64_t per_window, bool shortest_queue) {
-  if (shortest_queue) return per_window >= (i_pad <= 16u ? 11u : i_pad <= 64u ? 16u : 32u) && per_window <= 16384u;
-  if (i_pad <= 2u) return per_window >= 11u && per_window <= 16384u;
-  if (i_pad <= 8u) return per_window >= 48u && per_window <= 16384u;
-  if (i_pad <= 16u) return per_window >= 512u && per_window <= 16384u;
-  if (i_pad <= 64u) return per_window >= 2048u && per_window <= 16384u;
-  return per_window >= (i_pad <= 128u ? 4096u : 8192u) && per_window <= 8192u;
+// The same for the distributor (assign_ordered_kernels.hpp, against the persistent kernel): the chain of windows is then one block's, which looks for
+// the instances that count and bounds their slacks one after the other.  It pays with few slots, or where a placement is overloaded and most windows
+// admit nothing, which takes a stream long enough: with many different instances below or at their capacity it is slower.  A call of a few windows is
+// mostly the launches: 26 us, the persistent kernel's 34.  Measured, the persistent kernel's time over it, least and mean of empty and loaded
+// instances, smooth and jittered profiles, arrivals from a tenth of what the placement serves to many times that, by number of windows:
+//   largest slack: 2 slots: windows of 11: 1: 1.18 1.31, 1024: 1.46 3.36; 16,384: 1: 1.05 1.13, 256: 3.67 3.73; 4 slots: 64: 1024: 1.00 3.03; 4096:
+//   1: 1.23 1.29; 16,384: 2: 0.93 0.98, 32: 1.62 1.77; 8 slots: 64: 256: 0.68 1.57; 256: 128: 0.89 1.45; 512: 64: 0.93 1.71, 1024: 1.07 3.20; 4096:
+//   1: 1.15 1.21, 128: 1.05 1.75; 8192: 64: 0.80 1.81, 128: 1.47 1.99; 16 slots: 1024: 128: 0.88 1.34; 2048: 16: 0.98 1.15, 64: 0.97 1.46; 4096: 8:
+//   0.85 1.04, 32: 1.06 1.24; 8192: 128: 0.79 1.33, 256: 1.43 2.88; 32 slots: 2048: 4: 0.99 1.25, 16: 0.72 1.12, 64: 0.99 1.31; 8192: 256: 1.02 2.61;
+//   64 slots: 2048: 2: 1.04 1.14, 64: 0.64 0.97, 256: 0.95 1.54, 1024: 1.05 2.66; 4096: 1: 0.89 1.02, 64: 0.75 1.17, 128: 1.19 1.44, 1024: 1.38 3.32;
+//   16,384: 256: 0.85 1.95; 128 slots: 4096: 128: 0.79 1.15, 256: 1.30 1.59; 16,384: 256: 0.96 1.52; 256 slots: 8192: 256: 0.83 1.23, 512: 1.32 1.58.
+//   Shortest queue: 2 slots: 11: 1: 1.17 1.30; 8 slots: 11: 64: 0.86 1.15; 32: 1.04 1.99; 16,384: 32: 0.66 1.19, 64: 1.24 1.86; 16 slots: 32: 64:
+//   0.78 1.15; 128: 1.10 1.50; 16,384: 128: 1.42 1.91; 32 slots: 64: 0.89 1.69; 256: 1.16 1.72; 16,384: 128: 0.95 1.62, 256: 1.75 3.39; 64 slots: 64:
+//   0.77 1.27; 256: 1024: 0.92 2.84; 1024: 1.15 1.40; 4096: 1: 0.92 1.04, 4: 1.02 1.19; 16,384: 2: 0.88 0.94, 8: 1.00 1.06; 128 slots: 64: 8: 0.85
+//   1.13, 256: 0.73 1.62; 256: 8: 0.91 1.27; 512: 4: 1.00 1.35; 4096: 4: 0.94 1.14, 8: 1.16 1.29; 256 slots: 512: 8: 0.91 1.21, 16: 0.99 1.47; 1024:
+//   8: 0.97 1.26; 8192: 8: 1.17 1.34.
+// The line was laid where the mean of a shape is above one and its least, as a rule, above 0.8 (below it are 8 slots, windows of 64 to 255, at
+// capacity: 0.64 to 0.9, and a few more).
+constexpr bool assign_lays_out(uint32_t i_pad, uint64_t per_window, uint64_t n_windows, bool shortest_queue) {
+  if (per_window < 11u || per_window > 16384u) return false;
+  if (i_pad <= 2u) return true;
+  if (shortest_queue) {
+    if (i_pad <= 64u && per_window >= 16u && per_window <= 64u && n_windows >= 1024u) return true;
+    if (i_pad <= 32u) return per_window >= (i_pad <= 8u ? 11u : 32u) && (per_window <= 8192u || n_windows >= 64u);
+    if (i_pad <= 64u) return per_window >= 64u && (per_window <= 2048u || n_windows >= 8u);
+    return per_window >= (i_pad <= 128u ? 64u : 128u) && n_windows >= 4u;
+  }
+  if (i_pad <= 4u) return per_window >= 48u && (per_window <= 8192u || n_windows >= 8u);
+  if (i_pad <= 8u) return per_window >= (n_windows >= 1024u ? 48u : 64u) && (per_window <= 4096u || n_windows >= (per_window <= 8192u ? 16u : 64u));
+  if (i_pad <= 16u) return per_window >= 512u && (per_window <= 2048u || n_windows >= (per_window <= 4096u ? 32u : 128u));
+  if (per_window < 2048u) return false;
+  if (i_pad <= 32u) return n_windows >= (per_window <= 10240u ? 64u : 128u) || (n_windows <= 4u && per_window <= 4096u);
+  if (i_pad <= 64u) return n_windows >= 128u || (n_windows <= 2u && per_window < 4096u);
+  return per_window >= (i_pad <= 128u ? 4096u : 8192u) && per_window <= 8192u && n_windows >= (i_pad <= 128u ? 128u : 256u);
 }
 
 }  // namespace maaso

@@ -36,25 +36,32 @@ def variant_of(w, variant):
     return w
 
 
-# candidates enough for the laid-out form (1000 and more; fewer with windows of 2048 and 4096)
-@pytest.mark.parametrize("n_cand,i_pad,n_slo,window,n_req,variant", [
-    (1001, 3, 3, 257, 600, "mixed"), (1000, 2, 1, 300, 901, "alike"), (1003, 5, 16, 320, 700, "mixed"),
-    (1000, 4, 8, 384, 800, "alike"), (1000, 4, 8, 385, 800, "mixed"),           # 32 batches of 16, and one group more
-    (1002, 3, 3, 464, 930, "long"), (1002, 3, 3, 465, 940, "one class"), (1000, 3, 2, 512, 1024, "zeros"),
-    (1000, 70, 3, 500, 700, "mixed"), (1000, 130, 3, 300, 400, "alike"),        # two and four slots a lane
-    (400, 3, 3, 2048, 4100, "one length"), (64, 5, 5, 4095, 8190, "mixed"), (64, 4, 3, 4096, 8193, "long"),
-    (65, 4, 16, 4097, 9000, "zeros"), (64, 140, 3, 8200, 8300, "alike"), (4100, 2, 3, 256, 300, "mixed"),
+# candidates and windows enough for the laid-out form (tests/test_window_rules.py checks that), under the shortest-queue rule too from
+# 400 candidates on
+SWEEPS = [
+    (1001, 3, 3, 257, 3900, "mixed", 0), (1000, 2, 1, 300, 4600, "alike", 0),
+    (1003, 5, 16, 271, 4110, "mixed", 1), (1003, 5, 16, 272, 4200, "mixed", 0),   # 32 batches of 16, and one group more
+    (1000, 4, 8, 399, 6100, "alike", 0), (1000, 4, 8, 400, 6100, "mixed", 0),
+    (1002, 3, 3, 479, 7300, "long", 0), (1002, 3, 3, 480, 7300, "one class", 1), (1000, 3, 2, 512, 7900, "zeros", 0),
+    (1000, 70, 3, 500, 7600, "mixed", 0), (1000, 130, 3, 300, 2200, "alike", 0),  # two and four slots a lane
+    (1001, 131, 2, 600, 3300, "mixed", 1),
+    (400, 3, 3, 2048, 30_727, "one length", 0), (400, 5, 5, 4095, 61_428, "mixed", 0), (64, 4, 3, 4096, 126_977, "long", 0),
+    (65, 4, 16, 4097, 127_010, "zeros", 0), (64, 140, 3, 16_390, 49_181, "alike", 0), (4100, 2, 3, 256, 3900, "mixed", 0),
     # with the sums of batches worked out ahead
-    (400, 40, 3, 2048, 4100, "long"), (64, 33, 16, 4100, 8300, "one length"), (64, 70, 2, 2500, 5100, "alike"),
-    (64, 4, 3, 16_384, 16_900, "mixed"),
-    (1000, 3, 3, 5000, 300, "mixed"),                                           # one window, shorter than its size
-])
-def test_sweep_and_score(n_cand, i_pad, n_slo, window, n_req, variant):
+    (400, 40, 3, 2048, 30_727, "long", 0), (400, 40, 3, 2048, 30_727, "mixed", 1), (64, 33, 16, 4100, 127_103, "one length", 0),
+    (64, 70, 2, 4500, 139_505, "alike", 0), (64, 4, 3, 16_384, 49_652, "mixed", 1),
+    (4100, 3, 3, 5000, 4500, "mixed", 0),                                         # one window, shorter than its size
+]
+
+
+@pytest.mark.parametrize("n_cand,i_pad,n_slo,window,n_req,variant,mode", SWEEPS)
+def test_sweep_and_score(n_cand, i_pad, n_slo, window, n_req, variant, mode):
     w = variant_of(W.random_small(n_cand + 31 * i_pad + window, n_cand, i_pad, n_req, n_slo=n_slo, b_cap=64, pen_kappa=0.5,
                                   jitter=variant != "alike"), variant)
+    w = W.replace(w, tbt_mode=mode)
     for policy in (0, 1):
         wp = W.replace(w, policy=policy)
-        print(f"laid out C={n_cand} I={i_pad} K={n_slo} window={window} R={n_req} {variant} policy={policy}", flush=True)
+        print(f"laid out C={n_cand} I={i_pad} K={n_slo} window={window} R={n_req} {variant} mode={mode} policy={policy}", flush=True)
         dw = binding.DeviceWorkload(wp)
         try:
             cnt, _, best = dw.sweep(window=window)
@@ -88,15 +95,26 @@ def check_assign(w, window, latencies, out_of_range=False):
         dw.close()
 
 
-@pytest.mark.parametrize("i_pad,n_slo,window,n_req,policy,variant", [
-    (2, 3, 11, 500, 0, "mixed"), (1, 1, 64, 1000, 0, "alike"), (8, 3, 48, 999, 0, "mixed"), (8, 16, 4096, 9001, 0, "long"),
-    (16, 3, 512, 2600, 0, "mixed"), (16, 3, 1001, 5000, 0, "alike"), (40, 5, 2048, 7000, 0, "zeros"), (64, 3, 4097, 12_500, 0, "mixed"),
-    (64, 8, 16_384, 20_000, 0, "one length"), (100, 3, 4096, 9000, 0, "mixed"), (256, 3, 8192, 17_000, 0, "mixed"),
-    (16, 3, 11, 300, 1, "mixed"), (64, 3, 16, 330, 1, "mixed"), (100, 8, 32, 700, 1, "alike"), (256, 3, 333, 2000, 1, "mixed"),
-    (200, 16, 4096, 9000, 1, "long"), (3, 3, 16_384, 16_000, 1, "one class"),
-])
+DISTRIBUTORS = [
+    (2, 3, 11, 500, 0, "mixed"), (1, 1, 64, 1000, 0, "alike"), (4, 3, 48, 999, 0, "mixed"), (8, 3, 128, 1300, 0, "mixed"),
+    (8, 16, 4096, 9001, 0, "long"), (16, 3, 512, 2600, 0, "mixed"), (16, 3, 1001, 5000, 0, "alike"), (8, 8, 8190, 122_853, 0, "one length"),
+    (4, 3, 16_384, 114_689, 0, "mixed"), (32, 5, 2048, 129_033, 0, "zeros"), (64, 3, 4097, 520_324, 0, "mixed"),
+    (100, 3, 4096, 520_193, 0, "mixed"), (256, 3, 8192, 2_088_961, 0, "mixed"),
+    (2, 3, 11, 300, 1, "mixed"), (8, 3, 11, 300, 1, "mixed"), (16, 3, 32, 330, 1, "mixed"), (20, 3, 64, 700, 1, "mixed"),
+    (64, 3, 64, 700, 1, "mixed"), (100, 8, 128, 393, 1, "alike"), (256, 3, 333, 2000, 1, "mixed"), (200, 16, 4096, 12_293, 1, "long"),
+    (3, 3, 8192, 16_000, 1, "one class"),
+]
+
+
+@pytest.mark.parametrize("i_pad,n_slo,window,n_req,policy,variant", DISTRIBUTORS)
 def test_distributor(i_pad, n_slo, window, n_req, policy, variant):
-    w = variant_of(W.random_small(7 * i_pad + window, 1, i_pad, n_req, n_slo=n_slo, b_cap=64, jitter=variant != "alike"), variant)
+    half = n_req > 2_000_000  # (arrivals are 32-bit ticks: twice the requests at twice the rate)
+    w = W.random_small(7 * i_pad + window, 1, i_pad, (n_req + 1) // 2 if half else n_req, n_slo=n_slo, b_cap=64, jitter=variant != "alike")
+    if half:
+        a = w.arrival_ticks // np.uint32(2)
+        w = W.replace(w, **{k: np.tile(getattr(w, k), 2)[:n_req] for k in ("prompt_len", "out_len", "slo_class")},
+                      arrival_ticks=np.concatenate([a, a + a[-1]])[:n_req])
+    w = variant_of(w, variant)
     w = W.replace(w, policy=policy, n_inst=np.full_like(w.n_inst, max(1, i_pad - 1)))
     check_assign(w, window, latencies=policy == 1 or i_pad % 16 == 0)
     # no instances at all, then requests of a class that does not exist (given to nobody)
@@ -121,9 +139,10 @@ def test_distributor(i_pad, n_slo, window, n_req, policy, variant):
         dw.close()
 
 
-@pytest.mark.parametrize("i_pad,window,n_req,policy", [
-    (8, 48, 400, 0), (16, 512, 2600, 0), (64, 2048, 6200, 0), (8, 11, 200, 1), (64, 16, 330, 1), (100, 32, 500, 1), (256, 33, 500, 1),
-])
+FLAGGED = [(8, 128, 700, 0), (16, 512, 2600, 0), (32, 2048, 129_100, 0), (8, 11, 200, 1), (64, 64, 700, 1), (100, 128, 400, 1), (256, 128, 1000, 1)]
+
+
+@pytest.mark.parametrize("i_pad,window,n_req,policy", FLAGGED)
 @pytest.mark.parametrize("mode,kappa", [(0, 0.5), (1, 0.0)])
 @pytest.mark.parametrize("pause", [0, 4 << 20])
 def test_distributor_with_flagged_slots(i_pad, window, n_req, policy, mode, kappa, pause):
@@ -164,7 +183,7 @@ def test_distributor_overloaded_then_idle():
         ticks = np.minimum(np.cumsum(gaps) * (1 << 20), 2.0 ** 32 - 1).astype(np.uint32)
         w = W.replace(w, arrival_ticks=ticks, n_inst=np.full_like(w.n_inst, 8))
         for policy in (0, 1):
-            check_assign(W.replace(w, policy=policy), 100, latencies=False)
+            check_assign(W.replace(w, policy=policy), 128, latencies=False)
 
 
 def test_distributor_in_rounds():
@@ -181,7 +200,7 @@ def test_distributor_unaligned_arrays_and_state_alone():
     """Arrays at odd addresses (one request per thread), and a call that asks for the count alone."""
     w = W.random_small(21, 1, 8, 4001, b_cap=32)
     w = W.replace(w, n_inst=np.full_like(w.n_inst, 8))
-    ref = oracle.score_assign(w, window=64)
+    ref = oracle.score_assign(w, window=128)
     dw = binding.DeviceWorkload(w)
     try:
         up = lambda x, v: torch.from_numpy(np.concatenate([np.zeros(1, x.dtype), x]).view(v)).cuda()[1:]
@@ -189,7 +208,7 @@ def test_distributor_unaligned_arrays_and_state_alone():
                   slo_class=up(w.slo_class, np.uint8), arrival_ticks=up(w.arrival_ticks, np.int32))
         pl = lambda: dict(n_cand=1, i_pad=8, n_inst=dw.n_inst, tp_idx=dw.tp_idx, max_batch=dw.max_batch,
                           occ=dw.occ.clone(), q_ticks=dw.q_ticks.clone())
-        prm = dict(dw.param_args(), window=64)
+        prm = dict(dw.param_args(), window=128)
         chosen = torch.empty(w.n_req + 1, dtype=torch.int32, device="cuda")[1:]
         count = torch.empty(1, dtype=torch.int64, device="cuda")
         binding.maaso_score_assign(dw.ctx, **pl(), **rq, **prm, chosen=chosen, n_satisfied=count)
@@ -206,7 +225,7 @@ def test_distributor_unaligned_arrays_and_state_alone():
 
 def test_captured_sweep_keeps_off_the_workspace():
     """A windowed sweep captured in a graph replays beside other calls of the context, which use its workspace."""
-    w = W.random_small(33, 1200, 6, 1200, b_cap=32)
+    w = W.random_small(33, 1200, 6, 4800, b_cap=32)
     dw = binding.DeviceWorkload(w)
     try:
         s = torch.cuda.Stream()

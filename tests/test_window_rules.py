@@ -1,6 +1,6 @@
 """The rules of the windowed sweeps (window_rules.hpp), compiled for the CPU and run through every small case:
 which arrivals a set's windows read, which buffer of admitted sums is free to be cleared, in how many ticks nothing
-completes, and the longest windows that a wavefront with the instances in its lanes takes."""
+completes, the longest windows that a wavefront with the instances in its lanes takes, and which shapes are laid out."""
 import shutil
 import subprocess
 from pathlib import Path
@@ -102,3 +102,63 @@ def test_longest_short_windows(tmp_path):
         if i in slower:
             assert sweep_general < slower[i] and score_general < slower[i]
         assert assign_general < (9 if i <= 64 else 7 if i <= 128 else 6)
+
+
+def lays_out(tmp_path, sweeps=(), assigns=(), sums=()):
+    """What the rules say of (units, sets, slots, requests of a window, windows, shortest queue), (slots, requests of a window, windows,
+    shortest queue) and (slots, requests of a window, windows)."""
+    body = ""
+    for name, rows in (("sweep_lays_out", sweeps), ("assign_lays_out", assigns), ("sweep_sums_batches", sums)):
+        for r in rows:
+            args = ", ".join(str(int(x)) for x in r)
+            body += f'  printf("%d\\n", (int){name}({args}));\n'
+    return [row[0] for row in run_rules(tmp_path, body)]
+
+
+def test_shapes_that_were_measured_slower_are_not_laid_out(tmp_path):
+    """Few windows do not earn the launches, and a distributor's single block is slow where many different instances admit; the shapes that
+    were measured several times as fast stay laid out."""
+    slow_sweeps = [(64, 1, 4, 4096, 1, 0), (64, 1, 64, 4096, 4, 0), (1024, 1, 64, 512, 1, 0), (1024, 1, 64, 1024, 2, 0), (4096, 1, 4, 512, 2, 0),
+                   (8192, 1, 64, 256, 1, 0), (512, 1, 64, 2048, 2, 0), (558, 3, 16, 4096, 16, 0), (1134, 3, 32, 4096, 4, 0), (1000, 1, 4, 4096, 1, 0),
+                   (300, 1, 4, 65_536, 1, 0)]
+    slow_assigns = [(64, 4096, 16, 0), (128, 4096, 16, 0), (256, 8192, 64, 0), (8, 48, 256, 0), (16, 11, 64, 1), (256, 32, 64, 1),
+                    (32, 2048, 16, 0), (64, 16_384, 32, 0), (16, 16_384, 16, 0), (64, 2048, 32, 0), (8, 16_384, 4, 1), (64, 32_768, 64, 0)]
+    slow_sums = [(64, 2048, 4), (256, 2048, 1), (4, 2048, 64), (64, 4096, 2), (64, 300, 1000)]
+    assert lays_out(tmp_path, slow_sweeps, slow_assigns, slow_sums) == [0] * (len(slow_sweeps) + len(slow_assigns) + len(slow_sums))
+    fast_sweeps = [(8192, 1, 128, 4096, 32, 0), (2160, 3, 64, 256, 512, 0), (4096, 1, 64, 4096, 1, 0), (1024, 1, 64, 16_384, 8, 0),
+                   (512, 1, 64, 4096, 16, 0), (1024, 1, 64, 4096, 1, 1), (4096, 1, 256, 2048, 1, 0), (64, 1, 64, 16_384, 4, 0)]
+    fast_assigns = [(64, 4096, 1024, 0), (8, 512, 1024, 1), (2, 11, 1, 0), (16, 2048, 256, 0), (128, 8192, 512, 0), (256, 4096, 64, 1),
+                    (64, 1024, 64, 1), (4, 4096, 1, 0), (64, 16_384, 256, 0)]
+    fast_sums = [(128, 4096, 32), (64, 2048, 16), (4, 16_384, 4), (64, 16_384, 1)]
+    assert lays_out(tmp_path, fast_sweeps, fast_assigns, fast_sums) == [1] * (len(fast_sweeps) + len(fast_assigns) + len(fast_sums))
+
+
+def test_longer_streams_stay_laid_out(tmp_path):
+    """With more windows of one length the sweep gains, so no shape leaves the form again, and nor does a distributor's beyond four windows."""
+    rows = run_rules(tmp_path, """
+  const uint32_t units[] = {64, 400, 720, 1000, 2160, 4096, 9000}, lengths[] = {11, 48, 64, 128, 256, 300, 512, 1024, 2048, 4096, 8192, 16384, 65536};
+  int left = 0, laid = 0;
+  for (uint32_t sq = 0; sq < 2; ++sq)
+    for (uint32_t i = 1; i <= 256; ++i)
+      for (uint32_t w : lengths) {
+        bool a = false;
+        for (uint32_t n = 8; n <= 1024; n *= 2) { const bool b = assign_lays_out(i, w, n, sq); left += a && !b; laid += b; a = b; }
+        for (uint32_t u : units)
+          for (uint32_t sets = 1; sets <= 3; sets += 2) {
+            a = false;
+            for (uint32_t n = 1; n <= 1024; n *= 2) { const bool b = sweep_lays_out(u, sets, i, w, n, sq); left += a && !b; laid += b; a = b; }
+          }
+      }
+  printf("%d %d\\n", left, laid);""")
+    assert rows[0][0] == 0 and rows[0][1] > 10000
+
+
+def test_shapes_of_the_laid_out_tests_are_laid_out(tmp_path):
+    from tests import test_gpu_ordered_windows as T
+    windows = lambda n_req, window: (min(window, n_req), -(-n_req // window))
+    sweeps = [(c, 1, i, *windows(r, w), sq) for c, i, _, w, r, _, _ in T.SWEEPS for sq in (0, 1) if c >= 400 or not sq]
+    assigns = [(i, *windows(r, w), p) for i, _, w, r, p, _ in T.DISTRIBUTORS] + [(i, *windows(r, w), p) for i, w, r, p in T.FLAGGED]
+    got = lays_out(tmp_path, sweeps, assigns)
+    assert all(got), [x for x, ok in zip(sweeps + assigns, got) if not ok]
+    tables = [(i, *windows(r, w)) for _, i, _, w, r, _, _ in T.SWEEPS]
+    assert 5 <= sum(lays_out(tmp_path, sums=tables)) <= len(tables) - 10
