@@ -379,7 +379,8 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
     traffic, traffic_info = measured_traffic(w.name)
     if kind == "sweep" and sweep_window:
         roofline = {
-            "kernel": "sweep_seq_kernel" if sweep_window == 1 else "order_requests + batch_ticks + sweep_ordered kernels", "bound": "alu",
+            # which kernels take it goes by slots, candidates, window and stream: the figures are of all of them
+            "kernel": "windowed sweep (every launch of the call)", "bound": "alu",
             "achieved": None, "peak": VALU_PEAK_TLANEOPS, "unit": "Tlaneop/s", "frac": None,
             "traffic": traffic, "kernel_ms": k_avg_s * 1e3, "launches_timed": k_n,
             "kernel_triples_per_s": triples_sweep / k_avg_s,
@@ -419,8 +420,8 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
         hbm_frac = nbytes / k_avg_s / 1e9 / HBM_PEAK_GBS
         alu_frac = ops / k_avg_s / 1e12 / VALU_PEAK_TLANEOPS
         kname = "assign_static_kernel"
-        if w.window:  # which form takes the call: the library's own choice for this shape, or the persistent kernel asked for
-            kname = "assign_window_kernel" if args.window_blocks else "order_requests + assign_states + assign_recorded kernels"
+        if w.window:  # the persistent kernel where it is asked for, else as the library chooses by shape
+            kname = "assign_window_kernel" if args.window_blocks else "windowed distributor (every launch of the call)"
         roofline = {
             "kernel": kname, "bound": "hbm", "achieved": nbytes / k_avg_s / 1e9,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hbm_frac, "traffic": traffic,
@@ -433,15 +434,16 @@ def measure(name: str, steps: int, warmup: int, args, min_gpu_warm_ms: float = 0
                                 "is windows x per-window latency")
             roofline["windows"] = n_win
             roofline["us_per_window"] = k_avg_s * 1e6 / n_win
-            # where a window's time goes in the persistent kernel: one more call with its profiling variant (block 0
-            # sums its cycles per phase), cycles per window
-            binding.maaso_ctx_window_profile(dw.ctx, True)
-            dominant()
-            ph = binding.maaso_ctx_window_phases(dw.ctx)
-            binding.maaso_ctx_window_profile(dw.ctx, False)
-            if ph["loop"]:
-                roofline["persistent_kernel_cycles_per_window"] = {
-                    k: ph[k] / n_win for k in ("stage", "score", "exchange", "update", "loop")}
+            if args.window_blocks:
+                # where a window's time goes in the persistent kernel, which the timed calls ran: one more with its profiling
+                # variant (block 0 sums its cycles per phase), cycles per window
+                binding.maaso_ctx_window_profile(dw.ctx, True)
+                dominant()
+                ph = binding.maaso_ctx_window_phases(dw.ctx)
+                binding.maaso_ctx_window_profile(dw.ctx, False)
+                if ph["loop"]:
+                    roofline["persistent_kernel_cycles_per_window"] = {
+                        k: ph[k] / n_win for k in ("stage", "score", "exchange", "update", "loop")}
         elif w.n_req < (1 << 20):
             roofline["note"] = "launch latency: a single short kernel"
     roofline["traffic_info"] = traffic_info
@@ -585,7 +587,7 @@ def bench_alg2(args) -> int:
                            "Alg. 1's selection per set, partition scan; |R_t| stays on the device",
                    "partition": {"g_t": int(part[0]), "g_l": int(part[1]),
                                  "heterogeneous": int(part[2]), "phi_opt": float(res["phi_opt"].item())}},
-        "roofline": {"kernel": "order_requests + sweep_ordered kernels", "bound": "latency", "achieved": None, "peak": None,
+        "roofline": {"kernel": "windowed score (every launch of the call)", "bound": "latency", "achieved": None, "peak": None,
                      "unit": None, "frac": None, "traffic": None,
                      "kernel_ms": k_ms / max(k_n, 1), "launches_timed": k_n,
                      "kernel_triples_per_s": triples_step / k_total_s,
