@@ -130,9 +130,10 @@ bool is_captured(hipStream_t s) {
   return hip_ok(hipStreamIsCapturing(s, &status)) && status != hipStreamCaptureStatusNone;
 }
 
-// Calls that are charged with no workspace, the windowed sweep and the scores, lay requests out at its end, and keep out of what charged
-// calls have used at its start: one that was captured may replay beside any later call, and the windowed distributor's profile is
-// read from there later.  Whether a call is captured is not asked (0.2 to 0.3 us of a static sweep's 20).
+// Calls that are charged with no workspace, the windowed sweep and the scores, lay requests out at its end, and keep out of what
+// charged calls have used at its start: one that was captured may replay beside any later call, and the windowed distributor's
+// profile is read from there later.  Whether a charged call is captured is not asked, so capturing one costs later sweeps nothing but
+// the room it uses.
 void use_workspace(maaso_ctx* ctx, size_t bytes) {
   if (bytes > ctx->ws_low) ctx->ws_low = bytes;
 }
