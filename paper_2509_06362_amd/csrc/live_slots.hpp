@@ -47,14 +47,16 @@ struct LiveSlot {
   // stride.  A slot
   // outside the tables gets a record that is never chosen (an infinite wait) and drains with a service
   // time of one second; `bad` has its lane's bit.
-  template <uint32_t kStep = 1u>
+  // kPinned: the row is one value ahead of the three loads, so that none of their addresses is worked out from another's.
+  template <uint32_t kStep = 1u, bool kPinned = false>
   __device__ __forceinline__ void evaluate(const float* tab, uint32_t stride, const ModelParams& mp, SlotRecord& r,
                                            float& svc, float& past, unsigned long long& bad) const {
     bad = lane_mask(!configured | (occ < 0));
     const uint32_t arriving = (uint32_t)occ + 1u;
     uint32_t w = mp.tbt_mode == 1u ? B : min(arriving, B);
     if (bad != 0ull) w = in_mask(bad) ? 1u : w;
-    const uint32_t row = kStep == 1u ? row0 + w : (row0 + w) * kStep;
+    uint32_t row = kStep == 1u ? row0 + w : (row0 + w) * kStep;
+    if (kPinned) asm("" : "+v"(row));
     r.a = tab[row];
     r.p = tab[stride + row];
     r.tbt = tab[2u * stride + row];
@@ -84,10 +86,11 @@ struct LiveSlot {
   }
   __device__ __forceinline__ bool any_wide() const { return lane_mask((q >> 32) != 0ull) != 0ull; }
 
+  template <bool kPinned = false>
   __device__ __forceinline__ void stage(const float* tab, uint32_t cells, const ModelParams& mp, SlotRecord& r,
                                         float& svc, unsigned long long& bad) const {
     float past;
-    evaluate(tab, cells, mp, r, svc, past, bad);
+    evaluate<1u, kPinned>(tab, cells, mp, r, svc, past, bad);
     r.wait = wait_with(past, any_wide());
   }
 

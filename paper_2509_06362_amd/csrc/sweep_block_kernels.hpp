@@ -93,7 +93,8 @@ __global__ __launch_bounds__(kBlockThreads) void sweep_block_kernel(const SweepW
     SlotRecord rec;
     float svc;
     unsigned long long bad;
-    slot.stage(tab, a.cells, a.mp, rec, svc, bad);
+    // (kPinned, 37 to 900 candidates, windows of 8 to 200, largest slack: scores of 3 to 8 slots 0.97 to 0.98 of the time, sweeps 1.02 to 1.03)
+    slot.template stage<kScore>(tab, a.cells, a.mp, rec, svc, bad);
     bad_slot |= bad;  // (a thread without an instance is never bad)
     if (kScore && s0 == 0u) inv_tbt_first = in_mask(bad) ? 0.0f : 1.0f / rec.tbt;
     if (mine) {
