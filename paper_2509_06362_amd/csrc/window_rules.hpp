@@ -90,9 +90,10 @@ constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, u
   uint64_t gain = 1;
   if (shortest_queue) gain = i_pad >= 64u ? 8u : i_pad >= 16u ? 4u : per_window >= 1024u ? 2u : 1u;
   else if (per_window > 256u && i_pad > 8u) gain = i_pad > 128u ? 4u : per_window >= 1024u ? 2u : 1u;
-  const uint64_t work = units * n_windows * (per_window < 32768u ? per_window : 32768u) * gain;
-  if (per_window >= 16384u) return n_windows >= 4u || work >= 45u << 20;
-  return work >= (per_window > 256u && per_window < 465u ? 6u << 20 : 12u << 20);
+  const uint64_t chains = units * n_windows * gain;
+  if (per_window >= 16384u) return n_windows >= 4u || chains * (per_window < 32768u ? per_window : 32768u) >= 45u << 20;
+  // (500 candidates x 16 slots, one window of 16,000: 0.68)
+  return chains * (per_window < 4096u ? per_window : 4096u) >= (per_window > 256u && per_window < 465u ? 6u << 20 : 12u << 20);
 }
 
 // Whether the prefills of every batch are then summed up ahead, on every row of the tables (batch_ticks_kernel): a launch of some 0.8 us per 4096
@@ -120,19 +121,23 @@ constexpr bool sweep_sums_batches(uint32_t i_pad, uint64_t per_window, uint64_t 
 //   0.77 1.27; 256: 1024: 0.92 2.84; 1024: 1.15 1.40; 4096: 1: 0.92 1.04, 4: 1.02 1.19; 16,384: 2: 0.88 0.94, 8: 1.00 1.06; 128 slots: 64: 8: 0.85
 //   1.13, 256: 0.73 1.62; 256: 8: 0.91 1.27; 512: 4: 1.00 1.35; 4096: 4: 0.94 1.14, 8: 1.16 1.29; 256 slots: 512: 8: 0.91 1.21, 16: 0.99 1.47; 1024:
 //   8: 0.97 1.26; 8192: 8: 1.17 1.34.
-// The line was laid where the mean of a shape is above one and its least, as a rule, above 0.8 (below it are 8 slots, windows of 64 to 255, at
-// capacity: 0.64 to 0.9, and a few more).
+// The line was laid where the mean of a shape is above one and its least, as a rule, above 0.8 (below it are 8 slots, windows of 48 to 255, at capacity: 0.64 to
+// 0.9, and a few more).
 constexpr bool assign_lays_out(uint32_t i_pad, uint64_t per_window, uint64_t n_windows, bool shortest_queue) {
   if (per_window < 11u || per_window > 16384u) return false;
   if (i_pad <= 2u) return true;
   if (shortest_queue) {
-    if (i_pad <= 64u && per_window >= 16u && per_window <= 64u && n_windows >= 1024u) return true;
+    if (per_window <= 64u) {  // long streams
+      if (i_pad <= 16u && n_windows >= (per_window < 16u ? 512u : 128u)) return true;
+      if (i_pad <= 32u && per_window >= 24u && n_windows >= 256u) return true;
+      if (i_pad <= 64u && per_window >= 16u && n_windows >= 1024u) return true;
+    }
     if (i_pad <= 32u) return per_window >= (i_pad <= 8u ? 11u : 32u) && (per_window <= 8192u || n_windows >= 64u);
     if (i_pad <= 64u) return per_window >= 64u && (per_window <= 2048u || n_windows >= 8u);
     return per_window >= (i_pad <= 128u ? 64u : 128u) && n_windows >= 4u;
   }
   if (i_pad <= 4u) return per_window >= 48u && (per_window <= 8192u || n_windows >= 8u);
-  if (i_pad <= 8u) return per_window >= (n_windows >= 1024u ? 48u : 64u) && (per_window <= 4096u || n_windows >= (per_window <= 8192u ? 16u : 64u));
+  if (i_pad <= 8u) return per_window >= (n_windows >= 128u ? 48u : 64u) && (per_window <= 4096u || n_windows >= (per_window <= 8192u ? 16u : 64u));
   if (i_pad <= 16u) return per_window >= 512u && (per_window <= 2048u || n_windows >= (per_window <= 4096u ? 32u : 128u));
   if (per_window < 2048u) return false;
   if (i_pad <= 32u) return n_windows >= (per_window <= 10240u ? 64u : 128u) || (n_windows <= 4u && per_window <= 4096u);

@@ -120,8 +120,8 @@ def test_shapes_that_were_measured_slower_are_not_laid_out(tmp_path):
     were measured several times as fast stay laid out."""
     slow_sweeps = [(64, 1, 4, 4096, 1, 0), (64, 1, 64, 4096, 4, 0), (1024, 1, 64, 512, 1, 0), (1024, 1, 64, 1024, 2, 0), (4096, 1, 4, 512, 2, 0),
                    (8192, 1, 64, 256, 1, 0), (512, 1, 64, 2048, 2, 0), (558, 3, 16, 4096, 16, 0), (1134, 3, 32, 4096, 4, 0), (1000, 1, 4, 4096, 1, 0),
-                   (300, 1, 4, 65_536, 1, 0)]
-    slow_assigns = [(64, 4096, 16, 0), (128, 4096, 16, 0), (256, 8192, 64, 0), (8, 48, 256, 0), (16, 11, 64, 1), (256, 32, 64, 1),
+                   (300, 1, 4, 65_536, 1, 0), (500, 1, 16, 16_000, 1, 0), (500, 1, 3, 16_000, 3, 0)]
+    slow_assigns = [(64, 4096, 16, 0), (128, 4096, 16, 0), (256, 8192, 64, 0), (8, 48, 64, 0), (16, 11, 64, 1), (256, 32, 64, 1),
                     (32, 2048, 16, 0), (64, 16_384, 32, 0), (16, 16_384, 16, 0), (64, 2048, 32, 0), (8, 16_384, 4, 1), (64, 32_768, 64, 0)]
     slow_sums = [(64, 2048, 4), (256, 2048, 1), (4, 2048, 64), (64, 4096, 2), (64, 300, 1000)]
     assert lays_out(tmp_path, slow_sweeps, slow_assigns, slow_sums) == [0] * (len(slow_sweeps) + len(slow_assigns) + len(slow_sums))
