@@ -79,7 +79,7 @@ TRAFFIC = {
     # workload name: (kernel, bytes per launch, digest of the kernel's sources at measurement, summary)
     "cfg4_skewed_stress": ("static_sweep", 2.0660e7, "c7401be52b2fc5e1", "profiles/sweep_kernel_cfg4.md"),
     "cfg1_placer_sweep": ("static_sweep", 3.957e6, "c7401be52b2fc5e1", "profiles/sweep_kernel_cfg1.md"),
-    "streaming_i4": ("assign_static_kernel", 1.1410e9, "ca43c36aaa3e0f7f",
+    "streaming_i4": ("assign_static_kernel", 1.1410e9, "4d8cde2214c90722",
                      "profiles/assign_static_kernel_stream.md"),
 }
 

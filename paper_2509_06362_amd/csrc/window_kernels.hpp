@@ -3,7 +3,7 @@
 // (the simulator's clock-advance step, Sec. V-A "Simulator Implementation"; admission and blocking
 // as in Sec. IV-F).  The window loop is sequential, so it lives inside ONE persistent kernel: no
 // host round trip and no launch per window.  (Windows of a few requests: sweep_seq_kernels.hpp; few slots, the
-// shortest-queue rule, or windows of thousands: assign_ordered_kernels.hpp.)
+// shortest-queue rule, or long streams of windows of thousands: assign_ordered_kernels.hpp.)
 //
 // Layout.  The work of a window is small (window x instances triples), so it is spread thin: each
 // request is scored by LPR neighbouring lanes, each lane walking every LPR-th instance, followed by
