@@ -141,8 +141,9 @@ void maaso_ctx_destroy(maaso_ctx* ctx);
  * 4 bytes per 1024 requests for maaso_split_by_slo.  The static distributor uses none.  The windowed sweep and the
  * scores are charged with none.  With many candidates and windows of some hundred requests they lay the requests out at
  * its end: some 9 bytes a request (more with short windows and many classes), and with windows of 2048 and more
- * n_tp * (b_cap + 1) / 16 bytes a request for prefill sums.  They keep out of what the calls above have used since it was
- * allocated (but for a windowed distributor that was not captured).  Where there is no room left for the sums, or for the
+ * n_tp * (b_cap + 1) / 16 bytes a request for prefill sums.  They keep out of what calls above that were captured
+ * use, whose graphs may replay beside them (but for a replay beside one that was issued before the capture, which the caller orders); a
+ * captured windowed distributor takes three quarters of it at most.  Where there is no room left for the sums, or for the
  * requests, and in a stream that is being captured, the call is slower.  Never shrinks.  A set-up call: it synchronises the device and reallocates
  * when the workspace has to grow.  Errors: INVALID_ARG, SHAPE, HIP, NOMEM, BUSY. */
 int maaso_ctx_reserve(maaso_ctx* ctx, uint32_t max_cand, uint32_t i_pad, uint32_t max_req);

@@ -61,7 +61,7 @@ struct maaso_ctx {
   void* ws;             // device workspace: sized at load, resized only by maaso_ctx_reserve
   size_t ws_bytes;
   uint32_t ws_allocations;  // how often the workspace has been allocated (load counts as one)
-  size_t ws_low;        // bytes at its start that calls charged for them have used: a captured one may replay beside any later call
+  size_t ws_low;        // bytes at its start that captured calls use, which may replay beside any later call
   // one call at a time: the host part of a call is exclusive, and a call on another stream than the
   // context's previous call is ordered behind it with an event
   std::atomic<int> in_call;
@@ -126,16 +126,16 @@ int need_workspace(const maaso_ctx* ctx, size_t bytes) {
 }
 
 bool is_captured(hipStream_t s) {
+  if (s == nullptr) return false;  // (the null stream cannot be)
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   return hip_ok(hipStreamIsCapturing(s, &status)) && status != hipStreamCaptureStatusNone;
 }
 
 // Calls that are charged with no workspace, the windowed sweep and the scores, lay requests out at its end, and keep out of what
-// charged calls have used at its start: one that was captured may replay beside any later call, and the windowed distributor's
-// profile is read from there later.  Whether a charged call is captured is not asked, so capturing one costs later sweeps nothing but
-// the room it uses.
-void use_workspace(maaso_ctx* ctx, size_t bytes) {
-  if (bytes > ctx->ws_low) ctx->ws_low = bytes;
+// charged calls that were captured use at its start: these may replay beside any later call.  Others are ordered with them and leave
+// all of it.  (It is asked only where that much is not kept already.)
+void use_workspace(maaso_ctx* ctx, size_t bytes, hipStream_t s) {
+  if (bytes > ctx->ws_low && is_captured(s)) ctx->ws_low = bytes;
 }
 
 // Set-up only (load, maaso_ctx_reserve): (re)allocates the workspace when it is too small.
@@ -495,7 +495,9 @@ int launch_sweep_window(const SweepWindowArgs& a, uint32_t policy, const maaso_c
   const size_t lds = (size_t)3 * ctx->cells * sizeof(float);  // profile tables
   const uint32_t n_cu = (uint32_t)ctx->n_cu;
   unsigned char* end = may_lay_out ? static_cast<unsigned char*>(ctx->ws) + ctx->ws_bytes : nullptr;  // (whole MiB)
-  const size_t room = ctx->ws_bytes - std::min(up256(ctx->ws_low), ctx->ws_bytes);
+  // (the windowed distributor's profile is read from its start later)
+  const size_t low = std::max(ctx->ws_low, ctx->window_profiled ? sizeof(WindowWs) : 0u);
+  const size_t room = ctx->ws_bytes - std::min(up256(low), ctx->ws_bytes);
   return policy ? launch_sweep_window_v<kScore, true>(a, lds, n_cu, end, room, s)
                 : launch_sweep_window_v<kScore, false>(a, lds, n_cu, end, room, s);
 }
@@ -652,7 +654,7 @@ int launch_static_sweep(maaso_ctx* ctx, const maaso_placements* pl, const maaso_
   // 8974 x 8 x 151,529: 30.2 / 25.7; 59,250 x 3 x 188,741: 64 / 48.
   const size_t with_best = at_best + (size_t)rank_cap * sizeof(uint64_t);
   const bool beside = !small && !few && (C >= 512u || R >= 1u << 16) && with_best <= ws_bytes;
-  if (ws == ctx->ws && !small && !few) use_workspace(ctx, beside ? with_best : at_longest);
+  if (ws == ctx->ws && !small && !few) use_workspace(ctx, beside ? with_best : at_longest, s);
   TimedRegion timed(ctx, s);  // all launches of the call
   if (beside) {
     GroupArgs g;
@@ -888,7 +890,7 @@ int launch_split(maaso_ctx* ctx, const maaso_requests* rq, uint32_t tight_classe
   a.arrival_ticks = rq->arrival_ticks;
   a.tight_classes = tight_classes;
   a.n_slo = ctx->n_slo;
-  use_workspace(ctx, ((size_t)n_blocks + 1u) * sizeof(uint32_t));
+  use_workspace(ctx, ((size_t)n_blocks + 1u) * sizeof(uint32_t), s);
   a.block_tight = static_cast<uint32_t*>(ctx->ws);
   a.n_tight = n_tight;
   a.prompt_out = prompt_len_out;
@@ -1501,7 +1503,9 @@ int launch_assign_ordered(maaso_ctx* ctx, const AssignArgs& a, const maaso_place
   const OrderedSet one = plan_set(set, a.n_slo, size_log2, 1u, at);
   const uint64_t places = (uint64_t)one.batches << size_log2;
   const uint64_t per_window = places * 8u + (uint64_t)one.batches * sizeof(Batch) + 4u + (uint64_t)I * 20u;
-  const uint64_t room = ctx->ws_bytes > 8192u ? ctx->ws_bytes - 8192u : 0u;
+  // A captured one leaves a quarter of the workspace to the requests of windowed sweeps, which keep out of what it uses.
+  const uint64_t held = is_captured(s) ? ctx->ws_bytes / 4u * 3u : ctx->ws_bytes;
+  const uint64_t room = held > 8192u ? held - 8192u : 0u;
   uint64_t at_once = std::min(room / per_window, n_windows);
   at_once = std::min(at_once, (uint64_t)(1u << 24) / one.segments);
   if (at_once == 0u || (at_once < n_windows && at_once < 64u)) return kNotTaken;
@@ -1514,7 +1518,7 @@ int launch_assign_ordered(maaso_ctx* ctx, const AssignArgs& a, const maaso_place
   const uint32_t per_window_blocks = (window + per_block - 1u) / per_block;
   if ((uint64_t)per_window_blocks * at_once > 0x7fffffffull) return kNotTaken;
   const uint32_t segment = std::min(window, kSegment);
-  if (is_captured(s)) use_workspace(ctx, ctx->ws_bytes - room + at_once * per_window);
+  use_workspace(ctx, 8192u + at_once * per_window, s);
   TimedRegion timed(ctx, s);
   for (uint64_t w0 = 0; w0 < n_windows; w0 += at_once) {
     const uint32_t count = (uint32_t)std::min(at_once, n_windows - w0);
@@ -1694,7 +1698,7 @@ int score_assign_impl(maaso_ctx* ctx, const maaso_placements* pl, const uint32_t
   // most).  Each request is spread over LPR lanes so that a window fills the blocks.
   rc = need_workspace(ctx, sizeof(WindowWs));
   if (rc != MAASO_OK) return rc;
-  use_workspace(ctx, sizeof(WindowWs));
+  use_workspace(ctx, sizeof(WindowWs), s);
   WindowWs* ws = static_cast<WindowWs*>(ctx->ws);
   const uint32_t per_window = prm->window < R ? prm->window : R;
   // More blocks shorten a window's scoring (more lanes per request, shorter instance walks) and
