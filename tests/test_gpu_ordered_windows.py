@@ -52,9 +52,20 @@ SWEEPS = [
     (64, 70, 2, 4500, 139_505, "alike", 0), (64, 4, 3, 16_384, 49_652, "mixed", 1),
     (4100, 3, 3, 5000, 4500, "mixed", 0),                                         # one window, shorter than its size
 ]
+# the same in a few windows, which other kernels take
+FEW_WINDOWS = [
+    (1001, 3, 3, 257, 600, "mixed", 0), (1000, 2, 1, 300, 901, "alike", 0), (1003, 5, 16, 320, 700, "mixed", 0),
+    (1000, 4, 8, 384, 800, "alike", 0), (1000, 4, 8, 385, 800, "mixed", 0),
+    (1002, 3, 3, 464, 930, "long", 0), (1002, 3, 3, 465, 940, "one class", 0), (1000, 3, 2, 512, 1024, "zeros", 0),
+    (1000, 70, 3, 500, 700, "mixed", 0), (1000, 130, 3, 300, 400, "alike", 0),
+    (400, 3, 3, 2048, 4100, "one length", 0), (64, 5, 5, 4095, 8190, "mixed", 0), (64, 4, 3, 4096, 8193, "long", 0),
+    (65, 4, 16, 4097, 9000, "zeros", 0), (64, 140, 3, 8200, 8300, "alike", 0), (4100, 2, 3, 256, 300, "mixed", 0),
+    (400, 40, 3, 2048, 4100, "long", 0), (64, 33, 16, 4100, 8300, "one length", 0), (64, 70, 2, 2500, 5100, "alike", 0),
+    (64, 4, 3, 16_384, 16_900, "mixed", 0), (1000, 3, 3, 5000, 300, "mixed", 0),
+]
 
 
-@pytest.mark.parametrize("n_cand,i_pad,n_slo,window,n_req,variant,mode", SWEEPS)
+@pytest.mark.parametrize("n_cand,i_pad,n_slo,window,n_req,variant,mode", SWEEPS + FEW_WINDOWS)
 def test_sweep_and_score(n_cand, i_pad, n_slo, window, n_req, variant, mode):
     w = variant_of(W.random_small(n_cand + 31 * i_pad + window, n_cand, i_pad, n_req, n_slo=n_slo, b_cap=64, pen_kappa=0.5,
                                   jitter=variant != "alike"), variant)
@@ -104,9 +115,15 @@ DISTRIBUTORS = [
     (64, 3, 64, 700, 1, "mixed"), (100, 8, 128, 393, 1, "alike"), (256, 3, 333, 2000, 1, "mixed"), (200, 16, 4096, 12_293, 1, "long"),
     (3, 3, 8192, 16_000, 1, "one class"),
 ]
+# short streams, which the persistent kernel takes
+SHORT_STREAMS = [
+    (8, 3, 48, 999, 0, "mixed"), (40, 5, 2048, 7000, 0, "zeros"), (64, 3, 4097, 12_500, 0, "mixed"), (64, 8, 16_384, 20_000, 0, "one length"),
+    (100, 3, 4096, 9000, 0, "mixed"), (256, 3, 8192, 17_000, 0, "mixed"), (16, 3, 11, 300, 1, "mixed"), (64, 3, 16, 330, 1, "mixed"),
+    (100, 8, 32, 700, 1, "alike"), (200, 16, 4096, 9000, 1, "long"), (3, 3, 16_384, 16_000, 1, "one class"),
+]
 
 
-@pytest.mark.parametrize("i_pad,n_slo,window,n_req,policy,variant", DISTRIBUTORS)
+@pytest.mark.parametrize("i_pad,n_slo,window,n_req,policy,variant", DISTRIBUTORS + SHORT_STREAMS)
 def test_distributor(i_pad, n_slo, window, n_req, policy, variant):
     half = n_req > 2_000_000  # (arrivals are 32-bit ticks: twice the requests at twice the rate)
     w = W.random_small(7 * i_pad + window, 1, i_pad, (n_req + 1) // 2 if half else n_req, n_slo=n_slo, b_cap=64, jitter=variant != "alike")
