@@ -52,7 +52,7 @@ SWEEPS = [
     (64, 70, 2, 4500, 139_505, "alike", 0), (64, 4, 3, 16_384, 49_652, "mixed", 1),
     (4100, 3, 3, 5000, 4500, "mixed", 0),                                         # one window, shorter than its size
 ]
-# the same in a few windows, which other kernels take
+# the same in a few windows, most of which other kernels take
 FEW_WINDOWS = [
     (1001, 3, 3, 257, 600, "mixed", 0), (1000, 2, 1, 300, 901, "alike", 0), (1003, 5, 16, 320, 700, "mixed", 0),
     (1000, 4, 8, 384, 800, "alike", 0), (1000, 4, 8, 385, 800, "mixed", 0),
@@ -115,7 +115,7 @@ DISTRIBUTORS = [
     (64, 3, 64, 700, 1, "mixed"), (100, 8, 128, 393, 1, "alike"), (256, 3, 333, 2000, 1, "mixed"), (200, 16, 4096, 12_293, 1, "long"),
     (3, 3, 8192, 16_000, 1, "one class"),
 ]
-# short streams, which the persistent kernel takes
+# short streams, most of which the persistent kernel takes
 SHORT_STREAMS = [
     (8, 3, 48, 999, 0, "mixed"), (40, 5, 2048, 7000, 0, "zeros"), (64, 3, 4097, 12_500, 0, "mixed"), (64, 8, 16_384, 20_000, 0, "one length"),
     (100, 3, 4096, 9000, 0, "mixed"), (256, 3, 8192, 17_000, 0, "mixed"), (16, 3, 11, 300, 1, "mixed"), (64, 3, 16, 330, 1, "mixed"),
