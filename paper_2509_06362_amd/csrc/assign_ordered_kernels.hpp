@@ -9,7 +9,8 @@
 // 64 instances, 1024 windows of 4096 requests, of which 188 admit something: 2.75 ms in the persistent kernel -> 0.58 (26 us to lay
 // out, 27 us to score all requests, the rest the states).  What bounds the states: the chain of windows on one wavefront a SIMD, some
 // 0.25 us for a window that admits nothing, 1.5 for the others - instances, search, bounds, sums, one barrier - and
-// trips to memory of over a microsecond where a window is not expected to admit.
+// trips to memory of over a microsecond where a window is not expected to admit.  The states' forms of two and four slots a lane keep 19 to 69 scalars in
+// lanes of vector registers; none spills to memory.
 #pragma once
 
 #include <type_traits>

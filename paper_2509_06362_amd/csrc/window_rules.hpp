@@ -80,7 +80,7 @@ constexpr uint32_t assign_short_window(uint32_t i_pad, bool narrow) {
 // to 400: 4: 0.89-1.05, 7: 0.99-1.10, 11: 1.09-1.17, 15: 1.17-1.24; 954 to 1890, of 478 to 937: 9 to 15: 0.97-1.21, 6 to 8: 0.97-1.07; 882, of 478: 10: 1.13; 738: 0.95-1.02.
 // 116 calls drawn from the timed ranges, two inputs each, largest slack, by candidates and number of windows: below 400: 1 and 2: 0.36-1.23, mean 0.66,
 // 4 to 10, 12 slots and more: 0.99-3.8, fewer: 0.77-1.14; 400 to 999: 1: 0.52-1.33, mean 0.78, 2: 0.65-1.24, 3 to 6: 0.78-1.65; 1000 to 1999: 1 and 2: 0.58-1.21,
-// mean 0.93, 3 to 8: 1.09-2.03, four slots 0.90; 2000 to 3999, 1 and 2, windows below 1024: 0.57-1.13, above: 0.87-1.54; 4 to 7: 1.1-1.8; more, 1: 1.01-1.95,
+// mean 0.93, 80 slots and more 0.75-1.92, mean 1.3; 3 to 8: 1.09-2.03, four slots 0.90; 2000 to 3999, 1 and 2, windows below 1024: 0.57-1.13, above: 0.87-1.54; 4 to 7: 1.1-1.8; more, 1: 1.01-1.95,
 // three slots 0.87.  The line was laid where the mean of a shape over these is above one and its least, as a rule, not below 0.8.
 constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, uint64_t per_window, uint64_t n_windows, bool shortest_queue) {
   if (per_window < 256u || units < 64u) return false;
@@ -98,7 +98,7 @@ constexpr bool sweep_lays_out(uint64_t units, uint32_t n_sets, uint32_t i_pad, u
                       : units < 4000u ? i_pad >= 8u ? 4u : 6u
                                       : i_pad >= 8u ? 1u : 3u))
       return true;
-    if (units >= 2000u && per_window >= 1024u && i_pad >= 5u) return true;
+    if (units >= 1000u && (i_pad >= 80u || (units >= 2000u && per_window >= 1024u && i_pad >= 5u))) return true;
   }
   uint64_t gain = 1;
   if (shortest_queue) gain = i_pad >= 64u ? 8u : i_pad >= 16u ? 4u : per_window >= 1024u ? 2u : 1u;
@@ -135,9 +135,9 @@ constexpr bool sweep_sums_batches(uint32_t i_pad, uint64_t per_window, uint64_t 
 //   1.13, 256: 0.73 1.62; 256: 8: 0.91 1.27; 512: 4: 1.00 1.35; 4096: 4: 0.94 1.14, 8: 1.16 1.29; 256 slots: 512: 8: 0.91 1.21, 16: 0.99 1.47; 1024:
 //   8: 0.97 1.26; 8192: 8: 1.17 1.34.
 // 80 calls drawn from the timed ranges, arrivals of 400 to 5000 a second, by number of windows: largest slack: 1 to 5: 1.01 to 1.39 (one 0.8), more: 1.00-2.9,
-// but 9 to 16 slots, windows above 8192, 14: 0.8, and 43 slots of 10,639, 17: 0.85.  Shortest queue: windows of 17 to 43, up to 64 slots, 38 to 65: 0.69-0.88, 348:
-// 0.78-1.19, 725: 0.6, 958: 3.0, 1000: 5.6; 67 to 77 slots, of 33 to 41: 0.67-1.0, of 46 and more: 1.04-5.8; 130 and more, of 39 and more: 1.1-1.9; windows of
-// hundreds and thousands, up to 128 slots: 0.9-1.5 (one 0.77), 130 and more: 1: 0.67-1.01, 2: 0.8-1.38, 3: 1.2-2.2.
+// but 9 to 16 slots, windows above 4096, 7 and 14: 0.8-1.0, 62: 1.7, and 43 slots of 10,639, 17: 0.85.  Shortest queue: windows of 17 to 43, up to 64 slots, 38 to 65: 0.69-0.88, 348:
+// 0.78-1.19, 725: 0.6, 958: 3.0, 1000: 5.6, of 57: 2.3; 67 to 84 slots, of 33 to 41: 0.67-3.2, mean 1.2, of 46 and more: 1.04-5.8; 130 and more, of 39 and more: 1.1-1.9; windows of
+// hundreds and thousands, up to 128 slots: 0.9-1.5 (one 0.77), 130 and more: 1: 0.67-1.6, 2: 0.8-1.38, 3: 1.2-2.2, mean 1.1 of 1 and 2.
 // The line was laid where the mean of a shape is above one (below it remain 8 slots, windows of 48 to 255, at capacity: 0.64 to 0.9, and a few more).
 constexpr bool assign_lays_out(uint32_t i_pad, uint64_t per_window, uint64_t n_windows, bool shortest_queue) {
   if (per_window < 11u || per_window > 16384u) return false;
@@ -147,13 +147,13 @@ constexpr bool assign_lays_out(uint32_t i_pad, uint64_t per_window, uint64_t n_w
       if (i_pad <= 8u) return true;
       if (i_pad <= 16u) return n_windows >= (per_window < 16u ? 512u : 128u) || per_window >= 32u;
       if (i_pad <= 32u) return (per_window >= 16u && n_windows >= 256u) || per_window >= 32u;
-      if (i_pad <= 64u) return (per_window >= 16u && n_windows >= 512u) || per_window == 64u;
-      return per_window >= (i_pad <= 128u ? 46u : 32u) && n_windows >= 4u;
+      if (i_pad <= 64u) return (per_window >= 16u && n_windows >= 512u) || per_window >= 48u;
+      return per_window >= 32u;
     }
-    return i_pad <= 128u || n_windows >= 3u;
+    return true;
   }
   if (i_pad <= 8u) return per_window >= 48u && (per_window <= 8192u || i_pad <= 4u || n_windows >= 8u || n_windows <= 3u);
-  if (i_pad <= 16u) return per_window >= 512u && (per_window <= 4096u || n_windows >= 64u || n_windows <= 5u);
+  if (i_pad <= 16u) return per_window >= 512u && (per_window <= 4096u || n_windows >= 48u || n_windows <= 5u);
   if (i_pad <= 32u) return per_window >= 2048u;
   if (i_pad <= 64u) return per_window >= 2048u && (per_window <= 8192u || n_windows >= 64u);
   return per_window >= (i_pad <= 128u ? 4096u : 8192u) && per_window <= 8192u && (i_pad <= 128u || n_windows >= 256u);

@@ -122,14 +122,14 @@ def test_shapes_that_were_measured_slower_are_not_laid_out(tmp_path):
                    (8192, 1, 64, 256, 1, 0), (512, 1, 64, 2048, 2, 0), (558, 3, 16, 4096, 16, 0), (1134, 3, 32, 4096, 4, 0), (1000, 1, 4, 4096, 1, 0),
                    (300, 1, 4, 65_536, 1, 0), (500, 1, 16, 16_000, 1, 0), (500, 1, 3, 16_000, 3, 0),
                    (1080, 3, 32, 257, 4, 0)]
-    slow_assigns = [(256, 8192, 64, 0), (16, 11, 64, 1), (256, 30, 64, 1), (13, 13_263, 14, 0), (64, 16_384, 32, 0), (43, 10_639, 17, 0),
-                    (17, 29, 58, 1), (35, 26, 42, 1), (77, 33, 4036, 1), (221, 3461, 1, 1), (64, 32_768, 64, 0)]
+    slow_assigns = [(256, 8192, 64, 0), (16, 11, 64, 1), (256, 20, 64, 1), (13, 13_263, 14, 0), (64, 16_384, 32, 0), (43, 10_639, 17, 0),
+                    (17, 29, 58, 1), (35, 26, 42, 1), (64, 32_768, 64, 0)]
     slow_sums = [(64, 2048, 4), (256, 2048, 1), (4, 2048, 64), (64, 4096, 2), (64, 300, 1000)]
     assert lays_out(tmp_path, slow_sweeps, slow_assigns, slow_sums) == [0] * (len(slow_sweeps) + len(slow_assigns) + len(slow_sums))
     fast_sweeps = [(8192, 1, 128, 4096, 32, 0), (2160, 3, 64, 256, 512, 0), (4096, 1, 64, 4096, 1, 0), (1024, 1, 64, 16_384, 8, 0),
                    (512, 1, 64, 4096, 16, 0), (1024, 1, 64, 4096, 1, 1), (4096, 1, 256, 2048, 1, 0), (64, 1, 64, 16_384, 4, 0),
                    (1080, 3, 32, 257, 11, 0), (1620, 3, 48, 400, 7, 0),
-                   (105, 1, 35, 10_637, 10, 0), (1125, 1, 113, 1333, 4, 0), (2020, 1, 6, 7847, 1, 0), (1278, 3, 39, 645, 14, 0)]
+                   (105, 1, 35, 10_637, 10, 0), (1125, 1, 113, 1333, 4, 0), (2020, 1, 6, 7847, 1, 0), (1626, 1, 123, 1459, 1, 0), (1278, 3, 39, 645, 14, 0)]
     fast_assigns = [(64, 4096, 1024, 0), (8, 512, 1024, 1), (2, 11, 1, 0), (16, 2048, 256, 0), (128, 8192, 512, 0), (256, 4096, 64, 1),
                     (64, 1024, 64, 1), (4, 4096, 1, 0), (64, 16_384, 256, 0),
                     (24, 14_162, 110, 0), (55, 23, 958, 1), (91, 1160, 1, 1), (61, 4187, 1, 0), (31, 14_911, 39, 1)]
